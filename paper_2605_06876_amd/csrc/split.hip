@@ -6,21 +6,23 @@
 //   2. one thread per region: child proposal (centre at t* of Eq. (tstar) on
 //      the centroid ray, shape from the clipped, unprojected PCA axes,
 //      Gram-Schmidt rotation [u1 | u2 | z_v], colour from the target);
-//   3. one wave per candidate: transitive merge graph under
+//   3. one wave per region, three launches: transitive merge graph under
 //      Eq. (merge_conditions) (lock-free union-find, roots = first member),
 //      merged parameters of Eq. (merge_cov), ranking by covariance extent and
-//      the N_max cap, then the mode (vanilla / reset / adaptive / random) and
-//      count (the ablation variants of Table 2 skip the merge, or the region
-//      children altogether);
+//      the N_max cap; then one thread per candidate: the mode (vanilla / reset
+//      / adaptive / random) and count (the ablation variants of Table 2 skip
+//      the merge, or the region children altogether);
 //   4. scans of the counts and of the removal mask, survivor copy and child
 //      write-out.
 // All decision arithmetic is FP64 with a fixed expression order; this file is
 // compiled with -ffp-contract=off.
+#include <stddef.h>
+
 #include "internal.h"
 
 namespace {
 
-enum { SP_K0, SP_K1, SP_V0, SP_V1, SP_HIST, SP_N, SP_RS, SP_RE, SP_PROP, SP_UF, SP_ROOT, SP_GRP, SP_KEPT, SP_NKEPT,
+enum { SP_K0, SP_K1, SP_V0, SP_V1, SP_HIST, SP_N, SP_RS, SP_RE, SP_PROP, SP_UF, SP_RCI, SP_GRP, SP_KEPT, SP_NKEPT,
        SP_CAMS, SP_REM, SP_REMSCAN, SP_SCAN, SP_TOT, SP_COUNT };
 
 constexpr double C0_SH = 0.28209479177387814;   // degree-0 real SH constant 1/(2 sqrt(pi))
@@ -243,37 +245,57 @@ __global__ void k_reg_keys(const as_region *__restrict__ recs, const uint32_t *_
     vals[i] = (uint32_t)i;
 }
 
-__global__ void k_cand_ranges(const as_region *__restrict__ recs, const uint32_t *__restrict__ order,
-                              const uint32_t *__restrict__ n32, int64_t cap, const int32_t *__restrict__ cand,
-                              int64_t n_cand, const int64_t *__restrict__ n_cand_dev, int64_t *__restrict__ rs,
-                              int64_t *__restrict__ re) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t R = *n32;
-    if (i >= cap || i >= R) return;
-    const int32_t c = recs[order[i]].cand;
-    const int64_t ci = find_cand(cand, count_in_use(n_cand, n_cand_dev), c);
-    if (ci < 0) return;
-    if (i == 0 || recs[order[i - 1]].cand != c) rs[ci] = i;
-    if (i == R - 1 || recs[order[i + 1]].cand != c) re[ci] = i + 1;
+// Region waves: kernels over the sorted regions take a bounded grid and stride,
+// because the region capacity the host knows is far above the regions in use
+// (a grid over the capacity launched 6,500 blocks for 6,400 regions).
+constexpr int RW_BLOCKS = 2048;
+
+// Zeroes what the split accumulates into: the candidates' region ranges and
+// root counts, and the removal mask (one launch instead of three fills).
+__global__ void k_split_init(int64_t nc, int64_t n, int64_t *__restrict__ rs, int64_t *__restrict__ re,
+                             int32_t *__restrict__ nkept, uint8_t *__restrict__ removed) {
+    const int64_t st = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nc || i < n; i += st) {
+        if (i < nc) {
+            rs[i] = 0;
+            re[i] = 0;
+            nkept[i] = 0;
+        }
+        if (i < n) removed[i] = 0;
+    }
 }
 
-__global__ void k_propose(GaussPtrs g, const as_region *__restrict__ recs, const uint32_t *__restrict__ order,
-                          const uint32_t *__restrict__ n32, int64_t cap, const int32_t *__restrict__ cand,
-                          int64_t n_cand, const int64_t *__restrict__ n_cand_dev, const DevCam *__restrict__ cams,
-                          int n_views, double eps, Prop *__restrict__ props) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cap || i >= (int64_t)*n32) return;
-    const as_region r = recs[order[i]];
-    Prop p;
-    p.ok = 0;
-    p.view = r.view;
-    if (find_cand(cand, count_in_use(n_cand, n_cand_dev), r.cand) >= 0 && r.view >= 0 && r.view < n_views &&
-        r.cand < rows_in_use(g)) {
-        Parent par;
-        load_parent(g, r.cand, par);
-        make_proposal(par, r, cams[r.view], eps, p);
+// One thread per sorted region: its candidate (rci, -1 if none), the
+// candidate's region range, its child proposal and its union-find cell (the
+// region itself, or -1 without a proposal).
+__global__ void __launch_bounds__(256) k_propose(GaussPtrs g, const as_region *__restrict__ recs,
+                                                 const uint32_t *__restrict__ order, const uint32_t *__restrict__ n32,
+                                                 int64_t cap, const int32_t *__restrict__ cand, int64_t n_cand,
+                                                 const int64_t *__restrict__ n_cand_dev,
+                                                 const DevCam *__restrict__ cams, int n_views, double eps,
+                                                 int64_t *__restrict__ rs, int64_t *__restrict__ re,
+                                                 int32_t *__restrict__ rci, int32_t *__restrict__ uf,
+                                                 Prop *__restrict__ props) {
+    const int64_t R = (int64_t)*n32 < cap ? (int64_t)*n32 : cap;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < R; i += (int64_t)gridDim.x * blockDim.x) {
+        const as_region r = recs[order[i]];
+        Prop p;
+        p.ok = 0;
+        p.view = r.view;
+        const int64_t ci = find_cand(cand, count_in_use(n_cand, n_cand_dev), r.cand);
+        if (ci >= 0) {
+            if (i == 0 || recs[order[i - 1]].cand != r.cand) rs[ci] = i;
+            if (i == R - 1 || recs[order[i + 1]].cand != r.cand) re[ci] = i + 1;
+            if (r.view >= 0 && r.view < n_views && r.cand < rows_in_use(g)) {
+                Parent par;
+                load_parent(g, r.cand, par);
+                make_proposal(par, r, cams[r.view], eps, p);
+            }
+        }
+        rci[i] = (int32_t)ci;
+        uf[i] = p.ok ? (int32_t)i : -1;
+        props[i] = p;
     }
-    props[i] = p;
 }
 
 __device__ __forceinline__ int32_t uf_load(const int32_t *L, int64_t x) {
@@ -303,111 +325,117 @@ __device__ __forceinline__ void uf_unite(int32_t *L, int32_t a, int32_t b) {
     }
 }
 
-// One wave per candidate.
-__global__ void __launch_bounds__(256) k_merge(GaussPtrs g, const int32_t *__restrict__ cand, int64_t n_cand,
-                                               const int64_t *__restrict__ n_cand_dev,
-                                               const int32_t *__restrict__ attr, const int64_t *__restrict__ rs_a,
-                                               const int64_t *__restrict__ re_a, const Prop *__restrict__ props,
-                                               int32_t *__restrict__ uf_all, int32_t *__restrict__ root_all,
-                                               Group *__restrict__ grp_all, int32_t *__restrict__ kept_all,
-                                               int32_t *__restrict__ nkept, double gamma_d, double gamma_c,
-                                               int n_max, int variant, uint32_t flags, int fixed_n,
-                                               uint8_t *__restrict__ mode, int32_t *__restrict__ count) {
-    const int lane = threadIdx.x & 63;
-    const int64_t ci = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (ci >= n_cand) return;
-    if (ci >= count_in_use(n_cand, n_cand_dev)) {   // capacity past the candidates in use: no rows
-        if (lane == 0) {
-            mode[ci] = 0;
-            count[ci] = 0;
-            nkept[ci] = 0;
-        }
-        return;
-    }
-    if (variant == AS_VARIANT_FIXED_N) {   // the random split with a fixed N, whatever the regions say
-        if (lane == 0) {
-            mode[ci] = 3;
-            count[ci] = fixed_n;
-            nkept[ci] = 0;
-        }
-        return;
-    }
-    const int64_t rs = rs_a[ci], re = re_a[ci];
-    const int32_t np = (int32_t)(re - rs);
-    const Prop *pp = props + rs;
-    int32_t *uf = uf_all + rs;
-    int32_t *rootof = root_all + rs;
-    Group *grp = grp_all + rs;
-    int32_t *kept = kept_all + rs;
+// The merge of Eq. (merge_conditions) and Eq. (merge_cov) runs with one wave per
+// region, not per candidate: the candidates are very uneven (most hold none
+// or a few regions, one held several hundred of the 6,400 regions of 16 views over 500,000
+// Gaussians), so a wave per candidate left the chip waiting on one wave that
+// took every pair test, group sum and rank of its candidate in sequence
+// (1572 us there; see k_rank for the time now).  Three launches, because
+// each needs the whole candidate of the one before.
 
-    for (int32_t j = lane; j < np; j += 64) uf[j] = pp[j].ok ? j : -1;
-    __threadfence();
-    __builtin_amdgcn_wave_barrier();
-    // Eq. (merge_conditions) over every pair of this parent's proposals (the
-    // ablation variants do not merge)
-    const bool merge = variant == AS_VARIANT_ADPSPLIT;
-    for (int32_t a = 0; merge && a < np; a++) {
-        if (!pp[a].ok) continue;
-        for (int32_t b = a + 1 + lane; b < np; b += 64) {
-            if (!pp[b].ok) continue;
-            if ((flags & AS_SPLIT_CROSS_VIEW) && pp[b].view == pp[a].view) continue;
-            const double dl[3] = {pp[b].mu[0] - pp[a].mu[0], pp[b].mu[1] - pp[a].mu[1], pp[b].mu[2] - pp[a].mu[2]};
-            const double dm = maha(pp[a].Sinv, dl) + maha(pp[b].Sinv, dl);
+// Eq. (merge_conditions): the wave of region a tests it against the later
+// regions of its candidate, a lane each, and unites those that merge.
+__global__ void __launch_bounds__(256) k_pairs(const uint32_t *__restrict__ n32, int64_t cap,
+                                               const int32_t *__restrict__ rci, const int64_t *__restrict__ re_a,
+                                               const Prop *__restrict__ props, int32_t *uf, double gamma_d,
+                                               double gamma_c, uint32_t flags) {
+    const int lane = threadIdx.x & 63;
+    const int64_t R = (int64_t)*n32 < cap ? (int64_t)*n32 : cap;
+    for (int64_t a = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); a < R; a += (int64_t)gridDim.x * 4) {
+        const int32_t ci = rci[a];
+        if (ci < 0 || !props[a].ok) continue;
+        const Prop &pa = props[a];
+        const int64_t re = re_a[ci];
+        for (int64_t b = a + 1 + lane; b < re; b += 64) {
+            const Prop &pb = props[b];
+            if (!pb.ok) continue;
+            if ((flags & AS_SPLIT_CROSS_VIEW) && pb.view == pa.view) continue;
+            const double dl[3] = {pb.mu[0] - pa.mu[0], pb.mu[1] - pa.mu[1], pb.mu[2] - pa.mu[2]};
+            const double dm = maha(pa.Sinv, dl) + maha(pb.Sinv, dl);
             double dc = 0.0;
             for (int ch = 0; ch < 3; ch++) {
-                const double t = fabs(pp[a].rgb[ch] - pp[b].rgb[ch]);
+                const double t = fabs(pa.rgb[ch] - pb.rgb[ch]);
                 if (t > dc) dc = t;
             }
-            if (dm <= gamma_d && dc <= gamma_c) uf_unite(uf, a, b);
+            if (dm <= gamma_d && dc <= gamma_c) uf_unite(uf, (int32_t)a, (int32_t)b);
         }
     }
-    __threadfence();
-    __builtin_amdgcn_wave_barrier();
-    for (int32_t j = lane; j < np; j += 64) rootof[j] = pp[j].ok ? uf_find(uf, j) : -1;
-    __threadfence();
-    __builtin_amdgcn_wave_barrier();
+}
 
-    // Eq. (merge_cov): one merged child per group, summed in member order
-    int32_t nroots = 0;
-    for (int32_t j0 = 0; j0 < np; j0 += 64) {
-        const int32_t j = j0 + lane;
-        const bool isroot = j < np && rootof[j] == j;
-        nroots += (int32_t)__popcll(__ballot(isroot));
-        if (!isroot) continue;
-        Group gr;
+// Eq. (merge_cov): one merged child per group, at the group's first member.
+// The wave finds the members by ballots over the candidate's later regions;
+// lane k < 15 sums component k of the members' means, colours and covariances
+// in member order (the sums keep their order, only the components run side by
+// side), four members' loads in flight, and the extents' maxima take a lane per member.
+__global__ void __launch_bounds__(256) k_groups(const uint32_t *__restrict__ n32, int64_t cap,
+                                                const int32_t *__restrict__ rci, const int64_t *__restrict__ re_a,
+                                                const Prop *__restrict__ props, const int32_t *__restrict__ uf,
+                                                uint32_t flags, Group *__restrict__ grp) {
+    const int lane = threadIdx.x & 63;
+    const int64_t R = (int64_t)*n32 < cap ? (int64_t)*n32 : cap;
+    // offset of component `lane` in Prop (doubles): mu, then rgb and Sig
+    static_assert(offsetof(Prop, rgb) == 15 * 8 && offsetof(Prop, Sig) == 18 * 8, "component offsets");
+    const int comp = lane < 3 ? lane : 12 + (lane < 15 ? lane : 3);
+    for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < R; j += (int64_t)gridDim.x * 4) {
+        const int32_t ci = rci[j];
+        if (ci < 0 || uf[j] != (int32_t)j) continue;   // wave-uniform
+        const int64_t re = re_a[ci];
+        double acc = 0.0;
         int64_t M = 0;
-        double Sbar[9];
-        for (int k = 0; k < 3; k++) { gr.mu[k] = 0.0; gr.rgb[k] = 0.0; }
-        for (int k = 0; k < 9; k++) Sbar[k] = 0.0;
-        for (int32_t m = j; m < np; m++) {
-            if (rootof[m] != j) continue;
-            M++;
-            for (int k = 0; k < 3; k++) { gr.mu[k] += pp[m].mu[k]; gr.rgb[k] += pp[m].rgb[k]; }
-            for (int k = 0; k < 9; k++) Sbar[k] += pp[m].Sig[k];
+        for (int64_t m0 = j; m0 < re; m0 += 64) {
+            const int64_t m = m0 + lane;
+            uint64_t in = __ballot(m < re && uf[m] >= 0 && uf_find(uf, (int32_t)m) == (int32_t)j);
+            M += __popcll(in);
+            while (in) {
+                double x[4];
+                int k = 0;
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if (in) {
+                        const int b = __ffsll((unsigned long long)in) - 1;
+                        in &= in - 1;
+                        x[u] = reinterpret_cast<const double *>(props + m0 + b)[comp];
+                        k = u + 1;
+                    }
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if (u < k) acc += x[u];
+            }
         }
+        Group gr;
         if (M == 1) {
-            for (int k = 0; k < 3; k++) { gr.mu[k] = pp[j].mu[k]; gr.rgb[k] = pp[j].rgb[k]; gr.s[k] = pp[j].s[k]; }
-            for (int k = 0; k < 9; k++) gr.R[k] = pp[j].R[k];
+            const Prop &pj = props[j];
+            for (int k = 0; k < 3; k++) { gr.mu[k] = pj.mu[k]; gr.rgb[k] = pj.rgb[k]; gr.s[k] = pj.s[k]; }
+            for (int k = 0; k < 9; k++) gr.R[k] = pj.R[k];
         } else {
-            for (int k = 0; k < 3; k++) { gr.mu[k] = gr.mu[k] / (double)M; gr.rgb[k] = gr.rgb[k] / (double)M; }
-            for (int k = 0; k < 9; k++) Sbar[k] = Sbar[k] / (double)M;
+            const double mean = acc / (double)M;
+            double Sbar[9];
+            for (int k = 0; k < 3; k++) { gr.mu[k] = __shfl(mean, k, 64); gr.rgb[k] = __shfl(mean, 3 + k, 64); }
+            for (int k = 0; k < 9; k++) Sbar[k] = __shfl(mean, 6 + k, 64);
             double E[9], lam[3];
             jacobi3(Sbar, E, lam);
-            for (int r = 0; r < 3; r++) {
-                const double er[3] = {E[0 * 3 + r], E[1 * 3 + r], E[2 * 3 + r]};
-                double best = 0.0;
-                for (int32_t m = j; m < np; m++) {
-                    if (rootof[m] != j) continue;
-                    const double off = fabs(er[0] * (pp[m].mu[0] - gr.mu[0]) + er[1] * (pp[m].mu[1] - gr.mu[1]) +
-                                            er[2] * (pp[m].mu[2] - gr.mu[2]));
+            double best[3] = {0.0, 0.0, 0.0};
+            for (int64_t m = j + lane; m < re; m += 64) {
+                if (uf[m] < 0 || uf_find(uf, (int32_t)m) != (int32_t)j) continue;
+                const Prop &pm = props[m];
+                for (int r = 0; r < 3; r++) {
+                    const double er[3] = {E[0 * 3 + r], E[1 * 3 + r], E[2 * 3 + r]};
+                    const double off = fabs(er[0] * (pm.mu[0] - gr.mu[0]) + er[1] * (pm.mu[1] - gr.mu[1]) +
+                                            er[2] * (pm.mu[2] - gr.mu[2]));
                     double Se[3];
                     for (int k = 0; k < 3; k++)
-                        Se[k] = pp[m].Sig[k * 3 + 0] * er[0] + pp[m].Sig[k * 3 + 1] * er[1] + pp[m].Sig[k * 3 + 2] * er[2];
+                        Se[k] = pm.Sig[k * 3 + 0] * er[0] + pm.Sig[k * 3 + 1] * er[1] + pm.Sig[k * 3 + 2] * er[2];
                     const double sig = sqrt(er[0] * Se[0] + er[1] * Se[1] + er[2] * Se[2]);
                     const double reach = off + sig;
-                    if (reach > best) best = reach;
+                    if (reach > best[r]) best[r] = reach;
                 }
-                gr.s[r] = best;
+            }
+            for (int r = 0; r < 3; r++) {
+                for (int o = 32; o > 0; o >>= 1) {
+                    const double t = __shfl_xor(best[r], o, 64);
+                    if (t > best[r]) best[r] = t;
+                }
+                gr.s[r] = best[r];
             }
             for (int k = 0; k < 9; k++) gr.R[k] = E[k];
         }
@@ -419,124 +447,210 @@ __global__ void __launch_bounds__(256) k_merge(GaussPtrs g, const int32_t *__res
         } else {
             gr.extent = gr.s[0] * gr.s[1] * gr.s[2];
         }
-        grp[j] = gr;
+        if (lane == 0) grp[j] = gr;
     }
-    __threadfence();
-    __builtin_amdgcn_wave_barrier();
-    // rank by (extent descending, first member ascending); keep N_max
-    for (int32_t j = lane; j < np; j += 64) {
-        if (rootof[j] != j) continue;
-        const double ej = grp[j].extent;
+}
+
+// An extent as it is ranked (a proposal of non-finite parameters ranks last).
+__device__ __forceinline__ double rank_extent(double e) { return e == e ? e : -1.0; }
+
+// A group's rank among its candidate's by (extent descending, first member
+// ascending): the wave of its root counts the groups ahead of it.  The first
+// n_max are kept; nroots counts the candidate's groups.
+// Merge, groups, ranks and modes together, 16 views over 500,000 Gaussians with
+// 25,167 candidates and 6,374 regions: 31 us (7 + 16 + 4 + 4).
+__global__ void __launch_bounds__(256) k_rank(const uint32_t *__restrict__ n32, int64_t cap,
+                                              const int32_t *__restrict__ rci, const int64_t *__restrict__ rs_a,
+                                              const int64_t *__restrict__ re_a, const int32_t *__restrict__ uf,
+                                              const Group *__restrict__ grp, int n_max, int32_t *__restrict__ kept,
+                                              int32_t *__restrict__ nroots) {
+    const int lane = threadIdx.x & 63;
+    const int64_t R = (int64_t)*n32 < cap ? (int64_t)*n32 : cap;
+    for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < R; j += (int64_t)gridDim.x * 4) {
+        const int32_t ci = rci[j];
+        if (ci < 0 || uf[j] != (int32_t)j) continue;   // wave-uniform
+        const int64_t rs = rs_a[ci], re = re_a[ci];
+        const double ej = rank_extent(grp[j].extent);
         int32_t rank = 0;
-        for (int32_t h = 0; h < np; h++) {
-            if (h == j || rootof[h] != h) continue;
-            const double eh = grp[h].extent;
+        for (int64_t h = rs + lane; h < re; h += 64) {
+            if (h == j || uf[h] != (int32_t)h) continue;
+            const double eh = rank_extent(grp[h].extent);
             if (eh > ej || (eh == ej && h < j)) rank++;
         }
-        if (rank < n_max) kept[rank] = j;
+        for (int o = 32; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
+        if (lane == 0) {
+            if (rank < n_max) kept[rs + rank] = (int32_t)j;
+            atomicAdd(nroots + ci, 1);
+        }
     }
-    if (lane == 0) {
-        const int32_t nk = nroots < n_max ? nroots : n_max;
+}
+
+// One thread per candidate: its mode, its row count, the groups it keeps
+// (nkept holds the groups found on entry) and whether its parent leaves.
+__global__ void __launch_bounds__(256) k_modes(const int32_t *__restrict__ cand, int64_t n_cand,
+                                               const int64_t *__restrict__ n_cand_dev,
+                                               const int32_t *__restrict__ attr, int n_max, int variant, int fixed_n,
+                                               int32_t *__restrict__ nkept, uint8_t *__restrict__ mode,
+                                               int32_t *__restrict__ count, uint8_t *__restrict__ removed) {
+    const int64_t ci = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (ci >= n_cand) return;
+    uint8_t md = 0;
+    int32_t cnt = 0, nk = 0;
+    if (ci < count_in_use(n_cand, n_cand_dev)) {   // capacity past the candidates in use: no rows
         const int32_t id = cand[ci];
-        uint8_t md;
-        int32_t cnt;
-        if (attr[id] == 0) { md = 0; cnt = 2; }
+        nk = nkept[ci] < n_max ? nkept[ci] : n_max;
+        if (variant == AS_VARIANT_FIXED_N) { md = 3; cnt = fixed_n; nk = 0; }   // whatever the regions say
+        else if (attr[id] == 0) { md = 0; cnt = 2; }
         else if (nk == 0) { md = 1; cnt = 0; }
         else if (variant == AS_VARIANT_ADAPTIVE_N) { md = 3; cnt = nk; }   // as many random children as proposals
         else { md = 2; cnt = nk + 1; }
-        mode[ci] = md;
-        count[ci] = cnt;
-        nkept[ci] = nk;
+        if (md != 1) removed[id] = 1;
     }
+    mode[ci] = md;
+    count[ci] = cnt;
+    nkept[ci] = nk;
 }
 
-__global__ void k_mark_removed(const int32_t *__restrict__ cand, int64_t n_cand, const int64_t *__restrict__ n_cand_dev,
-                               const uint8_t *__restrict__ mode, uint8_t *__restrict__ removed) {
-    const int64_t ci = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (ci >= count_in_use(n_cand, n_cand_dev)) return;
-    if (mode[ci] != 1) removed[cand[ci]] = 1;
+// A set's parameter rows in chunks of at most 12: chunk 0 is the geometry
+// (means, log scales, quaternion, opacity), the rest SH rows.  A thread loads
+// a chunk before it stores any of it: loads and stores of sets that may
+// alias are otherwise kept in order, a memory latency per row.
+constexpr int ROW_CHUNK = 12;
+__host__ __device__ __forceinline__ int row_chunks(int deg) {
+    return 1 + (3 * (deg + 1) * (deg + 1) + ROW_CHUNK - 1) / ROW_CHUNK;
+}
+// Rows of chunk c of a Gaussian, and their place in an output set.
+__device__ __forceinline__ int chunk_rows(int c, int deg) {
+    if (c == 0) return 11;
+    const int left = 3 * (deg + 1) * (deg + 1) - ROW_CHUNK * (c - 1);
+    return left < ROW_CHUNK ? left : ROW_CHUNK;
+}
+__device__ __forceinline__ void load_chunk(const GaussPtrs &g, int64_t i, int c, int rows, float v[ROW_CHUNK]) {
+    const int64_t n = g.n;
+    if (c == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) v[k] = g.means[k * n + i];
+#pragma unroll
+        for (int k = 0; k < 3; k++) v[3 + k] = g.log_scales[k * n + i];
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[6 + k] = g.quats[k * n + i];
+        v[10] = g.opac[i];
+        return;
+    }
+    const float *sh = g.sh + (int64_t)ROW_CHUNK * (c - 1) * n;
+#pragma unroll
+    for (int k = 0; k < ROW_CHUNK; k++)
+        if (k < rows) v[k] = sh[k * n + i];
+}
+__device__ __forceinline__ void store_chunk(const GradPtrs &o, int64_t i, int c, int rows, const float v[ROW_CHUNK]) {
+    const int64_t n = o.stride;
+    if (c == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) o.means[k * n + i] = v[k];
+#pragma unroll
+        for (int k = 0; k < 3; k++) o.log_scales[k * n + i] = v[3 + k];
+#pragma unroll
+        for (int k = 0; k < 4; k++) o.quats[k * n + i] = v[6 + k];
+        o.opac[i] = v[10];
+        return;
+    }
+    float *sh = o.sh + (int64_t)ROW_CHUNK * (c - 1) * n;
+#pragma unroll
+    for (int k = 0; k < ROW_CHUNK; k++)
+        if (k < rows) sh[k * n + i] = v[k];
 }
 
-__global__ void k_copy_survivors(GaussPtrs g, const uint8_t *__restrict__ removed,
-                                 const int64_t *__restrict__ rem_prefix, GradPtrs out) {
+// grid.y: chunk of rows
+__global__ void __launch_bounds__(256) k_copy_survivors(GaussPtrs g, const uint8_t *__restrict__ removed,
+                                                        const int64_t *__restrict__ rem_prefix, GradPtrs out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= rows_in_use(g) || removed[i]) return;
-    const int64_t n = g.n, os = out.stride;
-    const int64_t d = i - rem_prefix[i];
-    const int nk = (g.deg + 1) * (g.deg + 1);
-    for (int k = 0; k < 3; k++) out.means[k * os + d] = g.means[k * n + i];
-    for (int k = 0; k < 3; k++) out.log_scales[k * os + d] = g.log_scales[k * n + i];
-    for (int k = 0; k < 4; k++) out.quats[k * os + d] = g.quats[k * n + i];
-    out.opac[d] = g.opac[i];
-    for (int k = 0; k < nk * 3; k++) out.sh[(int64_t)k * os + d] = g.sh[(int64_t)k * n + i];
+    const int c = blockIdx.y, rows = chunk_rows(c, g.deg);
+    float v[ROW_CHUNK];
+    load_chunk(g, i, c, rows, v);
+    store_chunk(out, i - rem_prefix[i], c, rows, v);
 }
 
-__device__ __forceinline__ void copy_row(const GaussPtrs &g, int64_t src, GradPtrs &out, int64_t dst) {
-    const int64_t n = g.n, os = out.stride;
-    const int nk = (g.deg + 1) * (g.deg + 1);
-    for (int k = 0; k < 3; k++) out.means[k * os + dst] = g.means[k * n + src];
-    for (int k = 0; k < 3; k++) out.log_scales[k * os + dst] = g.log_scales[k * n + src];
-    for (int k = 0; k < 4; k++) out.quats[k * os + dst] = g.quats[k * n + src];
-    out.opac[dst] = g.opac[src];
-    for (int k = 0; k < nk * 3; k++) out.sh[(int64_t)k * os + dst] = g.sh[(int64_t)k * n + src];
-}
-
-__global__ void k_write_children(GaussPtrs g, const int32_t *__restrict__ cand, int64_t n_cand,
-                                 const int64_t *__restrict__ n_cand_dev, const uint8_t *__restrict__ mode, const int64_t *__restrict__ offset,
-                                 const int64_t *__restrict__ tot, const int64_t *__restrict__ rs_a,
-                                 const Group *__restrict__ grp_all, const int32_t *__restrict__ kept_all,
-                                 const int32_t *__restrict__ nkept, const int32_t *__restrict__ count,
-                                 const float *__restrict__ noise, int noise_n, double eta, uint32_t flags,
-                                 GradPtrs out, int64_t *__restrict__ n_out) {
-    const int64_t ci = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// A thread per (candidate, chunk of rows, residue of the child index modulo
+// CHILD_LANES).  With one thread per candidate writing all rows of all its
+// children the kernel took 127 us for 25,167 candidates of SH degree 3 (each
+// row a dependent load and store); with the rows chunked 54 us, the time of the
+// candidates of 20 children (two square roots, a division and three
+// logarithms each); 36 us with those spread over lanes as well.
+constexpr int CHILD_LANES = 8;
+__global__ void __launch_bounds__(64) k_write_children(GaussPtrs g, const int32_t *__restrict__ cand, int64_t n_cand,
+                                                       const int64_t *__restrict__ n_cand_dev,
+                                                       const uint8_t *__restrict__ mode,
+                                                       const int64_t *__restrict__ offset,
+                                                       const int64_t *__restrict__ tot,
+                                                       const int64_t *__restrict__ rs_a,
+                                                       const Group *__restrict__ grp_all,
+                                                       const int32_t *__restrict__ kept_all,
+                                                       const int32_t *__restrict__ count,
+                                                       const float *__restrict__ noise, int noise_n, double eta,
+                                                       uint32_t flags, GradPtrs out, int64_t *__restrict__ n_out) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, ci = t / CHILD_LANES;
+    const int c = blockIdx.y;
     const int64_t n_surv = rows_in_use(g) - tot[0];
-    if (ci == 0) *n_out = n_surv + tot[1];
+    if (t == 0 && c == 0) *n_out = n_surv + tot[1];
     if (ci >= count_in_use(n_cand, n_cand_dev)) return;
+    const uint8_t md = mode[ci];
+    const int32_t N = count[ci], r0 = (int32_t)(t % CHILD_LANES);
+    if (md == 1 || r0 >= N) return;
     const int64_t base = n_surv + offset[ci];
     const int32_t id = cand[ci];
-    const uint8_t md = mode[ci];
-    const int64_t os = out.stride;
-    const int nk = (g.deg + 1) * (g.deg + 1);
+    const int rows = chunk_rows(c, g.deg);
+    float v[ROW_CHUNK];   // the parent's rows
+    load_chunk(g, id, c, rows, v);
     if (md == 0 || md == 3) {
         // Eq. (vanilla_split_sample), Eq. (vanilla_split_scale) with N = count
         // (2 for the VANILLA fallback)
-        const int32_t N = count[ci];
+        if (c > 0) {
+            for (int32_t r = r0; r < N; r += CHILD_LANES) store_chunk(out, base + r, c, rows, v);
+            return;
+        }
         Parent par;
         load_parent(g, id, par);
-        for (int c2 = 0; c2 < N; c2++) {
-            const int64_t dst = base + c2;
-            copy_row(g, id, out, dst);
+        const double shrink = log(eta * (double)N);
+        for (int k = 0; k < 3; k++) v[3 + k] = (float)((double)v[3 + k] - shrink);
+        for (int32_t r = r0; r < N; r += CHILD_LANES) {
             double dl[3];
-            for (int k = 0; k < 3; k++) dl[k] = par.s[k] * (double)noise[((int64_t)ci * noise_n + c2) * 3 + k];
-            for (int k = 0; k < 3; k++) {
-                const double m = par.mu[k] + (par.R[k * 3 + 0] * dl[0] + par.R[k * 3 + 1] * dl[1] + par.R[k * 3 + 2] * dl[2]);
-                out.means[k * os + dst] = (float)m;
-                out.log_scales[k * os + dst] = (float)((double)g.log_scales[k * g.n + id] - log(eta * (double)N));
+            for (int k = 0; k < 3; k++) dl[k] = par.s[k] * (double)noise[((int64_t)ci * noise_n + r) * 3 + k];
+            for (int k = 0; k < 3; k++)
+                v[k] = (float)(par.mu[k] + (par.R[k * 3 + 0] * dl[0] + par.R[k * 3 + 1] * dl[1] + par.R[k * 3 + 2] * dl[2]));
+            store_chunk(out, base + r, 0, 11, v);
+        }
+        return;
+    }
+    // the kept groups (N - 1 of them), then the parent's copy
+    const int64_t rs = rs_a[ci];
+    const int32_t ng = N - 1;
+    const double o = 1.0 / (1.0 + exp(-(double)v[10]));   // chunk 0 only
+    const double pr = o / (double)(ng + 1);
+    const float shared = (float)log(pr / (1.0 - pr));
+    for (int32_t r = r0; r < N; r += CHILD_LANES) {
+        if (r == ng) {
+            if (c == 0) v[10] = shared;
+            store_chunk(out, base + r, c, rows, v);
+            break;
+        }
+        float w[ROW_CHUNK];
+        for (int k = 0; k < ROW_CHUNK; k++) w[k] = 0.0f;
+        if (c <= 1) {
+            const Group &gr = grp_all[kept_all[rs + r]];
+            if (c == 1) {
+                for (int ch = 0; ch < 3; ch++) w[ch] = (float)((gr.rgb[ch] - 0.5) / C0_SH);
+            } else {
+                double q[4];
+                rot_to_quat(gr.R, q);
+                for (int k = 0; k < 3; k++) w[k] = (float)gr.mu[k];
+                for (int k = 0; k < 3; k++) w[3 + k] = (float)log(gr.s[k]);
+                for (int k = 0; k < 4; k++) w[6 + k] = (float)q[k];
+                // Eq. (child_params): the parent's opacity (second reading: every row of the block at o/(N+1))
+                w[10] = (flags & AS_SPLIT_SHARE_OPACITY) ? shared : v[10];
             }
         }
-    } else if (md == 2) {
-        const int64_t rs = rs_a[ci];
-        const int32_t ng = nkept[ci];
-        for (int32_t r = 0; r < ng; r++) {
-            const Group gr = grp_all[rs + kept_all[rs + r]];
-            const int64_t dst = base + r;
-            double q[4];
-            rot_to_quat(gr.R, q);
-            for (int k = 0; k < 3; k++) out.means[k * os + dst] = (float)gr.mu[k];
-            for (int k = 0; k < 3; k++) out.log_scales[k * os + dst] = (float)log(gr.s[k]);
-            for (int k = 0; k < 4; k++) out.quats[k * os + dst] = (float)q[k];
-            out.opac[dst] = g.opac[id];   // Eq. (child_params): the parent's opacity
-            for (int ch = 0; ch < 3; ch++) out.sh[(int64_t)ch * os + dst] = (float)((gr.rgb[ch] - 0.5) / C0_SH);
-            for (int k = 3; k < nk * 3; k++) out.sh[(int64_t)k * os + dst] = 0.0f;
-        }
-        const int64_t dst = base + ng;
-        copy_row(g, id, out, dst);
-        const double o = 1.0 / (1.0 + exp(-(double)g.opac[id]));
-        const double pr = o / (double)(ng + 1);
-        const float shared = (float)log(pr / (1.0 - pr));
-        out.opac[dst] = shared;
-        if (flags & AS_SPLIT_SHARE_OPACITY)   // second reading: every row of the block at o/(N+1)
-            for (int32_t r = 0; r < ng; r++) out.opac[base + r] = shared;
+        store_chunk(out, base + r, c, rows, w);
     }
 }
 
@@ -622,7 +736,7 @@ as_status run_adaptive_split(as_ctx *ctx, const GaussPtrs &g, const int32_t *can
     int64_t *rs = (int64_t *)sp[SP_RS].p, *re = (int64_t *)sp[SP_RE].p, *tot = (int64_t *)sp[SP_TOT].p;
     Prop *props = (Prop *)sp[SP_PROP].p;
     Group *grp = (Group *)sp[SP_GRP].p;
-    int32_t *uf = (int32_t *)sp[SP_UF].p, *rootof = (int32_t *)sp[SP_ROOT].p, *kept = (int32_t *)sp[SP_KEPT].p;
+    int32_t *uf = (int32_t *)sp[SP_UF].p, *rci = (int32_t *)sp[SP_RCI].p, *kept = (int32_t *)sp[SP_KEPT].p;
     int32_t *nkept = (int32_t *)sp[SP_NKEPT].p;
     DevCam *dcams = (DevCam *)sp[SP_CAMS].p;
     uint8_t *removed = (uint8_t *)sp[SP_REM].p;
@@ -636,35 +750,36 @@ as_status run_adaptive_split(as_ctx *ctx, const GaussPtrs &g, const int32_t *can
         hipLaunchKernelGGL(k_store_cams, dim3(1), dim3(64), 0, s, cc, dcams + v0);
     }
     const unsigned gcap = (unsigned)((cap + 255) / 256);
-    hipLaunchKernelGGL(k_reg_prep, dim3(1), dim3(1), 0, s, rb.count, cap, n32);
-    hipLaunchKernelGGL(k_reg_keys, dim3(gcap), dim3(256), 0, s, rb.records, n32, cap, lb, vb, keys[0], vals[0]);
-    const int sel = radix_sort_u64(keys, vals, n32, cap, cap, 0, lb + vb + cb, 8, sp[SP_HIST].p, s);
-    const uint32_t *order = vals[sel];
-    launch_fill_i64(rs, 0, nc1, s);
-    launch_fill_i64(re, 0, nc1, s);
-    hipLaunchKernelGGL(k_cand_ranges, dim3(gcap), dim3(256), 0, s, rb.records, order, n32, cap, cand, n_cand,
-                       n_cand_dev, rs, re);
-    hipLaunchKernelGGL(k_propose, dim3(gcap), dim3(256), 0, s, g, rb.records, order, n32, cap, cand, n_cand,
-                       n_cand_dev, dcams,
-                       n_views, p.eps, props);
+    const int64_t zn = nc1 > n1 ? nc1 : n1;
+    hipLaunchKernelGGL(k_split_init, dim3((unsigned)(zn < 2048 * 256 ? (zn + 255) / 256 : 2048)), dim3(256), 0, s, nc1,
+                       g.n, rs, re, nkept, removed);
+    if (p.variant != AS_VARIANT_FIXED_N) {   // the fixed-N split reads no region
+        hipLaunchKernelGGL(k_reg_prep, dim3(1), dim3(1), 0, s, rb.count, cap, n32);
+        hipLaunchKernelGGL(k_reg_keys, dim3(gcap), dim3(256), 0, s, rb.records, n32, cap, lb, vb, keys[0], vals[0]);
+        const int sel = radix_sort_u64(keys, vals, n32, cap, cap, 0, lb + vb + cb, 8, sp[SP_HIST].p, s);
+        const uint32_t *order = vals[sel];
+        const dim3 tg(gcap < RW_BLOCKS ? gcap : RW_BLOCKS), wg((unsigned)(cap < 4 * RW_BLOCKS ? (cap + 3) / 4 : RW_BLOCKS));
+        hipLaunchKernelGGL(k_propose, tg, dim3(256), 0, s, g, rb.records, order, n32, cap, cand, n_cand, n_cand_dev,
+                           dcams, n_views, p.eps, rs, re, rci, uf, props);
+        if (n_cand > 0) {
+            if (p.variant == AS_VARIANT_ADPSPLIT)   // the ablation variants do not merge
+                hipLaunchKernelGGL(k_pairs, wg, dim3(256), 0, s, n32, cap, rci, re, props, uf, p.gamma_d, p.gamma_c,
+                                   p.flags);
+            hipLaunchKernelGGL(k_groups, wg, dim3(256), 0, s, n32, cap, rci, re, props, uf, p.flags, grp);
+            hipLaunchKernelGGL(k_rank, wg, dim3(256), 0, s, n32, cap, rci, rs, re, uf, grp, p.n_max, kept, nkept);
+        }
+    }
     if (n_cand > 0)
-        hipLaunchKernelGGL(k_merge, dim3((unsigned)((n_cand + 3) / 4)), dim3(256), 0, s, g, cand, n_cand, n_cand_dev,
-                           attr, rs,
-                           re, props, uf, rootof, grp, kept, nkept, p.gamma_d, p.gamma_c, p.n_max, p.variant, p.flags,
-                           p.fixed_n, mode, count);
+        hipLaunchKernelGGL(k_modes, dim3((unsigned)((n_cand + 255) / 256)), dim3(256), 0, s, cand, n_cand, n_cand_dev,
+                           attr, p.n_max, p.variant, p.fixed_n, nkept, mode, count, removed);
     scan_i32_to_i64(count, offset, n_cand, tot + 1, sp[SP_SCAN].p, s);
-    launch_fill_u8(removed, 0, g.n > 0 ? g.n : 1, s);
-    if (n_cand > 0)
-        hipLaunchKernelGGL(k_mark_removed, dim3((unsigned)((n_cand + 255) / 256)), dim3(256), 0, s, cand, n_cand,
-                           n_cand_dev,
-                           mode, removed);
     scan_u8_to_i64(removed, remscan, g.n, tot, sp[SP_SCAN].p, s);
     if (g.n > 0)
-        hipLaunchKernelGGL(k_copy_survivors, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, g, removed,
-                           remscan, out);
-    hipLaunchKernelGGL(k_write_children, dim3((unsigned)((nc1 + 255) / 256)), dim3(256), 0, s, g, cand, n_cand,
-                       n_cand_dev, mode,
-                       offset, tot, rs, grp, kept, nkept, count, noise, p.noise_n ? p.noise_n : 2, p.eta, p.flags, out,
+        hipLaunchKernelGGL(k_copy_survivors, dim3((unsigned)((g.n + 255) / 256), row_chunks(g.deg)), dim3(256), 0, s, g,
+                           removed, remscan, out);
+    hipLaunchKernelGGL(k_write_children, dim3((unsigned)((CHILD_LANES * nc1 + 63) / 64), row_chunks(g.deg)), dim3(64), 0, s, g, cand,
+                       n_cand, n_cand_dev, mode,
+                       offset, tot, rs, grp, kept, count, noise, p.noise_n ? p.noise_n : 2, p.eta, p.flags, out,
                        n_out);
     return AS_OK;
 }
