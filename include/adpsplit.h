@@ -191,7 +191,7 @@ const char *as_version(void);
  * against the context's reservation and returns AS_ERR_CAPACITY (naming the
  * field to raise) when they exceed it. */
 typedef struct {
-    int64_t max_pixels;      /* largest W x H given to as_accumulate_error_stats */
+    int64_t max_pixels;      /* largest W x H given to as_accumulate_error_stats (of a batch: all views') */
     int64_t max_gaussians;   /* largest Gaussian set given to as_adaptive_split, as_densify_select,
                                 as_split_row_map and as_clone_prune */
     int64_t max_candidates;  /* largest candidate capacity given to as_adaptive_split */
@@ -340,6 +340,23 @@ as_status as_accumulate_error_stats(as_ctx *ctx, int32_t width, int32_t height, 
                                     const uint64_t *err_minmax, const int32_t *dom, const float *gt, int32_t view_id,
                                     int64_t n, const uint8_t *is_candidate, const as_split_params *params,
                                     as_region_buf *regions, int32_t *attr_count, void *stream);
+
+/* One view of as_accumulate_error_stats_batch. */
+typedef struct {
+    int32_t width, height, view_id;
+    const double *err;            /* [H][W] */
+    const uint64_t *err_minmax;   /* [2] */
+    const int32_t *dom;           /* [H][W] */
+    const float *gt;              /* [3][H][W] */
+} as_error_view;
+
+/* as_accumulate_error_stats of several views (host array, at most
+ * 16) in one set of launches: the results of the single calls in the order of
+ * the array.  AS_ERR_CAPACITY when the views' pixels together (each view's
+ * rounded up to a multiple of four) exceed the reservation's max_pixels. */
+as_status as_accumulate_error_stats_batch(as_ctx *ctx, int32_t n_views, const as_error_view *views, int64_t n,
+                                          const uint8_t *is_candidate, const as_split_params *params,
+                                          as_region_buf *regions, int32_t *attr_count, void *stream);
 
 /* For callers that cannot allocate device memory (code under graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): as_accumulate_error_stats

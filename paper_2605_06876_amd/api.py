@@ -98,7 +98,8 @@ EXPORTED = ("as_ctx_create", "as_ctx_destroy", "as_last_error", "as_version", "a
             "as_frame_bytes", "as_workspace_size", "as_frame_destroy", "as_frame_get_view", "as_frame_get_view_of",
             "as_frame_pair_count", "as_render",
             "as_render_backward", "as_render_batch", "as_render_backward_batch", "as_error_map",
-            "as_accumulate_error_stats", "as_accumulate_error_stats_noalloc", "as_adaptive_split", "as_set_tuning", "as_get_tuning", "as_timing_enable",
+            "as_accumulate_error_stats", "as_accumulate_error_stats_batch", "as_accumulate_error_stats_noalloc",
+            "as_adaptive_split", "as_set_tuning", "as_get_tuning", "as_timing_enable",
             "as_timing_read", "as_graph_begin", "as_graph_end", "as_graph_launch", "as_graph_destroy",
             "as_debug_sort_pairs", "as_debug_sort_u32", "as_debug_fp64_ops", "as_debug_blend_alpha", "as_debug_row_addressing", "as_adam_step", "as_l1_loss", "as_densify_select",
             "as_split_row_map", "as_clone_prune", "as_gather_rows", "as_reset_opacity")
@@ -602,6 +603,25 @@ def accumulate_error_stats(ctx, width, height, err, err_minmax, dom, gt, view_id
                                            addr(err_minmax), addr(dom), _ptr(gt), ctypes.c_int32(view_id),
                                            ctypes.c_int64(is_candidate.shape[0]), _ptr(is_candidate), ctypes.byref(p),
                                            ctypes.byref(rb), _ptr(attr_count), _stream(stream)))
+
+
+class _ErrorView(ctypes.Structure):
+    _fields_ = [("width", ctypes.c_int32), ("height", ctypes.c_int32), ("view_id", ctypes.c_int32),
+                ("err", ctypes.c_void_p), ("err_minmax", ctypes.c_void_p), ("dom", ctypes.c_void_p),
+                ("gt", ctypes.c_void_p)]
+
+
+def accumulate_error_stats_batch(ctx, views, is_candidate, params, regions, attr_count, stream=None):
+    """as_accumulate_error_stats_batch: views is a list of (width, height, err,
+    err_minmax, dom, gt, view_id), each as accumulate_error_stats takes them."""
+    addr = lambda x: x if isinstance(x, int) else _ptr(x).value
+    vs = (_ErrorView * max(len(views), 1))(*[_ErrorView(w, h, vid, addr(e), addr(mm), addr(d), _ptr(gt).value)
+                                             for w, h, e, mm, d, gt, vid in views])
+    p = params.struct()
+    rb = regions.struct()
+    _check(lib().as_accumulate_error_stats_batch(ctx.handle, ctypes.c_int32(len(views)), vs,
+                                                 ctypes.c_int64(is_candidate.shape[0]), _ptr(is_candidate),
+                                                 ctypes.byref(p), ctypes.byref(rb), _ptr(attr_count), _stream(stream)))
 
 
 NOALLOC_MAX_PIXELS = 1 << 20

@@ -931,25 +931,57 @@ as_status as_reset_opacity(as_ctx *ctx, as_gaussians_mut *g, double max_opacity,
     return launch_status(what);
 }
 
+static bool check_error_view(const as_error_view &v, const char *what) {
+    if (!v.err || !v.err_minmax || !v.dom || !v.gt || v.width < 1 || v.height < 1 || v.view_id < 0) {
+        as_set_error("%s: bad argument", what);
+        return false;
+    }
+    if ((int64_t)v.width * v.height > 0x7FFFFFFFll) { as_set_error("%s: image too large", what); return false; }
+    return true;
+}
+
+static bool check_error_call(const as_ctx *ctx, int64_t n, const uint8_t *is_candidate, const as_region_buf *regions,
+                             const int32_t *attr_count, const char *what) {
+    if (!ctx || !is_candidate || !regions || !regions->records || !regions->count || !attr_count || n < 1) {
+        as_set_error("%s: bad argument", what);
+        return false;
+    }
+    return true;
+}
+
+static as_status error_stats(as_ctx *ctx, int32_t n_views, const as_error_view *views, int64_t n,
+                             const uint8_t *is_candidate, const as_split_params *params, as_region_buf *regions,
+                             int32_t *attr_count, void *stream, const char *what) {
+    if (!check_error_call(ctx, n, is_candidate, regions, attr_count, what)) return AS_ERR_ARG;
+    for (int v = 0; v < n_views; v++)
+        if (!check_error_view(views[v], what)) return AS_ERR_ARG;
+    if (!check_params(params, what)) return AS_ERR_ARG;
+    as_status st;
+    {
+        StageTimer t(ctx, AS_STAGE_ERROR_STATS, (hipStream_t)stream);
+        st = run_error_stats(ctx, n_views, views, is_candidate, *params, *regions, attr_count, (hipStream_t)stream);
+    }
+    if (st != AS_OK) return st;
+    return launch_status(what);
+}
+
 as_status as_accumulate_error_stats(as_ctx *ctx, int32_t width, int32_t height, const double *err,
                                     const uint64_t *err_minmax, const int32_t *dom, const float *gt, int32_t view_id,
                                     int64_t n, const uint8_t *is_candidate, const as_split_params *params,
                                     as_region_buf *regions, int32_t *attr_count, void *stream) {
-    if (!ctx || !err || !err_minmax || !dom || !gt || !is_candidate || !regions || !regions->records ||
-        !regions->count || !attr_count || width < 1 || height < 1 || n < 1 || view_id < 0) {
-        as_set_error("as_accumulate_error_stats: bad argument");
+    const as_error_view v{width, height, view_id, err, err_minmax, dom, gt};
+    return error_stats(ctx, 1, &v, n, is_candidate, params, regions, attr_count, stream, "as_accumulate_error_stats");
+}
+
+as_status as_accumulate_error_stats_batch(as_ctx *ctx, int32_t n_views, const as_error_view *views, int64_t n,
+                                          const uint8_t *is_candidate, const as_split_params *params,
+                                          as_region_buf *regions, int32_t *attr_count, void *stream) {
+    const char *what = "as_accumulate_error_stats_batch";
+    if (!views || n_views < 1 || n_views > AS_MAX_VIEWS) {
+        as_set_error("%s: %d views (1 to %d)", what, n_views, AS_MAX_VIEWS);
         return AS_ERR_ARG;
     }
-    if ((int64_t)width * height > 0x7FFFFFFFll) { as_set_error("as_accumulate_error_stats: image too large"); return AS_ERR_ARG; }
-    if (!check_params(params, "as_accumulate_error_stats")) return AS_ERR_ARG;
-    as_status st;
-    {
-        StageTimer t(ctx, AS_STAGE_ERROR_STATS, (hipStream_t)stream);
-        st = run_error_stats(ctx, width, height, err, err_minmax, dom, gt, view_id, n, is_candidate, *params, *regions,
-                             attr_count, (hipStream_t)stream);
-    }
-    if (st != AS_OK) return st;
-    return launch_status("as_accumulate_error_stats");
+    return error_stats(ctx, n_views, views, n, is_candidate, params, regions, attr_count, stream, what);
 }
 
 as_status as_accumulate_error_stats_noalloc(as_ctx *ctx, int32_t width, int32_t height, const double *err,
@@ -957,20 +989,18 @@ as_status as_accumulate_error_stats_noalloc(as_ctx *ctx, int32_t width, int32_t 
                                             int32_t view_id, int64_t n, const uint8_t *is_candidate,
                                             const as_split_params *params, as_region_buf *regions,
                                             int32_t *attr_count, void *stream) {
-    if (!ctx || !err || !err_minmax || !dom || !gt || !is_candidate || !regions || !regions->records ||
-        !regions->count || !attr_count || width < 1 || height < 1 || n < 1 || view_id < 0) {
-        as_set_error("as_accumulate_error_stats_noalloc: bad argument");
+    const char *what = "as_accumulate_error_stats_noalloc";
+    const as_error_view v{width, height, view_id, err, err_minmax, dom, gt};
+    if (!check_error_call(ctx, n, is_candidate, regions, attr_count, what) || !check_error_view(v, what) ||
+        !check_params(params, what))
         return AS_ERR_ARG;
-    }
-    if (!check_params(params, "as_accumulate_error_stats_noalloc")) return AS_ERR_ARG;
     as_status st;
     {
         StageTimer t(ctx, AS_STAGE_ERROR_STATS, (hipStream_t)stream);
-        st = run_error_stats_noalloc(ctx, width, height, err, err_minmax, dom, gt, view_id, is_candidate, *params,
-                                     *regions, attr_count, (hipStream_t)stream);
+        st = run_error_stats_noalloc(ctx, v, is_candidate, *params, *regions, attr_count, (hipStream_t)stream);
     }
     if (st != AS_OK) return st;
-    return launch_status("as_accumulate_error_stats_noalloc");
+    return launch_status(what);
 }
 
 as_status as_adaptive_split(as_ctx *ctx, const as_gaussians *g, const int32_t *cand, int64_t n_cand,

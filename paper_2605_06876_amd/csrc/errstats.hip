@@ -9,26 +9,63 @@
 // roots are always the smallest pixel index of their component, so labels are
 // canonical and independent of thread scheduling: first inside 16x16 tiles in
 // LDS (fused with the classification and the erosion), then across tile
-// borders in global memory.  Kept regions take their record slots from per-block
-// counts scanned by one block, so records stay in ascending label order.
+// borders in global memory.  Kept regions take their record slots from the
+// counts of the pixel chunks before theirs, so records stay in ascending
+// (view, label) order.
+//
+// Every kernel covers the views of one call together (one view, or a batch):
+// a view of a megapixel keeps the chip busy for a few microseconds per pass,
+// less than a launch costs, so view by view the passes were launch-bound
+// (16 views of 1256x828: 70 us a view, 1120 us; 393 us in two batches of eight).
 #include <mutex>
 
 #include "internal.h"
 
 namespace {
 
-enum { ES_B, ES_LABEL, ES_MOM, ES_KEEP, ES_KIDX, ES_COUNT };
+constexpr int ES_MAX_BATCH = AS_MAX_VIEWS;   // views of one call
 
-// Bytes of each scratch slot for a view of P pixels: bands, labels, the six
-// integer moments per (root) pixel, keep flags, and two words per block of
-// 256 pixels.
+enum { ES_B, ES_LABEL, ES_MOM, ES_BASE, ES_KIDX, ES_COUNT };
+
+// Pixels per block of the region passes (four consecutive ones a thread).
+constexpr int ES_CHUNK = 4096;
+
+// Bytes of each scratch slot for views of P pixels in all (each view's pixels
+// rounded up to a multiple of four): bands, labels, the six integer moments
+// per (root) pixel, the record count on entry, and a word per chunk of pixels
+// (each view's last one may be partial).
 void es_need(int64_t P, size_t need[ES_COUNT]) {
     const size_t p = (size_t)(P > 0 ? P : 1);
     need[ES_B] = p;
     need[ES_LABEL] = p * 4;
     need[ES_MOM] = p * 48;
-    need[ES_KEEP] = p;
-    need[ES_KIDX] = (p + 255) / 256 * 8;
+    need[ES_BASE] = 8;
+    need[ES_KIDX] = ((p + 255) / 256 + ES_MAX_BATCH) * 8;
+}
+
+// One view of a call.  Its pixels, 16x16 tiles and chunks of ES_CHUNK pixels
+// are [pix0, ..), [tile0, ..) and [chunk0, ..) of the call's.
+struct EsView {
+    const double *err;
+    const unsigned long long *minmax;
+    const int32_t *dom;
+    const float *gt;
+    int64_t pix0;
+    int32_t W, H, tiles_x, tile0, chunk0, id;
+};
+struct EsBatch {
+    int32_t n, tiles, chunks;
+    EsView v[ES_MAX_BATCH];
+};
+__device__ __forceinline__ const EsView &view_of_es_tile(const EsBatch &b, int tile) {
+    int k = 0;
+    for (int q = 1; q < b.n; q++) k += tile >= b.v[q].tile0 ? 1 : 0;
+    return b.v[k];
+}
+__device__ __forceinline__ const EsView &view_of_es_chunk(const EsBatch &b, int chunk) {
+    int k = 0;
+    for (int q = 1; q < b.n; q++) k += chunk >= b.v[q].chunk0 ? 1 : 0;
+    return b.v[k];
 }
 
 __device__ __forceinline__ double dev_bits_to_double(unsigned long long b) { return __longlong_as_double((long long)b); }
@@ -36,10 +73,11 @@ __device__ __forceinline__ double dev_bits_to_double(unsigned long long b) { ret
 // Per-pixel L1 error and its range.  A bounded grid strides over the pixels
 // and each block issues one pair of range atomics: device-wide atomics on the
 // same two words serialise at the memory side, so there are few of them.
-__global__ void __launch_bounds__(256) k_error_map(int W, int H, const float *__restrict__ img,
+constexpr int EM_THREADS = 1024;
+__global__ void __launch_bounds__(EM_THREADS) k_error_map(int W, int H, const float *__restrict__ img,
                                                    const float *__restrict__ gt, double *__restrict__ err,
                                                    unsigned long long *__restrict__ minmax) {
-    __shared__ double s_mn[4], s_mx[4];
+    __shared__ double s_mn[EM_THREADS / 64], s_mx[EM_THREADS / 64];
     const int64_t P = (int64_t)W * H;
     double mn = __longlong_as_double(0x7ff0000000000000ll), mx = 0.0;
     for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < P; u += (int64_t)gridDim.x * blockDim.x) {
@@ -60,13 +98,18 @@ __global__ void __launch_bounds__(256) k_error_map(int W, int H, const float *__
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < 4; k++) {
+        for (int k = 1; k < EM_THREADS / 64; k++) {
             mn = fmin(mn, s_mn[k]);
             mx = fmax(mx, s_mx[k]);
         }
         atomicMin(&minmax[0], (unsigned long long)__double_as_longlong(mn));
         atomicMax(&minmax[1], (unsigned long long)__double_as_longlong(mx));
     }
+}
+
+__global__ void k_error_map_init(unsigned long long *__restrict__ minmax) {
+    minmax[0] = 0x7ff0000000000000ull;
+    minmax[1] = 0ull;
 }
 
 // E = normalised error (Eq. (l1map)), M = [E > tau], band B = floor((E - tau) L / (1 - tau)) clamped to L - 1
@@ -143,44 +186,73 @@ constexpr int ET = 16;      // pixel tile of the erosion / local components
 constexpr int EMAX_R = 8;   // erosion radii up to this use an LDS tile with halo
 constexpr int ES = ET + 2 * EMAX_R;
 
+// The smallest error that classify_px puts above tau, so that the halo
+// pixels take a compare instead of a division each: (e - emin) / (emax - emin)
+// rounds monotonically in e for a positive finite range, so {E > tau} is
+// {e >= threshold}.  Found by stepping from emin + tau (emax - emin), which is
+// within a few ulps of it.  False when there is no such threshold (an empty
+// or non-finite range, or a caller's range turned round): classify directly.
+__device__ bool error_threshold(double emin, double emax, double tau, double *thr) {
+    const double d = emax - emin;
+    if (!(d > 0.0) || !(d < __longlong_as_double(0x7ff0000000000000ll))) return false;
+    double c = emin + tau * d;
+    if (!(c >= 0.0)) return false;
+    int step = 0;
+    for (; step < 64 && !((c - emin) / d > tau); step++) c = __longlong_as_double(__double_as_longlong(c) + 1);
+    for (; step < 64 && c > 0.0; step++) {
+        const double below = __longlong_as_double(__double_as_longlong(c) - 1);
+        if (!((below - emin) / d > tau)) break;
+        c = below;
+    }
+    *thr = c;
+    return step < 64;
+}
+
 // M' = erosion of M with a square element of offsets [-lo, hi] per axis
 // ((2r+1)^2: lo = hi = r; pixels outside the image count as set); active = M'
 // and a candidate dominates the pixel.  Then the
 // 8-connected components of equal (D, B) inside the block's 16x16 tile, with
 // an LDS union-find whose roots are the smallest tile-local index, which is
 // also the smallest image index of the tile's part of the component.  Writes
-// label = image index of that root (-1 inactive).
-__global__ void __launch_bounds__(ET * ET) k_erode_ccl_local(int W, int H, int tiles_x, int r, int lo, int hi,
-                                                             const double *__restrict__ err,
-                                                             const unsigned long long *__restrict__ minmax, double tau,
-                                                             int L, const int32_t *__restrict__ dom,
-                                                             uint8_t *__restrict__ B,
+// label = image index of that root (-1 inactive) and, at active pixels, the
+// band.  A tile without a high-error pixel of a candidate stops after its own
+// pixels: the element holds the pixel itself, so nothing in it can be active.
+__global__ void __launch_bounds__(ET * ET) k_erode_ccl_local(const EsBatch eb, int r, int lo, int hi, double tau,
+                                                             int L, uint8_t *__restrict__ B_all,
                                                              const uint8_t *__restrict__ is_cand,
                                                              int32_t *__restrict__ attr,
-                                                             int32_t *__restrict__ label,
-                                                             unsigned long long *__restrict__ mom) {
+                                                             int32_t *__restrict__ label_all,
+                                                             unsigned long long *__restrict__ mom_all) {
     __shared__ uint8_t s_m[ES * ES];
     __shared__ uint8_t s_row[ES * ET];
     __shared__ int32_t s_par[ET * ET];
     __shared__ int32_t s_dom[ET * ET];
     __shared__ uint8_t s_b[ET * ET];
+    __shared__ double s_thr;
+    __shared__ int s_has_thr;
+    const EsView &ev = view_of_es_tile(eb, (int)blockIdx.x);
+    const int W = ev.W, H = ev.H;
+    const double *__restrict__ err = ev.err;
+    uint8_t *B = B_all + ev.pix0;
+    int32_t *label = label_all + ev.pix0;
+    unsigned long long *mom = mom_all + 6 * ev.pix0;
     const int tid = threadIdx.x;
-    const int tx = (int)blockIdx.x % tiles_x, ty = (int)blockIdx.x / tiles_x;
+    const int tile = (int)blockIdx.x - ev.tile0;
+    const int tx = tile % ev.tiles_x, ty = tile / ev.tiles_x;
     const int ox = tx * ET, oy = ty * ET;
     const int lx = tid % ET, ly = tid / ET, x = ox + lx, y = oy + ly;
     const bool inside = x < W && y < H;
     const int64_t u = (int64_t)y * W + x;
-    const double emin = dev_bits_to_double(minmax[0]), emax = dev_bits_to_double(minmax[1]);
+    const double emin = dev_bits_to_double(ev.minmax[0]), emax = dev_bits_to_double(ev.minmax[1]);
     uint8_t scratch_band;
-    // this pixel's class and band (written for the later passes), and the
-    // attribution count before erosion: attr[D] += 1 per high-error pixel
-    // dominated by a candidate, one atomic per wave when all hits share D
+    // this pixel's class and band, and the attribution count before erosion:
+    // attr[D] += 1 per high-error pixel dominated by a candidate, one atomic
+    // per wave when all hits share D
     uint8_t b = 0;
+    const int32_t d = inside ? ev.dom[u] : -1;
     const bool m_own = inside && classify_px(err[u], emin, emax, tau, L, &b);
-    if (inside) B[u] = b;
-    const int32_t d = inside ? dom[u] : -1;
+    const bool hit = m_own && d >= 0 && is_cand[d];
     {
-        const bool hit = m_own && d >= 0 && is_cand[d];
         const uint64_t hits = __ballot(hit);
         if (hits) {
             const int leader = __ffsll((unsigned long long)hits) - 1;
@@ -193,14 +265,33 @@ __global__ void __launch_bounds__(ET * ET) k_erode_ccl_local(int W, int H, int t
             }
         }
     }
+    if (!__syncthreads_or(hit)) {
+        if (inside) label[u] = -1;
+        return;
+    }
     bool e;
     if (r <= EMAX_R) {   // lo, hi <= r
+        if (tid == 0) s_has_thr = error_threshold(emin, emax, tau, &s_thr) ? 1 : 0;
         const int S = ET + lo + hi;
-        for (int i = tid; i < S * S; i += ET * ET) {
+        double h[(ES * ES) / (ET * ET)];   // the halo's errors, loaded before the threshold is known
+#pragma unroll
+        for (int q = 0; q < (ES * ES) / (ET * ET); q++) {
+            const int i = tid + q * ET * ET;
+            const int hx = i % S, hy = i / S, gx = ox + hx - lo, gy = oy + hy - lo;
+            h[q] = 0.0;
+            if (i < S * S && gx >= 0 && gy >= 0 && gx < W && gy < H) h[q] = err[(int64_t)gy * W + gx];
+        }
+        __syncthreads();
+        const bool has_thr = s_has_thr != 0;
+        const double thr = s_thr;
+#pragma unroll
+        for (int q = 0; q < (ES * ES) / (ET * ET); q++) {
+            const int i = tid + q * ET * ET;
+            if (i >= S * S) break;
             const int hx = i % S, hy = i / S, gx = ox + hx - lo, gy = oy + hy - lo;
             s_m[i] = (gx < 0 || gy < 0 || gx >= W || gy >= H)
                          ? 1
-                         : classify_px(err[(int64_t)gy * W + gx], emin, emax, tau, L, &scratch_band);
+                         : (has_thr ? h[q] >= thr : classify_px(h[q], emin, emax, tau, L, &scratch_band));
         }
         __syncthreads();
         for (int i = tid; i < S * ET; i += ET * ET) {   // AND along rows
@@ -248,6 +339,7 @@ __global__ void __launch_bounds__(ET * ET) k_erode_ccl_local(int W, int H, int t
     if (inside) {
         int32_t lab = -1;
         if (active) {
+            B[u] = b;
             const int rt = lds_find(s_par, tid);
             lab = (int32_t)((int64_t)(oy + rt / ET) * W + ox + rt % ET);
             // every component's final root (its smallest index) is the local
@@ -264,16 +356,20 @@ __global__ void __launch_bounds__(ET * ET) k_erode_ccl_local(int W, int H, int t
 // and right columns: 3 ET - 2 pixels, one thread each), with the global
 // union-find (roots are the smallest image index).
 constexpr int ES_BORDER = 3 * ET - 2;
-__global__ void k_ccl_border(int W, int H, int tiles_x, int64_t n_tiles, const int32_t *__restrict__ dom,
-                             const uint8_t *__restrict__ B, int32_t *label) {
+__global__ void k_ccl_border(const EsBatch eb, const uint8_t *__restrict__ B_all, int32_t *label_all) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_tiles * ES_BORDER) return;
-    const int64_t t = i / ES_BORDER;
-    const int j = (int)(i - t * ES_BORDER);
+    if (i >= (int64_t)eb.tiles * ES_BORDER) return;
+    const int64_t gt = i / ES_BORDER;
+    const int j = (int)(i - gt * ES_BORDER);
+    const EsView &ev = view_of_es_tile(eb, (int)gt);
+    const int W = ev.W, H = ev.H, t = (int)gt - ev.tile0;
+    const int32_t *__restrict__ dom = ev.dom;
+    const uint8_t *B = B_all + ev.pix0;
+    int32_t *label = label_all + ev.pix0;
     // j < ET: top row; then the left and the right column below it
     const int lx = j < ET ? j : (j < 2 * ET - 1 ? 0 : ET - 1);
     const int ly = j < ET ? 0 : (j < 2 * ET - 1 ? j - ET + 1 : j - 2 * ET + 2);
-    const int x = (int)(t % tiles_x) * ET + lx, y = (int)(t / tiles_x) * ET + ly;
+    const int x = (t % ev.tiles_x) * ET + lx, y = (t / ev.tiles_x) * ET + ly;
     if (x >= W || y >= H) return;
     const int64_t u = (int64_t)y * W + x;
     // a label's sign (active or not) never changes in this pass, only the
@@ -290,30 +386,34 @@ __global__ void k_ccl_border(int W, int H, int tiles_x, int64_t n_tiles, const i
         if (xx < 0 || yy < 0 || xx >= W) continue;
         if (xx / ET == x / ET && yy / ET == y / ET) continue;   // joined by the local pass
         const int64_t q = (int64_t)yy * W + xx;
-        if (dom[q] != d || B[q] != b || lv[q] < 0) continue;
+        if (lv[q] < 0 || dom[q] != d || B[q] != b) continue;    // an inactive pixel's band is not written
         uf_unite(label, (int32_t)u, (int32_t)q);
     }
 }
 
 // Exact integer moments A, Sx, Sy, Sxx, Sxy, Syy per component, stored at the
 // component's root pixel (the end of the pixel's parent chain: the labels no
-// longer change, so plain loads follow it).
-__global__ void k_moments(int W, int H, const int32_t *__restrict__ label, unsigned long long *__restrict__ mom) {
-    const int64_t P = (int64_t)W * H;
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// longer change, so plain loads follow it).  One block per tile.
+__global__ void __launch_bounds__(ET * ET) k_moments(const EsBatch eb, const int32_t *__restrict__ label_all,
+                                                     unsigned long long *__restrict__ mom_all) {
+    const EsView &ev = view_of_es_tile(eb, (int)blockIdx.x);
+    const int32_t *label = label_all + ev.pix0;
+    unsigned long long *mom = mom_all + 6 * ev.pix0;
+    const int tile = (int)blockIdx.x - ev.tile0;
+    const int64_t x = (int64_t)(tile % ev.tiles_x) * ET + threadIdx.x % ET;
+    const int64_t y = (int64_t)(tile / ev.tiles_x) * ET + threadIdx.x / ET;
     int64_t s = -1;
     int64_t v[6] = {0, 0, 0, 0, 0, 0};
-    if (u < P) {
-        int32_t l = label[u];
+    if (x < ev.W && y < ev.H) {
+        int32_t l = label[y * ev.W + x];
         if (l >= 0) {
             for (int32_t p = label[l]; p != l; p = label[l]) l = p;
             s = l;
-            const int64_t x = u % W, y = u / W;
             v[0] = 1; v[1] = x; v[2] = y; v[3] = x * x; v[4] = x * y; v[5] = y * y;
         }
     }
-    // one set of atomics per distinct region among the wave's 64 pixels (a
-    // wave spans one image row segment, which few regions cross)
+    // one set of atomics per distinct region among the wave's 64 pixels (four
+    // row segments of a tile, which few regions cross)
     uint64_t pending = __ballot(s >= 0);
     while (pending) {
         const int leader = __ffsll((unsigned long long)pending) - 1;
@@ -331,47 +431,41 @@ __global__ void k_moments(int W, int H, const int32_t *__restrict__ label, unsig
     }
 }
 
-// A component is kept (Eq. (min_region_area)) at its root pixel.
-// Kept components (roots with area >= m_min) and the number per block of 256
-// pixels.
-__global__ void __launch_bounds__(256) k_region_keep(int64_t P, const int32_t *__restrict__ label,
-                                                     const unsigned long long *__restrict__ mom, int m_min,
-                                                     uint8_t *__restrict__ keep, int64_t *__restrict__ part) {
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool k = u < P && label[u] == (int32_t)u && (int64_t)mom[u * 6] >= (int64_t)m_min;
-    if (u < P) keep[u] = k;
-    const int c = __syncthreads_count(k);
-    if (threadIdx.x == 0) part[blockIdx.x] = c;
+// The kept components (Eq. (min_region_area)) among a thread's four pixels of
+// a chunk: bit j for pixel u + j, a root whose area is at least m_min.
+__device__ __forceinline__ uint32_t kept_bits(const EsView &ev, const int32_t *label, const unsigned long long *mom,
+                                              int64_t u, int m_min) {
+    const int64_t P = (int64_t)ev.W * ev.H;
+    if (u >= P) return 0u;
+    // the chunk's labels are 16-byte aligned (pix0 is a multiple of four) and
+    // the slot holds each view's pixels rounded up to a multiple of four
+    const int4 l = *reinterpret_cast<const int4 *>(label + u);
+    const int32_t lab[4] = {l.x, l.y, l.z, l.w};
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        if (u + j < P && lab[j] == (int32_t)(u + j) && (int64_t)mom[(u + j) * 6] >= (int64_t)m_min) bits |= 1u << j;
+    return bits;
 }
 
-// One block: the per-block counts become the first record slot of each
-// block (after the records already in the buffer), and the buffer's count
-// advances by the total.
-__global__ void __launch_bounds__(1024) k_region_slots(int64_t *__restrict__ part, int64_t nblk,
-                                                       int64_t *__restrict__ count) {
-    __shared__ int64_t s_w[16];
-    __shared__ int64_t s_carry;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (tid == 0) s_carry = *count;
+// Kept components per chunk; the first block also notes the records already
+// in the buffer, which the next pass counts on while it advances the count.
+__global__ void __launch_bounds__(ES_CHUNK / 4) k_region_keep(const EsBatch eb, const int32_t *__restrict__ label_all,
+                                                              const unsigned long long *__restrict__ mom_all, int m_min,
+                                                              const int64_t *__restrict__ count,
+                                                              int64_t *__restrict__ base, int64_t *__restrict__ part) {
+    __shared__ int s_w[ES_CHUNK / 256];
+    const EsView &ev = view_of_es_chunk(eb, (int)blockIdx.x);
+    const int64_t u = (int64_t)((int)blockIdx.x - ev.chunk0) * ES_CHUNK + 4 * (int64_t)threadIdx.x;
+    int c = __popc(kept_bits(ev, label_all + ev.pix0, mom_all + 6 * ev.pix0, u, m_min));
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = c;
     __syncthreads();
-    for (int64_t b0 = 0; b0 < nblk; b0 += 1024) {
-        const int64_t b = b0 + tid;
-        const int64_t v = b < nblk ? part[b] : 0;
-        int64_t inc = v;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int64_t t = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += t;
-        }
-        if (lane == 63) s_w[w] = inc;
-        __syncthreads();
-        int64_t pre = s_carry;
-        for (int k = 0; k < w; k++) pre += s_w[k];
-        if (b < nblk) part[b] = pre + inc - v;
-        __syncthreads();
-        if (tid == 1023) s_carry = pre + inc;
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < ES_CHUNK / 256; k++) c += s_w[k];
+        part[blockIdx.x] = c;
+        if (blockIdx.x == 0) *base = *count;
     }
-    if (tid == 0) *count = s_carry;
 }
 
 __device__ __forceinline__ double central_moment(int64_t A, int64_t sab, int64_t sa, int64_t sb) {
@@ -383,76 +477,101 @@ __device__ __forceinline__ double central_moment(int64_t A, int64_t sab, int64_t
     return dnum / (dA * dA);
 }
 
-// One record per kept component, in ascending label order: a block's first
-// slot (k_region_slots) plus the kept pixels before this one in the block.
-__global__ void __launch_bounds__(256) k_region_emit(int W, int H, int view, const unsigned long long *__restrict__ mom,
-                                                     const uint8_t *__restrict__ keep, const int64_t *__restrict__ slot,
-                                                     const int32_t *__restrict__ dom, const uint8_t *__restrict__ B,
-                                                     const float *__restrict__ gt, as_region *__restrict__ out,
-                                                     int64_t out_cap) {
-    __shared__ int s_w[4];
-    const int64_t P = (int64_t)W * H;
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool k = s < P && keep[s];
+// One record per kept component, in ascending (view, label) order.  A block
+// sums the chunk counts before its own (at most a few loads a thread, less
+// than a launch of a scan between the passes) and the last one advances the
+// buffer's count.
+__global__ void __launch_bounds__(ES_CHUNK / 4) k_region_emit(const EsBatch eb, const int32_t *__restrict__ label_all,
+                                                              const unsigned long long *__restrict__ mom_all, int m_min,
+                                                              const uint8_t *__restrict__ B_all,
+                                                              const int64_t *__restrict__ base,
+                                                              const int64_t *__restrict__ part,
+                                                              as_region *__restrict__ out, int64_t out_cap,
+                                                              int64_t *__restrict__ count) {
+    constexpr int NW = ES_CHUNK / 256;
+    __shared__ int64_t s_pre[NW];
+    __shared__ int s_w[NW];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t bal = __ballot(k);
-    if (lane == 0) s_w[w] = __popcll(bal);
+    const int blk = (int)blockIdx.x;
+    const EsView &ev = view_of_es_chunk(eb, blk);
+    const int32_t *label = label_all + ev.pix0;
+    const unsigned long long *mom = mom_all + 6 * ev.pix0;
+    const int64_t u = (int64_t)(blk - ev.chunk0) * ES_CHUNK + 4 * (int64_t)threadIdx.x;
+    int64_t pre = 0;
+    for (int b = (int)threadIdx.x; b < blk; b += ES_CHUNK / 4) pre += part[b];
+    for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
+    const uint32_t bits = kept_bits(ev, label, mom, u, m_min);
+    int inc = __popc(bits);
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
+    }
+    if (lane == 63) s_w[w] = inc;
+    if (lane == 0) s_pre[w] = pre;
     __syncthreads();
-    int before = __popcll(bal & ((1ull << lane) - 1ull));
-    for (int q = 0; q < w; q++) before += s_w[q];
-    if (!k) return;
-    const int64_t pos = slot[blockIdx.x] + before;
-    if (pos >= out_cap) return;
-    as_region r;
-    const int32_t root = (int32_t)s;
-    r.cand = dom[root];
-    r.view = view;
-    r.label = root;
-    r.band = B[root];
-    r.pad0 = 0;
-    const int64_t A = (int64_t)mom[s * 6 + 0];
-    r.area = (int32_t)A;
-    r.sx = (int64_t)mom[s * 6 + 1];
-    r.sy = (int64_t)mom[s * 6 + 2];
-    r.sxx = (int64_t)mom[s * 6 + 3];
-    r.sxy = (int64_t)mom[s * 6 + 4];
-    r.syy = (int64_t)mom[s * 6 + 5];
-    const double dA = (double)A;
-    r.cx = (double)r.sx / dA + 0.5;
-    r.cy = (double)r.sy / dA + 0.5;
-    const double cxx = central_moment(A, r.sxx, r.sx, r.sx) + 1.0 / 12.0;
-    const double cxy = central_moment(A, r.sxy, r.sx, r.sy);
-    const double cyy = central_moment(A, r.syy, r.sy, r.sy) + 1.0 / 12.0;
-    r.cov[0] = cxx;
-    r.cov[1] = cxy;
-    r.cov[2] = cyy;
-    const double half_tr = 0.5 * (cxx + cyy);
-    const double half_dif = 0.5 * (cxx - cyy);
-    const double disc = sqrt(half_dif * half_dif + cxy * cxy);
-    const double l1 = half_tr + disc, l2 = half_tr - disc;
-    double ex, ey;
-    if (disc == 0.0) {
-        ex = 1.0; ey = 0.0;
-    } else if (half_dif >= 0.0) {
-        ex = half_dif + disc; ey = cxy;
-    } else {
-        ex = cxy; ey = -half_dif + disc;
+    int64_t first = *base;
+    for (int k = 0; k < NW; k++) first += s_pre[k];
+    if (blk == (int)gridDim.x - 1 && threadIdx.x == 0) *count = first + part[blk];
+    for (int k = 0; k < w; k++) first += s_w[k];
+    first += inc - __popc(bits);
+    const int W = ev.W;
+    const int64_t P = (int64_t)W * ev.H;
+    const uint8_t *B = B_all + ev.pix0;
+    for (uint32_t left = bits; left; left &= left - 1, first++) {
+        const int64_t s = u + __ffs((int)left) - 1;
+        const int64_t pos = first;
+        if (pos >= out_cap) return;
+        as_region r;
+        const int32_t root = (int32_t)s;
+        r.cand = ev.dom[root];
+        r.view = ev.id;
+        r.label = root;
+        r.band = B[root];
+        r.pad0 = 0;
+        const int64_t A = (int64_t)mom[s * 6 + 0];
+        r.area = (int32_t)A;
+        r.sx = (int64_t)mom[s * 6 + 1];
+        r.sy = (int64_t)mom[s * 6 + 2];
+        r.sxx = (int64_t)mom[s * 6 + 3];
+        r.sxy = (int64_t)mom[s * 6 + 4];
+        r.syy = (int64_t)mom[s * 6 + 5];
+        const double dA = (double)A;
+        r.cx = (double)r.sx / dA + 0.5;
+        r.cy = (double)r.sy / dA + 0.5;
+        const double cxx = central_moment(A, r.sxx, r.sx, r.sx) + 1.0 / 12.0;
+        const double cxy = central_moment(A, r.sxy, r.sx, r.sy);
+        const double cyy = central_moment(A, r.syy, r.sy, r.sy) + 1.0 / 12.0;
+        r.cov[0] = cxx;
+        r.cov[1] = cxy;
+        r.cov[2] = cyy;
+        const double half_tr = 0.5 * (cxx + cyy);
+        const double half_dif = 0.5 * (cxx - cyy);
+        const double disc = sqrt(half_dif * half_dif + cxy * cxy);
+        const double l1 = half_tr + disc, l2 = half_tr - disc;
+        double ex, ey;
+        if (disc == 0.0) {
+            ex = 1.0; ey = 0.0;
+        } else if (half_dif >= 0.0) {
+            ex = half_dif + disc; ey = cxy;
+        } else {
+            ex = cxy; ey = -half_dif + disc;
+        }
+        const double en = sqrt(ex * ex + ey * ey);
+        ex = ex / en;
+        ey = ey / en;
+        if (ex < 0.0 || (ex == 0.0 && ey < 0.0)) {
+            ex = -ex;
+            ey = -ey;
+        }
+        r.e1[0] = ex;
+        r.e1[1] = ey;
+        r.sigma1 = sqrt(l1);
+        r.sigma2 = sqrt(l2 > 0.0 ? l2 : 0.0);
+        const int64_t gx = (int64_t)floor(r.cx), gy = (int64_t)floor(r.cy);
+        for (int ch = 0; ch < 3; ch++) r.rgb[ch] = ev.gt[ch * P + gy * W + gx];
+        r.pad1 = 0.f;
+        out[pos] = r;
     }
-    const double en = sqrt(ex * ex + ey * ey);
-    ex = ex / en;
-    ey = ey / en;
-    if (ex < 0.0 || (ex == 0.0 && ey < 0.0)) {
-        ex = -ex;
-        ey = -ey;
-    }
-    r.e1[0] = ex;
-    r.e1[1] = ey;
-    r.sigma1 = sqrt(l1);
-    r.sigma2 = sqrt(l2 > 0.0 ? l2 : 0.0);
-    const int64_t gx = (int64_t)floor(r.cx), gy = (int64_t)floor(r.cy);
-    for (int ch = 0; ch < 3; ch++) r.rgb[ch] = gt[ch * P + gy * W + gx];
-    r.pad1 = 0.f;
-    out[pos] = r;
 }
 
 
@@ -460,12 +579,11 @@ __global__ void __launch_bounds__(256) k_region_emit(int W, int H, int view, con
 
 void launch_error_map(int W, int H, const float *image, const float *gt, double *err, uint64_t *minmax, hipStream_t s) {
     const int64_t P = (int64_t)W * H;
-    launch_fill_u64(minmax, 0x7ff0000000000000ull, 1, s);
-    launch_fill_u64(minmax + 1, 0ull, 1, s);
+    hipLaunchKernelGGL(k_error_map_init, dim3(1), dim3(1), 0, s, reinterpret_cast<unsigned long long *>(minmax));
     if (P == 0) return;
-    int64_t g = (P + 255) / 256;
-    if (g > 512) g = 512;
-    hipLaunchKernelGGL(k_error_map, dim3((unsigned)g), dim3(256), 0, s, W, H, image, gt, err,
+    int64_t g = (P + EM_THREADS - 1) / EM_THREADS;
+    if (g > 256) g = 256;
+    hipLaunchKernelGGL(k_error_map, dim3((unsigned)g), dim3(EM_THREADS), 0, s, W, H, image, gt, err,
                        reinterpret_cast<unsigned long long *>(minmax));
 }
 
@@ -492,30 +610,56 @@ struct EsScratch {
     uint8_t *B;
     int32_t *label;
     unsigned long long *mom;
-    uint8_t *keep;
-    int64_t *kidx;   // per block of 256 pixels: kept roots, then first record slot
+    int64_t *base;   // the record count on entry
+    int64_t *part;   // per chunk of pixels: kept components
 };
 
-void es_launch(const EsScratch &sc, int W, int H, const double *err, const uint64_t *minmax, const int32_t *dom,
-               const float *gt, int view, const uint8_t *is_cand, const as_split_params &p, as_region_buf &rb,
-               int32_t *attr, hipStream_t s);
+void es_launch(const EsScratch &sc, const EsBatch &eb, const uint8_t *is_cand, const as_split_params &p,
+               as_region_buf &rb, int32_t *attr, hipStream_t s);
+
+// The kernels' view table; returns the pixels the scratch has to hold.
+int64_t es_batch(int n, const as_error_view *views, EsBatch &eb) {
+    int64_t pix = 0, tiles = 0, chunks = 0;
+    for (int k = 0; k < n; k++) {
+        const as_error_view &a = views[k];
+        const int64_t P = (int64_t)a.width * a.height;
+        EsView &v = eb.v[k];
+        v.err = a.err;
+        v.minmax = reinterpret_cast<const unsigned long long *>(a.err_minmax);
+        v.dom = a.dom;
+        v.gt = a.gt;
+        v.pix0 = (pix + 3) & ~(int64_t)3;
+        v.W = a.width;
+        v.H = a.height;
+        v.tiles_x = (a.width + ET - 1) / ET;
+        v.tile0 = (int32_t)tiles;
+        v.chunk0 = (int32_t)chunks;
+        v.id = a.view_id;
+        pix = v.pix0 + P;
+        tiles += (int64_t)v.tiles_x * ((a.height + ET - 1) / ET);
+        chunks += (P + ES_CHUNK - 1) / ES_CHUNK;
+    }
+    eb.n = n;
+    eb.tiles = (int32_t)tiles;
+    eb.chunks = (int32_t)chunks;
+    return pix;
+}
 }  // namespace
 
-as_status run_error_stats(as_ctx *ctx, int W, int H, const double *err, const uint64_t *minmax, const int32_t *dom,
-                          const float *gt, int view, int64_t n, const uint8_t *is_cand, const as_split_params &p,
-                          as_region_buf &rb, int32_t *attr, hipStream_t s) {
-    (void)n;
-    const int64_t P = (int64_t)W * H;
-    if (P == 0) return AS_OK;
-    if (P > ctx->res.max_pixels) {
-        as_set_error("as_accumulate_error_stats: a %dx%d view needs max_pixels >= %lld in as_ctx_reserve (reserved "
-                     "%lld)", W, H, (long long)P, (long long)ctx->res.max_pixels);
+as_status run_error_stats(as_ctx *ctx, int n_views, const as_error_view *views, const uint8_t *is_cand,
+                          const as_split_params &p, as_region_buf &rb, int32_t *attr, hipStream_t s) {
+    EsBatch eb;
+    const int64_t pix = es_batch(n_views, views, eb);
+    if (pix > ctx->res.max_pixels) {
+        as_set_error("as_accumulate_error_stats: %d view%s (the first %dx%d) need max_pixels >= %lld in as_ctx_reserve "
+                     "(reserved %lld)", n_views, n_views == 1 ? "" : "s", views[0].width, views[0].height,
+                     (long long)pix, (long long)ctx->res.max_pixels);
         return AS_ERR_CAPACITY;
     }
     DevBuf *es = ctx->es;
     const EsScratch sc{(uint8_t *)es[ES_B].p, (int32_t *)es[ES_LABEL].p, (unsigned long long *)es[ES_MOM].p,
-                       (uint8_t *)es[ES_KEEP].p, (int64_t *)es[ES_KIDX].p};
-    es_launch(sc, W, H, err, minmax, dom, gt, view, is_cand, p, rb, attr, s);
+                       (int64_t *)es[ES_BASE].p, (int64_t *)es[ES_KIDX].p};
+    es_launch(sc, eb, is_cand, p, rb, attr, s);
     return AS_OK;
 }
 
@@ -537,8 +681,8 @@ constexpr size_t es_slot(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 constexpr size_t ES_NA_PIX = (size_t)AS_NOALLOC_MAX_PIXELS;
 constexpr size_t ES_NA_OFF_LABEL = es_slot(ES_NA_PIX);
 constexpr size_t ES_NA_OFF_MOM = ES_NA_OFF_LABEL + es_slot(ES_NA_PIX * 4);
-constexpr size_t ES_NA_OFF_KEEP = ES_NA_OFF_MOM + es_slot(ES_NA_PIX * 48);
-constexpr size_t ES_NA_OFF_KIDX = ES_NA_OFF_KEEP + es_slot(ES_NA_PIX);
+constexpr size_t ES_NA_OFF_BASE = ES_NA_OFF_MOM + es_slot(ES_NA_PIX * 48);
+constexpr size_t ES_NA_OFF_KIDX = ES_NA_OFF_BASE + es_slot(ES_NA_PIX);
 constexpr size_t ES_NA_BYTES = ES_NA_OFF_KIDX + es_slot((ES_NA_PIX + 255) / 256 * 8);
 constexpr int ES_NA_MAX_DEVICES = 64;
 
@@ -561,16 +705,15 @@ hipError_t errstats_noalloc_init(int device) {
 
 size_t errstats_noalloc_bytes() { return ES_NA_BYTES; }
 
-as_status run_error_stats_noalloc(as_ctx *ctx, int W, int H, const double *err, const uint64_t *minmax,
-                                  const int32_t *dom, const float *gt, int view, const uint8_t *is_cand,
+as_status run_error_stats_noalloc(as_ctx *ctx, const as_error_view &view, const uint8_t *is_cand,
                                   const as_split_params &p, as_region_buf &rb, int32_t *attr, hipStream_t s) {
+    const int W = view.width, H = view.height;
     const int64_t P = (int64_t)W * H;
     if (P > (int64_t)AS_NOALLOC_MAX_PIXELS) {
         as_set_error("as_accumulate_error_stats_noalloc: a %dx%d view has %lld pixels, above the static scratch's "
                      "maximum of %lld", W, H, (long long)P, (long long)AS_NOALLOC_MAX_PIXELS);
         return AS_ERR_CAPACITY;
     }
-    if (P == 0) return AS_OK;
     unsigned char *base = nullptr;
     if (ctx->device >= 0 && ctx->device < ES_NA_MAX_DEVICES) {
         std::lock_guard<std::mutex> lock(g_na_mutex);
@@ -581,40 +724,30 @@ as_status run_error_stats_noalloc(as_ctx *ctx, int W, int H, const double *err, 
         return AS_ERR_STATE;
     }
     const EsScratch sc{base, (int32_t *)(base + ES_NA_OFF_LABEL), (unsigned long long *)(base + ES_NA_OFF_MOM),
-                       base + ES_NA_OFF_KEEP, (int64_t *)(base + ES_NA_OFF_KIDX)};
-    es_launch(sc, W, H, err, minmax, dom, gt, view, is_cand, p, rb, attr, s);
+                       (int64_t *)(base + ES_NA_OFF_BASE), (int64_t *)(base + ES_NA_OFF_KIDX)};
+    EsBatch eb;
+    es_batch(1, &view, eb);
+    es_launch(sc, eb, is_cand, p, rb, attr, s);
     return AS_OK;
 }
 
 namespace {
-void es_launch(const EsScratch &sc, int W, int H, const double *err, const uint64_t *minmax, const int32_t *dom,
-               const float *gt, int view, const uint8_t *is_cand, const as_split_params &p, as_region_buf &rb,
-               int32_t *attr, hipStream_t s) {
-    const int64_t P = (int64_t)W * H;
-    uint8_t *B = sc.B;
-    uint8_t *keep = sc.keep;
-    int32_t *label = sc.label;
-    int64_t *kidx = sc.kidx;
-    unsigned long long *mom = sc.mom;
-    const unsigned grid = (unsigned)((P + 255) / 256);
-    const int tiles_x = (W + ET - 1) / ET, tiles = tiles_x * ((H + ET - 1) / ET);
-
+void es_launch(const EsScratch &sc, const EsBatch &eb, const uint8_t *is_cand, const as_split_params &p,
+               as_region_buf &rb, int32_t *attr, hipStream_t s) {
     // element offsets: [-r, r] per axis, or a side of r + 1 (flag)
     const int lo = (p.flags & AS_SPLIT_ERODE_SIDE) ? p.r_erode / 2 : p.r_erode;
     const int hi = (p.flags & AS_SPLIT_ERODE_SIDE) ? p.r_erode - p.r_erode / 2 : p.r_erode;
+    const dim3 tiles((unsigned)eb.tiles), chunks((unsigned)eb.chunks), cb(ES_CHUNK / 4);
     // classification, attribution, erosion and the tile-local components in one pass
-    hipLaunchKernelGGL(k_erode_ccl_local, dim3(tiles), dim3(ET * ET), 0, s, W, H, tiles_x, p.r_erode, lo, hi, err,
-                       reinterpret_cast<const unsigned long long *>(minmax), p.tau_l1, p.L, dom, B, is_cand, attr,
-                       label, mom);
-    const int64_t nb = ((int64_t)tiles * ES_BORDER + 255) / 256;
-    hipLaunchKernelGGL(k_ccl_border, dim3((unsigned)nb), dim3(256), 0, s, W, H, tiles_x, (int64_t)tiles, dom, B,
-                       label);
-    hipLaunchKernelGGL(k_moments, dim3(grid), dim3(256), 0, s, W, H, label, mom);
-    // kept roots, one record slot per block (advancing the buffer's count), records
-    hipLaunchKernelGGL(k_region_keep, dim3(grid), dim3(256), 0, s, P, label, mom, p.m_min, keep, kidx);
-    hipLaunchKernelGGL(k_region_slots, dim3(1), dim3(1024), 0, s, kidx, (int64_t)grid, rb.count);
-    hipLaunchKernelGGL(k_region_emit, dim3(grid), dim3(256), 0, s, W, H, view, mom, keep, kidx, dom, B, gt,
-                       rb.records, rb.capacity);
+    hipLaunchKernelGGL(k_erode_ccl_local, tiles, dim3(ET * ET), 0, s, eb, p.r_erode, lo, hi, p.tau_l1, p.L, sc.B,
+                       is_cand, attr, sc.label, sc.mom);
+    const int64_t nb = ((int64_t)eb.tiles * ES_BORDER + 255) / 256;
+    hipLaunchKernelGGL(k_ccl_border, dim3((unsigned)nb), dim3(256), 0, s, eb, sc.B, sc.label);
+    hipLaunchKernelGGL(k_moments, tiles, dim3(ET * ET), 0, s, eb, sc.label, sc.mom);
+    // kept roots per chunk, then their records (advancing the buffer's count)
+    hipLaunchKernelGGL(k_region_keep, chunks, cb, 0, s, eb, sc.label, sc.mom, p.m_min, rb.count, sc.base, sc.part);
+    hipLaunchKernelGGL(k_region_emit, chunks, cb, 0, s, eb, sc.label, sc.mom, p.m_min, sc.B, sc.base, sc.part,
+                       rb.records, rb.capacity, rb.count);
 }
 }  // namespace
 

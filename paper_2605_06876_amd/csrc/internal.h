@@ -305,16 +305,15 @@ void launch_error_map(int W, int H, const float *image, const float *gt, double 
 // Scratch of the error statistics for views of up to max_pixels pixels.
 size_t errstats_reserve_bytes(int64_t max_pixels);
 hipError_t errstats_reserve(as_ctx *ctx, int64_t max_pixels);
-as_status run_error_stats(as_ctx *ctx, int W, int H, const double *err, const uint64_t *minmax, const int32_t *dom,
-                          const float *gt, int view, int64_t n, const uint8_t *is_cand, const as_split_params &p,
-                          as_region_buf &rb, int32_t *attr, hipStream_t s);
+// The error statistics of up to AS_MAX_VIEWS views, appended in view order.
+as_status run_error_stats(as_ctx *ctx, int n_views, const as_error_view *views, const uint8_t *is_cand,
+                          const as_split_params &p, as_region_buf &rb, int32_t *attr, hipStream_t s);
 // The no-allocation variant: scratch from a static device array whose address
 // on each device errstats_noalloc_init records (called by as_ctx_create with
 // the device current).
 hipError_t errstats_noalloc_init(int device);
 size_t errstats_noalloc_bytes();
-as_status run_error_stats_noalloc(as_ctx *ctx, int W, int H, const double *err, const uint64_t *minmax,
-                                  const int32_t *dom, const float *gt, int view, const uint8_t *is_cand,
+as_status run_error_stats_noalloc(as_ctx *ctx, const as_error_view &view, const uint8_t *is_cand,
                                   const as_split_params &p, as_region_buf &rb, int32_t *attr, hipStream_t s);
 
 // adaptive split (split.hip)

@@ -29,6 +29,8 @@ import torch
 
 from . import api
 
+STAT_PIXELS = 1 << 23   # pixels of one batched error-statistics call (424 MiB of scratch)
+
 
 class DensifyStep:
     """Buffers and the call sequence of a densification of up to n rows (the
@@ -99,9 +101,12 @@ class DensifyStep:
             self.frame = api.BatchFrame.for_views(ctx, n, self.views[:k], key_cap=key_cap_per_entry * n * k,
                                                   auto_grow=False, forward_only=True)
             self.images = [torch.empty(3, H, W, dtype=torch.float32, **dev) for _ in range(k)]
+        # views whose error statistics run together: their scratch is 53 bytes a
+        # pixel, so no more than STAT_PIXELS pixels unless one view alone has more
+        px = max([(v.width * v.height + 3) // 4 * 4 for v in self.views] + [1])
+        self.stat_views = max(1, min(len(self.views), api.MAX_VIEWS, STAT_PIXELS // px))
         # set-up: the context scratch of every call of the step (none allocates)
-        ctx.reserve(max_gaussians=max(self.cap2, 1), max_candidates=self.cc,
-                    max_pixels=max([v.width * v.height for v in self.views] + [1]),
+        ctx.reserve(max_gaussians=max(self.cap2, 1), max_candidates=self.cc, max_pixels=self.stat_views * px,
                     max_regions=self.regions.capacity, max_views=max(len(self.views), 1))
 
     def set_views(self, views, gts):
@@ -126,10 +131,12 @@ class DensifyStep:
                 views = self.views[c0:c0 + api.MAX_VIEWS]
                 gts = self.gts[c0:c0 + api.MAX_VIEWS]
                 api.render_batch(ctx, g, views, self.frame, gts=gts, images=self.images[:len(views)])
-                for j in range(len(views)):
-                    mp = self.frame.device_maps(j)
-                    api.accumulate_error_stats(ctx, W, H, mp["err"], mp["err_minmax"], mp["dom"], gts[j], c0 + j,
-                                               is_cand, self.params, self.regions, self.attr[:n])
+                maps = [self.frame.device_maps(j) for j in range(len(views))]
+                for j0 in range(0, len(views), self.stat_views):
+                    api.accumulate_error_stats_batch(
+                        ctx, [(W, H, maps[j]["err"], maps[j]["err_minmax"], maps[j]["dom"], gts[j], c0 + j)
+                              for j in range(j0, min(j0 + self.stat_views, len(views)))],
+                        is_cand, self.params, self.regions, self.attr[:n])
         # 1. clones appended after the originals: candidate ids stay valid
         api.clone_prune(ctx, g, clone, None, 0.0, 0.0, out=self.g1, state_src=self.st1, n_out=self.n1)
         # 2. the split of the candidates, on the clone output's rows in use
