@@ -152,7 +152,7 @@ void frame_buffers(as_frame *f, bool keys_only, V &&visit) {
     dbuf(f->scan_tmp, scan_tmp_bytes(ent));
     // forward dispatch slots: the tiles, or 32 per 8 bins of 32 (at most 2 tile + 64)
     arr(&f->ranges, tile * 2); arr(&f->tile_order, 2 * tile + 64); arr(&f->queue, 2); arr(&f->tile_work, tile);
-    arr(&f->tile_order_bwd, tile); arr(&f->tile_hi, tile); arr(&f->n_items, 1);
+    arr(&f->tile_hi, tile); arr(&f->n_items, 1); arr(&f->order_table, (int64_t)order_table_words(tile));
     arr(&f->bwd_items, tile * (AS_CK_MAX + 1) * 2);
     arr(&f->tile_err, tile * 2);
     if (!(f->flags & AS_FRAME_FORWARD_ONLY)) arr(&f->ckpt, tile * AS_CK_MAX * 256 * 4);
@@ -669,7 +669,7 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
         StageTimer t(ctx, AS_STAGE_RANGES, s);
         launch_ranges(f->keys[sel], f->n_keys + 1, f->key_cap, bins, vt, f->ranges, s);
         f->use_order = ctx->longest_first;
-        if (f->use_order) launch_tile_order(f->ranges, vt, f->tile_order, s);
+        if (f->use_order) launch_tile_order(f, vt, s);
     }
     const BlendLaunch bl{ctx->lds_batch, ctx->persistent, ctx->n_cu, ctx->block_cull};
     {
@@ -683,9 +683,7 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
         f->g2d_zero = launch_blend_fwd(f, f->vals[sel], f->use_order ? f->tile_order : nullptr, bl, vt, gi, im, s,
                                        zg ? f->grad2d : nullptr, 9 * n) && zg;
         f->g2d_zero_capture = g_capture_id;
-        // the reverse pass's cost per tile follows its contributors, which only
-        // the forward pass knows: order the reverse dispatch by them
-        launch_after_fwd(f, vt, gi, f->use_order, s);
+        if (gt) launch_view_err(f, vt, gi, s);
     }
     const as_status st = launch_status("as_render");
     if (st != AS_OK) return st;
@@ -743,8 +741,11 @@ as_status as_render_backward_batch(as_ctx *ctx, const as_gaussians *g, as_frame 
         if (!f->g2d_zero || f->g2d_zero_capture != g_capture_id)
             launch_fill_u32(reinterpret_cast<uint32_t *>(f->grad2d), 0u, 9 * ents, s);
         f->g2d_zero = 0;
-        launch_blend_bwd(f, f->vals[f->sorted_sel], f->use_order ? f->tile_order_bwd : nullptr, bl, vt, dl,
-                         f->grad2d, s);
+        // the work items, heaviest first by the contributors the forward
+        // counted; listed by every reverse pass, since the render may since
+        // have been replayed from a graph
+        launch_bwd_items(f, f->use_order, s);
+        launch_blend_bwd(f, f->vals[f->sorted_sel], bl, vt, dl, f->grad2d, s);
     }
     {
         StageTimer t(ctx, AS_STAGE_PROJECT_BWD, s);

@@ -849,6 +849,103 @@ __global__ void __launch_bounds__(BWD_BLOCK) k_blend_bwd(const uint32_t *__restr
     }
 }
 
+// Counting sorts of the tiles into dispatch order.  Every block orders 1024
+// units (tiles or bins) and needs the class counts of the units before its own
+// and of all.  Up to ORDER_ALONE units every block counts them all itself
+// (CNT = false, one launch); above that a first launch writes each block's
+// counts to a table and the ordering blocks sum its rows (CNT = true): counting
+// all units takes a block about 0.5 us per 1024, the second launch 4 us.  One
+// block for everything, as this was, took 63 us for the list lengths and 271 us
+// for the work of 66,176 tiles (16 views of 1256x828), now 10 us each.  Lanes
+// count into ORDER_COPIES copies of the counters, since most units share few
+// classes.
+constexpr int ORDER_BLOCK = 1024, ORDER_COPIES = 8, ORDER_ALONE = 5 * 1024;
+constexpr int ORDER_NC_LEN = 33, ORDER_NC_WORK = 129;   // list length and work classes
+
+template <int NC>
+struct OrderShared {
+    uint32_t bef[ORDER_COPIES][NC], aft[ORDER_COPIES][NC], off[NC];
+};
+
+// Counts the units [0, n): unit u adds weight(u) to class cls(u); with own =
+// true only this block's units.
+template <int NC, typename Cls, typename Wgt>
+__device__ __forceinline__ void class_count(OrderShared<NC> &sh, int n, bool own, Cls cls, Wgt weight) {
+    const int tid = threadIdx.x, u0 = (int)blockIdx.x * ORDER_BLOCK;
+    for (int i = tid; i < ORDER_COPIES * NC; i += ORDER_BLOCK) (&sh.bef[0][0])[i] = (&sh.aft[0][0])[i] = 0u;
+    __syncthreads();
+    const int end = own && u0 + ORDER_BLOCK < n ? u0 + ORDER_BLOCK : n;
+#pragma unroll 4
+    for (int u = (own ? u0 : 0) + tid; u < end; u += ORDER_BLOCK) {
+        const uint32_t wt = weight(u);
+        const int c = cls(u);
+        if (wt) atomicAdd(u < u0 ? &sh.bef[tid % ORDER_COPIES][c] : &sh.aft[tid % ORDER_COPIES][c], wt);
+    }
+    __syncthreads();
+}
+
+// This block's counts as a row of the table.
+template <int NC>
+__device__ __forceinline__ void class_row(const OrderShared<NC> &sh, uint32_t *__restrict__ table) {
+    for (int c = threadIdx.x; c < NC; c += ORDER_BLOCK) {
+        uint32_t v = 0;
+        for (int q = 0; q < ORDER_COPIES; q++) v += sh.aft[q][c];
+        table[(int64_t)blockIdx.x * NC + c] = v;
+    }
+}
+
+// The table's rows summed: those before this block's, and the rest.
+template <int NC>
+__device__ __forceinline__ void class_rows_in(OrderShared<NC> &sh, const uint32_t *__restrict__ table) {
+    const int c = threadIdx.x % 256, q = threadIdx.x / 256;   // four threads a class, each every fourth row
+    static_assert(NC <= 256, "a class per thread");
+    if (c < NC) {
+        uint32_t bef = 0, aft = 0;
+#pragma unroll 4
+        for (int r = q; r < (int)gridDim.x; r += ORDER_BLOCK / 256) {
+            const uint32_t v = table[(int64_t)r * NC + c];
+            if (r < (int)blockIdx.x) bef += v;
+            else aft += v;
+        }
+        sh.bef[q][c] = bef;
+        sh.aft[q][c] = aft;
+        sh.bef[q + 4][c] = sh.aft[q + 4][c] = 0u;
+    }
+    static_assert(ORDER_COPIES == 8, "two copies a row quarter");
+    __syncthreads();
+}
+
+// The exclusive prefix over the classes, by the block's first wave: off[c]
+// gets the first slot of this block's units of class c; returns the total.
+template <int NC>
+__device__ __forceinline__ uint32_t class_offsets(OrderShared<NC> &sh) {
+    constexpr int PER = (NC + 63) / 64;
+    const int lane = threadIdx.x;
+    uint32_t bef[PER], all[PER], sum = 0;
+    for (int k = 0; k < PER; k++) {
+        const int c = PER * lane + k;
+        bef[k] = all[k] = 0u;
+        if (c < NC)
+            for (int q = 0; q < ORDER_COPIES; q++) {
+                bef[k] += sh.bef[q][c];
+                all[k] += sh.bef[q][c] + sh.aft[q][c];
+            }
+        sum += all[k];
+    }
+    uint32_t inc = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
+        if (lane >= o) inc += t;
+    }
+    uint32_t run = inc - sum;
+    for (int k = 0; k < PER; k++) {
+        const int c = PER * lane + k;
+        if (c < NC) sh.off[c] = run + bef[k];
+        run += all[k];
+    }
+    return (uint32_t)__shfl((int)inc, 63, 64);
+}
+
 // Tiles ordered by descending list length (33 length classes with power-of-two
 // boundaries), so the longest lists are dispatched first.  The order within a
 // class is irrelevant: every tile's outputs are independent of the others.
@@ -858,67 +955,68 @@ __global__ void __launch_bounds__(BWD_BLOCK) k_blend_bwd(const uint32_t *__restr
 // 32 (q / 8) + q % 8 + 8 i (i = 0..3), which the hardware hands to one XCD
 // (workgroups go to the eight XCDs round robin), so the bin's records are
 // fetched from HBM once into that XCD's L2.  Slots of tiles past the image
-// edge hold ORDER_NONE and their blocks do nothing.
-__global__ void __launch_bounds__(1024) k_tile_order(const uint32_t *__restrict__ ranges, const ViewTable vt,
-                                                     uint32_t *__restrict__ order) {
-    __shared__ uint32_t s_cnt[33], s_off[33];
-    const int tid = threadIdx.x;
-    const bool bins = vt.bin_shift != 4;
-    const int n = bins ? vt.bin_base[vt.n_views] : vt.tile_base[vt.n_views];
-    // the first tile of unit u (a tile, or the top-left tile of a bin) and
-    // the tile of quadrant i of bin u (-1 past the image edge)
-    auto quad = [&](int u, int i) -> int {
-        if (!bins) return i == 0 ? u : -1;
+// edge, and of the ranks past the last bin, hold ORDER_NONE and their blocks do nothing.
+struct ListOrder {
+    const uint32_t *ranges;
+    const ViewTable &vt;
+    __device__ int units() const { return vt.bin_shift != 4 ? vt.bin_base[vt.n_views] : vt.tile_base[vt.n_views]; }
+    // the tile of quadrant i of unit u (a tile, or a bin; -1 past the image edge)
+    __device__ int quad(int u, int i) const {
+        if (vt.bin_shift == 4) return i == 0 ? u : -1;
         const int v = view_of_bin(vt, u);
         const int lb = u - vt.bin_base[v], bx = lb % vt.bins_x[v], by = lb / vt.bins_x[v];
         const int tx_n = vt.tiles_x[v], ty_n = (vt.tile_base[v + 1] - vt.tile_base[v]) / tx_n;
         const int tx = 2 * bx + (i & 1), ty = 2 * by + (i >> 1);
         return tx < tx_n && ty < ty_n ? vt.tile_base[v] + ty * tx_n + tx : -1;
-    };
-    auto cls_of = [&](int u) {
-        const int t = quad(u, 0);
-        const uint32_t len = ranges[2 * t + 1] - ranges[2 * t];
-        return len ? 32 - __clz(len) : 0;   // 0..32, larger = longer
-    };
-    constexpr int TO_LDS_UNITS = 16384;   // classes of up to this many units are kept for the scatter pass
-    __shared__ uint8_t s_cls[TO_LDS_UNITS];
-    const bool keep = n <= TO_LDS_UNITS;
-    if (tid < 33) s_cnt[tid] = 0;
-    if (bins)
-        for (int i = tid; i < order_slots(vt); i += blockDim.x) order[i] = ORDER_NONE;
-    __syncthreads();
-    for (int u = tid; u < n; u += blockDim.x) {
-        const int c = cls_of(u);
-        if (keep) s_cls[u] = (uint8_t)c;
-        atomicAdd(&s_cnt[32 - c], 1u);
     }
-    __syncthreads();
-    if (tid < 64) {   // exclusive prefix over the 33 classes, one wave
-        const uint32_t v = tid < 33 ? s_cnt[tid] : 0u;
-        uint32_t inc = v;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
-            if (tid >= o) inc += t;
-        }
-        if (tid < 33) s_off[tid] = inc - v;
+    // 0..32, longest lists first
+    __device__ int cls(int u) const {
+        const uint2 r = reinterpret_cast<const uint2 *>(ranges)[quad(u, 0)];
+        const uint32_t len = r.y - r.x;
+        return len ? __clz(len) : 32;
     }
+};
+
+__global__ void __launch_bounds__(ORDER_BLOCK) k_tile_order_count(const uint32_t *__restrict__ ranges,
+                                                                  const ViewTable vt, uint32_t *__restrict__ table) {
+    __shared__ OrderShared<ORDER_NC_LEN> sh;
+    const ListOrder lo{ranges, vt};
+    class_count(sh, lo.units(), true, [&](int u) { return lo.cls(u); }, [](int) { return 1u; });
+    class_row(sh, table);
+}
+
+template <bool CNT>
+__global__ void __launch_bounds__(ORDER_BLOCK) k_tile_order(const uint32_t *__restrict__ ranges, const ViewTable vt,
+                                                            const uint32_t *__restrict__ table,
+                                                            uint32_t *__restrict__ order) {
+    __shared__ OrderShared<ORDER_NC_LEN> sh;
+    const ListOrder lo{ranges, vt};
+    const bool bins = vt.bin_shift != 4;
+    const int n = lo.units(), tid = threadIdx.x;
+    if constexpr (CNT) class_rows_in(sh, table);
+    else class_count(sh, n, false, [&](int u) { return lo.cls(u); }, [](int) { return 1u; });
+    if (tid < 64) (void)class_offsets(sh);
     __syncthreads();
-    for (int u = tid; u < n; u += blockDim.x) {
-        const uint32_t q = atomicAdd(&s_off[32 - (keep ? (int)s_cls[u] : cls_of(u))], 1u);
-        if (!bins) {
-            order[q] = (uint32_t)u;
-            continue;
-        }
-        for (int i = 0; i < 4; i++) {
-            const int t = quad(u, i);
-            if (t >= 0) order[32 * (q >> 3) + (q & 7) + 8 * i] = (uint32_t)t;
-        }
+    const int u = (int)blockIdx.x * ORDER_BLOCK + tid;
+    if (bins) {
+        const int n8 = (n + 7) / 8 * 8;   // ranks of the last group of eight that no bin takes
+        if (blockIdx.x == gridDim.x - 1 && tid < n8 - n)
+            for (int i = 0; i < 4; i++) order[32 * ((n + tid) >> 3) + ((n + tid) & 7) + 8 * i] = ORDER_NONE;
+    }
+    if (u >= n) return;
+    const uint32_t q = atomicAdd(&sh.off[lo.cls(u)], 1u);
+    if (!bins) {
+        order[q] = (uint32_t)u;
+        return;
+    }
+    for (int i = 0; i < 4; i++) {
+        const int t = lo.quad(u, i);
+        order[32 * (q >> 3) + (q & 7) + 8 * i] = t >= 0 ? (uint32_t)t : ORDER_NONE;
     }
 }
 
-// Tiles ordered by descending work (contributors summed over the tile's
-// pixels), in 129 classes: four per octave, so tiles of similar cost share a
-// class and the heaviest are dispatched first.
+// Class of a tile's work (contributors summed over its pixels): four per
+// octave, so tiles of similar cost share a class.
 __device__ __forceinline__ int work_class(uint32_t wk) {
     if (wk == 0) return 0;
     const int lg = 31 - __clz(wk);
@@ -926,221 +1024,99 @@ __device__ __forceinline__ int work_class(uint32_t wk) {
     return 1 + 4 * lg + frac;   // 1..128
 }
 
-// Exclusive prefix over the 129 work classes (s_cnt -> s_off), by the
-// block's first wave, three classes per lane.
-__device__ __forceinline__ void class_prefix129(const uint32_t *s_cnt, uint32_t *s_off, int tid) {
-    if (tid >= 64) return;
-    uint32_t v[3], sum = 0;
-    for (int k = 0; k < 3; k++) {
-        const int c = 3 * tid + k;
-        v[k] = c < 129 ? s_cnt[c] : 0u;
-        sum += v[k];
+// The error range of each view with a target, one block a view: minimum and
+// maximum over its tiles' ranges (device-wide atomics on one word per view
+// would serialise at the memory side).
+__global__ void __launch_bounds__(1024) k_view_err(const ViewTable vt, const ViewImagesC gts,
+                                                   const unsigned long long *__restrict__ tile_err,
+                                                   unsigned long long *__restrict__ minmax) {
+    __shared__ unsigned long long s_mn[16], s_mx[16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, v = (int)blockIdx.x;
+    if (!gts.p[v]) return;
+    unsigned long long mn = 0x7ff0000000000000ull, mx = 0ull;
+#pragma unroll 4
+    for (int t = vt.tile_base[v] + tid; t < vt.tile_base[v + 1]; t += 1024) {
+        const unsigned long long a = tile_err[2 * t], b = tile_err[2 * t + 1];
+        mn = a < mn ? a : mn;
+        mx = b > mx ? b : mx;
     }
-    uint32_t inc = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
-        if (tid >= o) inc += t;
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long a = __shfl_xor(mn, o, 64), b = __shfl_xor(mx, o, 64);
+        mn = a < mn ? a : mn;
+        mx = b > mx ? b : mx;
     }
-    uint32_t run = inc - sum;
-    for (int k = 0; k < 3; k++) {
-        const int c = 3 * tid + k;
-        if (c < 129) s_off[c] = run;
-        run += v[k];
+    if (lane == 0) {
+        s_mn[w] = mn;
+        s_mx[w] = mx;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        for (int k = 1; k < 16; k++) {
+            mn = s_mn[k] < mn ? s_mn[k] : mn;
+            mx = s_mx[k] > mx ? s_mx[k] : mx;
+        }
+        minmax[2 * v] = mn;
+        minmax[2 * v + 1] = mx;
     }
 }
 
-// After the forward blend, in one block: the error range of each view with a
-// target (minimum and maximum over its tiles' ranges; device-wide atomics on
-// one word per view would serialise at the memory side), the reverse pass's
-// dispatch order (tiles by descending contributor count, 129 classes: four
-// per octave, heaviest first) and its work items: the tiles in that order,
-// each expanded into its segments (one without checkpoints), by a block-wide
-// exclusive scan of the segment counts.
-__global__ void __launch_bounds__(1024) k_after_fwd(const ViewTable vt, const ViewImagesC gts,
-                                                    const unsigned long long *__restrict__ tile_err,
-                                                    unsigned long long *__restrict__ minmax,
-                                                    const uint32_t *__restrict__ work, int order_on,
-                                                    uint32_t *__restrict__ order, const uint32_t *__restrict__ ranges,
-                                                    const uint32_t *__restrict__ tile_hi, uint32_t seg_len, int ck,
-                                                    uint32_t *__restrict__ items, uint32_t *__restrict__ n_items) {
-    // up to AF_LDS_TILES tiles, the ordered tiles and their segment counts
-    // are also kept in LDS, so the item expansion gathers nothing from memory
-    constexpr int AF_LDS_TILES = 16384;
-    __shared__ uint16_t s_tile[AF_LDS_TILES];
-    __shared__ uint8_t s_nseg[AF_LDS_TILES];
-    __shared__ uint32_t s_cnt[129], s_off[129];
-    __shared__ unsigned long long s_mn[16], s_mx[16];
-    __shared__ uint32_t s_w[16];
-    __shared__ uint32_t s_carry;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int tiles = vt.tile_base[vt.n_views];
-    const bool in_lds = order_on && tiles <= AF_LDS_TILES;
+// The reverse pass's work items: every tile's segments (one without
+// checkpoints), tiles by descending work (129 classes, heaviest first) or, with
+// order_on = 0, in tile order.  Launched by the reverse pass, so renders that
+// none follows do not pay for it.
+struct WorkOrder {
+    const uint32_t *work, *ranges, *tile_hi;
+    uint32_t seg_len;
+    int ck, order_on;
     // segments of a tile: one per checkpointed batch boundary it crosses, plus one
-    auto nseg_from = [&](uint32_t start, uint32_t hi) -> uint32_t {
+    __device__ uint32_t nseg(int t) const {
+        const uint32_t start = ranges[2 * t], hi = tile_hi[t];
         if (hi <= start) return 0u;
         return ck ? min((hi - start + seg_len - 1) / seg_len, (uint32_t)AS_CK_MAX + 1u) : 1u;
-    };
-    auto nseg_of = [&](uint32_t tile) -> uint32_t { return nseg_from(ranges[2 * tile], tile_hi[tile]); };
-    // Up to AF_K tiles per thread (8192 tiles) every per-tile input (error
-    // range, work, range and end of list) is loaded once, all loads issued
-    // before the first use, and the passes below work from registers; the
-    // loops over memory that larger counts take wait for one load round trip
-    // per iteration in each pass.
-    constexpr int AF_K = 8;
-    constexpr unsigned long long ERR_HI = 0x7ff0000000000000ull;
-    if (tiles <= AF_K * 1024) {
-        unsigned long long ea[AF_K], eb[AF_K];
-        uint32_t wk[AF_K], r0[AF_K], rh[AF_K];
-#pragma unroll
-        for (int k = 0; k < AF_K; k++) {
-            const int t = tid + 1024 * k;
-            const bool in = t < tiles;
-            ea[k] = in ? tile_err[2 * t] : ERR_HI;
-            eb[k] = in ? tile_err[2 * t + 1] : 0ull;
-            wk[k] = in && order_on ? work[t] : 0u;
-            r0[k] = in && in_lds ? ranges[2 * t] : 0u;
-            rh[k] = in && in_lds ? tile_hi[t] : 0u;
-        }
-        for (int v = 0; v < vt.n_views; v++) {
-            if (!gts.p[v]) continue;
-            unsigned long long mn = ERR_HI, mx = 0ull;
-#pragma unroll
-            for (int k = 0; k < AF_K; k++) {
-                const int t = tid + 1024 * k;
-                if (t >= vt.tile_base[v] && t < vt.tile_base[v + 1]) {
-                    mn = ea[k] < mn ? ea[k] : mn;
-                    mx = eb[k] > mx ? eb[k] : mx;
-                }
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const unsigned long long a = __shfl_xor(mn, o, 64), b = __shfl_xor(mx, o, 64);
-                mn = a < mn ? a : mn;
-                mx = b > mx ? b : mx;
-            }
-            if (lane == 0) {
-                s_mn[w] = mn;
-                s_mx[w] = mx;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                for (int k = 1; k < 16; k++) {
-                    mn = s_mn[k] < mn ? s_mn[k] : mn;
-                    mx = s_mx[k] > mx ? s_mx[k] : mx;
-                }
-                minmax[2 * v] = mn;
-                minmax[2 * v + 1] = mx;
-            }
-            __syncthreads();
-        }
-        if (order_on) {
-            if (tid < 129) s_cnt[tid] = 0;
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < AF_K; k++)
-                if (tid + 1024 * k < tiles) atomicAdd(&s_cnt[128 - work_class(wk[k])], 1u);
-            __syncthreads();
-            class_prefix129(s_cnt, s_off, tid);
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < AF_K; k++) {
-                const int t = tid + 1024 * k;
-                if (t < tiles) {
-                    const uint32_t slot = atomicAdd(&s_off[128 - work_class(wk[k])], 1u);
-                    order[slot] = (uint32_t)t;
-                    if (in_lds) {
-                        s_tile[slot] = (uint16_t)t;
-                        s_nseg[slot] = (uint8_t)nseg_from(r0[k], rh[k]);
-                    }
-                }
-            }
-        }
-    } else {
-        for (int v = 0; v < vt.n_views; v++) {
-            if (!gts.p[v]) continue;
-            unsigned long long mn = 0x7ff0000000000000ull, mx = 0ull;
-            for (int t = vt.tile_base[v] + tid; t < vt.tile_base[v + 1]; t += 1024) {
-                const unsigned long long a = tile_err[2 * t], b = tile_err[2 * t + 1];
-                mn = a < mn ? a : mn;
-                mx = b > mx ? b : mx;
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const unsigned long long a = __shfl_xor(mn, o, 64), b = __shfl_xor(mx, o, 64);
-                mn = a < mn ? a : mn;
-                mx = b > mx ? b : mx;
-            }
-            if (lane == 0) {
-                s_mn[w] = mn;
-                s_mx[w] = mx;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                for (int k = 1; k < 16; k++) {
-                    mn = s_mn[k] < mn ? s_mn[k] : mn;
-                    mx = s_mx[k] > mx ? s_mx[k] : mx;
-                }
-                minmax[2 * v] = mn;
-                minmax[2 * v + 1] = mx;
-            }
-            __syncthreads();
-        }
-        if (order_on) {
-            if (tid < 129) s_cnt[tid] = 0;
-            __syncthreads();
-            for (int t = tid; t < tiles; t += 1024) atomicAdd(&s_cnt[128 - work_class(work[t])], 1u);
-            __syncthreads();
-            class_prefix129(s_cnt, s_off, tid);
-            __syncthreads();
-            for (int t = tid; t < tiles; t += 1024) {
-                const uint32_t ns = in_lds ? nseg_of((uint32_t)t) : 0u;
-                const uint32_t slot = atomicAdd(&s_off[128 - work_class(work[t])], 1u);
-                order[slot] = (uint32_t)t;
-                if (in_lds) {
-                    s_tile[slot] = (uint16_t)t;
-                    s_nseg[slot] = (uint8_t)ns;
-                }
-            }
-        }
     }
-    if (tid == 0) s_carry = 0;
-    __syncthreads();   // also: the order written above is visible to the whole block
-    // four consecutive dispatch slots per thread, 4096 per block-wide scan
-    for (int base = 0; base < tiles; base += 4096) {
-        uint32_t tl[4], ns[4], sum = 0;
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int i = base + 4 * tid + k;
-            tl[k] = 0u;
-            ns[k] = 0u;
-            if (i < tiles) {
-                if (in_lds) {
-                    tl[k] = s_tile[i];
-                    ns[k] = s_nseg[i];
-                } else {
-                    tl[k] = order_on ? order[i] : (uint32_t)i;
-                    ns[k] = nseg_of(tl[k]);
-                }
-            }
-            sum += ns[k];
-        }
-        uint32_t incl = sum;
+    __device__ int cls(int t) const { return order_on ? 128 - work_class(work[t]) : 0; }
+};
+
+__global__ void __launch_bounds__(ORDER_BLOCK) k_bwd_items_count(int tiles, const WorkOrder wo,
+                                                                 uint32_t *__restrict__ table) {
+    __shared__ OrderShared<ORDER_NC_WORK> sh;
+    class_count(sh, tiles, true, [&](int t) { return wo.cls(t); }, [&](int t) { return wo.nseg(t); });
+    class_row(sh, table);
+}
+
+template <bool CNT>
+__global__ void __launch_bounds__(ORDER_BLOCK) k_bwd_items(int tiles, const WorkOrder wo,
+                                                           const uint32_t *__restrict__ table,
+                                                           uint32_t *__restrict__ items,
+                                                           uint32_t *__restrict__ n_items) {
+    __shared__ OrderShared<ORDER_NC_WORK> sh;
+    __shared__ uint32_t s_w[ORDER_BLOCK / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if constexpr (CNT) class_rows_in(sh, table);
+    else class_count(sh, tiles, false, [&](int t) { return wo.cls(t); }, [&](int t) { return wo.nseg(t); });
+    if (tid < 64) {
+        const uint32_t all = class_offsets(sh);
+        if (tid == 0 && blockIdx.x == 0) *n_items = all;
+    }
+    const int t = (int)blockIdx.x * ORDER_BLOCK + tid;
+    const uint32_t ns = t < tiles ? wo.nseg(t) : 0u;
+    uint32_t off = 0;
+    if (wo.order_on) {
+        __syncthreads();
+        if (ns) off = atomicAdd(&sh.off[wo.cls(t)], ns);
+    } else {   // tile order: a prefix over the block
+        uint32_t inc = ns;
         for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = (uint32_t)__shfl_up((int)incl, o, 64);
-            if (lane >= o) incl += t;
+            const uint32_t x = (uint32_t)__shfl_up((int)inc, o, 64);
+            if (lane >= o) inc += x;
         }
-        if (lane == 63) s_w[w] = incl;
+        if (lane == 63) s_w[w] = inc;
         __syncthreads();
-        uint32_t before = s_carry;
-        for (int k = 0; k < w; k++) before += s_w[k];
-        uint32_t off = before + incl - sum;
-        uint2 *it = reinterpret_cast<uint2 *>(items);   // (tile, segment) pairs
-#pragma unroll
-        for (int k = 0; k < 4; k++)
-            for (uint32_t j = 0; j < ns[k]; j++) it[off++] = make_uint2(tl[k], j);
-        __syncthreads();
-        if (tid == 1023) s_carry = before + incl;
-        __syncthreads();
+        off = sh.off[0] + inc - ns;
+        for (int k = 0; k < w; k++) off += s_w[k];
     }
-    if (tid == 0) *n_items = s_carry;
+    uint2 *it = reinterpret_cast<uint2 *>(items);   // (tile, segment) pairs
+    for (uint32_t j = 0; j < ns; j++) it[off + j] = make_uint2((uint32_t)t, j);
 }
 
 // Test hook: the blend's unclamped alpha o G = exp2(q) of entry ent[i] at
@@ -1171,17 +1147,39 @@ void launch_debug_alpha(const as_frame *f, int64_t n, const int32_t *pix, const 
                        reinterpret_cast<const short4 *>(f->box), n, pix, ent, out);
 }
 
-void launch_tile_order(const uint32_t *ranges, const ViewTable &vt, uint32_t *order, hipStream_t s) {
-    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, s, ranges, vt, order);
+size_t order_table_words(int64_t tiles) {
+    return (size_t)((tiles + ORDER_BLOCK - 1) / ORDER_BLOCK) * ORDER_NC_WORK;
 }
 
-void launch_after_fwd(const as_frame *f, const ViewTable &vt, const ViewImagesC &gt, int order_on, hipStream_t s) {
-    const int tiles = vt.tile_base[vt.n_views];
-    if (tiles == 0) return;
-    hipLaunchKernelGGL(k_after_fwd, dim3(1), dim3(1024), 0, s, vt, gt,
+void launch_tile_order(const as_frame *f, const ViewTable &vt, hipStream_t s) {
+    const int n = vt.bin_shift != 4 ? vt.bin_base[vt.n_views] : vt.tile_base[vt.n_views];
+    if (n == 0) return;
+    const dim3 grid((unsigned)((n + ORDER_BLOCK - 1) / ORDER_BLOCK)), block(ORDER_BLOCK);
+    if (n <= ORDER_ALONE) {
+        hipLaunchKernelGGL((k_tile_order<false>), grid, block, 0, s, f->ranges, vt, f->order_table, f->tile_order);
+        return;
+    }
+    hipLaunchKernelGGL(k_tile_order_count, grid, block, 0, s, f->ranges, vt, f->order_table);
+    hipLaunchKernelGGL((k_tile_order<true>), grid, block, 0, s, f->ranges, vt, f->order_table, f->tile_order);
+}
+
+void launch_view_err(const as_frame *f, const ViewTable &vt, const ViewImagesC &gt, hipStream_t s) {
+    hipLaunchKernelGGL(k_view_err, dim3((unsigned)vt.n_views), dim3(1024), 0, s, vt, gt,
                        reinterpret_cast<const unsigned long long *>(f->tile_err),
-                       reinterpret_cast<unsigned long long *>(f->err_minmax), f->tile_work, order_on, f->tile_order_bwd,
-                       f->ranges, f->tile_hi, (uint32_t)f->ck_seg, f->ck_written ? 1 : 0, f->bwd_items, f->n_items);
+                       reinterpret_cast<unsigned long long *>(f->err_minmax));
+}
+
+void launch_bwd_items(const as_frame *f, int order_on, hipStream_t s) {
+    const int tiles = f->vt.tile_base[f->vt.n_views];
+    if (tiles == 0) return;
+    const dim3 grid((unsigned)((tiles + ORDER_BLOCK - 1) / ORDER_BLOCK)), block(ORDER_BLOCK);
+    const WorkOrder wo{f->tile_work, f->ranges, f->tile_hi, (uint32_t)f->ck_seg, f->ck_written ? 1 : 0, order_on};
+    if (tiles <= ORDER_ALONE) {
+        hipLaunchKernelGGL((k_bwd_items<false>), grid, block, 0, s, tiles, wo, f->order_table, f->bwd_items, f->n_items);
+        return;
+    }
+    hipLaunchKernelGGL(k_bwd_items_count, grid, block, 0, s, tiles, wo, f->order_table);
+    hipLaunchKernelGGL((k_bwd_items<true>), grid, block, 0, s, tiles, wo, f->order_table, f->bwd_items, f->n_items);
 }
 
 namespace {
@@ -1234,8 +1232,8 @@ bool launch_blend_fwd(const as_frame *f, const uint32_t *vals, const uint32_t *t
     return true;
 }
 
-void launch_blend_bwd(const as_frame *f, const uint32_t *vals, const uint32_t *tile_order, const BlendLaunch &bl,
-                      const ViewTable &vt, const ViewImagesC &dL_dimage, float *grad2d, hipStream_t s) {
+void launch_blend_bwd(const as_frame *f, const uint32_t *vals, const BlendLaunch &bl, const ViewTable &vt,
+                      const ViewImagesC &dL_dimage, float *grad2d, hipStream_t s) {
     const int tiles = vt.tile_base[vt.n_views];
     if (tiles == 0) return;
     const short4 *b4 = reinterpret_cast<const short4 *>(f->box);

@@ -124,8 +124,8 @@ struct as_frame {
     uint32_t *ranges;      // [tiles][2]
     uint32_t *tile_order;  // [2 tiles + 64] dispatch order of the forward blend (longest list first; with bins
                            // of 32, slots grouped by XCD with empty slots past the image edge)
+    uint32_t *order_table; // [order_table_words(tiles)] class counts per block of the dispatch orders
     uint32_t *tile_work;   // [tiles] contributors summed over the tile's pixels, from the forward blend
-    uint32_t *tile_order_bwd;  // [tiles] dispatch order of the reverse blend (most contributors first)
     uint32_t *tile_hi;     // [tiles] one past the tile's last contributor (0: none), from the forward blend
     float *ckpt;           // [tile_cap][AS_CK_MAX][256][4] per pixel (T, colour behind) at the forward's batch
                            // boundaries; NULL in forward-only frames
@@ -133,7 +133,8 @@ struct as_frame {
                            // blocks of the tile it may contribute to, from the forward blend for the reverse
                            // blend; NULL in forward-only frames
     int bm_written;        // the last render wrote bmask for every pair the reverse pass walks
-    uint32_t *bwd_items;   // [tile_cap * (AS_CK_MAX + 1)][2] (tile, segment) work items of the reverse blend
+    uint32_t *bwd_items;   // [tile_cap * (AS_CK_MAX + 1)][2] (tile, segment) work items of the reverse blend,
+                           // most contributors first
     uint32_t *n_items;     // [1] device count of bwd_items
     int ck_written;        // the last render wrote checkpoints
     int ck_seg;            // their spacing in list entries (the forward's batch depth)
@@ -259,10 +260,12 @@ struct BlendLaunch {
 };
 // The forward blend's LDS depth for a launch (256, 512 or 1024 records).
 int blend_fwd_batch(const BlendLaunch &bl);
-void launch_tile_order(const uint32_t *ranges, const ViewTable &vt, uint32_t *order, hipStream_t s);
-// After the forward blend: per-view error ranges, the reverse pass's dispatch
-// order (when order_on) and its work items, from the render's checkpoint state.
-void launch_after_fwd(const as_frame *f, const ViewTable &vt, const ViewImagesC &gt, int order_on, hipStream_t s);
+size_t order_table_words(int64_t tiles);
+void launch_tile_order(const as_frame *f, const ViewTable &vt, hipStream_t s);
+// After the forward blend of a render with targets: the views' error ranges.
+void launch_view_err(const as_frame *f, const ViewTable &vt, const ViewImagesC &gt, hipStream_t s);
+// The work items of the reverse pass of the last render.
+void launch_bwd_items(const as_frame *f, int order_on, hipStream_t s);
 // Forward blend; with zero_g2d it also clears zero_floats floats there (rounded
 // up to a multiple of four: the buffer needs that slack) and returns whether
 // it ran (no tiles: nothing launched, nothing cleared).
@@ -271,8 +274,8 @@ bool launch_blend_fwd(const as_frame *f, const uint32_t *vals, const uint32_t *t
                       float *zero_g2d = nullptr, int64_t zero_floats = 0);
 void launch_debug_alpha(const as_frame *f, int64_t n, const int32_t *pix, const uint32_t *ent, float *out,
                         hipStream_t s);
-void launch_blend_bwd(const as_frame *f, const uint32_t *vals, const uint32_t *tile_order, const BlendLaunch &bl,
-                      const ViewTable &vt, const ViewImagesC &dL_dimage, float *grad2d, hipStream_t s);
+void launch_blend_bwd(const as_frame *f, const uint32_t *vals, const BlendLaunch &bl, const ViewTable &vt,
+                      const ViewImagesC &dL_dimage, float *grad2d, hipStream_t s);
 
 // optimisation loop (train.hip)
 int train_set_rows(int deg);
