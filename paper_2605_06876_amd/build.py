@@ -24,6 +24,7 @@ SOURCES = {
     "project_bwd.hip": ["-ffp-contract=off"],
     "binning.hip": [],
     "radix.hip": [],
+    "depth_sort.hip": [],
     "blend.hip": [],
     "errstats.hip": ["-ffp-contract=off"],
     "split.hip": ["-ffp-contract=off"],

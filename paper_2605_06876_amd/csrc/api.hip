@@ -148,7 +148,7 @@ void frame_buffers(as_frame *f, bool keys_only, V &&visit) {
     arr(&f->grad2d, ent * 9);
     arr(&f->dkeys[0], ent); arr(&f->dkeys[1], ent); arr(&f->dvals[0], ent); arr(&f->dvals[1], ent);
     arr(&f->nt_sorted, ent); arr(&f->n_ent, 4); arr(&f->n_keys, 4);
-    dbuf(f->dsort_hist, sort_hist_bytes(ent));
+    dbuf(f->dsort_hist, sort_hist_bytes(ent) > depth_sort_bytes(ent) ? sort_hist_bytes(ent) : depth_sort_bytes(ent));
     dbuf(f->scan_tmp, scan_tmp_bytes(ent));
     // forward dispatch slots: the tiles, or 32 per 8 bins of 32 (at most 2 tile + 64)
     arr(&f->ranges, tile * 2); arr(&f->tile_order, 2 * tile + 64); arr(&f->queue, 2); arr(&f->tile_work, tile);
@@ -278,6 +278,7 @@ as_status as_ctx_create(int device, as_ctx **out) {
     warm_api(nullptr);
     warm_binning(nullptr);
     warm_blend(nullptr);
+    warm_depth_sort(nullptr);
     warm_errstats(nullptr);
     warm_project(nullptr);
     warm_project_bwd(nullptr);
@@ -629,22 +630,28 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
     f->has_render = 0;
     {
         StageTimer t(ctx, AS_STAGE_PROJECT, s);
-        launch_project(sc, vt, max_n, deg, f->rec, f->depth_key, f->box, f->ntiles, f->dkeys[0], f->dvals[0], f->n_ent,
-                       s, ctx->row_addr64 != 0);
+        launch_project(sc, vt, max_n, deg, f->rec, f->depth_key, f->box, f->ntiles, f->n_ent, s, ctx->row_addr64 != 0);
     }
     // Depth-first binning: a stable sort of the entries by depth, keys
     // emitted in that order, then a stable sort on the tile ids alone, gives
     // every tile the order of a stable sort of (tile | depth) keys emitted by id.
     const uint32_t *order;
+    bool lsd = (ctx->single_pass_sort & 1) != 0;   // (the one-launch-per-digit sort is asked for)
     {
         StageTimer t(ctx, AS_STAGE_SORT, s);
-        // 32-bit keys: 8-bit digits give the fewest passes (four); the last
-        // pass also gathers each entry's tile count into depth order
-        const int dsel = radix_sort_u32(f->dkeys, f->dvals, f->n_ent, f->ent_cap, n, 0, 32, 8,
-                                        f->dsort_hist.p, s, f->ntiles, f->nt_sorted, ctx->single_pass_sort & 1);
-        order = f->dvals[dsel];
+        if (!lsd)
+            lsd = depth_sort(f->depth_key, n, f->dkeys, f->dvals, f->ntiles, f->nt_sorted, f->offsets, f->n_keys,
+                             f->dsort_hist.p, s) != 0;
+        order = f->dvals[0];
+        if (lsd) {
+            // 32-bit keys: 8-bit digits give the fewest passes (four); the last
+            // pass also gathers each entry's tile count into depth order
+            const int dsel = radix_sort_u32(f->dkeys, f->dvals, f->n_ent, f->ent_cap, n, 0, 32, 8, f->dsort_hist.p, s,
+                                            f->ntiles, f->nt_sorted, ctx->single_pass_sort & 1, f->depth_key);
+            order = f->dvals[dsel];
+        }
     }
-    {
+    if (lsd) {
         StageTimer t(ctx, AS_STAGE_SCAN, s);
         scan_u32(f->nt_sorted, f->offsets, n, f->n_keys, f->scan_tmp.p, s);
     }

@@ -200,11 +200,10 @@ struct StageTimer {
 // ---- launchers (each defined in the .hip file that holds the kernel) -------------
 
 // projection (project.hip): every view's Gaussians into its entry range
-// Projection of every entry; also writes the depth sort's input pairs
-// (depth key, entry id) and the device entry count.
+// Projection of every entry; also writes the device entry count.
 void launch_project(const SceneTable &sc, const ViewTable &vt, int64_t max_n, int deg, BlendRec *rec,
-                    uint32_t *depth_key, int16_t *box, uint32_t *ntiles, uint32_t *sort_keys, uint32_t *sort_vals,
-                    uint32_t *n_ent, hipStream_t s, bool force_addr64 = false);
+                    uint32_t *depth_key, int16_t *box, uint32_t *ntiles, uint32_t *n_ent, hipStream_t s,
+                    bool force_addr64 = false);
 // projection backward (project_bwd.hip): one Gaussian set seen in every view
 // of vt; gradients summed over the views in view order
 void launch_project_bwd(const GaussPtrs &g, const ViewTable &vt, const uint32_t *ntiles, const float *grad2d,
@@ -228,13 +227,25 @@ size_t sort_hist_bytes(int64_t cap);
 // sort_single_pass_ok(cap)); otherwise three launches per digit.  Both give
 // the same order.  The single-pass sort raises a flag in the workspace at
 // byte sort_wait_flag_offset() if a look-back wait hit its limit.
+// first_keys (optional): the first pass reads its keys there, with the values
+// 0, 1, 2, .. (then neither keys[0] nor vals[0] is input).
 int radix_sort_u32(uint32_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, int64_t n_hint, int lo_bit,
                    int hi_bit, int radix_bits, void *hist, hipStream_t s, const uint32_t *gather_src = nullptr,
-                   uint32_t *gather_dst = nullptr, bool single_pass = false);
+                   uint32_t *gather_dst = nullptr, bool single_pass = false, const uint32_t *first_keys = nullptr);
 bool sort_single_pass_ok(int64_t cap);
 uint32_t sort_wait_flag_offset();
 int radix_sort_u64(uint64_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, int64_t n_hint, int lo_bit,
                    int hi_bit, int radix_bits, void *hist, hipStream_t s);
+// Depth order of n entries (depth_sort.hip): a stable sort of the entry ids by
+// depth_key into dvals[0], the tile counts in that order and their exclusive
+// prefix (their sum to *n_keys).  Returns 0, or -1 with nothing launched when n is 0
+// or above DEPTH_SORT_MAX.  dkeys and dvals[1] are scratch of n words, ws of
+// depth_sort_bytes(cap) for some cap >= n.
+constexpr int64_t DEPTH_SORT_MAX = 5 << 18;
+size_t depth_sort_bytes(int64_t cap);
+int depth_sort(const uint32_t *depth_key, int64_t n, uint32_t *const dkeys[2], uint32_t *const dvals[2],
+               const uint32_t *ntiles, uint32_t *nt_sorted, uint32_t *offsets, uint32_t *n_keys, void *ws,
+               hipStream_t s);
 // Depth-first binning: keys emitted in the depth order a stable depth sort
 // produced; the emission also empties the tile ranges ([0, 0) for every tile)
 // ahead of launch_ranges.  *n_emit gets the number of pairs written: all of
@@ -354,6 +365,7 @@ as_status run_adaptive_split(as_ctx *ctx, const GaussPtrs &g, const int32_t *can
 void warm_api(hipStream_t s);
 void warm_binning(hipStream_t s);
 void warm_blend(hipStream_t s);
+void warm_depth_sort(hipStream_t s);
 void warm_errstats(hipStream_t s);
 void warm_project(hipStream_t s);
 void warm_project_bwd(hipStream_t s);

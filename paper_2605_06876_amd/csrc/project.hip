@@ -23,8 +23,7 @@ __device__ __forceinline__ void quat_to_rot_d(double w, double x, double y, doub
 template <int DEG, bool BUF>
 __global__ void __launch_bounds__(256) k_project(const SceneTable sc, const ViewTable vt, BlendRec *__restrict__ rec,
                                                  uint32_t *__restrict__ depth_key, short4 *__restrict__ box,
-                                                 uint32_t *__restrict__ ntiles, uint32_t *__restrict__ sort_keys,
-                                                 uint32_t *__restrict__ sort_vals, uint32_t *__restrict__ n_ent) {
+                                                 uint32_t *__restrict__ ntiles, uint32_t *__restrict__ n_ent) {
     const int v = (int)(blockIdx.x % (unsigned)vt.n_views);
     const int64_t i = (int64_t)(blockIdx.x / (unsigned)vt.n_views) * blockDim.x + threadIdx.x;
     const GaussPtrs &g = sc.g[v];
@@ -48,11 +47,7 @@ __global__ void __launch_bounds__(256) k_project(const SceneTable sc, const View
     double tv[3];
     for (int r = 0; r < 3; r++) tv[r] = Rc[r * 3 + 0] * mu[0] + Rc[r * 3 + 1] * mu[1] + Rc[r * 3 + 2] * mu[2] + tc[r];
     const double tx = tv[0], ty = tv[1], tz = tv[2];
-    // the depth key, also as the (key, entry) input of the depth sort
-    const uint32_t dk = __float_as_uint((float)tz);
-    depth_key[e] = dk;
-    sort_keys[e] = dk;
-    sort_vals[e] = (uint32_t)e;
+    depth_key[e] = __float_as_uint((float)tz);
 
     BlendRec rr;
     rr.m = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -173,8 +168,8 @@ __global__ void __launch_bounds__(256) k_project(const SceneTable sc, const View
 }  // namespace
 
 void launch_project(const SceneTable &sc, const ViewTable &vt, int64_t max_n, int deg, BlendRec *rec,
-                    uint32_t *depth_key, int16_t *box, uint32_t *ntiles, uint32_t *sort_keys, uint32_t *sort_vals,
-                    uint32_t *n_ent, hipStream_t s, bool force_addr64) {
+                    uint32_t *depth_key, int16_t *box, uint32_t *ntiles, uint32_t *n_ent, hipStream_t s,
+                    bool force_addr64) {
     if (max_n == 0 || vt.n_views == 0) {
         launch_fill_u32(n_ent, 0u, 1, s);
         return;
@@ -186,9 +181,9 @@ void launch_project(const SceneTable &sc, const ViewTable &vt, int64_t max_n, in
 #define AS_PRJ(D)                                                                                                  \
     do {                                                                                                           \
         if (buf) hipLaunchKernelGGL((k_project<D, true>), dim3((unsigned)blocks), dim3(256), 0, s, sc, vt, rec,    \
-                                    depth_key, b4, ntiles, sort_keys, sort_vals, n_ent);                          \
+                                    depth_key, b4, ntiles, n_ent);                                                \
         else hipLaunchKernelGGL((k_project<D, false>), dim3((unsigned)blocks), dim3(256), 0, s, sc, vt, rec,       \
-                                depth_key, b4, ntiles, sort_keys, sort_vals, n_ent);                              \
+                                depth_key, b4, ntiles, n_ent);                                                \
     } while (0)
     switch (deg) {
     case 0: AS_PRJ(0); break;

@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
             const int idx = w * (RS_TILE / 4) + j * 64 + lane;
             const bool ok = idx < cnt;
             key[j] = ok ? kin[base + idx] : (K)0;
-            val[j] = ok ? vin[base + idx] : 0u;
+            val[j] = ok ? (vin ? vin[base + idx] : (uint32_t)(base + idx)) : 0u;
         }
         const uint32_t gstart = block_scan_excl(tt, s_wave);   // start of each digit's output range
 #pragma unroll
@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(RS_THREADS, ROUNDS >= 32 ? 1 : 2)
             const int idx = w * (TILE / 4) + j * 64 + lane;
             const bool ok = idx < cnt;
             key[j] = ok ? kin[base + idx] : 0u;
-            val[j] = ok ? vin[base + idx] : 0u;
+            val[j] = ok ? (vin ? vin[base + idx] : (uint32_t)(base + idx)) : 0u;
         }
 #pragma unroll
         for (int j = 0; j < ROUNDS; j++) {
@@ -455,7 +455,7 @@ constexpr int64_t OS_MAX_BLOCKS = 1024;
 size_t os_words_bytes(int64_t cap) { return (size_t)rs_tiles(cap, OS_TILE_MIN) * 256 * 4; }
 
 template <int RB, int R>
-void os_pass_r(uint32_t *ki, uint32_t *vi, uint32_t *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t nh,
+void os_pass_r(const uint32_t *ki, const uint32_t *vi, uint32_t *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t nh,
                int shift, uint32_t mask, uint32_t *head, int pass, uint32_t *st, uint32_t *st_next,
                const uint32_t *gsrc, uint32_t *gdst, hipStream_t s) {
     int64_t grid = rs_tiles(nh, RS_THREADS * R);
@@ -466,7 +466,7 @@ void os_pass_r(uint32_t *ki, uint32_t *vi, uint32_t *ko, uint32_t *vo, const uin
 
 template <int RB>
 int os_sort(uint32_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, int64_t nh, int lo_bit,
-            int hi_bit, void *ws, const uint32_t *gsrc, uint32_t *gdst, hipStream_t s) {
+            int hi_bit, void *ws, const uint32_t *gsrc, uint32_t *gdst, hipStream_t s, const uint32_t *first_keys) {
     uint32_t *head = reinterpret_cast<uint32_t *>(ws);
     uint32_t *words[2] = {reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(ws) + OS_HEAD),
                           reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(ws) + OS_HEAD + os_words_bytes(cap))};
@@ -477,7 +477,7 @@ int os_sort(uint32_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t
     int64_t hg = (nh + 8191) / 8192;
     hg = hg < 1 ? 1 : (hg > 512 ? 512 : hg);
     const size_t lds = (size_t)RS_COPIES * P * ((1 << RB) + 1) * 4;
-    hipLaunchKernelGGL((k_os_hist<RB>), dim3((unsigned)hg), dim3(256), lds, s, keys[0], n_dev, cap, lo_bit, hi_bit,
+    hipLaunchKernelGGL((k_os_hist<RB>), dim3((unsigned)hg), dim3(256), lds, s, first_keys ? first_keys : keys[0], n_dev, cap, lo_bit, hi_bit,
                        head, words[0], tile);
     int sel = 0;
     for (int p = 0; p < P; p++) {
@@ -486,11 +486,13 @@ int os_sort(uint32_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t
         const uint32_t mask = (1u << wdt) - 1u;
         const bool last = p == P - 1;
         uint32_t *st = words[p & 1], *stn = last ? nullptr : words[(p + 1) & 1];
+        const bool ids = first_keys && p == 0;
+        const uint32_t *ki = ids ? first_keys : keys[sel], *vi = ids ? nullptr : vals[sel];
         if (big)
-            os_pass_r<RB, 32>(keys[sel], vals[sel], keys[sel ^ 1], vals[sel ^ 1], n_dev, cap, nh, sh, mask, head, p, st,
+            os_pass_r<RB, 32>(ki, vi, keys[sel ^ 1], vals[sel ^ 1], n_dev, cap, nh, sh, mask, head, p, st,
                               stn, last ? gsrc : nullptr, last ? gdst : nullptr, s);
         else
-            os_pass_r<RB, 16>(keys[sel], vals[sel], keys[sel ^ 1], vals[sel ^ 1], n_dev, cap, nh, sh, mask, head, p, st,
+            os_pass_r<RB, 16>(ki, vi, keys[sel ^ 1], vals[sel ^ 1], n_dev, cap, nh, sh, mask, head, p, st,
                               stn, last ? gsrc : nullptr, last ? gdst : nullptr, s);
         sel ^= 1;
     }
@@ -498,7 +500,7 @@ int os_sort(uint32_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t
 }
 
 template <typename K, int RB, int R>
-void rs_pass_r(K *ki, uint32_t *vi, K *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t grid, int shift,
+void rs_pass_r(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t grid, int shift,
                uint32_t mask, uint32_t *total, uint32_t *counts, int64_t tstride, const uint32_t *gsrc, uint32_t *gdst,
                hipStream_t s) {
     hipLaunchKernelGGL((k_rs_up<K, RB, R>), dim3((unsigned)grid), dim3(RS_THREADS), 0, s, ki, n_dev, cap, shift, mask,
@@ -510,7 +512,7 @@ void rs_pass_r(K *ki, uint32_t *vi, K *ko, uint32_t *vo, const uint32_t *n_dev, 
 }
 
 template <typename K, int RB>
-void rs_pass(bool small, K *ki, uint32_t *vi, K *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t grid,
+void rs_pass(bool small, const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t grid,
              int shift, uint32_t mask, uint32_t *total, uint32_t *counts, int64_t tstride, const uint32_t *gsrc,
              uint32_t *gdst, hipStream_t s) {
     if (small)
@@ -523,7 +525,7 @@ void rs_pass(bool small, K *ki, uint32_t *vi, K *ko, uint32_t *vo, const uint32_
 
 template <typename K>
 int rs_sort(K *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, int64_t n_hint, int lo_bit, int hi_bit,
-            int rb, void *ws, const uint32_t *gsrc, uint32_t *gdst, hipStream_t s) {
+            int rb, void *ws, const uint32_t *gsrc, uint32_t *gdst, hipStream_t s, const K *first_keys = nullptr) {
     if (rb < 4) rb = 4;
     if (rb > 8) rb = 8;
     const int kbits = (int)sizeof(K) * 8;
@@ -540,8 +542,11 @@ int rs_sort(K *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, i
     for (int sh = lo_bit; sh < hi_bit; sh += rb) {
         const int wdt = hi_bit - sh < rb ? hi_bit - sh : rb;   // the last digit holds only the bits that are left
         const uint32_t mask = (1u << wdt) - 1u;
-        K *ki = keys[sel], *ko = keys[sel ^ 1];
-        uint32_t *vi = vals[sel], *vo = vals[sel ^ 1];
+        const bool ids = first_keys && sh == lo_bit;
+        const K *ki = ids ? first_keys : keys[sel];
+        const uint32_t *vi = ids ? nullptr : vals[sel];
+        K *ko = keys[sel ^ 1];
+        uint32_t *vo = vals[sel ^ 1];
         const bool last = sh + rb >= hi_bit;
         const uint32_t *gs = last ? gsrc : nullptr;
         uint32_t *gd = last ? gdst : nullptr;
@@ -569,22 +574,22 @@ bool sort_single_pass_ok(int64_t cap) { return cap < (int64_t)OS_VAL; }
 
 int radix_sort_u32(uint32_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, int64_t n_hint, int lo_bit,
                    int hi_bit, int radix_bits, void *hist, hipStream_t s, const uint32_t *gather_src,
-                   uint32_t *gather_dst, bool single_pass) {
+                   uint32_t *gather_dst, bool single_pass, const uint32_t *first_keys) {
     if (single_pass && sort_single_pass_ok(cap) && hi_bit > lo_bit) {
         int rb = radix_bits < 4 ? 4 : (radix_bits > 8 ? 8 : radix_bits);
         if (hi_bit > 32) hi_bit = 32;
         if ((hi_bit - lo_bit + rb - 1) / rb > OS_MAX_PASSES) rb = 8;
         const int64_t nh = n_hint < cap ? n_hint : cap;
         switch (rb) {
-        case 4: return os_sort<4>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s);
-        case 5: return os_sort<5>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s);
-        case 6: return os_sort<6>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s);
-        case 7: return os_sort<7>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s);
-        default: return os_sort<8>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s);
+        case 4: return os_sort<4>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s, first_keys);
+        case 5: return os_sort<5>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s, first_keys);
+        case 6: return os_sort<6>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s, first_keys);
+        case 7: return os_sort<7>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s, first_keys);
+        default: return os_sort<8>(keys, vals, n_dev, cap, nh, lo_bit, hi_bit, hist, gather_src, gather_dst, s, first_keys);
         }
     }
     return rs_sort<uint32_t>(keys, vals, n_dev, cap, n_hint, lo_bit, hi_bit, radix_bits, hist, gather_src, gather_dst,
-                             s);
+                             s, first_keys);
 }
 
 uint32_t sort_wait_flag_offset() { return OS_ERR * 4; }
