@@ -508,8 +508,9 @@ typedef struct {
     int32_t lds_batch;       /* Gaussian records staged per LDS batch by the blend kernels: 256, 512 or 1024 */
     int32_t longest_first;   /* nonzero: tiles are dispatched in descending order of list length */
     int32_t persistent;      /* nonzero: the blend kernels run as one resident grid pulling tiles from a queue */
-    int32_t radix_bits;      /* digit width of the (tile, entry) pair sort, 4..8 (the 32-bit
-                                depth keys always take 8: four passes) */
+    int32_t radix_bits;      /* digit width aimed at by the (tile, entry) pair sort, 4..8: the key's
+                                bits are spread evenly over bits / width passes, to the nearest
+                                (digits of at most 9 bits) */
     int32_t block_cull;      /* nonzero: the blend kernels skip a Gaussian for a 4x4 pixel block of a
                                 tile unless its alpha >= 1/255 ellipse (with a margin above the
                                 FP32 evaluation error) meets the block; zero: the pixel box alone

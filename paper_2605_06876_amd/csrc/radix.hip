@@ -25,8 +25,8 @@
 // cleared first.  Grids are sized from the host's element count hint (at most
 // 4096 blocks); blocks loop over tiles until the device-side count is covered.
 //
-// Workspace (sort_hist_bytes(cap)): digit totals [256] u32, then counts
-// [256][tiles(cap)] u32, sized for the 2048-key tiles and used with the row
+// Workspace (sort_hist_bytes(cap)): digit totals [512] u32, then counts
+// [512][tiles(cap)] u32, sized for the 2048-key tiles and used with the row
 // stride of the tile size a sort takes.
 //
 // 32-bit keys can instead take one launch per digit (single_pass): a first
@@ -58,7 +58,8 @@ constexpr int RS_TILE_MIN = RS_THREADS * RS_ROUNDS_SMALL;
 constexpr int64_t RS_SMALL_BELOW = 512;             // 4096-key tiles under which the small tiles are used
 constexpr int RS_COPIES = 8;                        // LDS histogram copies of the up pass
 constexpr int64_t RS_MAX_BLOCKS = 4096;
-constexpr size_t RS_HEAD = 256 * 4;                 // digit totals, bytes
+constexpr int RS_MAX_BITS = 9;                      // widest digit (64-bit keys: 8)
+constexpr size_t RS_HEAD = (1 << RS_MAX_BITS) * 4;  // digit totals, bytes
 
 __device__ __forceinline__ int64_t clamp_n(const uint32_t *n_dev, int64_t cap) {
     const int64_t n = *n_dev;
@@ -165,6 +166,7 @@ __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
               const uint32_t *__restrict__ offs, const uint32_t *__restrict__ total, int64_t tstride,
               const uint32_t *__restrict__ gsrc, uint32_t *__restrict__ gdst) {
     constexpr int NB = 1 << RB;
+    constexpr int PER = NB > RS_THREADS ? NB / RS_THREADS : 1;   // consecutive digits per thread
     constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;
     __shared__ uint32_t s_wcnt[4][NB];   // per-wave digit counts, then each wave's offset inside the tile's digit run
     __shared__ uint32_t s_boff[NB];      // tile-local start of each digit's run
@@ -179,8 +181,15 @@ __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
     for (int64_t tile = blockIdx.x; tile < T; tile += gridDim.x) {
         // the tile's offset in each digit's column and the digit totals are
         // loaded first, so the scan below waits for them alone
-        const uint32_t go = tid < NB ? offs[(int64_t)tid * tstride + tile] : 0u;
-        const uint32_t tt = tid < NB ? total[tid] : 0u;
+        uint32_t go[PER], tt[PER], tsum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const int d = tid * PER + k;
+            go[k] = d < NB ? offs[(int64_t)d * tstride + tile] : 0u;
+            tt[k] = d < NB ? total[d] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < PER; k++) tsum += tt[k];
         for (int i = tid; i < 4 * NB; i += RS_THREADS) (&s_wcnt[0][0])[i] = 0;
         const int64_t base = tile * RS_TILE;
         const int cnt = n - base < RS_TILE ? (int)(n - base) : RS_TILE;
@@ -194,11 +203,13 @@ __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
             key[j] = ok ? kin[base + idx] : (K)0;
             val[j] = ok ? (vin ? vin[base + idx] : (uint32_t)(base + idx)) : 0u;
         }
-        const uint32_t gstart = block_scan_excl(tt, s_wave);   // start of each digit's output range
+        uint32_t gstart = block_scan_excl(tsum, s_wave);   // start of the thread's first digit's output range
 #pragma unroll
         for (int j = 0; j < RS_ROUNDS; j++) {
             const bool ok = w * (RS_TILE / 4) + j * 64 + lane < cnt;
-            const uint32_t d = (uint32_t)(key[j] >> shift) & mask;
+            uint32_t d = (uint32_t)(key[j] >> shift) & mask;
+            // one key's ballots at a time: taken together they fill the registers
+            __asm__ __volatile__("" : "+v"(d));
             uint64_t peers = __ballot(ok);
 #pragma unroll
             for (int bit = 0; bit < RB; bit++) {
@@ -215,19 +226,31 @@ __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
         }
         __syncthreads();
         // per digit: tile total, wave offsets, tile-local run starts
-        uint32_t tot = 0;
-        if (tid < NB) {
-            const uint32_t c0 = s_wcnt[0][tid], c1 = s_wcnt[1][tid], c2 = s_wcnt[2][tid], c3 = s_wcnt[3][tid];
-            tot = c0 + c1 + c2 + c3;
-            s_wcnt[0][tid] = 0;
-            s_wcnt[1][tid] = c0;
-            s_wcnt[2][tid] = c0 + c1;
-            s_wcnt[3][tid] = c0 + c1 + c2;
+        uint32_t tot[PER], csum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const int d = tid * PER + k;
+            tot[k] = 0;
+            if (d < NB) {
+                const uint32_t c0 = s_wcnt[0][d], c1 = s_wcnt[1][d], c2 = s_wcnt[2][d], c3 = s_wcnt[3][d];
+                tot[k] = c0 + c1 + c2 + c3;
+                s_wcnt[0][d] = 0;
+                s_wcnt[1][d] = c0;
+                s_wcnt[2][d] = c0 + c1;
+                s_wcnt[3][d] = c0 + c1 + c2;
+            }
+            csum += tot[k];
         }
-        const uint32_t boff = block_scan_excl(tot, s_wave);
-        if (tid < NB) {
-            s_boff[tid] = boff;
-            s_gdst[tid] = gstart + go;
+        uint32_t boff = block_scan_excl(csum, s_wave);
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const int d = tid * PER + k;
+            if (d < NB) {
+                s_boff[d] = boff;
+                s_gdst[d] = gstart + go[k];
+            }
+            boff += tot[k];
+            gstart += tt[k];
         }
         __syncthreads();
 #pragma unroll
@@ -523,13 +546,28 @@ void rs_pass(bool small, const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, c
                                         gdst, s);
 }
 
+// The digit width a sort of `bits` bits takes when `aim` bits are asked for: as
+// many passes as bits / aim to the nearest, the bits spread evenly over them,
+// no digit above `most`.  A pass costs its memory traffic whatever its width, and
+// its ranking a ballot per bit of the widest digit: 17 bits in two passes of
+// nine and not 8 + 8 + 1 (58.8M pairs: 1256 -> 1075 us), 13 bits in 7 + 6 and not
+// 8 + 5 or 6 + 6 + 1 (41.5M pairs: 600 -> 480 us; 9.7M: 142 -> 123 us).
+int digit_bits(int bits, int aim, int most) {
+    if (aim < 4) aim = 4;
+    if (aim > 8) aim = 8;
+    int passes = (2 * bits + aim) / (2 * aim);
+    if (passes < 1) passes = 1;
+    while ((bits + passes - 1) / passes > most) passes++;
+    const int w = (bits + passes - 1) / passes;
+    return w < 4 ? 4 : w;
+}
+
 template <typename K>
 int rs_sort(K *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, int64_t n_hint, int lo_bit, int hi_bit,
             int rb, void *ws, const uint32_t *gsrc, uint32_t *gdst, hipStream_t s, const K *first_keys = nullptr) {
-    if (rb < 4) rb = 4;
-    if (rb > 8) rb = 8;
     const int kbits = (int)sizeof(K) * 8;
     if (hi_bit > kbits) hi_bit = kbits;
+    rb = digit_bits(hi_bit - lo_bit, rb, sizeof(K) == 4 ? RS_MAX_BITS : 8);
     const int64_t nh = n_hint < cap ? n_hint : cap;
     const bool small = rs_tiles(nh, RS_THREADS * RS_ROUNDS_BIG) < RS_SMALL_BELOW;
     const int tile = RS_THREADS * (small ? RS_ROUNDS_SMALL : RS_ROUNDS_BIG);
@@ -555,7 +593,11 @@ int rs_sort(K *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, i
         case 5: rs_pass<K, 5>(small, ki, vi, ko, vo, n_dev, cap, grid, sh, mask, total, counts, tstride, gs, gd, s); break;
         case 6: rs_pass<K, 6>(small, ki, vi, ko, vo, n_dev, cap, grid, sh, mask, total, counts, tstride, gs, gd, s); break;
         case 7: rs_pass<K, 7>(small, ki, vi, ko, vo, n_dev, cap, grid, sh, mask, total, counts, tstride, gs, gd, s); break;
-        default: rs_pass<K, 8>(small, ki, vi, ko, vo, n_dev, cap, grid, sh, mask, total, counts, tstride, gs, gd, s); break;
+        case 8: rs_pass<K, 8>(small, ki, vi, ko, vo, n_dev, cap, grid, sh, mask, total, counts, tstride, gs, gd, s); break;
+        default:
+            if constexpr (sizeof(K) == 4)
+                rs_pass<K, 9>(small, ki, vi, ko, vo, n_dev, cap, grid, sh, mask, total, counts, tstride, gs, gd, s);
+            break;
         }
         sel ^= 1;
     }
@@ -565,7 +607,7 @@ int rs_sort(K *keys[2], uint32_t *vals[2], const uint32_t *n_dev, int64_t cap, i
 }  // namespace
 
 size_t sort_hist_bytes(int64_t cap) {
-    const size_t rts = RS_HEAD + (size_t)rs_tiles(cap, RS_TILE_MIN) * 256 * 4 + 256;
+    const size_t rts = RS_HEAD + (size_t)rs_tiles(cap, RS_TILE_MIN) * (1 << RS_MAX_BITS) * 4 + 256;
     const size_t os = OS_HEAD + 2 * os_words_bytes(cap);
     return rts > os ? rts : os;
 }
