@@ -25,6 +25,7 @@ SOURCES = {
     "binning.hip": [],
     "radix.hip": [],
     "depth_sort.hip": [],
+    "pair_bins.hip": [],
     "blend.hip": [],
     "errstats.hip": ["-ffp-contract=off"],
     "split.hip": ["-ffp-contract=off"],

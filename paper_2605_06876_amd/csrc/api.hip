@@ -141,6 +141,7 @@ void frame_buffers(as_frame *f, bool keys_only, V &&visit) {
         arr(&f->vals[k], key);
     }
     dbuf(f->sort_hist, sort_hist_bytes(key));
+    dbuf(f->bin_ws, coarse_bins_bytes(tile, key));
     // block masks: one per sorted pair and blend tile of its bin (four for bins of 32)
     if (!(f->flags & AS_FRAME_FORWARD_ONLY)) arr(&f->bmask, key * 4);
     if (keys_only) return;
@@ -149,7 +150,8 @@ void frame_buffers(as_frame *f, bool keys_only, V &&visit) {
     arr(&f->dkeys[0], ent); arr(&f->dkeys[1], ent); arr(&f->dvals[0], ent); arr(&f->dvals[1], ent);
     arr(&f->nt_sorted, ent); arr(&f->n_ent, 4); arr(&f->n_keys, 4);
     dbuf(f->dsort_hist, sort_hist_bytes(ent) > depth_sort_bytes(ent) ? sort_hist_bytes(ent) : depth_sort_bytes(ent));
-    dbuf(f->scan_tmp, scan_tmp_bytes(ent));
+    const size_t scan = scan_tmp_bytes(ent > tile ? ent : tile), sums = pairs_tmp_bytes(ent);
+    dbuf(f->scan_tmp, scan > sums ? scan : sums);
     // forward dispatch slots: the tiles, or 32 per 8 bins of 32 (at most 2 tile + 64)
     arr(&f->ranges, tile * 2); arr(&f->tile_order, 2 * tile + 64); arr(&f->queue, 2); arr(&f->tile_work, tile);
     arr(&f->tile_hi, tile); arr(&f->n_items, 1); arr(&f->order_table, (int64_t)order_table_words(tile));
@@ -280,6 +282,7 @@ as_status as_ctx_create(int device, as_ctx **out) {
     warm_blend(nullptr);
     warm_depth_sort(nullptr);
     warm_errstats(nullptr);
+    warm_pair_bins(nullptr);
     warm_project(nullptr);
     warm_project_bwd(nullptr);
     warm_radix(nullptr);
@@ -635,7 +638,11 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
     // Depth-first binning: a stable sort of the entries by depth, keys
     // emitted in that order, then a stable sort on the tile ids alone, gives
     // every tile the order of a stable sort of (tile | depth) keys emitted by id.
+    // Large renders sort on coarse bins first (the pair sort by one launch a
+    // digit, when asked for, takes the bins directly).
     const uint32_t *order;
+    CoarseBins cb;
+    const bool coarse = !(ctx->single_pass_sort & 2) && coarse_bins(vt, n, f->key_cap, &cb);
     bool lsd = (ctx->single_pass_sort & 1) != 0;   // (the one-launch-per-digit sort is asked for)
     {
         StageTimer t(ctx, AS_STAGE_SORT, s);
@@ -647,11 +654,12 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
             // 32-bit keys: 8-bit digits give the fewest passes (four); the last
             // pass also gathers each entry's tile count into depth order
             const int dsel = radix_sort_u32(f->dkeys, f->dvals, f->n_ent, f->ent_cap, n, 0, 32, 8, f->dsort_hist.p, s,
-                                            f->ntiles, f->nt_sorted, ctx->single_pass_sort & 1, f->depth_key);
+                                            coarse ? nullptr : f->ntiles, coarse ? nullptr : f->nt_sorted,
+                                            ctx->single_pass_sort & 1, f->depth_key);
             order = f->dvals[dsel];
         }
     }
-    if (lsd) {
+    if (lsd && !coarse) {
         StageTimer t(ctx, AS_STAGE_SCAN, s);
         scan_u32(f->nt_sorted, f->offsets, n, f->n_keys, f->scan_tmp.p, s);
     }
@@ -661,20 +669,33 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
     const int64_t n_hint = f->key_cap;
     {
         StageTimer t(ctx, AS_STAGE_EMIT, s);
-        launch_emit_sorted(n, order, vt, f->box, f->nt_sorted, f->offsets, f->key_cap, f->keys[0], f->vals[0],
-                           f->n_keys + 1, f->ranges, tiles, s);
+        // (the sorted depth keys are not read again: their buffers hold the boxes in depth order)
+        if (coarse)
+            launch_pairs_emit(n, order, vt, cb, f->box, f->dkeys[0], f->dkeys[1], f->key_cap, f->keys[0], f->vals[0],
+                              f->n_keys, f->bin_ws.p, f->scan_tmp.p, s);
+        else
+            launch_emit_sorted(n, order, vt, f->box, f->nt_sorted, f->offsets, f->key_cap, f->keys[0], f->vals[0],
+                               f->n_keys + 1, f->ranges, tiles, s);
     }
     int sel;
     {
         StageTimer t(ctx, AS_STAGE_SORT, s);
         // only the pairs written (a render over the capacity writes a prefix)
-        sel = radix_sort_u32(f->keys, f->vals, f->n_keys + 1, f->key_cap, n_hint, 0, tile_bits(bins),
-                             ctx->radix_bits, f->sort_hist.p, s, nullptr, nullptr, (ctx->single_pass_sort & 2) != 0);
+        const int bits = tile_bits(coarse ? cb.bins : bins);
+        sel = radix_sort_u32(f->keys, f->vals, f->n_keys + (coarse ? 2 : 1), f->key_cap, n_hint, 0, bits,
+                             coarse && bits <= 9 ? 8 : ctx->radix_bits, f->sort_hist.p, s, nullptr, nullptr,
+                             (ctx->single_pass_sort & 2) != 0);
     }
-    f->sorted_sel = sel;
     {
         StageTimer t(ctx, AS_STAGE_RANGES, s);
-        launch_ranges(f->keys[sel], f->n_keys + 1, f->key_cap, bins, vt, f->ranges, s);
+        if (coarse) {
+            launch_bins_place(vt, cb, f->key_cap, f->keys[sel], f->vals[sel], f->keys[sel ^ 1], f->vals[sel ^ 1],
+                              f->n_keys, f->ranges, tiles, f->bin_ws.p, f->scan_tmp.p, s);
+            sel ^= 1;
+        } else {
+            launch_ranges(f->keys[sel], f->n_keys + 1, f->key_cap, bins, vt, f->ranges, s);
+        }
+        f->sorted_sel = sel;
         f->use_order = ctx->longest_first;
         if (f->use_order) launch_tile_order(f, vt, s);
     }

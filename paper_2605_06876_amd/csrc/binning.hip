@@ -229,26 +229,6 @@ __global__ void __launch_bounds__(256) k_emit_sorted(int64_t n, const uint32_t *
     }
 }
 
-// [start, end) of every bin in the sorted bin keys, written as the range of
-// each blend tile of the bin (tiles without keys keep the [0, 0) the caller
-// filled).
-__device__ __forceinline__ void set_bin_range(const ViewTable &vt, uint32_t bin, int end, uint32_t val,
-                                              uint32_t *__restrict__ ranges) {
-    if (vt.bin_shift == 4) {   // bins are the tiles
-        ranges[2 * bin + end] = val;
-        return;
-    }
-    const int v = view_of_bin(vt, (int)bin);
-    const int lb = (int)bin - vt.bin_base[v], bx = lb % vt.bins_x[v], by = lb / vt.bins_x[v];
-    const int tx_n = vt.tiles_x[v], ty_n = (vt.tile_base[v + 1] - vt.tile_base[v]) / tx_n;
-    const int f = 1 << (vt.bin_shift - 4);
-    for (int dy = 0; dy < f; dy++)
-        for (int dx = 0; dx < f; dx++) {
-            const int tx = bx * f + dx, ty = by * f + dy;
-            if (tx < tx_n && ty < ty_n) ranges[2 * (vt.tile_base[v] + ty * tx_n + tx) + end] = val;
-        }
-}
-
 __global__ void k_ranges(const uint32_t *__restrict__ keys, const uint32_t *n_dev, int64_t cap, int64_t n_bins,
                          const ViewTable vt, uint32_t *__restrict__ ranges) {
     int64_t n = *n_dev;
@@ -313,6 +293,9 @@ size_t scan_tmp_bytes(int64_t n) { return (size_t)((n + SCAN_TILE - 1) / SCAN_TI
 
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, void *tmp, hipStream_t s) {
     scan_impl<uint32_t, uint32_t>(in, out, n, total, tmp, s);
+}
+void scan_partials_u64(uint64_t *partials, int64_t nb, hipStream_t s) {
+    hipLaunchKernelGGL((k_scan_partials<uint64_t>), dim3(1), dim3(SCAN_THREADS), 0, s, partials, nb, (uint64_t *)nullptr);
 }
 void scan_u8_to_i64(const uint8_t *in, int64_t *out, int64_t n, int64_t *total, void *tmp, hipStream_t s) {
     scan_impl<uint8_t, int64_t>(in, out, n, total, tmp, s);

@@ -139,7 +139,8 @@ struct as_frame {
     int ck_written;        // the last render wrote checkpoints
     int ck_seg;            // their spacing in list entries (the forward's batch depth)
     int use_order;         // tile_order is valid for the last render
-    uint32_t *n_keys;      // [2] device: pairs the render needs, pairs it wrote (fewer when over key_cap)
+    uint32_t *n_keys;      // [3] device: pairs the render needs, pairs it wrote (fewer when over key_cap), and in
+                           // two-level binning the coarse pairs it wrote
     uint32_t *queue;       // [2] tile counters of the persistent blend kernels
     // per pixel, packed over the views
     float *t_final;
@@ -150,7 +151,7 @@ struct as_frame {
     uint64_t *err_minmax;  // [max_views][2]
     uint64_t *tile_err;    // [tile_cap][2] per-tile error min / max (IEEE bits), reduced into err_minmax
     // scratch for scans and the sorter
-    DevBuf scan_tmp, sort_hist;
+    DevBuf scan_tmp, sort_hist, bin_ws;
     // state of the last render
     int has_render;
     ViewTable vt;
@@ -212,6 +213,7 @@ void launch_project_bwd(const GaussPtrs &g, const ViewTable &vt, const uint32_t 
 // scans (binning.hip): exclusive scans with the total written to *total
 size_t scan_tmp_bytes(int64_t n);
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, void *tmp, hipStream_t s);
+void scan_partials_u64(uint64_t *partials, int64_t nb, hipStream_t s);   // in place, one block
 void scan_u8_to_i64(const uint8_t *in, int64_t *out, int64_t n, int64_t *total, void *tmp, hipStream_t s);
 void scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, int64_t *total, void *tmp, hipStream_t s);
 
@@ -256,6 +258,31 @@ void launch_emit_sorted(int64_t n, const uint32_t *order, const ViewTable &vt, c
 // [start, end) of each tile with keys (ranges emptied by launch_emit_sorted).
 void launch_ranges(const uint32_t *keys, const uint32_t *n_dev, int64_t cap, int64_t n_bins, const ViewTable &vt,
                    uint32_t *ranges, hipStream_t s);
+// Two-level binning (pair_bins.hip): pairs sorted on coarse bins of
+// 2^shift x 2^shift bins, then placed into the bins' lists.
+struct CoarseBins {
+    int32_t shift, bins;
+    int32_t base[AS_MAX_VIEWS], x[AS_MAX_VIEWS];
+};
+constexpr int64_t PAIR_BINS_PAIRS = 1 << 22, PAIR_BINS_ENTRIES = 1 << 15, PAIR_BINS_WIDE = 256, PAIR_BINS_FEW = 64;
+size_t coarse_bins_bytes(int64_t tiles, int64_t key_cap);
+size_t pairs_tmp_bytes(int64_t n);
+// Whether a render of n entries into a frame of key_cap pairs bins its pairs
+// this way, and its coarse bins.
+bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb);
+// The coarse pairs of the entries in depth order (key: coarse bin id in the
+// low 24 bits); box_lo, box_hi: scratch of n words; tmp: pairs_tmp_bytes(cap) for some cap >= n.
+// n_keys[0..2] get the pairs of the bins needed and written (as
+// launch_emit_sorted) and the coarse pairs written.
+void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
+                       uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals,
+                       uint32_t *n_keys, void *ws, void *tmp, hipStream_t s);
+// From the coarse pairs sorted by coarse bin, the pairs sorted by bin and the
+// range of every tile; ws of both: coarse_bins_bytes(tile_cap, key_cap) for a
+// tile_cap of at least the tiles; tmp: scan_tmp_bytes(tiles).
+void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_cap, const uint32_t *ckeys,
+                       const uint32_t *cvals, uint32_t *keys, uint32_t *vals, const uint32_t *n_keys, uint32_t *ranges,
+                       int64_t n_tiles, void *ws, void *tmp, hipStream_t s);
 void launch_fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s);
 void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 void launch_fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s);
@@ -367,6 +394,7 @@ void warm_binning(hipStream_t s);
 void warm_blend(hipStream_t s);
 void warm_depth_sort(hipStream_t s);
 void warm_errstats(hipStream_t s);
+void warm_pair_bins(hipStream_t s);
 void warm_project(hipStream_t s);
 void warm_project_bwd(hipStream_t s);
 void warm_radix(hipStream_t s);
@@ -414,6 +442,24 @@ __device__ __forceinline__ int view_of_bin(const ViewTable &vt, int bin) {
     int v = 0;
     for (int k = 1; k < vt.n_views; k++) v += bin >= vt.bin_base[k] ? 1 : 0;
     return v;
+}
+// One end of a bin's list, written as that of the range of each blend tile of
+// the bin.
+__device__ __forceinline__ void set_bin_range(const ViewTable &vt, uint32_t bin, int end, uint32_t val,
+                                              uint32_t *__restrict__ ranges) {
+    if (vt.bin_shift == 4) {   // bins are the tiles
+        ranges[2 * bin + end] = val;
+        return;
+    }
+    const int v = view_of_bin(vt, (int)bin);
+    const int lb = (int)bin - vt.bin_base[v], bx = lb % vt.bins_x[v], by = lb / vt.bins_x[v];
+    const int tx_n = vt.tiles_x[v], ty_n = (vt.tile_base[v + 1] - vt.tile_base[v]) / tx_n;
+    const int f = 1 << (vt.bin_shift - 4);
+    for (int dy = 0; dy < f; dy++)
+        for (int dx = 0; dx < f; dx++) {
+            const int tx = bx * f + dx, ty = by * f + dy;
+            if (tx < tx_n && ty < ty_n) ranges[2 * (vt.tile_base[v] + ty * tx_n + tx) + end] = val;
+        }
 }
 // Index of a blend tile's block mask for sorted pair i: bins of 32 keep the
 // masks of their four tiles side by side.

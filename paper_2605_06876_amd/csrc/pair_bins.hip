@@ -1,0 +1,538 @@
+// Pairs of large renders, binned in two levels.
+//
+// A pair list sorted by bin moves every (bin, entry) pair through each of the
+// sort's passes, although neighbouring bins hold mostly the same entries.
+// Here the sort works on coarse bins of F x F bins (F 2 or 4), which hold two to
+// four times fewer pairs; the pairs of the bins are written once, at the end:
+//   sum     the pixel boxes gathered into depth order, and per 2048 ranks the
+//           sums of the bins and of the coarse bins touched;
+//   emit    every rank's coarse pairs: key = coarse bin id | the rectangle of
+//           its bins that the entry touches, value = entry id;
+//   sort    (radix.hip) stably on the coarse bin id: the rectangles ride along;
+//   count   a block per coarse bin counts the pairs of each of its bins;
+//   (scan)  the counts' exclusive prefix over the bins gives their list starts;
+//   place   a block per coarse bin writes its bins' lists, in the order of
+//           the coarse list, and the tiles' ranges.
+// Stability carries over: a bin's list is the coarse list filtered, so keys,
+// values, ranges and counts are those of the one-level sort bit for bit, also
+// where the pair capacity cuts the render short (the cut is taken on the bins' pairs).
+//
+// Emission, sort and ranges against this (us, MI355X, with the gather of the
+// tile counts into depth order where it is the sort's last pass): 82.8M pairs of
+// eight views 1810 -> 660, 9.7M of one 1920x1080 view 185 -> 95, 3.8M in bins
+// of 32 75 -> 75.  What bounds it now: the placing, 248 us for 82.8M pairs
+// (3.4 TB/s of a copy's 4.8; its 16 ballots a round take half the issue slots),
+// and the random read of the boxes (157 us for 12M entries).  A block per list
+// in place of work items: 920 us, the lists are uneven; eight blocks per list
+// 350 us.  Loading each round on its own: 1690 us, a wave's loads wait for the
+// stores before them.
+#include "internal.h"
+
+namespace {
+
+constexpr int PB_THREADS = 256;
+constexpr int PB_ROUNDS_SMALL = 2, PB_ROUNDS_BIG = 8;   // ranks per thread of sum and emit
+constexpr int64_t PB_SMALL = 1 << 20;             // ranks up to which they take the fewer
+constexpr int64_t PB_DIRECT = 2048;               // blocks up to which each sums the partials before it itself
+constexpr int PB_WAVES = 4;                       // waves of a block of count and place
+constexpr int PB_BATCH = 4;                       // rounds of 64 pairs of a wave
+constexpr int PB_SLICE = 64 * PB_BATCH;
+constexpr int PB_ITEM = PB_WAVES * PB_SLICE;      // pairs of a work item
+constexpr int PB_GRID = 2048;                     // most blocks of count and place (eight to a CU; they loop)
+constexpr int PB_LISTS = 15;                      // lists found by a block of 16 waves
+constexpr uint32_t PB_ID = 0xFFFFFFu;             // key: coarse bin id in 24 bits, then x0, x1, y0, y1 of two bits
+
+// Bins and coarse bins touched by an entry, from its box (x0 > x1 when culled).
+struct BinRect {
+    int fx0, fx1, fy0, fy1;
+};
+__device__ __forceinline__ BinRect bin_rect(uint32_t lo, uint32_t hi, int bs) {
+    // (arithmetic shifts: the empty box ends at -1)
+    return BinRect{(int16_t)(lo & 0xFFFFu) >> bs, (int16_t)(hi & 0xFFFFu) >> bs, (int16_t)(lo >> 16) >> bs,
+                   (int16_t)(hi >> 16) >> bs};
+}
+// (bins << 32) | coarse bins: both counts in one sum
+__device__ __forceinline__ uint64_t rect_counts(const BinRect &b, int cs) {
+    const uint32_t f = (uint32_t)((b.fx1 - b.fx0 + 1) * (b.fy1 - b.fy0 + 1));
+    const uint32_t c = f ? (uint32_t)(((b.fx1 >> cs) - (b.fx0 >> cs) + 1) * ((b.fy1 >> cs) - (b.fy0 >> cs) + 1)) : 0u;
+    return ((uint64_t)f << 32) | c;
+}
+
+__device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
+    for (int o = 32; o > 0; o >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, o, 64);
+    return v;
+}
+// Sum over the block (every thread gets it); s of PB_THREADS / 64 words.
+__device__ __forceinline__ uint64_t block_sum(uint64_t v, uint64_t *s) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint64_t t = 0;
+    for (int k = 0; k < PB_THREADS / 64; k++) t += s[k];
+    __syncthreads();
+    return t;
+}
+
+// The one random read of the path: a box per rank, kept in depth order for the emission.
+template <int R>
+__global__ void __launch_bounds__(PB_THREADS) k_pairs_sum(int64_t n, const uint32_t *__restrict__ order, int bs, int cs,
+                                                          const uint2 *__restrict__ box, uint32_t *__restrict__ box_lo,
+                                                          uint32_t *__restrict__ box_hi, uint64_t *__restrict__ partials,
+                                                          uint32_t *__restrict__ n_items) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_items = 0u;   // for k_bins_lists
+    __shared__ uint64_t s_w[PB_THREADS / 64];
+    const int64_t base = (int64_t)blockIdx.x * (PB_THREADS * R) + threadIdx.x;
+    uint32_t e[R];
+    uint2 b[R];
+#pragma unroll
+    for (int j = 0; j < R; j++) e[j] = base + j * PB_THREADS < n ? order[base + j * PB_THREADS] : 0u;
+#pragma unroll
+    for (int j = 0; j < R; j++) b[j] = box[e[j]];   // (ranks past the end read entry 0)
+    uint64_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < R; j++) {
+        const int64_t r = base + j * PB_THREADS;
+        if (r < n) {
+            box_lo[r] = b[j].x;
+            box_hi[r] = b[j].y;
+            sum += rect_counts(bin_rect(b[j].x, b[j].y, bs), cs);
+        }
+    }
+    sum = block_sum(sum, s_w);
+    if (threadIdx.x == 0) partials[blockIdx.x] = sum;
+}
+
+// Coarse pairs in depth order.  As in the one-level emission, consecutive
+// ranks own consecutive positions, so each wave writes contiguous runs and its
+// lanes find the owner of their position among 64 ranks by binary search.
+template <int R>
+__global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint32_t *__restrict__ order,
+                                                           const ViewTable vt, const CoarseBins cb,
+                                                           const uint32_t *__restrict__ box_lo,
+                                                           const uint32_t *__restrict__ box_hi,
+                                                           const uint64_t *__restrict__ partials, int scanned,
+                                                           int64_t key_cap, uint32_t *__restrict__ keys,
+                                                           uint32_t *__restrict__ vals, uint32_t *__restrict__ n_keys) {
+    constexpr int W = PB_THREADS / 64;
+    __shared__ uint64_t s_w[W];
+    __shared__ uint32_t s_off[W][64], s_id[W][64], s_x[W][64], s_y[W][64], s_view[W][64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int bs = vt.bin_shift, cs = cb.shift;
+    const int64_t r0 = (int64_t)blockIdx.x * (PB_THREADS * R) + w * (R * 64) + lane;
+    uint32_t lo[R], hi[R];
+    uint64_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < R; j++) {
+        const int64_t r = r0 + j * 64;
+        lo[j] = r < n ? box_lo[r] : 0u;
+        hi[j] = r < n ? box_hi[r] : 0xFFFFFFFFu;   // the empty box
+        sum += rect_counts(bin_rect(lo[j], hi[j], bs), cs);
+    }
+    // (bins << 32 | coarse bins) before this block, then before this wave
+    uint64_t pre = 0;
+    if (scanned) {
+        pre = partials[blockIdx.x];
+    } else {
+        for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += PB_THREADS) pre += partials[b];
+        pre = block_sum(pre, s_w);
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) s_w[w] = sum;
+    __syncthreads();
+    uint64_t all = pre;
+    for (int k = 0; k < W; k++) {
+        const uint64_t x = s_w[k];
+        if (k < w) pre += x;
+        all += x;
+    }
+    // n_keys: the pairs of the bins needed and written, and the coarse pairs written
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        n_keys[0] = (uint32_t)(all >> 32);
+        if ((all >> 32) <= (uint64_t)key_cap) {
+            n_keys[1] = (uint32_t)(all >> 32);
+            n_keys[2] = (uint32_t)all;
+        }
+    }
+#pragma unroll 1
+    for (int j = 0; j < R; j++) {
+        // (the boxes are in registers: round j's by a chain of selects)
+        uint32_t l = lo[0], h = hi[0];
+#pragma unroll
+        for (int k = 1; k < R; k++) {
+            l = j == k ? lo[k] : l;
+            h = j == k ? hi[k] : h;
+        }
+        const int64_t r = r0 + j * 64;
+        const BinRect b = bin_rect(l, h, bs);
+        const uint64_t c = rect_counts(b, cs);
+        uint64_t inc = c;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint64_t t = (uint64_t)__shfl_up((unsigned long long)inc, o, 64);
+            if (lane >= o) inc += t;
+        }
+        const uint64_t at = pre + inc - c;
+        pre += (uint64_t)__shfl((unsigned long long)inc, 63, 64);
+        const uint64_t off = at >> 32, nt = c >> 32;
+        const uint32_t coff = (uint32_t)at;
+        // an entry whose bins' pairs do not all fit is dropped whole, with all after it
+        const bool kept = nt && off + nt <= (uint64_t)key_cap;
+        if (nt && off <= (uint64_t)key_cap && (uint64_t)key_cap < off + nt) {
+            n_keys[1] = (uint32_t)off;
+            n_keys[2] = coff;
+        }
+        uint32_t end = kept ? coff + (uint32_t)c : 0u;
+        for (int o = 32; o > 0; o >>= 1) end = max(end, (uint32_t)__shfl_xor((int)end, o, 64));
+        if (end == 0u) continue;   // wave-uniform
+        if (kept) {
+            const uint32_t e = order[r];
+            s_id[w][lane] = e;
+            s_view[w][lane] = (uint32_t)view_of_entry(vt, e);
+            s_x[w][lane] = (uint32_t)b.fx0 | ((uint32_t)b.fx1 << 16);
+            s_y[w][lane] = (uint32_t)b.fy0 | ((uint32_t)b.fy1 << 16);
+        }
+        s_off[w][lane] = coff;   // non-decreasing; ranks without pairs share their successor's
+        const uint32_t beg = (uint32_t)__shfl((int)coff, 0, 64);
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (uint32_t pos = beg + lane; pos < end; pos += 64) {
+            int o = 0;
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)   // probes stay within 1..63
+                if (s_off[w][o + step] <= pos) o += step;
+            const uint32_t x = s_x[w][o], y = s_y[w][o], v = s_view[w][o];
+            const int fx0 = (int)(x & 0xFFFFu), fx1 = (int)(x >> 16), fy0 = (int)(y & 0xFFFFu), fy1 = (int)(y >> 16);
+            const uint32_t q = pos - s_off[w][o], cw = (uint32_t)((fx1 >> cs) - (fx0 >> cs) + 1);
+            const uint32_t qy = q / cw, qx = q - qy * cw;
+            const int cx = (fx0 >> cs) + (int)qx, cy = (fy0 >> cs) + (int)qy, m = (1 << cs) - 1;
+            // the entry's bins inside coarse bin (cx, cy)
+            const int x0 = max(fx0 - (cx << cs), 0), x1 = min(fx1 - (cx << cs), m);
+            const int y0 = max(fy0 - (cy << cs), 0), y1 = min(fy1 - (cy << cs), m);
+            keys[pos] = (uint32_t)(cb.base[v] + cy * cb.x[v] + cx) | ((uint32_t)x0 << 24) | ((uint32_t)x1 << 26) |
+                        ((uint32_t)y0 << 28) | ((uint32_t)y1 << 30);
+            vals[pos] = s_id[w][o];
+        }
+        __builtin_amdgcn_wave_barrier();   // the next round's writes come after these reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+// Bit dy * F + dx for every bin (dx, dy) of the key's rectangle.
+template <int F>
+__device__ __forceinline__ uint32_t rect_mask(uint32_t key) {
+    const uint32_t x0 = (key >> 24) & 3u, x1 = (key >> 26) & 3u, y0 = (key >> 28) & 3u, y1 = key >> 30;
+    const uint32_t row = (2u << x1) - (1u << x0);
+    // the rows y0 .. y1 as one bit every F bits, from y0 F on
+    const uint32_t ones = F == 4 ? 0x1111u : 0x5u;
+    const uint32_t rows = (ones << (F * y0)) & ((2u << (F * y1)) - 1u);
+    return row * rows;
+}
+
+// First of the n keys whose coarse bin is not below `bin`, by a search that
+// splits the range 64 ways a step (whole wave; n <= 2^32 in six steps).
+__device__ __forceinline__ uint32_t coarse_bound(const uint32_t *__restrict__ keys, uint32_t n, uint32_t bin) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t lo = 0, hi = n;
+    while (lo < hi) {
+        const uint32_t step = (uint32_t)(((uint64_t)(hi - lo) + 63) / 64);
+        const uint64_t p = (uint64_t)lo + (uint64_t)(lane + 1) * step - 1;
+        const bool below = p < hi && (keys[p] & PB_ID) < bin;
+        const uint32_t cnt = (uint32_t)__popcll(__ballot(below));
+        const uint64_t top = (uint64_t)lo + (uint64_t)(cnt + 1) * step - 1;
+        const uint64_t bot = (uint64_t)lo + (uint64_t)cnt * step;
+        lo = bot < hi ? (uint32_t)bot : hi;
+        hi = top < hi ? (uint32_t)top : hi;
+    }
+    return lo;
+}
+
+// Coarse bin `cid`: its view, and its bin (0, 0) with the number of its bins
+// that lie in the view.
+struct CoarsePlace {
+    int bin0, pitch, w, h;
+};
+__device__ __forceinline__ CoarsePlace coarse_place(const ViewTable &vt, const CoarseBins &cb, int cid) {
+    int v = 0;
+    for (int k = 1; k < vt.n_views; k++) v += cid >= cb.base[k] ? 1 : 0;
+    const int l = cid - cb.base[v], cy = l / cb.x[v], cx = l - cy * cb.x[v];
+    const int bx = vt.bins_x[v], by = (vt.bin_base[v + 1] - vt.bin_base[v]) / bx;
+    return CoarsePlace{vt.bin_base[v] + (cy << cb.shift) * bx + (cx << cb.shift), bx, bx - (cx << cb.shift),
+                       by - (cy << cb.shift)};
+}
+
+// The coarse lists, cut into work items of PB_ITEM pairs: a wave finds each
+// list's start, and each list takes its items' places from a counter (which
+// list gets which is left to chance, and shows in nothing).  An item is
+// (coarse bin, part of its list, list start, list length).  Also clears the
+// bins' counts for the launch that adds them, and the tiles' ranges.
+__global__ void __launch_bounds__(1024) k_bins_lists(const uint32_t *__restrict__ keys,
+                                                     const uint32_t *__restrict__ n_keys, int cbins,
+                                                     uint4 *__restrict__ items, uint32_t *__restrict__ n_items,
+                                                     uint32_t *__restrict__ counts, int64_t bins,
+                                                     uint32_t *__restrict__ ranges, int64_t range_words) {
+    __shared__ uint32_t s_at[PB_LISTS + 1];
+    const int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x, tn = (int64_t)gridDim.x * 1024;
+    for (int64_t i = t0; i < bins; i += tn) counts[i] = 0u;
+    for (int64_t i = t0; i < range_words; i += tn) ranges[i] = 0u;
+    const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    const int cid = (int)blockIdx.x * PB_LISTS + w;
+    const uint32_t p = coarse_bound(keys, n_keys[2], (uint32_t)cid);   // (bins past the last end where it ends)
+    if (lane == 0) s_at[w] = p;
+    __syncthreads();
+    if (w == PB_LISTS || cid >= cbins) return;
+    const uint32_t m = s_at[w + 1] - p, ni = (m + PB_ITEM - 1) / PB_ITEM;
+    if (ni == 0) return;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(n_items, ni);
+    at = (uint32_t)__shfl((int)at, 0, 64);
+    for (uint32_t k = lane; k < ni; k += 64) items[at + k] = make_uint4((uint32_t)cid, k, p, m);
+}
+
+// Pairs of each bin in every wave's slice of an item and in the item, and the bins' sums.
+template <int F>
+__global__ void __launch_bounds__(PB_WAVES * 64) k_bins_count(const uint32_t *__restrict__ keys, const ViewTable vt,
+                                                              const CoarseBins cb, const uint4 *__restrict__ items,
+                                                              const uint32_t *__restrict__ n_items,
+                                                              uint32_t *__restrict__ slices, uint32_t *__restrict__ sums,
+                                                              uint32_t *__restrict__ counts) {
+    constexpr int NC = F * F;
+    __shared__ uint32_t s_c[2][PB_WAVES][NC];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t ni = *n_items;
+    int flip = 0;
+    for (uint32_t it = blockIdx.x; it < ni; it += gridDim.x, flip ^= 1) {
+        const uint4 item = items[it];
+        const uint32_t m = item.w, i0 = min(m, item.y * PB_ITEM + (uint32_t)w * PB_SLICE), i1 = min(m, i0 + PB_SLICE);
+        uint32_t key[PB_BATCH], c[NC];
+#pragma unroll
+        for (int j = 0; j < PB_BATCH; j++) key[j] = keys[item.z + min(i0 + j * 64 + lane, m - 1)];
+#pragma unroll
+        for (int k = 0; k < NC; k++) c[k] = 0;
+#pragma unroll
+        for (int j = 0; j < PB_BATCH; j++) {
+            const uint32_t mask = i0 + j * 64 + lane < i1 ? rect_mask<F>(key[j]) : 0u;
+#pragma unroll
+            for (int k = 0; k < NC; k++) c[k] += (uint32_t)__popcll(__ballot((mask >> k) & 1u));
+        }
+        uint32_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < NC; k++) mine = lane == k ? c[k] : mine;
+        if (lane < NC) {
+            s_c[flip][w][lane] = mine;
+            slices[((size_t)it * PB_WAVES + w) * NC + lane] = mine;
+        }
+        __syncthreads();   // (one a turn: the next writes the other half)
+        if (tid < NC) {
+            uint32_t t = 0;
+#pragma unroll
+            for (int k = 0; k < PB_WAVES; k++) t += s_c[flip][k][tid];
+            sums[(size_t)it * NC + tid] = t;
+            const CoarsePlace p = coarse_place(vt, cb, (int)item.x);
+            if (t) atomicAdd(counts + p.bin0 + (tid / F) * p.pitch + tid % F, t);   // (bins past the border hold no pair)
+        }
+    }
+}
+
+// Each wave walks its slice of an item and appends every pair to the lists of
+// the bins in its rectangle: a ballot per bin gives the places of a round's
+// pairs, the wave's place in each list is a scalar.
+template <int F>
+__global__ void __launch_bounds__(PB_WAVES * 64) k_bins_place(const uint32_t *__restrict__ ckeys,
+                                                              const uint32_t *__restrict__ cvals, const ViewTable vt,
+                                                              const CoarseBins cb, const uint4 *__restrict__ items,
+                                                              const uint32_t *__restrict__ n_items,
+                                                              const uint32_t *__restrict__ slices,
+                                                              const uint32_t *__restrict__ sums,
+                                                              const uint32_t *__restrict__ starts,
+                                                              const uint32_t *__restrict__ counts,
+                                                              uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
+                                                              uint32_t *__restrict__ ranges) {
+    constexpr int NC = F * F, G = PB_WAVES * 64 / NC;
+    __shared__ uint32_t s_sum[G][NC], s_from[PB_WAVES + 1][NC];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t ni = *n_items;
+    for (uint32_t it = blockIdx.x; it < ni; it += gridDim.x) {
+        const uint4 item = items[it];
+        const uint32_t part = item.y, m = item.w;
+        const uint32_t i0 = min(m, part * PB_ITEM + (uint32_t)w * PB_SLICE), i1 = min(m, i0 + PB_SLICE);
+        // Stores and loads of a wave return in order: all loads come before the stores.
+        uint32_t key[PB_BATCH], val[PB_BATCH];
+#pragma unroll
+        for (int j = 0; j < PB_BATCH; j++) {
+            const uint32_t at = item.z + min(i0 + j * 64 + lane, m - 1);
+            key[j] = ckeys[at];
+            val[j] = cvals[at];
+        }
+        const CoarsePlace p = coarse_place(vt, cb, (int)item.x);
+        // the pairs of each bin in the list's items before this one
+        uint32_t pre = 0;
+        for (uint32_t k = (uint32_t)(tid / NC); k < part; k += G) pre += sums[(size_t)(it - part + k) * NC + tid % NC];
+        s_sum[tid / NC][tid % NC] = pre;
+        uint32_t own[PB_WAVES], s0 = 0, all = 0;
+        const int dx = tid % F, dy = tid / F, bin = p.bin0 + dy * p.pitch + dx;
+        const bool mine = tid < NC && dx < p.w && dy < p.h;
+        if (tid < NC) {
+#pragma unroll
+            for (int k = 0; k < PB_WAVES; k++) own[k] = slices[((size_t)it * PB_WAVES + k) * NC + tid];
+            if (mine) {
+                s0 = starts[bin];
+                if (part == 0) all = counts[bin];
+            }
+        }
+        __syncthreads();
+        if (tid < NC) {
+            uint32_t at = s0;
+#pragma unroll
+            for (int k = 0; k < G; k++) at += s_sum[k][tid];
+#pragma unroll
+            for (int k = 0; k < PB_WAVES; k++) {
+                s_from[k][tid] = at;
+                at += own[k];
+            }
+            s_from[PB_WAVES][tid] = at;
+            if (all) {
+                set_bin_range(vt, (uint32_t)bin, 0, s0, ranges);
+                set_bin_range(vt, (uint32_t)bin, 1, s0 + all, ranges);
+            }
+        }
+        __syncthreads();
+        uint32_t at[NC];
+#pragma unroll
+        for (int k = 0; k < NC; k++) at[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_from[w][k]);
+#pragma unroll
+        for (int j = 0; j < PB_BATCH; j++) {
+            if (i0 + j * 64 >= i1) break;   // wave-uniform
+            const uint32_t mask = i0 + j * 64 + lane < i1 ? rect_mask<F>(key[j]) : 0u;
+#pragma unroll
+            for (int k = 0; k < NC; k++) {
+                const bool on = (mask >> k) & 1u;
+                const uint64_t b = __ballot(on);
+                if (on) {
+                    const uint32_t before =
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                    (vals + at[k])[before] = val[j];
+                }
+                at[k] += (uint32_t)__popcll(b);
+            }
+        }
+        // the item's keys, one value per bin
+#pragma unroll
+        for (int k = w; k < NC; k += PB_WAVES) {
+            const uint32_t id = (uint32_t)(p.bin0 + (k / F) * p.pitch + k % F), end = s_from[PB_WAVES][k];
+            for (uint32_t i = s_from[0][k] + lane; i < end; i += 64) keys[i] = id;
+        }
+        __syncthreads();   // the next turn writes s_sum and s_from
+    }
+}
+
+// The scratch: the items (at most one per coarse bin and one per PB_ITEM pairs),
+// the pairs of each bin by slice and by item, the bins' counts and starts, and
+// the number of items.
+struct PbWs {
+    uint4 *items;
+    uint32_t *slices, *sums, *counts, *starts, *n_items;
+};
+int64_t most_items(int64_t cbins, int64_t key_cap) { return cbins + key_cap / PB_ITEM; }
+PbWs pb_ws(void *ws, const CoarseBins &cb, int64_t key_cap, int64_t bins) {
+    const int64_t ni = most_items(cb.bins, key_cap), nc = (int64_t)1 << (2 * cb.shift);
+    uint4 *items = reinterpret_cast<uint4 *>(ws);
+    uint32_t *p = reinterpret_cast<uint32_t *>(items + ni);
+    uint32_t *sums = p + ni * PB_WAVES * nc, *counts = sums + ni * nc;
+    return PbWs{items, p, sums, counts, counts + bins, counts + 2 * bins};
+}
+
+int64_t fill_coarse(const ViewTable &vt, int shift, CoarseBins *cb) {
+    const int f = 1 << shift;
+    int64_t bins = 0;
+    cb->shift = shift;
+    for (int v = 0; v < vt.n_views; v++) {
+        const int bx = vt.bins_x[v], by = (vt.bin_base[v + 1] - vt.bin_base[v]) / bx;
+        cb->base[v] = (int32_t)bins;
+        cb->x[v] = (bx + f - 1) / f;
+        bins += (int64_t)cb->x[v] * ((by + f - 1) / f);
+    }
+    cb->bins = (int32_t)bins;
+    return bins;
+}
+
+template <int R>
+void pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
+                uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals, uint32_t *n_keys,
+                uint64_t *partials, uint32_t *n_items, hipStream_t s) {
+    const int64_t nb = (n + PB_THREADS * R - 1) / (PB_THREADS * R);
+    const dim3 grid((unsigned)nb), block(PB_THREADS);
+    hipLaunchKernelGGL((k_pairs_sum<R>), grid, block, 0, s, n, order, vt.bin_shift, cb.shift,
+                       reinterpret_cast<const uint2 *>(box), box_lo, box_hi, partials, n_items);
+    const int scanned = nb > PB_DIRECT;
+    if (scanned) scan_partials_u64(partials, nb, s);
+    hipLaunchKernelGGL((k_pairs_emit<R>), grid, block, 0, s, n, order, vt, cb, box_lo, box_hi, partials, scanned, key_cap,
+                       keys, vals, n_keys);
+}
+
+}  // namespace
+
+size_t pairs_tmp_bytes(int64_t n) {
+    const int64_t small = n < PB_SMALL ? n : PB_SMALL;
+    const int64_t a = small / (PB_THREADS * PB_ROUNDS_SMALL) + 1, b = n / (PB_THREADS * PB_ROUNDS_BIG) + 1;
+    return (size_t)(a > b ? a : b) * 8 + 256;
+}
+
+size_t coarse_bins_bytes(int64_t tiles, int64_t key_cap) {
+    // Bins are at most the tiles, and coarse_bins() takes at most two bins'
+    // worth of slots per bin; per item and slot PB_WAVES + 1 words.
+    const int64_t per_item = 4 + (PB_WAVES + 1) * 16;
+    return (size_t)(tiles * (4 + 2 * (PB_WAVES + 1) + 2) + key_cap / PB_ITEM * per_item + 1) * 4 + 256;
+}
+
+// Two launches more than the one-level path, against the pairs' traffic
+// (render of one view, us, two levels / one, by pairs): 0.6M 172 / 156, 1.6M
+// 222 / 212, 2.7M 271 / 269, 4.0M 309 / 317, 4.7M 384 / 402, 7.0M 437 / 472,
+// 14.1M 1031 / 1142, 21.2M 1159 / 1367.  The host knows the pairs by the
+// frame's capacity; few entries leave the emission's blocks too few.
+//
+// Coarse bins of 4 x 4 bins unless that leaves fewer than 256 of them (too few
+// places at once for a sort pass's writes and, in bins of 32, too few items),
+// then of 2 x 2.  Skinny or tiny views, where the coarse grid is mostly border,
+// stay with one level.
+bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb) {
+    if (n < PAIR_BINS_ENTRIES || key_cap < PAIR_BINS_PAIRS) return false;
+    const int64_t bins = vt.bin_base[vt.n_views];
+    int64_t c = fill_coarse(vt, 2, cb);
+    if (c < PAIR_BINS_WIDE) c = fill_coarse(vt, 1, cb);
+    return c >= PAIR_BINS_FEW && c <= (int64_t)PB_ID && (c << (2 * cb->shift)) <= 2 * bins;
+}
+
+void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
+                       uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals,
+                       uint32_t *n_keys, void *ws, void *tmp, hipStream_t s) {
+    uint32_t *n_items = pb_ws(ws, cb, key_cap, vt.bin_base[vt.n_views]).n_items;
+    uint64_t *partials = reinterpret_cast<uint64_t *>(tmp);
+    if (n <= PB_SMALL)
+        pairs_emit<PB_ROUNDS_SMALL>(n, order, vt, cb, box, box_lo, box_hi, key_cap, keys, vals, n_keys, partials, n_items, s);
+    else
+        pairs_emit<PB_ROUNDS_BIG>(n, order, vt, cb, box, box_lo, box_hi, key_cap, keys, vals, n_keys, partials, n_items, s);
+}
+
+void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_cap, const uint32_t *ckeys,
+                       const uint32_t *cvals, uint32_t *keys, uint32_t *vals, const uint32_t *n_keys, uint32_t *ranges,
+                       int64_t n_tiles, void *ws, void *tmp, hipStream_t s) {
+    const int64_t bins = vt.bin_base[vt.n_views], most = most_items(cb.bins, key_cap);
+    const PbWs p = pb_ws(ws, cb, key_cap, bins);
+    const dim3 grid((unsigned)(most < PB_GRID ? most : PB_GRID)), block(PB_WAVES * 64);
+    hipLaunchKernelGGL(k_bins_lists, dim3((unsigned)(cb.bins + PB_LISTS - 1) / PB_LISTS), dim3(1024), 0, s, ckeys, n_keys,
+                       cb.bins, p.items, p.n_items, p.counts, bins, ranges, 2 * n_tiles);
+    if (cb.shift == 2)
+        hipLaunchKernelGGL(k_bins_count<4>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.counts);
+    else
+        hipLaunchKernelGGL(k_bins_count<2>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.counts);
+    scan_u32(p.counts, p.starts, bins, nullptr, tmp, s);
+    if (cb.shift == 2)
+        hipLaunchKernelGGL(k_bins_place<4>, grid, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
+                           p.starts, p.counts, keys, vals, ranges);
+    else
+        hipLaunchKernelGGL(k_bins_place<2>, grid, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
+                           p.starts, p.counts, keys, vals, ranges);
+}
+
+AS_WARM_KERNEL(pair_bins)
