@@ -154,7 +154,7 @@ void frame_buffers(as_frame *f, bool keys_only, V &&visit) {
     dbuf(f->scan_tmp, scan > sums ? scan : sums);
     // forward dispatch slots: the tiles, or 32 per 8 bins of 32 (at most 2 tile + 64)
     arr(&f->ranges, tile * 2); arr(&f->tile_order, 2 * tile + 64); arr(&f->queue, 2); arr(&f->tile_work, tile);
-    arr(&f->tile_hi, tile); arr(&f->n_items, 1); arr(&f->order_table, (int64_t)order_table_words(tile));
+    arr(&f->tile_hi, tile); arr(&f->tile_seg, tile); arr(&f->n_items, 1); arr(&f->order_table, (int64_t)order_table_words(tile));
     arr(&f->bwd_items, tile * (AS_CK_MAX + 1) * 2);
     arr(&f->tile_err, tile * 2);
     if (!(f->flags & AS_FRAME_FORWARD_ONLY)) arr(&f->ckpt, tile * AS_CK_MAX * 256 * 4);
@@ -704,7 +704,6 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
         StageTimer t(ctx, AS_STAGE_BLEND_FWD, s);
         f->ck_written = f->ckpt != nullptr;
         f->bm_written = f->bmask != nullptr;
-        f->ck_seg = blend_fwd_batch(bl);
         // frames that can take a reverse pass have the forward clear the 2D
         // gradient rows it will add into
         const bool zg = !(f->flags & AS_FRAME_FORWARD_ONLY);

@@ -227,9 +227,9 @@ __device__ __forceinline__ LaneGeom lane_geom(int tid) {
 // hits[row][..]; returns this lane's row count.  Row r takes the blocks of
 // sel0 << r (sel0: the bits of row 0's block or blocks).  `ok(j)` adds a
 // condition that is the same for the whole wave.
-template <int BATCH, typename Ok>
+template <int BATCH, typename Ok, typename Chunk>
 __device__ __forceinline__ int compact_rows(const uint16_t *s_bm, int cnt, HitT<BATCH> (*hits)[BATCH + 4],
-                                            uint32_t sel0, int row, Ok ok) {
+                                            uint32_t sel0, int row, Ok ok, Chunk chunk) {
     const int lane = threadIdx.x & 63;
     const uint64_t lt = lanemask_lt();
     int n[4] = {0, 0, 0, 0};
@@ -245,6 +245,7 @@ __device__ __forceinline__ int compact_rows(const uint16_t *s_bm, int cnt, HitT<
             if (hit) hits[r][n[r] + __popcll(bal & lt)] = (HitT<BATCH>)j;
             n[r] += __popcll(bal);
         }
+        chunk(k, n);
     }
     return row == 0 ? n[0] : row == 1 ? n[1] : row == 2 ? n[2] : n[3];
 }
@@ -301,6 +302,7 @@ struct BlendShared {
     StagedRec rec[BATCH];
     uint16_t bm[BATCH];                              // block masks (block_mask)
     HitT<BATCH> hits[AS_BLOCK / 64][4][BATCH + 4];  // +4: the loops read one index ahead
+    uint16_t below[AS_BLOCK / 64][BATCH / 64][4];   // the rows' hits below record 64 (k + 1)
 };
 
 // Next tile of this block: a queue slot (persistent grid) or the block index;
@@ -317,6 +319,16 @@ __device__ __forceinline__ bool next_tile(uint32_t *queue, int n_tiles, int iter
     __syncthreads();   // all have read the slot before thread 0 takes the next one
     return idx < (uint32_t)n_tiles;
 }
+
+// Spacing of the forward's checkpoints, in list entries.  Up to CK_TILES tiles
+// the reverse pass's items do not fill the device, so its time is that of the
+// longest one, a chain of dependent steps (about 1000 cycles each): the spacing
+// starts fine and doubles as a list goes on.  From 256 from the start to this: 2,000
+// Gaussians at 128x128 53 -> 28 us, 20,000 at 640x480 88 -> 74 (the forward
+// 46 -> 49).  Above, the items' own cost shows: 801x603 (1938 tiles) 102 -> 105,
+// 1256x828 190 -> 206.
+constexpr uint32_t CK_FINE = 64, CK_COARSE = 256;
+constexpr int CK_TILES = 1536;
 
 // Forward dispatch slots (k_tile_order): a tile id, or ORDER_NONE for a slot
 // without a tile (slots grouped by bin of 32 past the image edge).
@@ -339,7 +351,8 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
                                                         int32_t *__restrict__ dom_out, double *__restrict__ err,
                                                         unsigned long long *__restrict__ tile_err,
                                                         uint32_t *__restrict__ tile_work,
-                                                        uint32_t *__restrict__ tile_hi, float4 *__restrict__ ckpt,
+                                                        uint32_t *__restrict__ tile_hi, uint32_t *__restrict__ tile_seg,
+                                                        float4 *__restrict__ ckpt, uint32_t ck_first,
                                                         uint16_t *__restrict__ bm_out, int ellipse,
                                                         uint32_t *queue, int n_tiles, uint4 *__restrict__ zero4,
                                                         int64_t zero_n4) {
@@ -374,11 +387,13 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
         int32_t dom = -1;
         uint32_t last = 0, nc = 0;
         int done = inside ? 0 : 1;
-        // checkpoint slots of this pixel: (T, colour composited so far) at
-        // the top of batches 1 .. AS_CK_MAX; the epilogue turns the colour
-        // into the colour behind the boundary
+        // checkpoint slots of this pixel: (T, colour composited so far) in
+        // front of list entries seg, 2 seg, .. (nck of them); the epilogue
+        // turns the colour into the colour behind the boundary.  When a fourth
+        // comes up and seg is below CK_COARSE, it doubles: the second becomes
+        // the first, the fourth the second.
         float4 *ck = ckpt ? ckpt + (size_t)tile * AS_CK_MAX * 256 + lg.ly * 16 + lg.lx : nullptr;
-        int nck = 0;
+        uint32_t nck = 0, seg = ck_first, next_ck = ckpt ? ck_first : 0xFFFFFFFFu;
 
         Fetched nf[R];
 #pragma unroll
@@ -386,10 +401,6 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
             if (start + k * AS_BLOCK + tid < end) fetch(vals, rec, box, start + k * AS_BLOCK + tid, ox, oy, nf[k]);
         for (uint32_t b0 = start; b0 < end; b0 += BATCH) {
             if (__syncthreads_count(done) == AS_BLOCK) break;   // also: the previous batch is consumed
-            if (ck && b0 > start && nck < AS_CK_MAX) {
-                if (inside) ck[nck * 256] = make_float4(T, C0, C1, C2);
-                nck++;
-            }
 #pragma unroll
             for (int k = 0; k < R; k++) {
                 const int t = k * AS_BLOCK + tid;
@@ -406,68 +417,92 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
                 if (b0 + BATCH + t < end) fetch(vals, rec, box, b0 + BATCH + t, ox, oy, nf[k]);
             }
             __syncthreads();
-            if (__ballot(!done) == 0) continue;                 // the whole wave has saturated
+            const bool live = __ballot(!done) != 0;             // not the whole wave has saturated
             const int cnt = (int)min((uint32_t)BATCH, end - b0);
             // wave w's rows are the 4x4 blocks 4 w .. 4 w + 3
-            const int nh = compact_rows<BATCH>(sh.bm, cnt, sh.hits[w], 1u << (4 * w), lg.row,
-                                               [](int) { return true; });
-            if (done) continue;
-            // Two hits per step: both records' loads and alpha evaluations are
-            // independent and overlap; only the compositing is sequential.
-            // The next step's indices are loaded one step ahead.
-            int ja = hits[0], jb = hits[1];
+            int nh = 0;
+            if (live)
+                nh = compact_rows<BATCH>(sh.bm, cnt, sh.hits[w], 1u << (4 * w), lg.row, [](int) { return true; },
+                                         [&](int k, const int *n) {
+                                             if (lane < 4)
+                                                 sh.below[w][k][lane] = (uint16_t)(lane == 0 ? n[0] : lane == 1 ? n[1]
+                                                                                   : lane == 2 ? n[2] : n[3]);
+                                         });
+            // The batch in one run, or cut at the checkpoints inside it.
+            const uint32_t rel = b0 - start, rel_end = rel + (uint32_t)cnt;
             int h = 0;
-            for (; h < nh; h += 2) {
-                const bool two = h + 1 < nh;
-                const int j0 = ja, j1 = two ? jb : ja;
-                ja = hits[h + 2];
-                jb = hits[h + 3];
-                const float4 a0 = sh.rec[j0].mc, a1 = sh.rec[j0].cc, a2 = sh.rec[j0].ex;
-                const float4 b0q = sh.rec[j1].mc, b1q = sh.rec[j1].cc, b2q = sh.rec[j1].ex;
-                const uint32_t ma = __float_as_uint(a2.y), mb = __float_as_uint(b2q.y);
-                const float dxa = a0.x - px, dya = a0.y - py, dxb = b0q.x - px, dyb = b0q.y - py;
-                const float rawa = __builtin_amdgcn_exp2f(blend_exponent(dxa, dya, a0, a1));
-                const float rawb = __builtin_amdgcn_exp2f(blend_exponent(dxb, dyb, b0q, b1q));
-                const float alpha_a = fminf(ALPHA_MAX, rawa), alpha_b = fminf(ALPHA_MAX, rawb);
-                const bool oka = (ma & lg.pbits) == lg.pbits && alpha_a >= ALPHA_MIN;   // box holds the pixel
-                const bool okb = two && (mb & lg.pbits) == lg.pbits && alpha_b >= ALPHA_MIN;
-                // Both records are decided with selects and the loop leaves
-                // once after them, so the second record's loads are not held
-                // back behind a branch.  A record that would take T below the
-                // stop threshold is not added, and nothing after it is; a
-                // non-contributor adds exactly zero and changes nothing.
-                const float tA = T * (1.0f - alpha_a);
-                const bool stopA = oka && tA < T_STOP;
-                const bool useA = oka && !stopA;
-                float wgt = useA ? alpha_a * T : 0.0f;
-                C0 += wgt * a1.z;
-                C1 += wgt * a1.w;
-                C2 += wgt * a2.x;
-                if (wgt > wbest) {
-                    wbest = wgt;
-                    dom = (int32_t)__float_as_uint(a2.z);
+            for (uint32_t at = rel; at < rel_end;) {
+                if (at == next_ck) {
+                    if (nck == AS_CK_MAX) {
+                        if (inside) ck[0] = ck[256];
+                        nck = 1;
+                        seg *= 2;
+                    }
+                    if (inside) ck[nck * 256] = make_float4(T, C0, C1, C2);
+                    nck++;
+                    next_ck = nck == AS_CK_MAX && seg >= CK_COARSE ? 0xFFFFFFFFu : next_ck + seg;
                 }
-                T = useA ? tA : T;
-                last = useA ? b0 + (uint32_t)j0 : last;
-                nc += useA ? 1u : 0u;
-                const float tB = T * (1.0f - alpha_b);
-                const bool stopB = !stopA && okb && tB < T_STOP;
-                const bool useB = !stopA && okb && !stopB;
-                wgt = useB ? alpha_b * T : 0.0f;
-                C0 += wgt * b1q.z;
-                C1 += wgt * b1q.w;
-                C2 += wgt * b2q.x;
-                if (wgt > wbest) {
-                    wbest = wgt;
-                    dom = (int32_t)__float_as_uint(b2q.z);
+                const uint32_t to = min(next_ck, rel_end);
+                const int he = to == rel_end ? nh : (int)sh.below[w][(to - rel) / 64 - 1][lg.row];
+                at = to;
+                if (!live || done) continue;
+                // Two hits per step: both records' loads and alpha evaluations are
+                // independent and overlap; only the compositing is sequential.
+                // The next step's indices are loaded one step ahead.
+                int ja = hits[h], jb = hits[h + 1];
+                for (; h < he; h += 2) {
+                    const bool two = h + 1 < he;
+                    const int j0 = ja, j1 = two ? jb : ja;
+                    ja = hits[h + 2];
+                    jb = hits[h + 3];
+                    const float4 a0 = sh.rec[j0].mc, a1 = sh.rec[j0].cc, a2 = sh.rec[j0].ex;
+                    const float4 b0q = sh.rec[j1].mc, b1q = sh.rec[j1].cc, b2q = sh.rec[j1].ex;
+                    const uint32_t ma = __float_as_uint(a2.y), mb = __float_as_uint(b2q.y);
+                    const float dxa = a0.x - px, dya = a0.y - py, dxb = b0q.x - px, dyb = b0q.y - py;
+                    const float rawa = __builtin_amdgcn_exp2f(blend_exponent(dxa, dya, a0, a1));
+                    const float rawb = __builtin_amdgcn_exp2f(blend_exponent(dxb, dyb, b0q, b1q));
+                    const float alpha_a = fminf(ALPHA_MAX, rawa), alpha_b = fminf(ALPHA_MAX, rawb);
+                    const bool oka = (ma & lg.pbits) == lg.pbits && alpha_a >= ALPHA_MIN;   // box holds the pixel
+                    const bool okb = two && (mb & lg.pbits) == lg.pbits && alpha_b >= ALPHA_MIN;
+                    // Both records are decided with selects and the loop leaves
+                    // once after them, so the second record's loads are not held
+                    // back behind a branch.  A record that would take T below the
+                    // stop threshold is not added, and nothing after it is; a
+                    // non-contributor adds exactly zero and changes nothing.
+                    const float tA = T * (1.0f - alpha_a);
+                    const bool stopA = oka && tA < T_STOP;
+                    const bool useA = oka && !stopA;
+                    float wgt = useA ? alpha_a * T : 0.0f;
+                    C0 += wgt * a1.z;
+                    C1 += wgt * a1.w;
+                    C2 += wgt * a2.x;
+                    if (wgt > wbest) {
+                        wbest = wgt;
+                        dom = (int32_t)__float_as_uint(a2.z);
+                    }
+                    T = useA ? tA : T;
+                    last = useA ? b0 + (uint32_t)j0 : last;
+                    nc += useA ? 1u : 0u;
+                    const float tB = T * (1.0f - alpha_b);
+                    const bool stopB = !stopA && okb && tB < T_STOP;
+                    const bool useB = !stopA && okb && !stopB;
+                    wgt = useB ? alpha_b * T : 0.0f;
+                    C0 += wgt * b1q.z;
+                    C1 += wgt * b1q.w;
+                    C2 += wgt * b2q.x;
+                    if (wgt > wbest) {
+                        wbest = wgt;
+                        dom = (int32_t)__float_as_uint(b2q.z);
+                    }
+                    T = useB ? tB : T;
+                    last = useB ? b0 + (uint32_t)j1 : last;
+                    nc += useB ? 1u : 0u;
+                    if (stopA || stopB) {
+                        done = 1;
+                        break;
+                    }
                 }
-                T = useB ? tB : T;
-                last = useB ? b0 + (uint32_t)j1 : last;
-                nc += useB ? 1u : 0u;
-                if (stopA || stopB) {
-                    done = 1;
-                    break;
-                }
+                h = he;
             }
         }
 
@@ -486,7 +521,7 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
             t_final[pix] = T;
             last_out[pix] = last;
             ncontrib_out[pix] = nc;
-            for (int k = 0; k < nck; k++) {
+            for (uint32_t k = 0; k < nck; k++) {
                 const float4 c = ck[k * 256];
                 ck[k * 256] = make_float4(c.x, C0 - c.y, C1 - c.z, C2 - c.w);
             }
@@ -534,6 +569,7 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
             }
             tile_work[tile] = nsum;
             tile_hi[tile] = hmax;
+            tile_seg[tile] = seg;
             if (gt) {
                 tile_err[2 * tile] = a;
                 tile_err[2 * tile + 1] = b;
@@ -565,6 +601,7 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
 // conic and opacity gradients and issues the global atomics: one set per
 // (Gaussian, tile).
 constexpr int BWD_BLOCK = 128;
+constexpr int BWD_GRID = 8192;   // blocks for renders with fewer items at hand: four segments a tile get one each
 
 template <int BATCH>
 struct BwdShared {
@@ -599,7 +636,8 @@ __global__ void __launch_bounds__(BWD_BLOCK) k_blend_bwd(const uint32_t *__restr
                                                          const uint32_t *__restrict__ items,
                                                          const uint32_t *__restrict__ n_items,
                                                          const uint32_t *__restrict__ tile_hi,
-                                                         const float4 *__restrict__ ckpt, uint32_t seg_len,
+                                                         const uint32_t *__restrict__ tile_seg,
+                                                         const float4 *__restrict__ ckpt,
                                                          const uint32_t *__restrict__ vals,
                                                          const BlendRec *__restrict__ rec,
                                                          const short4 *__restrict__ box, const ViewTable vt,
@@ -639,6 +677,7 @@ __global__ void __launch_bounds__(BWD_BLOCK) k_blend_bwd(const uint32_t *__restr
         uint32_t s0 = start, s1 = hi;
         bool last_seg = true;
         if (ckpt) {
+            const uint32_t seg_len = tile_seg[tile];
             const uint32_t nseg = min((hi - start + seg_len - 1) / seg_len, (uint32_t)AS_CK_MAX + 1u);
             s0 = start + seg * seg_len;
             last_seg = seg + 1 == nseg;
@@ -728,7 +767,7 @@ __global__ void __launch_bounds__(BWD_BLOCK) k_blend_bwd(const uint32_t *__restr
             }
             __syncthreads();
             const int nh = compact_rows<BATCH>(sh.bm, (int)(b1 - b0), sh.hits[w], sel0, row,
-                                               [&](int j) { return b0 + (uint32_t)j < wlast; });
+                                               [&](int j) { return b0 + (uint32_t)j < wlast; }, [](int, const int *) {});
             // the wave walks max over its rows of the row counts; rows past their
             // own count idle
             int nmax = nh;
@@ -1065,14 +1104,13 @@ __global__ void __launch_bounds__(1024) k_view_err(const ViewTable vt, const Vie
 // order_on = 0, in tile order.  Launched by the reverse pass, so renders that
 // none follows do not pay for it.
 struct WorkOrder {
-    const uint32_t *work, *ranges, *tile_hi;
-    uint32_t seg_len;
+    const uint32_t *work, *ranges, *tile_hi, *tile_seg;
     int ck, order_on;
-    // segments of a tile: one per checkpointed batch boundary it crosses, plus one
+    // segments of a tile: one per checkpoint in front of its last contributor, plus one
     __device__ uint32_t nseg(int t) const {
         const uint32_t start = ranges[2 * t], hi = tile_hi[t];
         if (hi <= start) return 0u;
-        return ck ? min((hi - start + seg_len - 1) / seg_len, (uint32_t)AS_CK_MAX + 1u) : 1u;
+        return ck ? min((hi - start + tile_seg[t] - 1) / tile_seg[t], (uint32_t)AS_CK_MAX + 1u) : 1u;
     }
     __device__ int cls(int t) const { return order_on ? 128 - work_class(work[t]) : 0; }
 };
@@ -1173,7 +1211,7 @@ void launch_bwd_items(const as_frame *f, int order_on, hipStream_t s) {
     const int tiles = f->vt.tile_base[f->vt.n_views];
     if (tiles == 0) return;
     const dim3 grid((unsigned)((tiles + ORDER_BLOCK - 1) / ORDER_BLOCK)), block(ORDER_BLOCK);
-    const WorkOrder wo{f->tile_work, f->ranges, f->tile_hi, (uint32_t)f->ck_seg, f->ck_written ? 1 : 0, order_on};
+    const WorkOrder wo{f->tile_work, f->ranges, f->tile_hi, f->tile_seg, f->ck_written ? 1 : 0, order_on};
     if (tiles <= ORDER_ALONE) {
         hipLaunchKernelGGL((k_bwd_items<false>), grid, block, 0, s, tiles, wo, f->order_table, f->bwd_items, f->n_items);
         return;
@@ -1192,8 +1230,6 @@ int resident_blocks(Kern k, int n_cu, int block = AS_BLOCK) {
 }
 }  // namespace
 
-int blend_fwd_batch(const BlendLaunch &bl) { return bl.batch >= 1024 ? 1024 : bl.batch >= 512 ? 512 : 256; }
-
 bool launch_blend_fwd(const as_frame *f, const uint32_t *vals, const uint32_t *tile_order, const BlendLaunch &bl,
                       const ViewTable &vt, const ViewImagesC &gt, const ViewImages &image, hipStream_t s,
                       float *zero_g2d, int64_t zero_floats) {
@@ -1206,6 +1242,7 @@ bool launch_blend_fwd(const as_frame *f, const uint32_t *vals, const uint32_t *t
     const short4 *b4 = reinterpret_cast<const short4 *>(f->box);
     unsigned long long *te = reinterpret_cast<unsigned long long *>(f->tile_err);
     if (bl.persistent) launch_fill_u32(f->queue, 0u, 1, s);
+    const uint32_t ck_first = vt.tile_base[vt.n_views] <= CK_TILES ? CK_FINE : CK_COARSE;
 #define AS_FWD(B, PER)                                                                                             \
     do {                                                                                                           \
         static int grid_p = 0;                                                                                     \
@@ -1216,8 +1253,8 @@ bool launch_blend_fwd(const as_frame *f, const uint32_t *vals, const uint32_t *t
         }                                                                                                          \
         hipLaunchKernelGGL((k_blend_fwd<B, PER>), dim3(grid), dim3(AS_BLOCK), 0, s, f->ranges, tile_order, vals,  \
                            f->rec, b4, vt, gt, image, f->t_final, f->last, f->n_contrib, f->dom, f->err, te,      \
-                           f->tile_work, f->tile_hi, reinterpret_cast<float4 *>(f->ckpt), f->bmask,               \
-                           bl.ellipse, f->queue, tiles, z4, zn4);                                                  \
+                           f->tile_work, f->tile_hi, f->tile_seg, reinterpret_cast<float4 *>(f->ckpt), ck_first,   \
+                           f->bmask, bl.ellipse, f->queue, tiles, z4, zn4);                                                  \
     } while (0)
     if (bl.persistent) {
         if (bl.batch >= 1024) AS_FWD(1024, true);
@@ -1238,12 +1275,10 @@ void launch_blend_bwd(const as_frame *f, const uint32_t *vals, const BlendLaunch
     if (tiles == 0) return;
     const short4 *b4 = reinterpret_cast<const short4 *>(f->box);
     const bool ck = f->ck_written && f->ckpt;
-    const uint32_t seg_len = (uint32_t)f->ck_seg;
     if (bl.persistent) launch_fill_u32(f->queue + 1, 0u, 1, s);
     const float4 *ckp = ck ? reinterpret_cast<const float4 *>(f->ckpt) : nullptr;
-    // one block per item for the usual count (most tiles are one segment);
-    // blocks stride over the items beyond the grid
-    const int grid_items = ck ? 2 * tiles : tiles;
+    // one block per item for the usual count; blocks stride over the items beyond the grid
+    const int grid_items = !ck ? tiles : 4 * tiles < BWD_GRID ? 4 * tiles : 2 * tiles < BWD_GRID ? BWD_GRID : 2 * tiles;
 #define AS_BWD(B, PER)                                                                                             \
     do {                                                                                                           \
         static int grid_p = 0;                                                                                     \
@@ -1253,7 +1288,7 @@ void launch_blend_bwd(const as_frame *f, const uint32_t *vals, const BlendLaunch
             grid = grid_p < grid_items ? grid_p : grid_items;                                                      \
         }                                                                                                          \
         hipLaunchKernelGGL((k_blend_bwd<B, PER>), dim3(grid), dim3(BWD_BLOCK), 0, s, f->ranges, f->bwd_items,     \
-                           f->n_items, f->tile_hi, ckp, seg_len, vals, f->rec, b4, vt, f->t_final, f->last,        \
+                           f->n_items, f->tile_hi, f->tile_seg, ckp, vals, f->rec, b4, vt, f->t_final, f->last,        \
                            f->n_contrib, dL_dimage, grad2d, f->bm_written ? f->bmask : nullptr, f->queue + 1);    \
     } while (0)
     // the reverse pass stages half the forward's depth: two waves per tile

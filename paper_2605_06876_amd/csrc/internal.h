@@ -127,8 +127,9 @@ struct as_frame {
     uint32_t *order_table; // [order_table_words(tiles)] class counts per block of the dispatch orders
     uint32_t *tile_work;   // [tiles] contributors summed over the tile's pixels, from the forward blend
     uint32_t *tile_hi;     // [tiles] one past the tile's last contributor (0: none), from the forward blend
-    float *ckpt;           // [tile_cap][AS_CK_MAX][256][4] per pixel (T, colour behind) at the forward's batch
-                           // boundaries; NULL in forward-only frames
+    uint32_t *tile_seg;    // [tiles] the spacing of the tile's checkpoints in list entries, from the forward blend
+    float *ckpt;           // [tile_cap][AS_CK_MAX][256][4] per pixel (T, colour behind) at the checkpoints; NULL in
+                           // forward-only frames
     uint16_t *bmask;       // [key_cap][4] per sorted pair and blend tile of its bin (mask_slot): the 4x4 pixel
                            // blocks of the tile it may contribute to, from the forward blend for the reverse
                            // blend; NULL in forward-only frames
@@ -137,7 +138,6 @@ struct as_frame {
                            // most contributors first
     uint32_t *n_items;     // [1] device count of bwd_items
     int ck_written;        // the last render wrote checkpoints
-    int ck_seg;            // their spacing in list entries (the forward's batch depth)
     int use_order;         // tile_order is valid for the last render
     uint32_t *n_keys;      // [3] device: pairs the render needs, pairs it wrote (fewer when over key_cap), and in
                            // two-level binning the coarse pairs it wrote
@@ -297,7 +297,6 @@ struct BlendLaunch {
     int ellipse;       // 1: per-block culling by the alpha >= 1/255 ellipse, not only the box
 };
 // The forward blend's LDS depth for a launch (256, 512 or 1024 records).
-int blend_fwd_batch(const BlendLaunch &bl);
 size_t order_table_words(int64_t tiles);
 void launch_tile_order(const as_frame *f, const ViewTable &vt, hipStream_t s);
 // After the forward blend of a render with targets: the views' error ranges.
