@@ -255,6 +255,13 @@ void as_frame_destroy(as_frame *f);
  * memory) on `stream`, after the work already queued there; lets a caller
  * that never synchronises the render check it against key_cap later. */
 as_status as_frame_pair_count(const as_frame *f, uint32_t *dst, void *stream);
+/* A host that checks every render against key_cap (set-up call: allocates):
+ * from now on the frame's eager renders report the pairs they need to the host
+ * as soon as they are counted, before the pairs are sorted and blended. */
+as_status as_frame_watch_pairs(as_frame *f);
+/* Wait for the pair count of the last render, queued on `stream`.  AS_ERR_STATE:
+ * it reports none (recorded in a graph, or without entries); read n_keys. */
+as_status as_frame_wait_pairs(const as_frame *f, uint32_t *needed, void *stream);
 /* View 0 (as_frame_get_view) or view v of the last render. */
 as_status as_frame_get_view(const as_frame *f, as_frame_view *out);
 as_status as_frame_get_view_of(const as_frame *f, int32_t view, as_frame_view *out);

@@ -96,7 +96,7 @@ FRAME_FORWARD_ONLY = 1
 EXPORTED = ("as_ctx_create", "as_ctx_destroy", "as_last_error", "as_version", "as_ctx_reserve", "as_ctx_get_reserve",
             "as_ctx_reserve_bytes", "as_frame_create", "as_frame_create_batch", "as_frame_reserve_keys",
             "as_frame_bytes", "as_workspace_size", "as_frame_destroy", "as_frame_get_view", "as_frame_get_view_of",
-            "as_frame_pair_count", "as_render",
+            "as_frame_pair_count", "as_frame_watch_pairs", "as_frame_wait_pairs", "as_render",
             "as_render_backward", "as_render_batch", "as_render_backward_batch", "as_error_map",
             "as_accumulate_error_stats", "as_accumulate_error_stats_batch", "as_accumulate_error_stats_noalloc",
             "as_adaptive_split", "as_set_tuning", "as_get_tuning", "as_timing_enable",
@@ -302,9 +302,11 @@ class Frame:
     """Rasterizer state (as_frame): one view of a fixed size, or (batch=True
     through BatchFrame) up to 16 views of any sizes.  The library renders into
     a frame without allocating or synchronising; with auto_grow the binding's
-    render helpers read the pair count back after each render and, when it
+    render helpers wait for the pair count of each render and, when it
     exceeds the capacity, reserve more (as_frame_reserve_keys) and render
-    again.  forward_only frames hold no reverse-pass checkpoints."""
+    again.  The count is there before the pairs are sorted and blended, so the
+    helpers return while those run (on a stream other than torch's current one
+    they wait for the whole render).  forward_only frames hold no reverse-pass checkpoints."""
 
     def __init__(self, ctx, n_cap, width, height, key_cap=None, auto_grow=True, forward_only=False):
         if key_cap is None:
@@ -315,6 +317,8 @@ class Frame:
                                      ctypes.byref(h)))
         self.ctx, self.handle, self.width, self.height, self.n_cap = ctx, h, width, height, n_cap
         self.auto_grow = auto_grow
+        if auto_grow:
+            _check(lib().as_frame_watch_pairs(h))
 
     def reserve_keys(self, key_cap):
         """as_frame_reserve_keys (a set-up call: synchronises, may allocate)."""
@@ -325,12 +329,20 @@ class Frame:
             raise AdpSplitError(AS_ERR_STATE, "a frame with auto_grow reads its pair count back after each render "
                                               "and cannot be captured in a graph")
 
-    def _fit_keys(self):
-        """After a render: True (and the pair buffers grown) when its pairs did
-        not fit, so the caller renders again."""
+    def _fit_keys(self, stream):
+        """After a render on `stream`: True (and the pair buffers grown) when
+        its pairs did not fit, so the caller renders again."""
         if not self.auto_grow:
             return False
-        K = self.n_keys()
+        K = None
+        if stream is None or stream.cuda_stream == torch.cuda.current_stream().cuda_stream:
+            count = ctypes.c_uint32()
+            rc = lib().as_frame_wait_pairs(self.handle, ctypes.byref(count), _stream(stream))
+            if rc != AS_ERR_STATE:
+                _check(rc)
+                K = count.value
+        if K is None:
+            K = self.n_keys()
         if K <= self.key_cap:
             return False
         self.reserve_keys(min(K + K // 4 + 1024, 0xFFFFFFFF))
@@ -435,6 +447,8 @@ class BatchFrame(Frame):
                                            ctypes.byref(h)))
         self.ctx, self.handle, self.n_cap, self.max_views = ctx, h, entry_cap, max_views
         self.auto_grow = auto_grow
+        if auto_grow:
+            _check(lib().as_frame_watch_pairs(h))
 
     @staticmethod
     def for_views(ctx, n_per_view, cams, key_cap=None, auto_grow=True, forward_only=False):
@@ -473,7 +487,7 @@ def render(ctx, g, cam, frame, gt=None, image=None, stream=None):
     while True:
         _check(lib().as_render(ctx.handle, ctypes.byref(gs), ctypes.byref(c), frame.handle, _ptr(gt), _ptr(image),
                                _stream(stream)))
-        if not frame._fit_keys():
+        if not frame._fit_keys(stream):
             return image
 
 
@@ -504,7 +518,7 @@ def render_batch(ctx, scenes, cams, frame, gts=None, images=None, stream=None):
     frame._check_capturable()
     while True:
         _check(lib().as_render_batch(ctx.handle, ss, cs, ctypes.c_int32(V), frame.handle, gp, ims, _stream(stream)))
-        if not frame._fit_keys():
+        if not frame._fit_keys(stream):
             return images
 
 

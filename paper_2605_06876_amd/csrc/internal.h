@@ -150,6 +150,12 @@ struct as_frame {
     double *err;
     uint64_t *err_minmax;  // [max_views][2]
     uint64_t *tile_err;    // [tile_cap][2] per-tile error min / max (IEEE bits), reduced into err_minmax
+    // the pair count for a host that waits for it (as_frame_watch_pairs): the
+    // number of the render << 32 | count, in host memory the device writes
+    uint64_t *pair_host = nullptr, *pair_dev = nullptr;
+    uint32_t pair_seq = 0;
+    int pair_sent = 0;     // the last render reports its count there
+    void *slab[2] = {nullptr, nullptr};   // the allocations behind the buffers: all but the pair buffers, those
     // scratch for scans and the sorter
     DevBuf scan_tmp, sort_hist, bin_ws;
     // state of the last render
@@ -248,13 +254,25 @@ size_t depth_sort_bytes(int64_t cap);
 int depth_sort(const uint32_t *depth_key, int64_t n, uint32_t *const dkeys[2], uint32_t *const dvals[2],
                const uint32_t *ntiles, uint32_t *nt_sorted, uint32_t *offsets, uint32_t *n_keys, void *ws,
                hipStream_t s);
+// Where a render's pair count goes as soon as it is known (dst: NULL for
+// nowhere): one word, so a host that reads it needs no other ordering.
+struct PairReport {
+    uint64_t *dst;
+    uint32_t seq;
+};
+__device__ __forceinline__ void send_report(const PairReport &r, uint32_t count) {
+    if (r.dst)
+        __hip_atomic_store(r.dst, ((uint64_t)r.seq << 32) | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // Depth-first binning: keys emitted in the depth order a stable depth sort
 // produced; the emission also empties the tile ranges ([0, 0) for every tile)
-// ahead of launch_ranges.  *n_emit gets the number of pairs written: all of
-// them when they fit in key_cap, else the offset of the first entry dropped.
+// ahead of launch_ranges.  n_keys[1] gets the number of pairs written: all of
+// them when they fit in key_cap, else the offset of the first entry dropped
+// (n_keys[0], the pairs needed, is there already).
 void launch_emit_sorted(int64_t n, const uint32_t *order, const ViewTable &vt, const int16_t *box,
                         const uint32_t *nt_sorted, const uint32_t *offsets, int64_t key_cap, uint32_t *keys,
-                        uint32_t *vals, uint32_t *n_emit, uint32_t *ranges, int64_t n_tiles, hipStream_t s);
+                        uint32_t *vals, uint32_t *n_keys, const PairReport &report, uint32_t *ranges, int64_t n_tiles,
+                        hipStream_t s);
 // [start, end) of each tile with keys (ranges emptied by launch_emit_sorted).
 void launch_ranges(const uint32_t *keys, const uint32_t *n_dev, int64_t cap, int64_t n_bins, const ViewTable &vt,
                    uint32_t *ranges, hipStream_t s);
@@ -276,7 +294,7 @@ bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb
 // launch_emit_sorted) and the coarse pairs written.
 void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
                        uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals,
-                       uint32_t *n_keys, void *ws, void *tmp, hipStream_t s);
+                       uint32_t *n_keys, const PairReport &report, void *ws, void *tmp, hipStream_t s);
 // From the coarse pairs sorted by coarse bin, the pairs sorted by bin and the
 // range of every tile; ws of both: coarse_bins_bytes(tile_cap, key_cap) for a
 // tile_cap of at least the tiles; tmp: scan_tmp_bytes(tiles).

@@ -112,7 +112,8 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
                                                            const uint32_t *__restrict__ box_hi,
                                                            const uint64_t *__restrict__ partials, int scanned,
                                                            int64_t key_cap, uint32_t *__restrict__ keys,
-                                                           uint32_t *__restrict__ vals, uint32_t *__restrict__ n_keys) {
+                                                           uint32_t *__restrict__ vals, uint32_t *__restrict__ n_keys,
+                                                           const PairReport report) {
     constexpr int W = PB_THREADS / 64;
     __shared__ uint64_t s_w[W];
     __shared__ uint32_t s_off[W][64], s_id[W][64], s_x[W][64], s_y[W][64], s_view[W][64];
@@ -148,6 +149,7 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
     // n_keys: the pairs of the bins needed and written, and the coarse pairs written
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         n_keys[0] = (uint32_t)(all >> 32);
+        send_report(report, (uint32_t)(all >> 32));
         if ((all >> 32) <= (uint64_t)key_cap) {
             n_keys[1] = (uint32_t)(all >> 32);
             n_keys[2] = (uint32_t)all;
@@ -459,7 +461,7 @@ int64_t fill_coarse(const ViewTable &vt, int shift, CoarseBins *cb) {
 template <int R>
 void pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
                 uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals, uint32_t *n_keys,
-                uint64_t *partials, uint32_t *n_items, hipStream_t s) {
+                const PairReport &report, uint64_t *partials, uint32_t *n_items, hipStream_t s) {
     const int64_t nb = (n + PB_THREADS * R - 1) / (PB_THREADS * R);
     const dim3 grid((unsigned)nb), block(PB_THREADS);
     hipLaunchKernelGGL((k_pairs_sum<R>), grid, block, 0, s, n, order, vt.bin_shift, cb.shift,
@@ -467,7 +469,7 @@ void pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const Coa
     const int scanned = nb > PB_DIRECT;
     if (scanned) scan_partials_u64(partials, nb, s);
     hipLaunchKernelGGL((k_pairs_emit<R>), grid, block, 0, s, n, order, vt, cb, box_lo, box_hi, partials, scanned, key_cap,
-                       keys, vals, n_keys);
+                       keys, vals, n_keys, report);
 }
 
 }  // namespace
@@ -505,13 +507,15 @@ bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb
 
 void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
                        uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals,
-                       uint32_t *n_keys, void *ws, void *tmp, hipStream_t s) {
+                       uint32_t *n_keys, const PairReport &report, void *ws, void *tmp, hipStream_t s) {
     uint32_t *n_items = pb_ws(ws, cb, key_cap, vt.bin_base[vt.n_views]).n_items;
     uint64_t *partials = reinterpret_cast<uint64_t *>(tmp);
     if (n <= PB_SMALL)
-        pairs_emit<PB_ROUNDS_SMALL>(n, order, vt, cb, box, box_lo, box_hi, key_cap, keys, vals, n_keys, partials, n_items, s);
+        pairs_emit<PB_ROUNDS_SMALL>(n, order, vt, cb, box, box_lo, box_hi, key_cap, keys, vals, n_keys, report, partials,
+                                    n_items, s);
     else
-        pairs_emit<PB_ROUNDS_BIG>(n, order, vt, cb, box, box_lo, box_hi, key_cap, keys, vals, n_keys, partials, n_items, s);
+        pairs_emit<PB_ROUNDS_BIG>(n, order, vt, cb, box, box_lo, box_hi, key_cap, keys, vals, n_keys, report, partials,
+                                    n_items, s);
 }
 
 void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_cap, const uint32_t *ckeys,
