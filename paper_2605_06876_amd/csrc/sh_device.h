@@ -77,7 +77,6 @@ __device__ __forceinline__ void sh_eval_basis_grad(double x, double y, double z,
 // the 48 partial derivatives is held.
 __device__ __forceinline__ void sh_weighted_grad(double x, double y, double z, int deg, const double w[16],
                                                  double g[3]) {
-#pragma clang fp contract(fast)
     g[0] = g[1] = g[2] = 0.0;
     if (deg < 1) return;
     g[1] += -SH_K1 * w[1];
