@@ -60,9 +60,12 @@ __device__ __forceinline__ uint32_t span_mask(int lo, int hi) {   // bits lo..hi
     return ((2u << hi) - 1u) & ~((1u << lo) - 1u);
 }
 
-// Index type of the per-row hit lists: one byte covers a batch of 256.
+// Entries of the reverse pass's hit lists, record indices: one byte covers a
+// batch of 256.  The forward's are byte offsets of the records.
 template <int BATCH>
 using HitT = typename std::conditional<(BATCH <= 256), uint8_t, uint16_t>::type;
+constexpr int REC_BYTES = 48;
+static_assert(sizeof(StagedRec) == REC_BYTES && 1024 * REC_BYTES <= 65535, "record offsets of 16 bits");
 
 // Registers of one record fetched ahead of its batch.
 struct Fetched {
@@ -222,32 +225,31 @@ __device__ __forceinline__ LaneGeom lane_geom(int tid) {
     return g;
 }
 
-// For each row of this wave, the indices j < cnt (ascending) of the staged
-// records whose block mask (block_mask) meets the row's pixel block, into
-// hits[row][..]; returns this lane's row count.  Row r takes the blocks of
-// sel0 << r (sel0: the bits of row 0's block or blocks).  `ok(j)` adds a
-// condition that is the same for the whole wave.
-template <int BATCH, typename Ok, typename Chunk>
-__device__ __forceinline__ int compact_rows(const uint16_t *s_bm, int cnt, HitT<BATCH> (*hits)[BATCH + 4],
-                                            uint32_t sel0, int row, Ok ok, Chunk chunk) {
+// For each row of this wave, the indices j of first .. cnt - 1 (ascending) of
+// the staged records whose block mask (block_mask) meets the row's pixel
+// block, times SCALE, into hits[row][..], their numbers into n.  Row r takes
+// the blocks of sel0 << r (sel0: the bits of row 0's block or blocks).
+// `ok(j)` adds a condition that is the same for the whole wave.
+template <int BATCH, int SCALE, typename Hit, typename Ok>
+__device__ __forceinline__ void compact_rows(const uint16_t *s_bm, int first, int cnt, Hit (*hits)[BATCH + 4],
+                                             uint32_t sel0, int (&n)[4], Ok ok) {
     const int lane = threadIdx.x & 63;
     const uint64_t lt = lanemask_lt();
-    int n[4] = {0, 0, 0, 0};
+    n[0] = n[1] = n[2] = n[3] = 0;
 #pragma unroll
     for (int k = 0; k < BATCH / 64; k++) {
+        if (k * 64 + 64 <= first || k * 64 >= cnt) continue;
         const int j = k * 64 + lane;
-        const uint32_t bm = j < cnt ? (uint32_t)s_bm[j] : 0u;
+        const uint32_t bm = j >= first && j < cnt ? (uint32_t)s_bm[j] : 0u;
         const bool any = (bm & (sel0 * 0xFu)) && ok(j);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const bool hit = any && (bm & (sel0 << r));
             const uint64_t bal = __ballot(hit);
-            if (hit) hits[r][n[r] + __popcll(bal & lt)] = (HitT<BATCH>)j;
+            if (hit) hits[r][n[r] + __popcll(bal & lt)] = (Hit)(j * SCALE);
             n[r] += __popcll(bal);
         }
-        chunk(k, n);
     }
-    return row == 0 ? n[0] : row == 1 ? n[1] : row == 2 ? n[2] : n[3];
 }
 
 // Row sums of nine values over the 16 lanes of each DPP row, scattered over
@@ -299,10 +301,9 @@ __device__ __forceinline__ void row_sums9(float (&g)[9]) {
 
 template <int BATCH>
 struct BlendShared {
-    StagedRec rec[BATCH];
-    uint16_t bm[BATCH];                              // block masks (block_mask)
-    HitT<BATCH> hits[AS_BLOCK / 64][4][BATCH + 4];  // +4: the loops read one index ahead
-    uint16_t below[AS_BLOCK / 64][BATCH / 64][4];   // the rows' hits below record 64 (k + 1)
+    StagedRec rec[BATCH + 1];                     // the last one all zeros: it contributes to no pixel
+    uint16_t bm[BATCH];                           // block masks (block_mask)
+    uint16_t hits[AS_BLOCK / 64][4][BATCH + 4];   // byte offsets of records
 };
 
 // Next tile of this block: a queue slot (persistent grid) or the block index;
@@ -330,6 +331,31 @@ __device__ __forceinline__ bool next_tile(uint32_t *queue, int n_tiles, int iter
 constexpr uint32_t CK_FINE = 64, CK_COARSE = 256;
 constexpr int CK_TILES = 1536;
 
+// A staged record by its byte offset.
+__device__ __forceinline__ const StagedRec &rec_at(const StagedRec *rec, uint32_t off) {
+    return *reinterpret_cast<const StagedRec *>(reinterpret_cast<const char *>(rec) + off);
+}
+// The lanes whose pixel the record's box holds and alpha reaches the minimum.
+__device__ __forceinline__ uint64_t meets(const float4 &ex, float alpha, uint32_t pbits) {
+    return __builtin_amdgcn_ballot_w64((__float_as_uint(ex.y) & pbits) == pbits) &
+           __builtin_amdgcn_ballot_w64(alpha >= ALPHA_MIN);
+}
+// a in the lanes of m, b in the others: the mask is the select's condition as
+// it stands (a condition made from it again would take two instructions).
+__device__ __forceinline__ float sel(uint64_t m, float a, float b) {
+    float r;
+    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(m));
+    return r;
+}
+__device__ __forceinline__ uint32_t sel(uint64_t m, uint32_t a, uint32_t b) {
+    return __float_as_uint(sel(m, __uint_as_float(a), __uint_as_float(b)));
+}
+// n += 1 in the lanes of m: the mask as an add's carries.  (The masks of both
+// are written by scalar instructions, which a vector instruction may read at once.)
+__device__ __forceinline__ void count(uint32_t &n, uint64_t m) {
+    __asm__("v_addc_co_u32_e64 %0, vcc, 0, %0, %1" : "+v"(n) : "s"(m) : "vcc");
+}
+
 // Forward dispatch slots (k_tile_order): a tile id, or ORDER_NONE for a slot
 // without a tile (slots grouped by bin of 32 past the image edge).
 constexpr uint32_t ORDER_NONE = 0xFFFFFFFFu;
@@ -340,7 +366,7 @@ __host__ __device__ inline int order_slots(const ViewTable &vt) {
 }
 
 template <int BATCH, bool PERSIST>
-__global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restrict__ ranges,
+__global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__restrict__ ranges,
                                                         const uint32_t *__restrict__ tile_order,
                                                         const uint32_t *__restrict__ vals,
                                                         const BlendRec *__restrict__ rec,
@@ -367,7 +393,8 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
     __shared__ uint32_t s_nc[AS_BLOCK / 64], s_hi[AS_BLOCK / 64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const LaneGeom lg = lane_geom(tid);
-    const HitT<BATCH> *hits = sh.hits[w][lg.row];
+    const uint16_t *hits = sh.hits[w][lg.row];
+    if (tid < REC_BYTES / 4) reinterpret_cast<uint32_t *>(&sh.rec[BATCH])[tid] = 0u;   // (the tile loop synchronises)
     const float px = (float)lg.lx + 0.5f, py = (float)lg.ly + 0.5f;
     uint32_t idx;
     for (int iter = 0; next_tile<PERSIST>(queue, n_tiles, iter, idx, &s_next); iter++) {
@@ -419,18 +446,9 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
             __syncthreads();
             const bool live = __ballot(!done) != 0;             // not the whole wave has saturated
             const int cnt = (int)min((uint32_t)BATCH, end - b0);
-            // wave w's rows are the 4x4 blocks 4 w .. 4 w + 3
-            int nh = 0;
-            if (live)
-                nh = compact_rows<BATCH>(sh.bm, cnt, sh.hits[w], 1u << (4 * w), lg.row, [](int) { return true; },
-                                         [&](int k, const int *n) {
-                                             if (lane < 4)
-                                                 sh.below[w][k][lane] = (uint16_t)(lane == 0 ? n[0] : lane == 1 ? n[1]
-                                                                                   : lane == 2 ? n[2] : n[3]);
-                                         });
             // The batch in one run, or cut at the checkpoints inside it.
             const uint32_t rel = b0 - start, rel_end = rel + (uint32_t)cnt;
-            int h = 0;
+            uint32_t loff = 0xFFFFFFFFu;   // the batch's last contributor, as a record offset
             for (uint32_t at = rel; at < rel_end;) {
                 if (at == next_ck) {
                     if (nck == AS_CK_MAX) {
@@ -442,37 +460,48 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
                     nck++;
                     next_ck = nck == AS_CK_MAX && seg >= CK_COARSE ? 0xFFFFFFFFu : next_ck + seg;
                 }
-                const uint32_t to = min(next_ck, rel_end);
-                const int he = to == rel_end ? nh : (int)sh.below[w][(to - rel) / 64 - 1][lg.row];
+                const uint32_t from = at - rel, to = min(next_ck, rel_end);
                 at = to;
-                if (!live || done) continue;
+                uint64_t act = live ? __builtin_amdgcn_ballot_w64(!done) : 0u;   // the pixels still compositing
+                if (!act) continue;
+                // Every row walks its own hits, the wave as many steps as its
+                // longest row has: shorter rows are filled up with the record
+                // of zeros.  wave w's rows are the 4x4 blocks 4 w .. 4 w + 3.
+                int n[4];
+                compact_rows<BATCH, REC_BYTES>(sh.bm, (int)from, (int)(to - rel), sh.hits[w], 1u << (4 * w), n,
+                                               [](int) { return true; });
+                // (rows whose pixels have all saturated count no steps)
+                auto steps_of = [&](uint64_t m) {
+                    int t = 0;
+#pragma unroll
+                    for (int r = 0; r < 4; r++) t = max(t, (m >> (16 * r)) & 0xFFFFu ? n[r] : 0);
+                    return (t + 1) / 2;
+                };
+                int steps = steps_of(act);
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    for (int p = n[r] + lane; p < 2 * steps; p += 64) sh.hits[w][r][p] = BATCH * REC_BYTES;
                 // Two hits per step: both records' loads and alpha evaluations are
                 // independent and overlap; only the compositing is sequential.
-                // The next step's indices are loaded one step ahead.
-                int ja = hits[h], jb = hits[h + 1];
-                for (; h < he; h += 2) {
-                    const bool two = h + 1 < he;
-                    const int j0 = ja, j1 = two ? jb : ja;
-                    ja = hits[h + 2];
-                    jb = hits[h + 3];
-                    const float4 a0 = sh.rec[j0].mc, a1 = sh.rec[j0].cc, a2 = sh.rec[j0].ex;
-                    const float4 b0q = sh.rec[j1].mc, b1q = sh.rec[j1].cc, b2q = sh.rec[j1].ex;
-                    const uint32_t ma = __float_as_uint(a2.y), mb = __float_as_uint(b2q.y);
-                    const float dxa = a0.x - px, dya = a0.y - py, dxb = b0q.x - px, dyb = b0q.y - py;
-                    const float rawa = __builtin_amdgcn_exp2f(blend_exponent(dxa, dya, a0, a1));
-                    const float rawb = __builtin_amdgcn_exp2f(blend_exponent(dxb, dyb, b0q, b1q));
-                    const float alpha_a = fminf(ALPHA_MAX, rawa), alpha_b = fminf(ALPHA_MAX, rawb);
-                    const bool oka = (ma & lg.pbits) == lg.pbits && alpha_a >= ALPHA_MIN;   // box holds the pixel
-                    const bool okb = two && (mb & lg.pbits) == lg.pbits && alpha_b >= ALPHA_MIN;
-                    // Both records are decided with selects and the loop leaves
-                    // once after them, so the second record's loads are not held
-                    // back behind a branch.  A record that would take T below the
-                    // stop threshold is not added, and nothing after it is; a
-                    // non-contributor adds exactly zero and changes nothing.
-                    const float tA = T * (1.0f - alpha_a);
-                    const bool stopA = oka && tA < T_STOP;
-                    const bool useA = oka && !stopA;
-                    float wgt = useA ? alpha_a * T : 0.0f;
+                // Which pixels take a record is kept as lane masks in scalar
+                // registers, where combining them costs no vector instruction
+                // (those bound the kernel): a record that would take T below the
+                // stop threshold is not added, and nothing after it is; for the
+                // others a non-contributor adds exactly zero.
+                const uint16_t *hp = hits;
+                const uint64_t was = act;
+                for (int h = 0; h < steps; h++, hp += 2) {
+                    const uint32_t oa = hp[0], ob = hp[1];
+                    const StagedRec &ra = rec_at(sh.rec, oa), &rb = rec_at(sh.rec, ob);
+                    const float4 a0 = ra.mc, a1 = ra.cc, a2 = ra.ex, b0 = rb.mc, b1 = rb.cc, b2 = rb.ex;
+                    const float alpha_a =
+                        fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(blend_exponent(a0.x - px, a0.y - py, a0, a1)));
+                    const float alpha_b =
+                        fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(blend_exponent(b0.x - px, b0.y - py, b0, b1)));
+                    const uint64_t oka = meets(a2, alpha_a, lg.pbits) & act, okb = meets(b2, alpha_b, lg.pbits) & act;
+                    const float ta = T * (1.0f - alpha_a);
+                    const uint64_t lowa = __builtin_amdgcn_ballot_w64(ta < T_STOP), usea = oka & ~lowa;
+                    float wgt = sel(usea, alpha_a * T, 0.0f);
                     C0 += wgt * a1.z;
                     C1 += wgt * a1.w;
                     C2 += wgt * a2.x;
@@ -480,30 +509,33 @@ __global__ void __launch_bounds__(AS_BLOCK) k_blend_fwd(const uint32_t *__restri
                         wbest = wgt;
                         dom = (int32_t)__float_as_uint(a2.z);
                     }
-                    T = useA ? tA : T;
-                    last = useA ? b0 + (uint32_t)j0 : last;
-                    nc += useA ? 1u : 0u;
-                    const float tB = T * (1.0f - alpha_b);
-                    const bool stopB = !stopA && okb && tB < T_STOP;
-                    const bool useB = !stopA && okb && !stopB;
-                    wgt = useB ? alpha_b * T : 0.0f;
-                    C0 += wgt * b1q.z;
-                    C1 += wgt * b1q.w;
-                    C2 += wgt * b2q.x;
+                    T = sel(usea, ta, T);
+                    loff = sel(usea, oa, loff);
+                    count(nc, usea);
+                    const uint64_t stopa = oka & lowa;
+                    const float tb = T * (1.0f - alpha_b);
+                    const uint64_t lowb = __builtin_amdgcn_ballot_w64(tb < T_STOP), liveb = okb & ~stopa;
+                    const uint64_t useb = liveb & ~lowb;
+                    wgt = sel(useb, alpha_b * T, 0.0f);
+                    C0 += wgt * b1.z;
+                    C1 += wgt * b1.w;
+                    C2 += wgt * b2.x;
                     if (wgt > wbest) {
                         wbest = wgt;
-                        dom = (int32_t)__float_as_uint(b2q.z);
+                        dom = (int32_t)__float_as_uint(b2.z);
                     }
-                    T = useB ? tB : T;
-                    last = useB ? b0 + (uint32_t)j1 : last;
-                    nc += useB ? 1u : 0u;
-                    if (stopA || stopB) {
-                        done = 1;
-                        break;
+                    T = sel(useb, tb, T);
+                    loff = sel(useb, ob, loff);
+                    count(nc, useb);
+                    const uint64_t stop = stopa | (liveb & lowb);
+                    if (stop) {
+                        act &= ~stop;
+                        steps = steps_of(act);
                     }
                 }
-                h = he;
+                done |= (int)(((was & ~act) >> lane) & 1u);
             }
+            if (loff != 0xFFFFFFFFu) last = b0 + loff / REC_BYTES;
         }
 
         const float *gt = gts.p[v];
@@ -766,13 +798,13 @@ __global__ void __launch_bounds__(BWD_BLOCK) k_blend_bwd(const uint32_t *__restr
                                  nbm[k]);
             }
             __syncthreads();
-            const int nh = compact_rows<BATCH>(sh.bm, (int)(b1 - b0), sh.hits[w], sel0, row,
-                                               [&](int j) { return b0 + (uint32_t)j < wlast; }, [](int, const int *) {});
+            int nr[4];
+            compact_rows<BATCH, 1>(sh.bm, 0, (int)(b1 - b0), sh.hits[w], sel0, nr,
+                                   [&](int j) { return b0 + (uint32_t)j < wlast; });
+            const int nh = row == 0 ? nr[0] : row == 1 ? nr[1] : row == 2 ? nr[2] : nr[3];
             // the wave walks max over its rows of the row counts; rows past their
             // own count idle
-            int nmax = nh;
-            for (int o = 16; o < 64; o <<= 1) nmax = max(nmax, __shfl_xor(nmax, o, 64));
-            nmax = __builtin_amdgcn_readfirstlane(nmax);   // wave-uniform: scalar loop control
+            const int nmax = max(max(nr[0], nr[1]), max(nr[2], nr[3]));   // wave-uniform: scalar loop control
             // The step's geometry (mean, conic, log2 o, box mask) is read from
             // LDS one step ahead, so its exponent does not wait on the read;
             // the record index two steps ahead.
