@@ -70,24 +70,6 @@ __device__ __forceinline__ void each(F f) {
     }
 }
 
-// Inclusive prefix over the wave by DPP adds (within rows of 16, then the row
-// totals broadcast onwards): lane exchanges through LDS would be a third of
-// the LDS instructions of a bucket's sort, which its LDS pipe bounds.
-__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
-    auto add = [&](auto ctrl, auto rows) {
-        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
-    };
-    using std::integral_constant;
-    add(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr:1
-    add(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
-    add(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
-    add(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
-    add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
-    add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2 and 3
-    return x;
-}
-__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
-
 // Exclusive scan of one value per thread over the block; *sum gets the total.
 // s_w: a word per wave (NW); a barrier before its first write.
 template <int NW = DW>

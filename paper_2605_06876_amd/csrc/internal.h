@@ -460,6 +460,26 @@ __device__ __forceinline__ int view_of_bin(const ViewTable &vt, int bin) {
     for (int k = 1; k < vt.n_views; k++) v += bin >= vt.bin_base[k] ? 1 : 0;
     return v;
 }
+// x plus its DPP neighbours' (control CTRL) in the rows of ROWS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+// Inclusive prefix over each row of 16 lanes, and over the wave (the row
+// totals broadcast onwards), by DPP adds: they leave the LDS pipe alone, which
+// lane exchanges go through.
+__device__ __forceinline__ uint32_t row_prefix(uint32_t x) {
+    x = dpp_add<0x111, 0xf>(x);   // row_shr:1
+    x = dpp_add<0x112, 0xf>(x);
+    x = dpp_add<0x114, 0xf>(x);
+    return dpp_add<0x118, 0xf>(x);
+}
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+    x = dpp_add<0x142, 0xa>(row_prefix(x));   // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(x);            // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+
 // One end of a bin's list, written as that of the range of each blend tile of
 // the bin.
 __device__ __forceinline__ void set_bin_range(const ViewTable &vt, uint32_t bin, int end, uint32_t val,

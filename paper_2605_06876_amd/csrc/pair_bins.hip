@@ -19,13 +19,14 @@
 //
 // Emission, sort and ranges against this (us, MI355X, with the gather of the
 // tile counts into depth order where it is the sort's last pass): 82.8M pairs of
-// eight views 1810 -> 660, 9.7M of one 1920x1080 view 185 -> 95, 3.8M in bins
-// of 32 75 -> 75.  What bounds it now: the placing, 248 us for 82.8M pairs
-// (3.4 TB/s of a copy's 4.8; its 16 ballots a round take half the issue slots),
-// and the random read of the boxes (157 us for 12M entries).  A block per list
-// in place of work items: 920 us, the lists are uneven; eight blocks per list
-// 350 us.  Loading each round on its own: 1690 us, a wave's loads wait for the
-// stores before them.
+// eight views 1810 -> 740, 9.7M of one 1920x1080 view 175 -> 100.  What bounds
+// it now: the placing, 244 us for 82.8M pairs (3.4 TB/s of a copy's 4.8; its 16
+// ballots a round take half the issue slots), and the random read of the boxes
+// (157 us for 8.2M entries).  Placing by a block per list in place of work items:
+// 920 us, the lists are uneven; eight blocks per list 350 us.  Loading each
+// round on its own: 1690 us, a wave's loads wait for the stores before them.
+// Counting by ballots as the placing does: 67 us, by packed counts 33.  Emitting
+// with lanes that search for the owner of their position: 105 us, by owner 89.
 #include "internal.h"
 
 namespace {
@@ -34,12 +35,13 @@ constexpr int PB_THREADS = 256;
 constexpr int PB_ROUNDS_SMALL = 2, PB_ROUNDS_BIG = 8;   // ranks per thread of sum and emit
 constexpr int64_t PB_SMALL = 1 << 20;             // ranks up to which they take the fewer
 constexpr int64_t PB_DIRECT = 2048;               // blocks up to which each sums the partials before it itself
+constexpr uint32_t PB_OWN = 8;                    // coarse pairs that an entry's own lane writes
 constexpr int PB_WAVES = 4;                       // waves of a block of count and place
 constexpr int PB_BATCH = 4;                       // rounds of 64 pairs of a wave
 constexpr int PB_SLICE = 64 * PB_BATCH;
 constexpr int PB_ITEM = PB_WAVES * PB_SLICE;      // pairs of a work item
 constexpr int PB_GRID = 2048;                     // most blocks of count and place (eight to a CU; they loop)
-constexpr int PB_LISTS = 15;                      // lists found by a block of 16 waves
+constexpr int PB_LISTS = 63;                      // lists found by a block: a row of 16 lanes for each start, and the last one's end
 constexpr uint32_t PB_ID = 0xFFFFFFu;             // key: coarse bin id in 24 bits, then x0, x1, y0, y1 of two bits
 
 // Bins and coarse bins touched by an entry, from its box (x0 > x1 when culled).
@@ -58,10 +60,15 @@ __device__ __forceinline__ uint64_t rect_counts(const BinRect &b, int cs) {
     return ((uint64_t)f << 32) | c;
 }
 
-__device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
-    for (int o = 32; o > 0; o >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, o, 64);
-    return v;
+// Prefix and sum of (bins << 32) | coarse bins over the wave: the halves apart
+// (the coarse bins of a render stay below 2^32).
+__device__ __forceinline__ uint64_t wave_prefix2(uint64_t v) {
+    return ((uint64_t)wave_prefix((uint32_t)(v >> 32)) << 32) | wave_prefix((uint32_t)v);
 }
+__device__ __forceinline__ uint64_t last_lane2(uint64_t v) {
+    return ((uint64_t)last_lane((uint32_t)(v >> 32)) << 32) | last_lane((uint32_t)v);
+}
+__device__ __forceinline__ uint64_t wave_sum(uint64_t v) { return last_lane2(wave_prefix2(v)); }
 // Sum over the block (every thread gets it); s of PB_THREADS / 64 words.
 __device__ __forceinline__ uint64_t block_sum(uint64_t v, uint64_t *s) {
     v = wave_sum(v);
@@ -102,9 +109,10 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_sum(int64_t n, const uint3
     if (threadIdx.x == 0) partials[blockIdx.x] = sum;
 }
 
-// Coarse pairs in depth order.  As in the one-level emission, consecutive
-// ranks own consecutive positions, so each wave writes contiguous runs and its
-// lanes find the owner of their position among 64 ranks by binary search.
+// Coarse pairs in depth order: consecutive ranks own consecutive positions.
+// Most entries touch one to four coarse bins, so each lane writes the first
+// PB_OWN pairs of its own rank (a wave's stores of one step lie within a few
+// lines), and the wave together what a larger entry has beyond them.
 template <int R>
 __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint32_t *__restrict__ order,
                                                            const ViewTable vt, const CoarseBins cb,
@@ -116,19 +124,25 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
                                                            const PairReport report) {
     constexpr int W = PB_THREADS / 64;
     __shared__ uint64_t s_w[W];
-    __shared__ uint32_t s_off[W][64], s_id[W][64], s_x[W][64], s_y[W][64], s_view[W][64];
+    __shared__ int s_base[AS_MAX_VIEWS], s_pitch[AS_MAX_VIEWS];   // of the lanes' views (read by lane: not from the arguments)
+    if (threadIdx.x < AS_MAX_VIEWS) {
+        s_base[threadIdx.x] = cb.base[threadIdx.x];
+        s_pitch[threadIdx.x] = cb.x[threadIdx.x];
+    }
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int bs = vt.bin_shift, cs = cb.shift;
     const int64_t r0 = (int64_t)blockIdx.x * (PB_THREADS * R) + w * (R * 64) + lane;
-    uint32_t lo[R], hi[R];
+    uint32_t lo[R], hi[R], id[R];
     uint64_t sum = 0;
 #pragma unroll
     for (int j = 0; j < R; j++) {
         const int64_t r = r0 + j * 64;
         lo[j] = r < n ? box_lo[r] : 0u;
         hi[j] = r < n ? box_hi[r] : 0xFFFFFFFFu;   // the empty box
-        sum += rect_counts(bin_rect(lo[j], hi[j], bs), cs);
+        id[j] = r < n ? order[r] : 0u;
     }
+#pragma unroll
+    for (int j = 0; j < R; j++) sum += rect_counts(bin_rect(lo[j], hi[j], bs), cs);
     // (bins << 32 | coarse bins) before this block, then before this wave
     uint64_t pre = 0;
     if (scanned) {
@@ -155,68 +169,52 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
             n_keys[2] = (uint32_t)all;
         }
     }
-#pragma unroll 1
-    for (int j = 0; j < R; j++) {
-        // (the boxes are in registers: round j's by a chain of selects)
-        uint32_t l = lo[0], h = hi[0];
+    const int m = (1 << cs) - 1;
 #pragma unroll
-        for (int k = 1; k < R; k++) {
-            l = j == k ? lo[k] : l;
-            h = j == k ? hi[k] : h;
-        }
-        const int64_t r = r0 + j * 64;
-        const BinRect b = bin_rect(l, h, bs);
-        const uint64_t c = rect_counts(b, cs);
-        uint64_t inc = c;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint64_t t = (uint64_t)__shfl_up((unsigned long long)inc, o, 64);
-            if (lane >= o) inc += t;
-        }
-        const uint64_t at = pre + inc - c;
-        pre += (uint64_t)__shfl((unsigned long long)inc, 63, 64);
+    for (int j = 0; j < R; j++) {
+        const BinRect b = bin_rect(lo[j], hi[j], bs);
+        const uint64_t c = rect_counts(b, cs), inc = wave_prefix2(c), at = pre + inc - c;
+        pre += last_lane2(inc);
         const uint64_t off = at >> 32, nt = c >> 32;
-        const uint32_t coff = (uint32_t)at;
         // an entry whose bins' pairs do not all fit is dropped whole, with all after it
         const bool kept = nt && off + nt <= (uint64_t)key_cap;
         if (nt && off <= (uint64_t)key_cap && (uint64_t)key_cap < off + nt) {
             n_keys[1] = (uint32_t)off;
-            n_keys[2] = coff;
+            n_keys[2] = (uint32_t)at;
         }
-        uint32_t end = kept ? coff + (uint32_t)c : 0u;
-        for (int o = 32; o > 0; o >>= 1) end = max(end, (uint32_t)__shfl_xor((int)end, o, 64));
-        if (end == 0u) continue;   // wave-uniform
-        if (kept) {
-            const uint32_t e = order[r];
-            s_id[w][lane] = e;
-            s_view[w][lane] = (uint32_t)view_of_entry(vt, e);
-            s_x[w][lane] = (uint32_t)b.fx0 | ((uint32_t)b.fx1 << 16);
-            s_y[w][lane] = (uint32_t)b.fy0 | ((uint32_t)b.fy1 << 16);
-        }
-        s_off[w][lane] = coff;   // non-decreasing; ranks without pairs share their successor's
-        const uint32_t beg = (uint32_t)__shfl((int)coff, 0, 64);
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (uint32_t pos = beg + lane; pos < end; pos += 64) {
-            int o = 0;
-#pragma unroll
-            for (int step = 32; step > 0; step >>= 1)   // probes stay within 1..63
-                if (s_off[w][o + step] <= pos) o += step;
-            const uint32_t x = s_x[w][o], y = s_y[w][o], v = s_view[w][o];
-            const int fx0 = (int)(x & 0xFFFFu), fx1 = (int)(x >> 16), fy0 = (int)(y & 0xFFFFu), fy1 = (int)(y >> 16);
-            const uint32_t q = pos - s_off[w][o], cw = (uint32_t)((fx1 >> cs) - (fx0 >> cs) + 1);
-            const uint32_t qy = q / cw, qx = q - qy * cw;
-            const int cx = (fx0 >> cs) + (int)qx, cy = (fy0 >> cs) + (int)qy, m = (1 << cs) - 1;
-            // the entry's bins inside coarse bin (cx, cy)
+        const uint32_t ct = kept ? (uint32_t)c : 0u, coff = (uint32_t)at;
+        if (!__builtin_amdgcn_ballot_w64(ct != 0)) continue;
+        const int v = view_of_entry(vt, id[j]), pitch = s_pitch[v], base = s_base[v];
+        const int cx0 = b.fx0 >> cs, cx1 = b.fx1 >> cs, cy0 = b.fy0 >> cs;
+        // pair (cx, cy) of an entry: the coarse bin and the entry's bins inside it
+        auto key_of = [&](int bin0, int p, int cx, int cy, int fx0, int fx1, int fy0, int fy1) {
             const int x0 = max(fx0 - (cx << cs), 0), x1 = min(fx1 - (cx << cs), m);
             const int y0 = max(fy0 - (cy << cs), 0), y1 = min(fy1 - (cy << cs), m);
-            keys[pos] = (uint32_t)(cb.base[v] + cy * cb.x[v] + cx) | ((uint32_t)x0 << 24) | ((uint32_t)x1 << 26) |
-                        ((uint32_t)y0 << 28) | ((uint32_t)y1 << 30);
-            vals[pos] = s_id[w][o];
+            return (uint32_t)(bin0 + cy * p + cx) | ((uint32_t)(x0 | (x1 << 2) | (y0 << 4) | (y1 << 6)) << 24);
+        };
+        int cx = cx0, cy = cy0;
+        for (uint32_t t = 0; t < PB_OWN && __builtin_amdgcn_ballot_w64(t < ct); t++) {
+            if (t < ct) {
+                keys[coff + t] = key_of(base, pitch, cx, cy, b.fx0, b.fx1, b.fy0, b.fy1);
+                vals[coff + t] = id[j];
+            }
+            const bool wrap = cx == cx1;
+            cx = wrap ? cx0 : cx + 1;
+            cy += wrap ? 1 : 0;
         }
-        __builtin_amdgcn_wave_barrier();   // the next round's writes come after these reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (uint64_t big = __builtin_amdgcn_ballot_w64(ct > PB_OWN); big; big &= big - 1) {
+            const int l = __builtin_ctzll(big);
+            auto get = [&](int x) { return __builtin_amdgcn_readlane(x, l); };
+            const uint32_t lct = (uint32_t)get((int)ct), loff = (uint32_t)get((int)coff), lid = (uint32_t)get((int)id[j]);
+            const int fx0 = get(b.fx0), fx1 = get(b.fx1), fy0 = get(b.fy0), fy1 = get(b.fy1);
+            const int bin0 = get(base), p = get(pitch);
+            const uint32_t cw = (uint32_t)((fx1 >> cs) - (fx0 >> cs) + 1);
+            for (uint32_t q = PB_OWN + lane; q < lct; q += 64) {
+                const uint32_t qy = q / cw;
+                keys[loff + q] = key_of(bin0, p, (fx0 >> cs) + (int)(q - qy * cw), (fy0 >> cs) + (int)qy, fx0, fx1, fy0, fy1);
+                vals[loff + q] = lid;
+            }
+        }
     }
 }
 
@@ -231,20 +229,24 @@ __device__ __forceinline__ uint32_t rect_mask(uint32_t key) {
     return row * rows;
 }
 
-// First of the n keys whose coarse bin is not below `bin`, by a search that
-// splits the range 64 ways a step (whole wave; n <= 2^32 in six steps).
+// First of the n keys whose coarse bin is not below `bin`: each row of 16 lanes
+// searches for its own bin, splitting the range 16 ways a step (n <= 2^32 in
+// eight steps; 64 ways would read three times the lines, 27 us against 12 for 4,080 lists).
 __device__ __forceinline__ uint32_t coarse_bound(const uint32_t *__restrict__ keys, uint32_t n, uint32_t bin) {
-    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t lane = threadIdx.x & 63, sub = lane & 15;
     uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        const uint32_t step = (uint32_t)(((uint64_t)(hi - lo) + 63) / 64);
-        const uint64_t p = (uint64_t)lo + (uint64_t)(lane + 1) * step - 1;
-        const bool below = p < hi && (keys[p] & PB_ID) < bin;
-        const uint32_t cnt = (uint32_t)__popcll(__ballot(below));
-        const uint64_t top = (uint64_t)lo + (uint64_t)(cnt + 1) * step - 1;
-        const uint64_t bot = (uint64_t)lo + (uint64_t)cnt * step;
-        lo = bot < hi ? (uint32_t)bot : hi;
-        hi = top < hi ? (uint32_t)top : hi;
+    while (__builtin_amdgcn_ballot_w64(lo < hi)) {
+        const uint32_t step = (uint32_t)(((uint64_t)(hi - lo) + 15) / 16);
+        const uint64_t p = (uint64_t)lo + (uint64_t)(sub + 1) * step - 1;
+        const bool below = lo < hi && p < hi && (keys[p] & PB_ID) < bin;
+        const uint64_t all = __builtin_amdgcn_ballot_w64(below);
+        const uint32_t cnt = (uint32_t)__popc((uint32_t)(all >> (lane & 48)) & 0xFFFFu);
+        if (lo < hi) {
+            const uint64_t top = (uint64_t)lo + (uint64_t)(cnt + 1) * step - 1;
+            const uint64_t bot = (uint64_t)lo + (uint64_t)cnt * step;
+            lo = bot < hi ? (uint32_t)bot : hi;
+            hi = top < hi ? (uint32_t)top : hi;
+        }
     }
     return lo;
 }
@@ -263,8 +265,8 @@ __device__ __forceinline__ CoarsePlace coarse_place(const ViewTable &vt, const C
                        by - (cy << cb.shift)};
 }
 
-// The coarse lists, cut into work items of PB_ITEM pairs: a wave finds each
-// list's start, and each list takes its items' places from a counter (which
+// The coarse lists, cut into work items of PB_ITEM pairs: a row of lanes finds
+// each list's start, and each list takes its items' places from a counter (which
 // list gets which is left to chance, and shows in nothing).  An item is
 // (coarse bin, part of its list, list start, list length).  Also clears the
 // bins' counts for the launch that adds them, and the tiles' ranges.
@@ -273,22 +275,24 @@ __global__ void __launch_bounds__(1024) k_bins_lists(const uint32_t *__restrict_
                                                      uint4 *__restrict__ items, uint32_t *__restrict__ n_items,
                                                      uint32_t *__restrict__ counts, int64_t bins,
                                                      uint32_t *__restrict__ ranges, int64_t range_words) {
-    __shared__ uint32_t s_at[PB_LISTS + 1];
+    __shared__ uint32_t s_at[PB_LISTS + 1], s_item[PB_LISTS + 1];
     const int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x, tn = (int64_t)gridDim.x * 1024;
     for (int64_t i = t0; i < bins; i += tn) counts[i] = 0u;
     for (int64_t i = t0; i < range_words; i += tn) ranges[i] = 0u;
-    const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    const int w = (int)(threadIdx.x >> 4), sub = (int)(threadIdx.x & 15);
     const int cid = (int)blockIdx.x * PB_LISTS + w;
     const uint32_t p = coarse_bound(keys, n_keys[2], (uint32_t)cid);   // (bins past the last end where it ends)
-    if (lane == 0) s_at[w] = p;
+    if (sub == 0) s_at[w] = p;
     __syncthreads();
     if (w == PB_LISTS || cid >= cbins) return;
     const uint32_t m = s_at[w + 1] - p, ni = (m + PB_ITEM - 1) / PB_ITEM;
     if (ni == 0) return;
-    uint32_t at = 0;
-    if (lane == 0) at = atomicAdd(n_items, ni);
-    at = (uint32_t)__shfl((int)at, 0, 64);
-    for (uint32_t k = lane; k < ni; k += 64) items[at + k] = make_uint4((uint32_t)cid, k, p, m);
+    if (sub == 0) s_item[w] = atomicAdd(n_items, ni);
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t at = s_item[w];
+    for (uint32_t k = sub; k < ni; k += 16) items[at + k] = make_uint4((uint32_t)cid, k, p, m);
 }
 
 // Pairs of each bin in every wave's slice of an item and in the item, and the bins' sums.
@@ -299,39 +303,46 @@ __global__ void __launch_bounds__(PB_WAVES * 64) k_bins_count(const uint32_t *__
                                                               uint32_t *__restrict__ slices, uint32_t *__restrict__ sums,
                                                               uint32_t *__restrict__ counts) {
     constexpr int NC = F * F;
-    __shared__ uint32_t s_c[2][PB_WAVES][NC];
+    __shared__ uint32_t s_c[2][PB_WAVES][4][4];   // per wave and row of 16 lanes: 16 counts of a byte
+    static_assert(PB_BATCH * 16 < 256 && PB_BATCH < 16, "counts of a lane in four bits, of a row in eight");
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t ni = *n_items;
     int flip = 0;
     for (uint32_t it = blockIdx.x; it < ni; it += gridDim.x, flip ^= 1) {
         const uint4 item = items[it];
         const uint32_t m = item.w, i0 = min(m, item.y * PB_ITEM + (uint32_t)w * PB_SLICE), i1 = min(m, i0 + PB_SLICE);
-        uint32_t key[PB_BATCH], c[NC];
+        uint32_t key[PB_BATCH], top = 0, bot = 0;   // rows 0, 1 and 2, 3 of 4 x 4 counts of four bits
 #pragma unroll
         for (int j = 0; j < PB_BATCH; j++) key[j] = keys[item.z + min(i0 + j * 64 + lane, m - 1)];
 #pragma unroll
-        for (int k = 0; k < NC; k++) c[k] = 0;
-#pragma unroll
         for (int j = 0; j < PB_BATCH; j++) {
-            const uint32_t mask = i0 + j * 64 + lane < i1 ? rect_mask<F>(key[j]) : 0u;
-#pragma unroll
-            for (int k = 0; k < NC; k++) c[k] += (uint32_t)__popcll(__ballot((mask >> k) & 1u));
+            const uint32_t k = key[j], x0 = (k >> 24) & 3u, x1 = (k >> 26) & 3u, y0 = (k >> 28) & 3u, y1 = k >> 30;
+            uint32_t row = (0x1111u << (4 * x0)) & (0xFFFFu >> (12 - 4 * x1));
+            row = i0 + j * 64 + lane < i1 ? row : 0u;
+            const uint32_t rows = (2u << y1) - (1u << y0);
+            top += __umul24(row, (rows & 1u) | ((rows & 2u) << 15));
+            if (F == 4) bot += __umul24(row, ((rows >> 2) & 1u) | ((rows & 8u) << 13));
         }
-        uint32_t mine = 0;
+        // the wave's sums by row of lanes: even and odd columns in bytes
+        const uint32_t q[4] = {row_prefix(top & 0x0F0F0F0Fu), row_prefix((top >> 4) & 0x0F0F0F0Fu),
+                               F == 4 ? row_prefix(bot & 0x0F0F0F0Fu) : 0u,
+                               F == 4 ? row_prefix((bot >> 4) & 0x0F0F0F0Fu) : 0u};
+        if ((lane & 15) == 15)
 #pragma unroll
-        for (int k = 0; k < NC; k++) mine = lane == k ? c[k] : mine;
-        if (lane < NC) {
-            s_c[flip][w][lane] = mine;
-            slices[((size_t)it * PB_WAVES + w) * NC + lane] = mine;
-        }
+            for (int k = 0; k < 4; k++) s_c[flip][w][lane >> 4][k] = q[k];
         __syncthreads();   // (one a turn: the next writes the other half)
-        if (tid < NC) {
+        if (tid < PB_WAVES * NC) {
+            const int sw = tid / NC, k = tid % NC, c = (k / F) * 4 + k % F;   // wave, bin, its place in the 4 x 4
             uint32_t t = 0;
 #pragma unroll
-            for (int k = 0; k < PB_WAVES; k++) t += s_c[flip][k][tid];
-            sums[(size_t)it * NC + tid] = t;
-            const CoarsePlace p = coarse_place(vt, cb, (int)item.x);
-            if (t) atomicAdd(counts + p.bin0 + (tid / F) * p.pitch + tid % F, t);   // (bins past the border hold no pair)
+            for (int r = 0; r < 4; r++) t += (s_c[flip][sw][r][2 * (c / 8) + c % 2] >> (8 * (c / 2 % 4))) & 0xFFu;
+            slices[((size_t)it * PB_WAVES + sw) * NC + k] = t;
+            for (int o = NC; o < PB_WAVES * NC; o *= 2) t += (uint32_t)__shfl_xor((int)t, o, 64);
+            if (sw == 0) {
+                sums[(size_t)it * NC + k] = t;
+                const CoarsePlace p = coarse_place(vt, cb, (int)item.x);
+                if (t) atomicAdd(counts + p.bin0 + (k / F) * p.pitch + k % F, t);   // (bins past the border hold no pair)
+            }
         }
     }
 }
