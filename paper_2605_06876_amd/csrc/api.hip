@@ -703,8 +703,8 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
     {
         StageTimer t(ctx, AS_STAGE_SORT, s);
         if (!lsd)
-            lsd = depth_sort(f->depth_key, n, f->dkeys, f->dvals, f->ntiles, f->nt_sorted, f->offsets, f->n_keys,
-                             f->dsort_hist.p, s) != 0;
+            lsd = depth_sort(f->depth_key, n, f->dkeys, f->dvals, coarse ? nullptr : f->ntiles,
+                             coarse ? nullptr : f->nt_sorted, f->offsets, f->n_keys, f->dsort_hist.p, s) != 0;
         order = f->dvals[0];
         if (lsd) {
             // 32-bit keys: 8-bit digits give the fewest passes (four); the last

@@ -395,7 +395,7 @@ __global__ void __launch_bounds__(DT) k_ds_down(const uint32_t *__restrict__ key
     for (int j = 0; j < R; j++) {
         const int i = w * (64 * R) + j * 64 + lane;
         key[j] = ok(j) ? keys[base + i] : 0u;
-        cn[j] = ok(j) ? nt[base + i] : 0u;
+        cn[j] = nt && ok(j) ? nt[base + i] : 0u;
     }
     // the tile's offset in each bucket and the bucket totals
     uint32_t before = 0, total = 0;
@@ -546,6 +546,13 @@ __device__ __forceinline__ void write_bucket(const uint32_t (&val)[ITEMS], uint3
                                              uint32_t *__restrict__ nt_sorted, uint32_t *__restrict__ offsets) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t i0 = (uint32_t)(w * (64 * ITEMS) + lane);
+    if (!nt_sorted) {   // the order alone
+        each<ITEMS>([&](auto J) {
+            constexpr int j = J;
+            if (i0 + j * 64 < m) order[i0 + j * 64] = val[j];
+        });
+        return;
+    }
     uint32_t sum = 0;
     each<ITEMS>([&](auto J) { sum += cn[J]; });
     sum = wave_prefix(sum);
@@ -597,7 +604,7 @@ __device__ __forceinline__ bool cell_sort(const uint32_t *__restrict__ kin, cons
         constexpr int j = J;
         const bool in = i0 + j * 64 < m;
         val[j] = in ? sh.key[i0 + j * 64] : 0u;
-        key[j] = in ? nt[val[j]] : 0u;
+        key[j] = nt && in ? nt[val[j]] : 0u;
     });
     write_bucket<T, ITEMS>(val, key, m, base, sh.w, order, nt_sorted, offsets);
     return true;
@@ -631,7 +638,7 @@ __device__ __forceinline__ void local_sort(const uint32_t *__restrict__ kin, con
     for (int p = 0; p < passes; p++) local_pass<T, ITEMS>(key, val, (int)m, lo, p * nbits, (1u << nbits) - 1u, sh, buf);
     each<ITEMS>([&](auto J) {   // (key[] is free for the tile counts)
         constexpr int j = J;
-        key[j] = i0 + j * 64 < m ? nt[val[j]] : 0u;
+        key[j] = nt && i0 + j * 64 < m ? nt[val[j]] : 0u;
     });
     write_bucket<T, ITEMS>(val, key, m, base, sh.w, order, nt_sorted, offsets);
 }
@@ -708,12 +715,14 @@ __device__ __attribute__((noinline)) void slow_sort(uint32_t *k0, uint32_t *v0, 
     __syncthreads();
     for (int64_t i0 = 0; i0 < m; i0 += T) {
         const int64_t i = i0 + tid;
-        const uint32_t v = i < m ? vs[i] : 0u, c = i < m ? nt[v] : 0u;
+        const uint32_t v = i < m ? vs[i] : 0u, c = nt && i < m ? nt[v] : 0u;
         const uint32_t pre = scan_block<T / 64>(c, sh.w, &sum);
         if (i < m) {
             v0[start + i] = v;
-            nt_sorted[start + i] = c;
-            offsets[start + i] = base + pre;
+            if (nt) {
+                nt_sorted[start + i] = c;
+                offsets[start + i] = base + pre;
+            }
         }
         base += sum;
         __syncthreads();
@@ -780,13 +789,13 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, uint32_t *k0, uint32
         pre += pl.b[k];
         all += pl.c[k];
     }
-    if (b == 0 && tid == 0) *n_keys = all;
+    if (b == 0 && tid == 0 && nt) *n_keys = all;
     // (uniform: scalar bases for the bucket's addresses)
     const int64_t start = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)first);
     const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)pre);
     const uint32_t m = ws.total[b];
     const uint32_t *kin = k1 + start, *vin = v1 + start;
-    uint32_t *o = v0 + start, *ns = nt_sorted + start, *off = offsets + start;
+    uint32_t *o = v0 + start, *ns = nt ? nt_sorted + start : nullptr, *off = offsets + start;
     if (m == 0) return;
     const CellMap map = b == 0 ? CELLS_FROM_HI : b == NB - 1 ? CELLS_FROM_LO : CELLS_EVEN;
     bool done = false;
@@ -817,7 +826,7 @@ __global__ void __launch_bounds__(DT) k_ds_one(const uint32_t *__restrict__ keys
         local_sort<T, I>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, sh.digits.d, sh.digits.buf);
     }
     __syncthreads();
-    if (threadIdx.x == 0) *n_keys = offsets[n - 1] + nt_sorted[n - 1];   // the last entry's end
+    if (threadIdx.x == 0 && nt) *n_keys = offsets[n - 1] + nt_sorted[n - 1];   // the last entry's end
 }
 
 template <int R, int S, int T>

@@ -246,7 +246,8 @@ int radix_sort_u64(uint64_t *keys[2], uint32_t *vals[2], const uint32_t *n_dev, 
                    int hi_bit, int radix_bits, void *hist, hipStream_t s);
 // Depth order of n entries (depth_sort.hip): a stable sort of the entry ids by
 // depth_key into dvals[0], the tile counts in that order and their exclusive
-// prefix (their sum to *n_keys).  Returns 0, or -1 with nothing launched when n is 0
+// prefix (their sum to *n_keys); with ntiles and nt_sorted NULL the sort alone.
+// Returns 0, or -1 with nothing launched when n is 0
 // or above DEPTH_SORT_MAX.  dkeys and dvals[1] are scratch of n words, ws of
 // depth_sort_bytes(cap) for some cap >= n.
 constexpr int64_t DEPTH_SORT_MAX = 5 << 18;
