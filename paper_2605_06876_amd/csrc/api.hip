@@ -996,8 +996,7 @@ as_status as_clone_prune(as_ctx *ctx, const as_gaussians *g, const uint8_t *clon
     uint8_t *keep = (uint8_t *)ctx->tr[TR_FLAG].p, *dup = (uint8_t *)ctx->tr[TR_DUP].p;
     int64_t *kpos = (int64_t *)ctx->tr[TR_SCAN].p, *dpos = (int64_t *)ctx->tr[TR_DSCAN].p;
     launch_prune_flags(*g, clone_mask, min_opacity, max_scale, keep, dup, s);
-    scan_u8_to_i64(keep, kpos, n, tot, ctx->tr[TR_TMP].p, s);
-    scan_u8_to_i64(dup, dpos, n, tot + 1, ctx->tr[TR_TMP2].p, s);
+    scan_flags(keep, kpos, tot, dup, dpos, tot + 1, n, ctx->tr[TR_TMP].p, s);
     launch_clone_prune_write(*g, *out, keep, dup, kpos, dpos, tot, tot + 1, state_in, state_src, n_out, s);
     return launch_status(what);
 }

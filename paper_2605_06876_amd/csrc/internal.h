@@ -220,6 +220,9 @@ void launch_project_bwd(const GaussPtrs &g, const ViewTable &vt, const uint32_t 
 size_t scan_tmp_bytes(int64_t n);
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, void *tmp, hipStream_t s);
 void scan_partials_u64(uint64_t *partials, int64_t nb, hipStream_t s);   // in place, one block
+// two arrays of flags of one length (the second may be NULL) in the same launches
+void scan_flags(const uint8_t *in0, int64_t *out0, int64_t *total0, const uint8_t *in1, int64_t *out1, int64_t *total1,
+                int64_t n, void *tmp, hipStream_t s);
 void scan_u8_to_i64(const uint8_t *in, int64_t *out, int64_t n, int64_t *total, void *tmp, hipStream_t s);
 void scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, int64_t *total, void *tmp, hipStream_t s);
 
@@ -283,7 +286,7 @@ struct CoarseBins {
     int32_t shift, bins;
     int32_t base[AS_MAX_VIEWS], x[AS_MAX_VIEWS];
 };
-constexpr int64_t PAIR_BINS_PAIRS = 1 << 22, PAIR_BINS_ENTRIES = 1 << 15, PAIR_BINS_WIDE = 256, PAIR_BINS_FEW = 64;
+constexpr int64_t PAIR_BINS_PAIRS = 1 << 22, PAIR_BINS_ENTRIES = 1 << 15, PAIR_BINS_LISTS = 256;
 size_t coarse_bins_bytes(int64_t tiles, int64_t key_cap);
 size_t pairs_tmp_bytes(int64_t n);
 // Whether a render of n entries into a frame of key_cap pairs bins its pairs

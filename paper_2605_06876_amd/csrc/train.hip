@@ -187,6 +187,12 @@ __global__ void __launch_bounds__(TB) k_prune_flags(int64_t n, const int64_t *__
     dup[i] = k && clone_mask && clone_mask[i] ? 1 : 0;
 }
 
+// Rows are copied a chunk at a time (blockIdx.y), all of a chunk's loads in
+// flight together: one thread walking the 59 rows waits for each in turn (36,000
+// Gaussians 27 -> 8 us, 500,000 77 -> 68; a gather with a thread per row reads the
+// map 59 times, 17 -> 12 and 86 -> 82).
+constexpr int ROW_CHUNK = 8;
+
 // kept rows in order, then the clones; the output has at least 2 n rows
 __global__ void __launch_bounds__(TB) k_clone_prune_write(int64_t n, RowSet src, RowSet dst, int nrows,
                                                           const uint8_t *__restrict__ keep,
@@ -198,15 +204,24 @@ __global__ void __launch_bounds__(TB) k_clone_prune_write(int64_t n, RowSet src,
                                                           int32_t *__restrict__ state_src) {
     const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
     if (i >= n) return;
-    if (keep[i]) {
-        const int64_t r = kpos[i];
-        for (int k = 0; k < nrows; k++) row_ptr(dst, k)[r] = row_ptr(src, k)[i];
-        state_src[r] = state_in ? state_in[i] : (int32_t)i;
-    }
-    if (dup[i]) {
-        const int64_t r = *n_keep + dpos[i];
-        for (int k = 0; k < nrows; k++) row_ptr(dst, k)[r] = row_ptr(src, k)[i];
-        state_src[r] = -1;
+    const bool kept = keep[i], cloned = dup[i];
+    if (!kept && !cloned) return;
+    const int64_t rk = kept ? kpos[i] : 0, rd = cloned ? *n_keep + dpos[i] : 0;
+    const int k0 = (int)blockIdx.y * ROW_CHUNK;
+    float v[ROW_CHUNK];
+#pragma unroll
+    for (int c = 0; c < ROW_CHUNK; c++)
+        if (k0 + c < nrows) v[c] = row_ptr(src, k0 + c)[i];
+#pragma unroll
+    for (int c = 0; c < ROW_CHUNK; c++)
+        if (k0 + c < nrows) {
+            float *D = row_ptr(dst, k0 + c);
+            if (kept) D[rk] = v[c];
+            if (cloned) D[rd] = v[c];
+        }
+    if (k0 == 0) {
+        if (kept) state_src[rk] = state_in ? state_in[i] : (int32_t)i;
+        if (cloned) state_src[rd] = -1;
     }
 }
 
@@ -214,16 +229,21 @@ __global__ void k_add_totals(const int64_t *__restrict__ a, const int64_t *__res
     if (threadIdx.x == 0 && blockIdx.x == 0) *out = *a + *b;
 }
 
-__global__ void __launch_bounds__(TB) k_gather_rows(RowSet src, int64_t src_n, const int32_t *__restrict__ map,
+__global__ void __launch_bounds__(TB) k_gather_rows(RowSet src, int64_t src_n, int nrows, const int32_t *__restrict__ map,
                                                     int64_t n_rows, const int64_t *__restrict__ n_rows_dev,
                                                     RowSet dst) {
-    const int r = blockIdx.y;
-    const float *S = row_ptr(src, r);
-    float *D = row_ptr(dst, r);
+    const int k0 = (int)blockIdx.y * ROW_CHUNK;
     const int64_t m = count_in_use(n_rows, n_rows_dev);
     for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < m; i += (int64_t)gridDim.x * TB) {
         const int32_t s = map[i];
-        D[i] = s >= 0 && s < src_n ? S[s] : 0.0f;
+        const bool in = s >= 0 && s < src_n;
+        float v[ROW_CHUNK];
+#pragma unroll
+        for (int c = 0; c < ROW_CHUNK; c++)
+            if (k0 + c < nrows) v[c] = in ? row_ptr(src, k0 + c)[s] : 0.0f;
+#pragma unroll
+        for (int c = 0; c < ROW_CHUNK; c++)
+            if (k0 + c < nrows) row_ptr(dst, k0 + c)[i] = v[c];
     }
 }
 
@@ -241,6 +261,8 @@ unsigned blocks_for(int64_t n, int64_t cap) {
     if (b > cap) b = cap;
     return (unsigned)(b > 0 ? b : 1);
 }
+
+unsigned row_chunks(int deg) { return (unsigned)((set_rows(deg) + ROW_CHUNK - 1) / ROW_CHUNK); }
 
 }  // namespace
 
@@ -311,7 +333,7 @@ void launch_clone_prune_write(const as_gaussians &g, const as_gaussians_mut &out
                               const int64_t *n_dup, const int32_t *state_in, int32_t *state_src, int64_t *n_out,
                               hipStream_t s) {
     if (g.n > 0)
-        hipLaunchKernelGGL(k_clone_prune_write, dim3(blocks_for(g.n, 1ll << 30)), dim3(TB), 0, s, g.n, rows_of(g),
+        hipLaunchKernelGGL(k_clone_prune_write, dim3(blocks_for(g.n, 1ll << 30), row_chunks(g.sh_degree)), dim3(TB), 0, s, g.n, rows_of(g),
                            rows_of(out), set_rows(g.sh_degree), keep, dup, kpos, dpos, n_keep, state_in, state_src);
     hipLaunchKernelGGL(k_add_totals, dim3(1), dim3(64), 0, s, n_keep, n_dup, n_out);
 }
@@ -319,8 +341,8 @@ void launch_clone_prune_write(const as_gaussians &g, const as_gaussians_mut &out
 void launch_gather_rows(const as_gaussians &src, const int32_t *map, int64_t n_rows, const int64_t *n_rows_dev,
                         const as_gaussians_mut &dst, hipStream_t s) {
     if (n_rows == 0) return;
-    const dim3 grid(blocks_for(n_rows, 1024), (unsigned)set_rows(src.sh_degree));
-    hipLaunchKernelGGL(k_gather_rows, grid, dim3(TB), 0, s, rows_of(src), src.n, map, n_rows, n_rows_dev,
+    const dim3 grid(blocks_for(n_rows, 4096), row_chunks(src.sh_degree));
+    hipLaunchKernelGGL(k_gather_rows, grid, dim3(TB), 0, s, rows_of(src), src.n, set_rows(src.sh_degree), map, n_rows, n_rows_dev,
                        rows_of(dst));
 }
 
