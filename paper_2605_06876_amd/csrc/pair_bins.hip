@@ -499,21 +499,22 @@ size_t coarse_bins_bytes(int64_t tiles, int64_t key_cap) {
 }
 
 // Two launches more than the one-level path, against the pairs' traffic
-// (render of one view, us, two levels / one, by pairs): 0.6M 172 / 156, 1.6M
-// 222 / 212, 2.7M 271 / 269, 4.0M 309 / 317, 4.7M 384 / 402, 7.0M 437 / 472,
-// 14.1M 1031 / 1142, 21.2M 1159 / 1367.  The host knows the pairs by the
-// frame's capacity; few entries leave the emission's blocks too few.
+// (render of one view, us, two levels / one, by pairs): 0.6M 159 / 150, 1.0M
+// 181 / 177, 1.7M 208 / 210, 2.7M 246 / 258, 4.7M 350 / 383, 7.0M 398 / 448,
+// 14.1M 937 / 1071, 21.2M 1056 / 1290.  The host knows the pairs by the frame's
+// capacity, which is a few times what a render needs; few entries leave the
+// emission's blocks too few.
 //
-// Coarse bins of 4 x 4 bins unless that leaves fewer than 256 of them (too few
-// places at once for a sort pass's writes and, in bins of 32, too few items),
-// then of 2 x 2.  Skinny or tiny views, where the coarse grid is mostly border,
-// stay with one level.
+// Coarse bins of 4 x 4 bins, or of 2 x 2 where that leaves fewer than 256 of
+// them: fewer lists are too few places at once for a sort pass's writes (130
+// lists of a 400x300 view, 1.3M pairs: 229 / 215).  Skinny or tiny views,
+// where the coarse grid is mostly border, stay with one level.
 bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb) {
     if (n < PAIR_BINS_ENTRIES || key_cap < PAIR_BINS_PAIRS) return false;
     const int64_t bins = vt.bin_base[vt.n_views];
     int64_t c = fill_coarse(vt, 2, cb);
-    if (c < PAIR_BINS_WIDE) c = fill_coarse(vt, 1, cb);
-    return c >= PAIR_BINS_FEW && c <= (int64_t)PB_ID && (c << (2 * cb->shift)) <= 2 * bins;
+    if (c < PAIR_BINS_LISTS) c = fill_coarse(vt, 1, cb);
+    return c >= PAIR_BINS_LISTS && c <= (int64_t)PB_ID && (c << (2 * cb->shift)) <= 2 * bins;
 }
 
 void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,

@@ -37,16 +37,16 @@ LEAST = 1 << 22   # the smallest pair capacity that takes this path
 
 
 @pytest.mark.parametrize("n,sizes,bin_tile,cap,grow,where", [
-    (32_768, [(333, 250)], 16, LEAST, 0.0, "front"),
-    (300_000, [(333, 250)], 16, LEAST, 0.0, "front"),
+    (32_768, [(615, 437)], 16, LEAST, 0.0, "front"),
+    (300_000, [(615, 437)], 16, LEAST, 0.0, "front"),
     (400_000, [(1031, 1029)], 16, None, 0.0, "front"),
     (400_000, [(1031, 1029)], 16, LEAST, 2.5, "front"),
     (300_000, [(1031, 1029)], 32, None, 0.0, "front"),
     (150_000, [(640, 333), (517, 300), (16, 16)], 16, None, 0.0, "front"),
-    (150_000, [(640, 333), (517, 300), (16, 16)], 32, LEAST + 1, 3.5, "front"),
+    (150_000, [(1040, 700), (800, 600), (16, 16)], 32, LEAST + 1, 3.5, "front"),
     (1_048_577, [(1040, 1024)], 16, None, 0.0, "half"),
     (1_400_000, [(1040, 1024)], 16, LEAST, 2.5, "half"),
-    (2_200_000, [(1000, 400)] * 2, 16, None, 0.0, "half"),
+    (2_200_000, [(1000, 403)] * 2, 16, None, 0.0, "half"),
     (320_000, [(640, 480)], 16, LEAST, 0.0, "behind"),
 ])
 def test_pairs_match_a_stable_sort_by_bin(n, sizes, bin_tile, cap, grow, where):
