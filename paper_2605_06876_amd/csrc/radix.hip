@@ -9,7 +9,8 @@
 //          lane adds into copy lane % 8, so lanes with equal digits mostly hit
 //          different words), stored digit-major: counts[d][tile];
 //   scan   one block per digit turns its column into the exclusive prefix
-//          over tiles and writes the column's total;
+//          over tiles and writes the column's total (sorts of few tiles leave
+//          it out: RS_ROWS);
 //   down   each tile scans the digit totals for the start of every digit's
 //          output range, ranks its keys among equal digits (per wave: RB ballots
 //          give the lanes with the same digit; per-wave counters in LDS carry
@@ -56,6 +57,7 @@ constexpr int RS_THREADS = 256;
 constexpr int RS_ROUNDS_BIG = 16, RS_ROUNDS_SMALL = 8;
 constexpr int RS_TILE_MIN = RS_THREADS * RS_ROUNDS_SMALL;
 constexpr int64_t RS_SMALL_BELOW = 512;             // 4096-key tiles under which the small tiles are used
+constexpr int64_t RS_ROWS = 24576;                  // counts (tiles x digits) up to which each tile sums them itself
 constexpr int RS_COPIES = 8;                        // LDS histogram copies of the up pass
 constexpr int64_t RS_MAX_BLOCKS = 4096;
 constexpr int RS_MAX_BITS = 9;                      // widest digit (64-bit keys: 8)
@@ -90,7 +92,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *s_wave
 template <typename K, int RB, int RS_ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS) k_rs_up(const K *__restrict__ keys, const uint32_t *n_dev, int64_t cap,
                                                       int shift, uint32_t mask, uint32_t *__restrict__ counts,
-                                                      int64_t tstride) {
+                                                      int64_t tstride, int rows) {
     constexpr int NB = 1 << RB, HS = NB + 1;   // copy stride: equal digits of different copies sit in different banks
     constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;
     __shared__ uint32_t s_h[RS_COPIES * HS];
@@ -117,7 +119,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_up(const K *__restrict__ keys
             uint32_t c = 0;
 #pragma unroll
             for (int q = 0; q < RS_COPIES; q++) c += s_h[q * HS + d];
-            counts[(int64_t)d * tstride + t] = c;
+            counts[rows ? t * NB + d : (int64_t)d * tstride + t] = c;
         }
         __syncthreads();   // the histogram is cleared for the next tile
     }
@@ -163,7 +165,7 @@ template <typename K, int RB, int RS_ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
     k_rs_down(const K *__restrict__ kin, const uint32_t *__restrict__ vin, K *__restrict__ kout,
               uint32_t *__restrict__ vout, const uint32_t *n_dev, int64_t cap, int shift, uint32_t mask,
-              const uint32_t *__restrict__ offs, const uint32_t *__restrict__ total, int64_t tstride,
+              const uint32_t *__restrict__ offs, const uint32_t *__restrict__ total, int64_t tstride, int rows,
               const uint32_t *__restrict__ gsrc, uint32_t *__restrict__ gdst) {
     constexpr int NB = 1 << RB;
     constexpr int PER = NB > RS_THREADS ? NB / RS_THREADS : 1;   // consecutive digits per thread
@@ -182,11 +184,42 @@ __global__ void __launch_bounds__(RS_THREADS, sizeof(K) == 4 ? 3 : 2)
         // the tile's offset in each digit's column and the digit totals are
         // loaded first, so the scan below waits for them alone
         uint32_t go[PER], tt[PER], tsum = 0;
+        if (rows) {
+            // the tiles' counts as they are: G groups of threads, a digit (or
+            // PER) each, sum every G-th tile's
+            constexpr int G = NB < RS_THREADS ? RS_THREADS / NB : 1;
+            uint32_t bef[PER], all[PER];
 #pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const int d = tid * PER + k;
-            go[k] = d < NB ? offs[(int64_t)d * tstride + tile] : 0u;
-            tt[k] = d < NB ? total[d] : 0u;
+            for (int k = 0; k < PER; k++) bef[k] = all[k] = 0u;
+#pragma unroll 16
+            for (int64_t t = tid * PER / NB; t < T; t += G)
+#pragma unroll
+                for (int k = 0; k < PER; k++) {
+                    const uint32_t c = offs[t * NB + tid * PER % NB + k];
+                    all[k] += c;
+                    if (t < tile) bef[k] += c;
+                }
+            if (G > 1) {   // (in the arrays of the runs' places, not in use yet)
+                for (int i = tid; i < NB; i += RS_THREADS) s_boff[i] = s_gdst[i] = 0u;
+                __syncthreads();
+                atomicAdd(&s_boff[tid % NB], bef[0]);
+                atomicAdd(&s_gdst[tid % NB], all[0]);
+                __syncthreads();
+                bef[0] = tid < NB ? s_boff[tid] : 0u;
+                all[0] = tid < NB ? s_gdst[tid] : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < PER; k++) {
+                go[k] = bef[k];
+                tt[k] = all[k];
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < PER; k++) {
+                const int d = tid * PER + k;
+                go[k] = d < NB ? offs[(int64_t)d * tstride + tile] : 0u;
+                tt[k] = d < NB ? total[d] : 0u;
+            }
         }
 #pragma unroll
         for (int k = 0; k < PER; k++) tsum += tt[k];
@@ -526,12 +559,14 @@ template <typename K, int RB, int R>
 void rs_pass_r(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, const uint32_t *n_dev, int64_t cap, int64_t grid, int shift,
                uint32_t mask, uint32_t *total, uint32_t *counts, int64_t tstride, const uint32_t *gsrc, uint32_t *gdst,
                hipStream_t s) {
+    const int rows = tstride << RB <= RS_ROWS ? 1 : 0;
     hipLaunchKernelGGL((k_rs_up<K, RB, R>), dim3((unsigned)grid), dim3(RS_THREADS), 0, s, ki, n_dev, cap, shift, mask,
-                       counts, tstride);
-    hipLaunchKernelGGL(k_rs_scan, dim3(1u << RB), dim3(RS_THREADS), 0, s, counts, tstride, n_dev, cap,
-                       RS_THREADS * R, total);
+                       counts, tstride, rows);
+    if (!rows)
+        hipLaunchKernelGGL(k_rs_scan, dim3(1u << RB), dim3(RS_THREADS), 0, s, counts, tstride, n_dev, cap,
+                           RS_THREADS * R, total);
     hipLaunchKernelGGL((k_rs_down<K, RB, R>), dim3((unsigned)grid), dim3(RS_THREADS), 0, s, ki, vi, ko, vo, n_dev,
-                       cap, shift, mask, counts, total, tstride, gsrc, gdst);
+                       cap, shift, mask, counts, total, tstride, rows, gsrc, gdst);
 }
 
 template <typename K, int RB>
