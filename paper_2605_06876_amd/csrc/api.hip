@@ -741,6 +741,7 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
                                f->n_keys, report, f->ranges, tiles, s);
     }
     int sel;
+    bool fwd_order;
     {
         StageTimer t(ctx, AS_STAGE_SORT, s);
         // only the pairs written (a render over the capacity writes a prefix)
@@ -760,7 +761,8 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
         }
         f->sorted_sel = sel;
         f->use_order = ctx->longest_first;
-        if (f->use_order) launch_tile_order(f, vt, s);
+        fwd_order = f->use_order && (tiles > ORDER_TILES || n > ORDER_ENTRIES);
+        if (fwd_order) launch_tile_order(f, vt, s);
     }
     const BlendLaunch bl{ctx->lds_batch, ctx->persistent, ctx->n_cu, ctx->block_cull};
     {
@@ -770,7 +772,7 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
         // frames that can take a reverse pass have the forward clear the 2D
         // gradient rows it will add into
         const bool zg = !(f->flags & AS_FRAME_FORWARD_ONLY);
-        f->g2d_zero = launch_blend_fwd(f, f->vals[sel], f->use_order ? f->tile_order : nullptr, bl, vt, gi, im, s,
+        f->g2d_zero = launch_blend_fwd(f, f->vals[sel], fwd_order ? f->tile_order : nullptr, bl, vt, gi, im, s,
                                        zg ? f->grad2d : nullptr, 9 * n) && zg;
         f->g2d_zero_capture = g_capture_id;
         if (gt) launch_view_err(f, vt, gi, s);
