@@ -155,6 +155,34 @@ void scan_impl(const Tin *in, Tout *out, int64_t n, Tout *total, void *tmp, hipS
     if (n > 0) hipLaunchKernelGGL((k_scan_down<Tin, Tout>), dim3((unsigned)nb), dim3(SCAN_THREADS), 0, s, in, n, partials, out);
 }
 
+// Up to SCAN_ONE values by one block: its loads are one round, and a launch and a
+// gap are saved (the 8,160 bins of a 1920x1080 view: 9.7 us in two launches, 4.8).
+constexpr int SCAN_ONE_THREADS = 1024, SCAN_ONE = SCAN_ONE_THREADS * 8;
+
+__global__ void __launch_bounds__(SCAN_ONE_THREADS) k_scan_one(const uint32_t *in, int n, uint32_t *out,
+                                                               uint32_t *__restrict__ total) {
+    // wave w takes values 512 w .. 512 w + 511, 64 side by side at a time
+    __shared__ uint32_t s_wave[SCAN_ONE_THREADS / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, base = 512 * w + lane;
+    uint32_t v[8], pre[8], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = base + 64 * k < n ? in[base + 64 * k] : 0u;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const uint32_t inc = wave_prefix(v[k]);
+        pre[k] = sum + inc - v[k];
+        sum += last_lane(inc);
+    }
+    if (lane == 0) s_wave[w] = sum;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int k = 0; k < w; k++) before += s_wave[k];
+    if (total && threadIdx.x == SCAN_ONE_THREADS - 1) *total = before + sum;
+#pragma unroll
+    for (int k = 0; k < 8; k++)
+        if (base + 64 * k < n) out[base + 64 * k] = before + pre[k];
+}
+
 // Scans of flags (bytes), up to two arrays of one length in the same launches:
 // 16 bytes a thread from one load, summed by v_sad_u8.  A byte load per element
 // and lanes eight bytes apart took 13 us for the two launches at 500,000 flags, this 10.5.
@@ -349,6 +377,10 @@ void fill_impl(T *p, T v, int64_t n, hipStream_t s) {
 size_t scan_tmp_bytes(int64_t n) { return (size_t)((n + SCAN_TILE - 1) / SCAN_TILE + 1) * 8 + 256; }
 
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, void *tmp, hipStream_t s) {
+    if (n > 0 && n <= SCAN_ONE) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(SCAN_ONE_THREADS), 0, s, in, (int)n, out, total);
+        return;
+    }
     scan_impl<uint32_t, uint32_t>(in, out, n, total, tmp, s);
 }
 void scan_partials_u64(uint64_t *partials, int64_t nb, hipStream_t s) {

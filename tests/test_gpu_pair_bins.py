@@ -48,6 +48,8 @@ LEAST = 1 << 22   # the smallest pair capacity that takes this path
     (1_400_000, [(1040, 1024)], 16, LEAST, 2.5, "half"),
     (2_200_000, [(1000, 403)] * 2, 16, None, 0.0, "half"),
     (320_000, [(640, 480)], 16, LEAST, 0.0, "behind"),
+    (200_000, [(2048, 1024)], 16, LEAST, 0.0, "front"),    # 8,192 bins, scanned by one block
+    (200_000, [(2049, 1024)], 16, LEAST, 0.0, "front"),    # 8,256
 ])
 def test_pairs_match_a_stable_sort_by_bin(n, sizes, bin_tile, cap, grow, where):
     rng = np.random.default_rng(n + bin_tile)
