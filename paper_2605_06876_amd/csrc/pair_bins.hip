@@ -19,13 +19,12 @@
 //
 // Emission, sort and ranges against this (us, MI355X, with the gather of the
 // tile counts into depth order where it is the sort's last pass): 82.8M pairs of
-// eight views 1810 -> 740, 9.7M of one 1920x1080 view 175 -> 100.  What bounds
-// it now: the placing, 244 us for 82.8M pairs (3.4 TB/s of a copy's 4.8; its 16
-// ballots a round take half the issue slots), and the random read of the boxes
+// eight views 1810 -> 700, 9.7M of one 1920x1080 view 175 -> 95.  What bounds
+// it now: the placing, 208 us for 82.8M pairs (4.0 TB/s of a copy's 4.8), and the random read of the boxes
 // (157 us for 8.2M entries).  Placing by a block per list in place of work items:
 // 920 us, the lists are uneven; eight blocks per list 350 us.  Loading each
 // round on its own: 1690 us, a wave's loads wait for the stores before them.
-// Counting by ballots as the placing does: 67 us, by packed counts 33.  Emitting
+// Counting by ballots as the placing does: 67 us, by packed counts 28.  Emitting
 // with lanes that search for the owner of their position: 105 us, by owner 89.
 #include "internal.h"
 
@@ -37,10 +36,13 @@ constexpr int64_t PB_SMALL = 1 << 20;             // ranks up to which they take
 constexpr int64_t PB_DIRECT = 2048;               // blocks up to which each sums the partials before it itself
 constexpr uint32_t PB_OWN = 8;                    // coarse pairs that an entry's own lane writes
 constexpr int PB_WAVES = 4;                       // waves of a block of count and place
-constexpr int PB_BATCH = 4;                       // rounds of 64 pairs of a wave
+constexpr int PB_BATCH = 6;                       // rounds of 64 pairs of a wave (place and count, 82.8M pairs / 0.6M: 236 / 12.5 us; 4: 246 / 11.7, 8: 238 / 13.4)
 constexpr int PB_SLICE = 64 * PB_BATCH;
 constexpr int PB_ITEM = PB_WAVES * PB_SLICE;      // pairs of a work item
-constexpr int PB_GRID = 2048;                     // most blocks of count and place (eight to a CU; they loop)
+// Most blocks of count and of place, which loop over the items.  The placing's items
+// are uneven and wait for their writes, so it takes many more blocks than
+// are resident: 2048 blocks 245 us at 82.8M pairs, 16384 209.
+constexpr int PB_GRID_COUNT = 2048, PB_GRID_PLACE = 16384;
 constexpr int PB_LISTS = 63;                      // lists found by a block: a row of 16 lanes for each start, and the last one's end
 constexpr uint32_t PB_ID = 0xFFFFFFu;             // key: coarse bin id in 24 bits, then x0, x1, y0, y1 of two bits
 
@@ -535,7 +537,8 @@ void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_ca
                        int64_t n_tiles, void *ws, void *tmp, hipStream_t s) {
     const int64_t bins = vt.bin_base[vt.n_views], most = most_items(cb.bins, key_cap);
     const PbWs p = pb_ws(ws, cb, key_cap, bins);
-    const dim3 grid((unsigned)(most < PB_GRID ? most : PB_GRID)), block(PB_WAVES * 64);
+    const dim3 grid((unsigned)(most < PB_GRID_COUNT ? most : PB_GRID_COUNT)), block(PB_WAVES * 64);
+    const dim3 wide((unsigned)(most < PB_GRID_PLACE ? most : PB_GRID_PLACE));
     hipLaunchKernelGGL(k_bins_lists, dim3((unsigned)(cb.bins + PB_LISTS - 1) / PB_LISTS), dim3(1024), 0, s, ckeys, n_keys,
                        cb.bins, p.items, p.n_items, p.counts, bins, ranges, 2 * n_tiles);
     if (cb.shift == 2)
@@ -544,10 +547,10 @@ void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_ca
         hipLaunchKernelGGL(k_bins_count<2>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.counts);
     scan_u32(p.counts, p.starts, bins, nullptr, tmp, s);
     if (cb.shift == 2)
-        hipLaunchKernelGGL(k_bins_place<4>, grid, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
+        hipLaunchKernelGGL(k_bins_place<4>, wide, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
                            p.starts, p.counts, keys, vals, ranges);
     else
-        hipLaunchKernelGGL(k_bins_place<2>, grid, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
+        hipLaunchKernelGGL(k_bins_place<2>, wide, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
                            p.starts, p.counts, keys, vals, ranges);
 }
 
