@@ -52,6 +52,29 @@ def test_batch_matches_the_oracle_view_by_view(sizes, r):
     np.testing.assert_array_equal(attr.cpu().numpy() - 3, 2 * (attr_o - 3))
 
 
+@pytest.mark.parametrize("W,H", [(1, 1), (16, 16), (17, 15), (63, 65), (64, 64), (91, 90), (4097, 1)])
+def test_one_view_matches_the_oracle_through_both_calls(W, H):
+    """The single call and a batch of one view have the same kernels with a
+    table of one view: bit-exact, at the edges of tiles and chunks."""
+    prm = oracle.SplitParams(r_erode=1, m_min=1)
+    img, gt, dom, is_cand = stripes_fixture(H, W, seed=7, widen=1)
+    attr_o = np.full(4, 3, np.int32)
+    want, _ = oracle.error_stats(img, gt, dom, is_cand, 5, prm, attr_o)
+    ctx = api.Context(0, max_pixels=W * H)
+    gtt, cand, domt = torch.from_numpy(gt).cuda(), torch.from_numpy(is_cand).cuda(), torch.from_numpy(dom).cuda()
+    err, mm = api.error_map(ctx, torch.from_numpy(img).cuda(), gtt)
+    for batch in (False, True):
+        regions = api.RegionBuffer(W * H)
+        attr = torch.full((4,), 3, dtype=torch.int32, device="cuda")
+        if batch:
+            api.accumulate_error_stats_batch(ctx, [(W, H, err, mm, domt, gtt, 5)], cand, gparams(prm), regions, attr)
+        else:
+            api.accumulate_error_stats(ctx, W, H, err, mm, domt, gtt, 5, cand, gparams(prm), regions, attr)
+        torch.cuda.synchronize()
+        compare_regions(regions.host(), want)
+        np.testing.assert_array_equal(attr.cpu().numpy(), attr_o)
+
+
 def test_batch_refuses_what_does_not_fit():
     ctx = api.Context(0, max_pixels=100)
     z = lambda *s, d=torch.float32: torch.zeros(*s, dtype=d, device="cuda")
