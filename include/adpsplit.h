@@ -145,7 +145,8 @@ typedef struct {
     uint32_t ent_base;        /* global entry id of the view's Gaussian 0 */
     uint32_t *n_keys;         /* [2] (tile, entry) pairs of the last render, all views: [0] the
                                  number it needed, [1] the number written to keys / vals
-                                 (fewer when [0] > key_cap) */
+                                 (fewer when [0] > key_cap; 2^32 - 1 in [0] of a frame of 2^22 pairs
+                                 or more may stand for any number from there on) */
     uint32_t *keys;           /* [key_cap] sorted global bin ids (tile ids when bin_size = 16) */
     uint32_t *vals;           /* [key_cap] entry id of each sorted pair (entry = ent_base of its view + Gaussian id) */
     uint32_t *ranges;         /* [tiles][2] start, end into keys/vals of the view's tiles */

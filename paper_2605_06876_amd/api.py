@@ -92,6 +92,7 @@ class _Reserve(ctypes.Structure):
 
 RESERVE_FIELDS = ("max_pixels", "max_gaussians", "max_candidates", "max_regions", "max_views")
 FRAME_FORWARD_ONLY = 1
+MAX_PAIRS = 0xFFFFFFFF   # a pair count of a large render that stands for this many or more
 
 EXPORTED = ("as_ctx_create", "as_ctx_destroy", "as_last_error", "as_version", "as_ctx_reserve", "as_ctx_get_reserve",
             "as_ctx_reserve_bytes", "as_frame_create", "as_frame_create_batch", "as_frame_reserve_keys",
@@ -345,6 +346,8 @@ class Frame:
             K = self.n_keys()
         if K <= self.key_cap:
             return False
+        if K == MAX_PAIRS:
+            raise AdpSplitError(AS_ERR_CAPACITY, "the render needs 2^32 - 1 pairs or more, above what a frame can hold")
         self.reserve_keys(min(K + K // 4 + 1024, 0xFFFFFFFF))
         return True
 

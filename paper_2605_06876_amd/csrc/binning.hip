@@ -383,9 +383,6 @@ void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, voi
     }
     scan_impl<uint32_t, uint32_t>(in, out, n, total, tmp, s);
 }
-void scan_partials_u64(uint64_t *partials, int64_t nb, hipStream_t s) {
-    hipLaunchKernelGGL((k_scan_partials<uint64_t>), dim3(1), dim3(SCAN_THREADS), 0, s, partials, nb, (uint64_t *)nullptr);
-}
 void scan_flags(const uint8_t *in0, int64_t *out0, int64_t *total0, const uint8_t *in1, int64_t *out1, int64_t *total1,
                 int64_t n, void *tmp, hipStream_t s) {
     const int64_t nb = (n + FLAG_TILE - 1) / FLAG_TILE;

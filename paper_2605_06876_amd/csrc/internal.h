@@ -219,7 +219,6 @@ void launch_project_bwd(const GaussPtrs &g, const ViewTable &vt, const uint32_t 
 // scans (binning.hip): exclusive scans with the total written to *total
 size_t scan_tmp_bytes(int64_t n);
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, void *tmp, hipStream_t s);
-void scan_partials_u64(uint64_t *partials, int64_t nb, hipStream_t s);   // in place, one block
 // two arrays of flags of one length (the second may be NULL) in the same launches
 void scan_flags(const uint8_t *in0, int64_t *out0, int64_t *total0, const uint8_t *in1, int64_t *out1, int64_t *total1,
                 int64_t n, void *tmp, hipStream_t s);
@@ -294,8 +293,8 @@ size_t pairs_tmp_bytes(int64_t n);
 bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb);
 // The coarse pairs of the entries in depth order (key: coarse bin id in the
 // low 24 bits); box_lo, box_hi: scratch of n words; tmp: pairs_tmp_bytes(cap) for some cap >= n.
-// n_keys[0..2] get the pairs of the bins needed and written (as
-// launch_emit_sorted) and the coarse pairs written.
+// n_keys[0..2] get the pairs of the bins needed (2^32 - 1 for that many or more) and
+// written (as launch_emit_sorted) and the coarse pairs written.
 void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const CoarseBins &cb, const int16_t *box,
                        uint32_t *box_lo, uint32_t *box_hi, int64_t key_cap, uint32_t *keys, uint32_t *vals,
                        uint32_t *n_keys, const PairReport &report, void *ws, void *tmp, hipStream_t s);

@@ -27,6 +27,7 @@
 // Counting by ballots as the placing does: 67 us, by packed counts 28.  Emitting
 // with lanes that search for the owner of their position: 105 us, by owner 89.
 #include "internal.h"
+#include "pair_count.h"
 
 namespace {
 
@@ -55,15 +56,16 @@ __device__ __forceinline__ BinRect bin_rect(uint32_t lo, uint32_t hi, int bs) {
     return BinRect{(int16_t)(lo & 0xFFFFu) >> bs, (int16_t)(hi & 0xFFFFu) >> bs, (int16_t)(lo >> 16) >> bs,
                    (int16_t)(hi >> 16) >> bs};
 }
-// (bins << 32) | coarse bins: both counts in one sum
+// (bins << 32) | coarse bins: both counts in one sum (pair_count.h)
 __device__ __forceinline__ uint64_t rect_counts(const BinRect &b, int cs) {
     const uint32_t f = (uint32_t)((b.fx1 - b.fx0 + 1) * (b.fy1 - b.fy0 + 1));
     const uint32_t c = f ? (uint32_t)(((b.fx1 >> cs) - (b.fx0 >> cs) + 1) * ((b.fy1 >> cs) - (b.fy0 >> cs) + 1)) : 0u;
     return ((uint64_t)f << 32) | c;
 }
 
-// Prefix and sum of (bins << 32) | coarse bins over the wave: the halves apart
-// (the coarse bins of a render stay below 2^32).
+// Prefix and sum over the wave of the counts of up to 8 entries a lane, the
+// halves apart and exact: an entry touches at most 2^22 bins (a view is at most
+// 32,767 pixels a side), 512 of them 2^31.  Sums beyond a wave saturate.
 __device__ __forceinline__ uint64_t wave_prefix2(uint64_t v) {
     return ((uint64_t)wave_prefix((uint32_t)(v >> 32)) << 32) | wave_prefix((uint32_t)v);
 }
@@ -71,15 +73,55 @@ __device__ __forceinline__ uint64_t last_lane2(uint64_t v) {
     return ((uint64_t)last_lane((uint32_t)(v >> 32)) << 32) | last_lane((uint32_t)v);
 }
 __device__ __forceinline__ uint64_t wave_sum(uint64_t v) { return last_lane2(wave_prefix2(v)); }
-// Sum over the block (every thread gets it); s of PB_THREADS / 64 words.
-__device__ __forceinline__ uint64_t block_sum(uint64_t v, uint64_t *s) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+__device__ __forceinline__ uint64_t wave_sum_sat(uint64_t v) {
+    for (int o = 32; o > 0; o >>= 1) v = sat_add(v, __shfl_xor(v, o, 64));
+    return v;
+}
+// The waves' sums added (every thread gets it); s of PB_THREADS / 64 words.
+__device__ __forceinline__ uint64_t block_sum(uint64_t wave, uint64_t *s) {
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = wave;
     __syncthreads();
     uint64_t t = 0;
-    for (int k = 0; k < PB_THREADS / 64; k++) t += s[k];
+    for (int k = 0; k < PB_THREADS / 64; k++) t = sat_add(t, s[k]);
     __syncthreads();
     return t;
+}
+
+// Exclusive prefix of the blocks' sums, in place, by one block.
+__global__ void __launch_bounds__(PB_THREADS) k_pairs_scan(uint64_t *__restrict__ partials, int64_t nb) {
+    constexpr int ITEMS = 8, W = PB_THREADS / 64;
+    __shared__ uint64_t s_w[2][W];   // (one barrier a turn: the next writes the other half)
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint64_t carry = 0;
+    int flip = 0;
+    for (int64_t c0 = 0; c0 < nb; c0 += PB_THREADS * ITEMS, flip ^= 1) {
+        const int64_t base = c0 + (int64_t)threadIdx.x * ITEMS;
+        uint64_t v[ITEMS], sum = 0;
+#pragma unroll
+        for (int k = 0; k < ITEMS; k++) {
+            v[k] = base + k < nb ? partials[base + k] : 0ull;
+            sum = sat_add(sum, v[k]);
+        }
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint64_t t = __shfl_up(sum, o, 64);
+            if (lane >= o) sum = sat_add(sum, t);
+        }
+        if (lane == 63) s_w[flip][w] = sum;
+        const uint64_t up = __shfl_up(sum, 1, 64);
+        __syncthreads();
+        uint64_t run = carry;
+        for (int k = 0; k < W; k++) {
+            const uint64_t x = s_w[flip][k];
+            if (k < w) run = sat_add(run, x);
+            carry = sat_add(carry, x);
+        }
+        if (lane > 0) run = sat_add(run, up);
+#pragma unroll
+        for (int k = 0; k < ITEMS; k++) {
+            if (base + k < nb) partials[base + k] = run;
+            run = sat_add(run, v[k]);
+        }
+    }
 }
 
 // The one random read of the path: a box per rank, kept in depth order for the emission.
@@ -107,7 +149,7 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_sum(int64_t n, const uint3
             sum += rect_counts(bin_rect(b[j].x, b[j].y, bs), cs);
         }
     }
-    sum = block_sum(sum, s_w);
+    sum = block_sum(wave_sum(sum), s_w);
     if (threadIdx.x == 0) partials[blockIdx.x] = sum;
 }
 
@@ -150,8 +192,8 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
     if (scanned) {
         pre = partials[blockIdx.x];
     } else {
-        for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += PB_THREADS) pre += partials[b];
-        pre = block_sum(pre, s_w);
+        for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += PB_THREADS) pre = sat_add(pre, partials[b]);
+        pre = block_sum(wave_sum_sat(pre), s_w);
     }
     sum = wave_sum(sum);
     if (lane == 0) s_w[w] = sum;
@@ -159,8 +201,8 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
     uint64_t all = pre;
     for (int k = 0; k < W; k++) {
         const uint64_t x = s_w[k];
-        if (k < w) pre += x;
-        all += x;
+        if (k < w) pre = sat_add(pre, x);
+        all = sat_add(all, x);
     }
     // n_keys: the pairs of the bins needed and written, and the coarse pairs written
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
@@ -175,16 +217,14 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
 #pragma unroll
     for (int j = 0; j < R; j++) {
         const BinRect b = bin_rect(lo[j], hi[j], bs);
-        const uint64_t c = rect_counts(b, cs), inc = wave_prefix2(c), at = pre + inc - c;
-        pre += last_lane2(inc);
-        const uint64_t off = at >> 32, nt = c >> 32;
-        // an entry whose bins' pairs do not all fit is dropped whole, with all after it
-        const bool kept = nt && off + nt <= (uint64_t)key_cap;
-        if (nt && off <= (uint64_t)key_cap && (uint64_t)key_cap < off + nt) {
-            n_keys[1] = (uint32_t)off;
+        const uint64_t c = rect_counts(b, cs), inc = wave_prefix2(c), at = sat_add(pre, inc - c);
+        pre = sat_add(pre, last_lane2(inc));
+        const PairCut cut = pair_cut(at, c, (uint64_t)key_cap);
+        if (cut.crosses) {
+            n_keys[1] = (uint32_t)(at >> 32);
             n_keys[2] = (uint32_t)at;
         }
-        const uint32_t ct = kept ? (uint32_t)c : 0u, coff = (uint32_t)at;
+        const uint32_t ct = cut.kept ? (uint32_t)c : 0u, coff = (uint32_t)at;
         if (!__builtin_amdgcn_ballot_w64(ct != 0)) continue;
         const int v = view_of_entry(vt, id[j]), pitch = s_pitch[v], base = s_base[v];
         const int cx0 = b.fx0 >> cs, cx1 = b.fx1 >> cs, cy0 = b.fy0 >> cs;
@@ -273,7 +313,7 @@ __device__ __forceinline__ CoarsePlace coarse_place(const ViewTable &vt, const C
 // (coarse bin, part of its list, list start, list length).  Also clears the
 // bins' counts for the launch that adds them, and the tiles' ranges.
 __global__ void __launch_bounds__(1024) k_bins_lists(const uint32_t *__restrict__ keys,
-                                                     const uint32_t *__restrict__ n_keys, int cbins,
+                                                     const uint32_t *__restrict__ n_keys, int64_t key_cap, int cbins,
                                                      uint4 *__restrict__ items, uint32_t *__restrict__ n_items,
                                                      uint32_t *__restrict__ counts, int64_t bins,
                                                      uint32_t *__restrict__ ranges, int64_t range_words) {
@@ -283,7 +323,7 @@ __global__ void __launch_bounds__(1024) k_bins_lists(const uint32_t *__restrict_
     for (int64_t i = t0; i < range_words; i += tn) ranges[i] = 0u;
     const int w = (int)(threadIdx.x >> 4), sub = (int)(threadIdx.x & 15);
     const int cid = (int)blockIdx.x * PB_LISTS + w;
-    const uint32_t p = coarse_bound(keys, n_keys[2], (uint32_t)cid);   // (bins past the last end where it ends)
+    const uint32_t p = coarse_bound(keys, (uint32_t)min((int64_t)n_keys[2], key_cap), (uint32_t)cid);   // (bins past the last end where it ends)
     if (sub == 0) s_at[w] = p;
     __syncthreads();
     if (w == PB_LISTS || cid >= cbins) return;
@@ -480,7 +520,7 @@ void pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const Coa
     hipLaunchKernelGGL((k_pairs_sum<R>), grid, block, 0, s, n, order, vt.bin_shift, cb.shift,
                        reinterpret_cast<const uint2 *>(box), box_lo, box_hi, partials, n_items);
     const int scanned = nb > PB_DIRECT;
-    if (scanned) scan_partials_u64(partials, nb, s);
+    if (scanned) hipLaunchKernelGGL(k_pairs_scan, dim3(1), block, 0, s, partials, nb);
     hipLaunchKernelGGL((k_pairs_emit<R>), grid, block, 0, s, n, order, vt, cb, box_lo, box_hi, partials, scanned, key_cap,
                        keys, vals, n_keys, report);
 }
@@ -512,7 +552,7 @@ size_t coarse_bins_bytes(int64_t tiles, int64_t key_cap) {
 // lists of a 400x300 view, 1.3M pairs: 229 / 215).  Skinny or tiny views,
 // where the coarse grid is mostly border, stay with one level.
 bool coarse_bins(const ViewTable &vt, int64_t n, int64_t key_cap, CoarseBins *cb) {
-    if (n < PAIR_BINS_ENTRIES || key_cap < PAIR_BINS_PAIRS) return false;
+    if (n < PAIR_BINS_ENTRIES || key_cap < PAIR_BINS_PAIRS || key_cap > MAX_PAIR_CAP) return false;
     const int64_t bins = vt.bin_base[vt.n_views];
     int64_t c = fill_coarse(vt, 2, cb);
     if (c < PAIR_BINS_LISTS) c = fill_coarse(vt, 1, cb);
@@ -540,7 +580,7 @@ void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_ca
     const dim3 grid((unsigned)(most < PB_GRID_COUNT ? most : PB_GRID_COUNT)), block(PB_WAVES * 64);
     const dim3 wide((unsigned)(most < PB_GRID_PLACE ? most : PB_GRID_PLACE));
     hipLaunchKernelGGL(k_bins_lists, dim3((unsigned)(cb.bins + PB_LISTS - 1) / PB_LISTS), dim3(1024), 0, s, ckeys, n_keys,
-                       cb.bins, p.items, p.n_items, p.counts, bins, ranges, 2 * n_tiles);
+                       key_cap, cb.bins, p.items, p.n_items, p.counts, bins, ranges, 2 * n_tiles);
     if (cb.shift == 2)
         hipLaunchKernelGGL(k_bins_count<4>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.counts);
     else
