@@ -5,8 +5,8 @@
 // radix sort that is four digit passes of three launches and two launches of
 // the scan, most of them launch latency below a few hundred thousand
 // entries, and every entry moved four times through memory above.  Here:
-//   up      every block takes NB - 1 splitters from the same strided sample
-//           of the keys, then counts its tile's keys per bucket
+//   up      every block takes NB - 1 splitters from the same sample of the
+//           keys, then counts its tile's keys per bucket
 //           (bucket = splitters <= key, so equal keys share a bucket);
 //   scan    (above DS_ROWS tiles) the counts' prefixes over the tiles; below,
 //           each block of the next launch sums the tiles' rows itself;
@@ -14,7 +14,7 @@
 //           tile counts summed per bucket;
 //   local   one block per bucket: its keys placed by counting (cell_places) or,
 //           where they are too uneven for that, sorted by digit passes, in
-//           registers and LDS; then the entries, their tile counts and the
+//           registers and LDS or in global memory; then the entries, their tile counts and the
 //           counts' exclusive prefix written once.
 // A sort of up to DS_ONE entries is the local step alone, one launch.
 // Radix sort and scan against this (us, MI355X): 2,000 entries 50 -> 9, 20,000
@@ -23,8 +23,16 @@
 // of the CU with the fullest bucket.
 //
 // Buckets follow the keys' distribution (the splitters are quantiles of the
-// sample), so a bucket over the LDS capacity needs many equal keys beside
-// others; its block then sorts it in global memory, correct at any size.
+// sample), except that equal keys cannot be told apart by splitters.  A depth that
+// more than one splitter falls on gets a bucket of its own, which needs no sorting
+// and which the blocks of the buckets left empty write with its own (splitters,
+// share_bucket).  Left to be sorted in global memory by one block are buckets of few
+// depths above 4 T keys, or above the LDS capacity (two or three depths with a
+// 200th of a million entries each).
+// Depth order, scan and pair sort of 1,048,576 entries (us; in brackets with one
+// block for every bucket, then with the radix sort): spread depths 110 (110, 141), all
+// equal 103 (1467, 132), nine in ten equal 122 (3063, 136), 160 depths 174 (468, 139),
+// two clouds' entries in turn 176 (3919, 141).
 // Values are the entry ids, so the first scatter reads only keys, straight
 // from the projection's depth keys.
 #include <type_traits>
@@ -50,13 +58,15 @@ constexpr int DS_ITEMS = 16;             // keys per thread of the largest bucke
 constexpr int DS_ROWS = 64;              // tiles whose counts the scatter sums itself
 constexpr int SLOW_ITEMS = 4;            // keys per thread and step of the global-memory path
 
-// Workspace words: splitters, bucket totals, tile-count sums, then the counts.
+// Workspace words: splitters, bucket totals, tile-count sums, then per tile the
+// counts and, of the buckets of one depth, (keys, their tile counts' sum).
 struct DsWs {
     uint32_t *split, *total, *ntsum, *counts;
+    uint2 *part;
 };
-DsWs ds_ws(void *ws) {
+DsWs ds_ws(void *ws, int64_t tiles) {
     uint32_t *p = reinterpret_cast<uint32_t *>(ws);
-    return DsWs{p, p + NB, p + 2 * NB, p + 3 * NB};
+    return DsWs{p, p + NB, p + 2 * NB, p + 3 * NB, reinterpret_cast<uint2 *>(p + 3 * NB + tiles * NB)};
 }
 
 // f(0), f(1), .. f(N - 1) with compile-time indices: the per-thread arrays
@@ -217,30 +227,57 @@ __device__ __forceinline__ bool cell_places(const uint32_t (&key)[ITEMS], uint32
     return true;
 }
 
-// The block's 1024 keys ascending over its threads (bitonic: strides below a
-// wave by lane exchange, the others through LDS; s: 1024 words).
-__device__ __forceinline__ uint32_t bitonic_block(uint32_t v, uint32_t *s) {
+// The block's I * 1024 keys ascending, key j of thread t at j * 1024 + t (bitonic:
+// strides below a wave by lane exchange, up to the block through LDS, s: I * 1024
+// words, the last one between a thread's two).
+template <int I>
+__device__ __forceinline__ void bitonic_block(uint32_t (&v)[I], uint32_t *s) {
+    static_assert(I <= 2, "at most two keys a thread");
     const int tid = threadIdx.x;
-    for (int k = 2; k <= DT; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            uint32_t o;
-            if (j < 64) {
-                o = (uint32_t)__shfl_xor((int)v, j, 64);
-            } else {
-                __syncthreads();
-                s[tid] = v;
-                __syncthreads();
-                o = s[tid ^ j];
+    for (int k = 2; k <= I * DT; k <<= 1)
+        for (int st = k >> 1; st > 0; st >>= 1) {
+            if (st >= DT) {
+                const uint32_t a = v[0], b = v[I - 1];
+                v[0] = min(a, b);
+                v[I - 1] = max(a, b);
+                continue;
             }
-            const bool lower = (tid & j) == 0, up = (tid & k) == 0;
-            v = lower == up ? min(v, o) : max(v, o);
+            if (st >= 64) {
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < I; j++) s[j * DT + tid] = v[j];
+                __syncthreads();
+            }
+#pragma unroll
+            for (int j = 0; j < I; j++) {
+                const uint32_t o = st < 64 ? (uint32_t)__shfl_xor((int)v[j], st, 64) : s[j * DT + (tid ^ st)];
+                const bool lower = (tid & st) == 0, up = ((j * DT + tid) & k) == 0;
+                v[j] = lower == up ? min(v[j], o) : max(v[j], o);
+            }
         }
-    __syncthreads();
-    return v;
 }
 
-// NB - 1 splitters from a strided sample of S keys, into s_split.  The sample is
-// placed by cells; a skewed one (see cell_places) falls back to a sorted 1024 of it.
+// Where sample k of S is taken: somewhere in the k-th of S equal parts of the
+// entries.  Always in the middle, it would be every 2^m-th entry of most sets, and see
+// one kind of entries where kinds alternate.
+template <int S>
+__device__ __forceinline__ uint32_t sample_at(uint32_t k, uint32_t n) {
+    static_assert((int64_t)S * DEPTH_SORT_MAX <= 0xFFFFFFFFll, "products of 32 bits");
+    const uint32_t lo = k * n / S, hi = (k + 1) * n / S;
+    uint32_t h = (k + 1) * 0x9E3779B1u;
+    h = (h ^ (h >> 15)) * 0x85EBCA77u;
+    return lo + __umulhi(h, hi - lo);
+}
+
+// NB - 1 splitters from a sample of S keys, into s_split.  The sample is
+// placed by cells, a skewed one (see cell_places) sorted.
+//
+// Where splitters are equal, a depth holds more than about one in 128 of the
+// entries.  Of a run of equal splitters the last is raised by one: the bucket
+// before it then holds that depth alone, in order as it stands, and the buckets of the
+// run before that one are empty, in number as the share of the entries it holds,
+// so their blocks can write it between them (share_bucket).
+// (To be seen by other threads after the caller's next barrier.)
 template <int S>
 __device__ __forceinline__ void splitters(const uint32_t *__restrict__ keys, int64_t n, CellShared<DT, S, 2 * DT> &sh,
                                           uint32_t *s_split) {
@@ -248,19 +285,29 @@ __device__ __forceinline__ void splitters(const uint32_t *__restrict__ keys, int
     const int tid = threadIdx.x;
     uint32_t v[I], place[I];
 #pragma unroll
-    for (int j = 0; j < I; j++) v[j] = keys[(2 * (int64_t)(tid + j * DT) + 1) * n / (2 * S)];
-    if (cell_places<DT, I, S, 2 * DT>(v, (uint32_t)tid, DT, (uint32_t)S, CELLS_EVEN, sh, place)) {
+    for (int j = 0; j < I; j++) v[j] = keys[sample_at<S>((uint32_t)(tid + j * DT), (uint32_t)n)];
+    if (!cell_places<DT, I, S, 2 * DT>(v, (uint32_t)tid, DT, (uint32_t)S, CELLS_EVEN, sh, place)) {
+        __syncthreads();
+        bitonic_block<I>(v, sh.key);
         each<I>([&](auto J) {
             constexpr int j = J;
-            if (place[j] % (S / NB) == 0 && place[j] > 0) s_split[place[j] / (S / NB) - 1] = v[j];
+            place[j] = (uint32_t)(j * DT + tid);
         });
-    } else {
-        __syncthreads();
-        const uint32_t x = bitonic_block(v[0], sh.key);
-        if (tid % (DT / NB) == 0 && tid > 0) s_split[tid / (DT / NB) - 1] = x;
     }
+    each<I>([&](auto J) {
+        constexpr int j = J;
+        if (place[j] % (S / NB) == 0 && place[j] > 0) s_split[place[j] / (S / NB) - 1] = v[j];
+    });
     __syncthreads();
+    const uint32_t x = tid < NB - 1 ? s_split[tid] : 0u;
+    const bool raise = tid > 0 && tid < NB - 1 && s_split[tid - 1] == x && (tid == NB - 2 || s_split[tid + 1] != x) &&
+                       x != 0xFFFFFFFFu;
+    __syncthreads();
+    if (raise) s_split[tid] = x + 1;
 }
+
+// Whether bucket b (one of 1 .. NB - 2) holds one depth at most, between its splitters.
+__device__ __forceinline__ bool one_depth(const uint32_t *split, int b) { return split[b] - split[b - 1] <= 1u; }
 
 // Ranks a wave's keys among equal digits, in order: loc[j] is the number of
 // the wave's keys of digit dig(j) before key j among those with ok(j); cnt[]
@@ -445,6 +492,7 @@ __global__ void __launch_bounds__(DT) k_ds_down(const uint32_t *__restrict__ key
             tot += c;
         }
         if (s_nt[tid]) atomicAdd(&ws.ntsum[tid], s_nt[tid]);
+        if (nt && tid > 0 && tid < NB - 1 && one_depth(s_split, tid)) ws.part[tile * NB + tid] = make_uint2(tot, s_nt[tid]);
     }
     const uint32_t boff = scan_block(tot, s_w, &sum);
     if (tid < NB) {
@@ -540,8 +588,9 @@ __device__ __forceinline__ void digits_of(uint32_t lo, uint32_t hi, int *passes,
 
 // The sorted bucket's entries, tile counts and their exclusive prefix
 // from base: element j of a thread is index w (64 ITEMS) + 64 j + lane.
+// Returns the prefix after the last.
 template <int T, int ITEMS>
-__device__ __forceinline__ void write_bucket(const uint32_t (&val)[ITEMS], uint32_t (&cn)[ITEMS], uint32_t m,
+__device__ __forceinline__ uint32_t write_bucket(const uint32_t (&val)[ITEMS], uint32_t (&cn)[ITEMS], uint32_t m,
                                              uint32_t base, uint32_t *s_w, uint32_t *__restrict__ order,
                                              uint32_t *__restrict__ nt_sorted, uint32_t *__restrict__ offsets) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -551,7 +600,7 @@ __device__ __forceinline__ void write_bucket(const uint32_t (&val)[ITEMS], uint3
             constexpr int j = J;
             if (i0 + j * 64 < m) order[i0 + j * 64] = val[j];
         });
-        return;
+        return base;
     }
     uint32_t sum = 0;
     each<ITEMS>([&](auto J) { sum += cn[J]; });
@@ -559,7 +608,11 @@ __device__ __forceinline__ void write_bucket(const uint32_t (&val)[ITEMS], uint3
     __syncthreads();
     if (lane == 63) s_w[w] = sum;
     __syncthreads();
-    for (int k = 0; k < w; k++) base += s_w[k];
+    uint32_t end = base;
+    for (int k = 0; k < T / 64; k++) {
+        end += s_w[k];
+        if (k < w) base += s_w[k];
+    }
     each<ITEMS>([&](auto J) {
         constexpr int j = J;
         const uint32_t inc = wave_prefix(cn[j]);
@@ -571,6 +624,7 @@ __device__ __forceinline__ void write_bucket(const uint32_t (&val)[ITEMS], uint3
         }
         base += last_lane(inc);
     });
+    return end;
 }
 
 // A bucket of m <= T * ITEMS keys (kin, vin: its first; vin NULL: the ids are
@@ -729,12 +783,57 @@ __device__ __attribute__((noinline)) void slow_sort(uint32_t *k0, uint32_t *v0, 
     }
 }
 
+// A bucket of one depth is in order as it stands.  Its block and the blocks of the
+// empty buckets before it (as many as splitters are equal to the depth, so parts are no
+// larger than other buckets) write a part of it each: where a part's prefix starts
+// follows from the tiles' sums.  b: the block's bucket, of one depth; start of vin, order,
+// .. and base: those of the buckets from b on.
+template <int T>
+__device__ __attribute__((noinline)) void share_bucket(DsWs ws, int tiles, int b, const uint32_t *__restrict__ vin,
+                                                       uint32_t *__restrict__ order, uint32_t base,
+                                                       const uint32_t *__restrict__ nt, uint32_t *__restrict__ nt_sorted,
+                                                       uint32_t *__restrict__ offsets, LocalShared<T> &sh) {
+    static_assert(T >= NB && DS_LIGHT <= 256 * 2 * DT && DS_SMALL <= DT * 2 * DT && DEPTH_SORT_MAX <= DT * 4 * DT,
+                  "a splitter and a tile for each thread");
+    constexpr int I = 4;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // the run: its first splitter, and its bucket (the first splitter above the depth)
+    const uint32_t depth = ws.split[b - 1], x = tid < NB - 1 ? ws.split[tid] : 0xFFFFFFFFu;
+    const int first = __syncthreads_count(tid < NB - 1 && x < depth);
+    const int own = __syncthreads_count(tid < NB - 1 && x <= depth);
+    if (own == NB - 1 || ws.split[own] != depth + 1) return;   // (two equal splitters: b is empty)
+    const uint32_t m = ws.total[own], parts = (uint32_t)(own - first), k = (uint32_t)(b - 1 - first);
+    if (m == 0) return;
+    const uint32_t p0 = (uint32_t)((uint64_t)m * k / parts), p1 = (uint32_t)((uint64_t)m * (k + 1) / parts);
+    uint32_t sum = 0, all;
+    if (nt) {   // the tile counts before this part: whole tiles', then those of the tile it starts in
+        const uint2 t = tid < tiles ? ws.part[tid * NB + own] : make_uint2(0u, 0u);
+        const uint32_t at = scan_block<T / 64>(t.x, sh.w, &all);
+        if (at + t.x <= p0) sum = t.y;
+        else if (at <= p0) sh.boff[0] = at;
+        __syncthreads();
+        for (uint32_t i = sh.boff[0] + tid; i < p0; i += T) sum += nt[vin[i]];
+        (void)scan_block<T / 64>(sum, sh.w, &all);
+        base += all;
+    }
+    for (uint32_t i0 = p0; i0 < p1; i0 += I * T) {
+        const uint32_t at = i0 + (uint32_t)(w * (64 * I) + lane);
+        uint32_t val[I], cn[I];
+#pragma unroll
+        for (int j = 0; j < I; j++) val[j] = at + j * 64 < p1 ? vin[at + j * 64] : 0u;
+#pragma unroll
+        for (int j = 0; j < I; j++) cn[j] = nt && at + j * 64 < p1 ? nt[val[j]] : 0u;
+        base = write_bucket<T, I>(val, cn, min(p1 - i0, (uint32_t)(I * T)), base, sh.w, order + i0,
+                                  nt ? nt_sorted + i0 : nullptr, offsets + i0);
+    }
+}
+
 // LDS of a bucket's sort: the cells', or the digit passes' and their reorder buffer.
 template <int T, int ITEMS, int SB>
 struct BucketShared {
     struct Digits {
         LocalShared<T> d;
-        uint32_t buf[T * ITEMS];
+        uint32_t buf[4 * T];
     };
     union {
         CellShared<T, T * ITEMS, SB> cells;
@@ -750,10 +849,11 @@ __device__ __forceinline__ bool bucket_cells(const uint32_t *kin, const uint32_t
     return cell_sort<T, ITEMS, T * MAXI, SB>(kin, vin, m, base, nt, order, nt_sorted, offsets, map, sh.cells);
 }
 
-// One block per bucket: up to DT * DS_ITEMS keys by cells or by digit passes in
-// LDS, more in global memory.
+// One block per bucket: up to T * DS_ITEMS keys by cells, or where cells are too full by
+// digit passes, of up to 4 T keys in LDS and of more in global memory; buckets of one
+// depth as share_bucket says.
 template <int T>
-__global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1,
+__global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, int tiles, uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1,
                                                  const uint32_t *__restrict__ nt, uint32_t *__restrict__ nt_sorted,
                                                  uint32_t *__restrict__ offsets, uint32_t *__restrict__ n_keys) {
     constexpr int I = DS_ITEMS, SB = 4 * T;
@@ -762,6 +862,7 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, uint32_t *k0, uint32
         uint32_t a[T / 64], b[T / 64], c[T / 64];
     } pl;
     const int tid = threadIdx.x, b = (int)blockIdx.x;
+    const bool one = b > 0 && b < NB - 1 && one_depth(ws.split, b);
     // this bucket's place: the totals and the tile-count sums before it
     uint32_t first = 0, pre = 0, all = 0;
     if (tid < NB) {
@@ -796,6 +897,10 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, uint32_t *k0, uint32
     const uint32_t m = ws.total[b];
     const uint32_t *kin = k1 + start, *vin = v1 + start;
     uint32_t *o = v0 + start, *ns = nt ? nt_sorted + start : nullptr, *off = offsets + start;
+    if (one) {
+        share_bucket<T>(ws, tiles, b, vin, o, base, nt, ns, off, sh.digits.d);
+        return;
+    }
     if (m == 0) return;
     const CellMap map = b == 0 ? CELLS_FROM_HI : b == NB - 1 ? CELLS_FROM_LO : CELLS_EVEN;
     bool done = false;
@@ -806,7 +911,6 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, uint32_t *k0, uint32
     if (done) return;
     __syncthreads();
     if (m <= 4 * T) local_sort<T, 4>(kin, vin, m, base, nt, o, ns, off, sh.digits.d, sh.digits.buf);
-    else if (m <= I * T) local_sort<T, I>(kin, vin, m, base, nt, o, ns, off, sh.digits.d, sh.digits.buf);
     else slow_sort<T>(k0, v0, k1, v1, start, m, base, nt, nt_sorted, offsets, sh.digits.d);
 }
 
@@ -832,14 +936,14 @@ __global__ void __launch_bounds__(DT) k_ds_one(const uint32_t *__restrict__ keys
 template <int R, int S, int T>
 void ds_run(const uint32_t *keys, int64_t n, uint32_t *const dkeys[2], uint32_t *const dvals[2], const uint32_t *nt,
             uint32_t *nt_sorted, uint32_t *offsets, uint32_t *n_keys, void *wsp, hipStream_t s) {
-    const DsWs ws = ds_ws(wsp);
     const int64_t tiles = (n + DT * R - 1) / (DT * R);
+    const DsWs ws = ds_ws(wsp, tiles);
     const int rows = tiles <= DS_ROWS ? 1 : 0;
     const dim3 tg((unsigned)tiles), block(DT);
     hipLaunchKernelGGL((k_ds_up<R, S>), tg, block, 0, s, keys, n, ws, tiles, rows);
     if (!rows) hipLaunchKernelGGL(k_ds_scan, dim3(NB), dim3(256), 0, s, ws, tiles);
     hipLaunchKernelGGL((k_ds_down<R>), tg, block, 0, s, keys, nt, n, ws, tiles, rows, dkeys[1], dvals[1]);
-    hipLaunchKernelGGL((k_ds_local<T>), dim3(NB), dim3(T), 0, s, ws, dkeys[0], dvals[0], dkeys[1], dvals[1], nt, nt_sorted,
+    hipLaunchKernelGGL((k_ds_local<T>), dim3(NB), dim3(T), 0, s, ws, (int)tiles, dkeys[0], dvals[0], dkeys[1], dvals[1], nt, nt_sorted,
                        offsets, n_keys);
 }
 
@@ -847,7 +951,7 @@ void ds_run(const uint32_t *keys, int64_t n, uint32_t *const dkeys[2], uint32_t 
 
 size_t depth_sort_bytes(int64_t cap) {
     if (cap > DEPTH_SORT_MAX) cap = DEPTH_SORT_MAX;
-    return (size_t)(3 * NB + (cap + 2 * DT - 1) / (2 * DT) * NB) * 4;   // counts per tile of 2048 keys
+    return (size_t)(3 * NB + (cap + 2 * DT - 1) / (2 * DT) * NB * 3) * 4;   // three words a bucket and tile of 2048 keys
 }
 
 int depth_sort(const uint32_t *depth_key, int64_t n, uint32_t *const dkeys[2], uint32_t *const dvals[2],

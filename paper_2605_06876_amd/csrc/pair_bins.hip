@@ -73,9 +73,11 @@ __device__ __forceinline__ uint64_t last_lane2(uint64_t v) {
     return ((uint64_t)last_lane((uint32_t)(v >> 32)) << 32) | last_lane((uint32_t)v);
 }
 __device__ __forceinline__ uint64_t wave_sum(uint64_t v) { return last_lane2(wave_prefix2(v)); }
+// The same of saturated sums: the bins in two parts of 16 bits, whose sums do not carry.
 __device__ __forceinline__ uint64_t wave_sum_sat(uint64_t v) {
-    for (int o = 32; o > 0; o >>= 1) v = sat_add(v, __shfl_xor(v, o, 64));
-    return v;
+    const uint32_t b = (uint32_t)(v >> 32);
+    const uint64_t bins = ((uint64_t)last_lane(wave_prefix(b >> 16)) << 16) + last_lane(wave_prefix(b & 0xFFFFu));
+    return bins >> 32 ? ~0ull : (bins << 32) | last_lane(wave_prefix((uint32_t)v));
 }
 // The waves' sums added (every thread gets it); s of PB_THREADS / 64 words.
 __device__ __forceinline__ uint64_t block_sum(uint64_t wave, uint64_t *s) {
