@@ -356,6 +356,39 @@ __device__ __forceinline__ void count(uint32_t &n, uint64_t m) {
     __asm__("v_addc_co_u32_e64 %0, vcc, 0, %0, %1" : "+v"(n) : "s"(m) : "vcc");
 }
 
+// Colours that are not finite.  The forward's loop adds zero times the colour for
+// every record that a pixel does not take, which would be NaN, so such records are staged
+// with zero for the channel; after the loop the pixels that took one get it.  A pixel took
+// every record up to its last contributor that it meets.
+__device__ __forceinline__ bool odd_colour(const float4 &c) {
+    return !(fabsf(c.x) + fabsf(c.y) + fabsf(c.z) < __builtin_inff());
+}
+__device__ __forceinline__ bool is_finite(float c) { return fabsf(c) < __builtin_inff(); }
+__device__ __forceinline__ float finite_or_zero(float c) { return is_finite(c) ? c : 0.f; }
+
+__device__ void add_odd_colours(const uint32_t *__restrict__ vals, const BlendRec *__restrict__ rec,
+                                const short4 *__restrict__ box, uint32_t start, uint32_t end, int ox, int oy, float px,
+                                float py, uint32_t pbits, int64_t last, float &C0, float &C1, float &C2) {
+    const int lane = threadIdx.x & 63;
+    for (uint32_t i0 = start; i0 < end; i0 += 64) {
+        const uint32_t id = i0 + lane < end ? vals[i0 + lane] : 0u;
+        const bool odd = i0 + lane < end && box_meets_tile(box[id], ox, oy) && odd_colour(rec[id].rgb);
+        for (uint64_t m = __builtin_amdgcn_ballot_w64(odd); m; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            Fetched f;
+            f.id = (uint32_t)__builtin_amdgcn_readlane((int)id, l);
+            f.b = box[f.id];
+            f.r = rec[f.id];
+            const StagedRec r = make_staged(f, ox, oy);
+            const float alpha = fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(blend_exponent(r.mc.x - px, r.mc.y - py, r.mc, r.cc)));
+            if ((int64_t)i0 + l > last || (__float_as_uint(r.ex.y) & pbits) != pbits || !(alpha >= ALPHA_MIN)) continue;
+            if (!is_finite(r.cc.z)) C0 += r.cc.z;
+            if (!is_finite(r.cc.w)) C1 += r.cc.w;
+            if (!is_finite(r.ex.x)) C2 += r.ex.x;
+        }
+    }
+}
+
 // Forward dispatch slots (k_tile_order): a tile id, or ORDER_NONE for a slot
 // without a tile (slots grouped by bin of 32 past the image edge).
 constexpr uint32_t ORDER_NONE = 0xFFFFFFFFu;
@@ -389,6 +422,7 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
         zero4[i] = make_uint4(0u, 0u, 0u, 0u);
     __shared__ BlendShared<BATCH> sh;
     __shared__ uint32_t s_next;
+    __shared__ int s_odd;   // a record of this tile so far has a colour that is not finite
     __shared__ unsigned long long s_emin[AS_BLOCK / 64], s_emax[AS_BLOCK / 64];
     __shared__ uint32_t s_nc[AS_BLOCK / 64], s_hi[AS_BLOCK / 64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -414,6 +448,7 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
         int32_t dom = -1;
         uint32_t last = 0, nc = 0;
         int done = inside ? 0 : 1;
+        if (tid == 0) s_odd = 0;
         // checkpoint slots of this pixel: (T, colour composited so far) in
         // front of list entries seg, 2 seg, .. (nck of them); the epilogue
         // turns the colour into the colour behind the boundary.  When a fourth
@@ -434,7 +469,13 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
                 if (b0 + t < end) {
                     uint32_t bm = 0u;   // a record whose box misses the tile is not staged
                     if (nf[k].live) {
-                        const StagedRec sr = make_staged(nf[k], ox, oy);
+                        StagedRec sr = make_staged(nf[k], ox, oy);
+                        if (odd_colour(nf[k].r.rgb)) {
+                            sr.cc.z = finite_or_zero(sr.cc.z);
+                            sr.cc.w = finite_or_zero(sr.cc.w);
+                            sr.ex.x = finite_or_zero(sr.ex.x);
+                            s_odd = 1;
+                        }
                         bm = block_mask(sr, ellipse != 0);
                         sh.rec[t] = sr;
                     }
@@ -537,6 +578,7 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
             }
             if (loff != 0xFFFFFFFFu) last = b0 + loff / REC_BYTES;
         }
+        if (s_odd) add_odd_colours(vals, rec, box, start, end, ox, oy, px, py, lg.pbits, nc ? (int64_t)last : -1, C0, C1, C2);
 
         const float *gt = gts.p[v];
         double e = 0.0;
