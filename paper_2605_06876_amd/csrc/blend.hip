@@ -327,7 +327,12 @@ __device__ __forceinline__ bool next_tile(uint32_t *queue, int n_tiles, int iter
 // starts fine and doubles as a list goes on.  From 256 from the start to this: 2,000
 // Gaussians at 128x128 53 -> 28 us, 20,000 at 640x480 88 -> 74 (the forward
 // 46 -> 49).  Above, the items' own cost shows: 801x603 (1938 tiles) 102 -> 105,
-// 1256x828 190 -> 206.
+// 1256x828 190 -> 206.  It starts with CK_COARSE there and doubles up to the forward's
+// batch depth: deeper batches are chosen for long lists, whose last segment would
+// take the longest (1256x828, 500,000 Gaussians of opacity 0.05, all lists walked to
+// the end, us in segments of 256 / as wide as the batch / doubling up to that: depth 512
+// 761 / 514 / 508, depth 1024 766 / 603 / 518; of opacity 0.5, four times the pairs: 182 / 206 / 183,
+// 186 / 217 / 183).
 constexpr uint32_t CK_FINE = 64, CK_COARSE = 256;
 constexpr int CK_TILES = 1536;
 
@@ -452,7 +457,7 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
         // checkpoint slots of this pixel: (T, colour composited so far) in
         // front of list entries seg, 2 seg, .. (nck of them); the epilogue
         // turns the colour into the colour behind the boundary.  When a fourth
-        // comes up and seg is below CK_COARSE, it doubles: the second becomes
+        // comes up and seg is below BATCH, it doubles: the second becomes
         // the first, the fourth the second.
         float4 *ck = ckpt ? ckpt + (size_t)tile * AS_CK_MAX * 256 + lg.ly * 16 + lg.lx : nullptr;
         uint32_t nck = 0, seg = ck_first, next_ck = ckpt ? ck_first : 0xFFFFFFFFu;
@@ -499,7 +504,7 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
                     }
                     if (inside) ck[nck * 256] = make_float4(T, C0, C1, C2);
                     nck++;
-                    next_ck = nck == AS_CK_MAX && seg >= CK_COARSE ? 0xFFFFFFFFu : next_ck + seg;
+                    next_ck = nck == AS_CK_MAX && seg >= BATCH ? 0xFFFFFFFFu : next_ck + seg;
                 }
                 const uint32_t from = at - rel, to = min(next_ck, rel_end);
                 at = to;
