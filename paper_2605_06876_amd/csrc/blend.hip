@@ -371,10 +371,11 @@ __device__ __forceinline__ bool odd_colour(const float4 &c) {
 __device__ __forceinline__ bool is_finite(float c) { return fabsf(c) < __builtin_inff(); }
 __device__ __forceinline__ float finite_or_zero(float c) { return is_finite(c) ? c : 0.f; }
 
-__device__ void add_odd_colours(const uint32_t *__restrict__ vals, const BlendRec *__restrict__ rec,
+__device__ __attribute__((noinline)) float3 odd_colours(const uint32_t *__restrict__ vals, const BlendRec *__restrict__ rec,
                                 const short4 *__restrict__ box, uint32_t start, uint32_t end, int ox, int oy, float px,
-                                float py, uint32_t pbits, int64_t last, float &C0, float &C1, float &C2) {
+                                float py, uint32_t pbits, int64_t last) {
     const int lane = threadIdx.x & 63;
+    float3 sum = make_float3(0.f, 0.f, 0.f);
     for (uint32_t i0 = start; i0 < end; i0 += 64) {
         const uint32_t id = i0 + lane < end ? vals[i0 + lane] : 0u;
         const bool odd = i0 + lane < end && box_meets_tile(box[id], ox, oy) && odd_colour(rec[id].rgb);
@@ -387,11 +388,12 @@ __device__ void add_odd_colours(const uint32_t *__restrict__ vals, const BlendRe
             const StagedRec r = make_staged(f, ox, oy);
             const float alpha = fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(blend_exponent(r.mc.x - px, r.mc.y - py, r.mc, r.cc)));
             if ((int64_t)i0 + l > last || (__float_as_uint(r.ex.y) & pbits) != pbits || !(alpha >= ALPHA_MIN)) continue;
-            if (!is_finite(r.cc.z)) C0 += r.cc.z;
-            if (!is_finite(r.cc.w)) C1 += r.cc.w;
-            if (!is_finite(r.ex.x)) C2 += r.ex.x;
+            if (!is_finite(r.cc.z)) sum.x += r.cc.z;
+            if (!is_finite(r.cc.w)) sum.y += r.cc.w;
+            if (!is_finite(r.ex.x)) sum.z += r.ex.x;
         }
     }
+    return sum;
 }
 
 // Forward dispatch slots (k_tile_order): a tile id, or ORDER_NONE for a slot
@@ -583,7 +585,12 @@ __global__ void __launch_bounds__(AS_BLOCK, 5) k_blend_fwd(const uint32_t *__res
             }
             if (loff != 0xFFFFFFFFu) last = b0 + loff / REC_BYTES;
         }
-        if (s_odd) add_odd_colours(vals, rec, box, start, end, ox, oy, px, py, lg.pbits, nc ? (int64_t)last : -1, C0, C1, C2);
+        if (s_odd) {
+            const float3 c = odd_colours(vals, rec, box, start, end, ox, oy, px, py, lg.pbits, nc ? (int64_t)last : -1);
+            C0 += c.x;
+            C1 += c.y;
+            C2 += c.z;
+        }
 
         const float *gt = gts.p[v];
         double e = 0.0;
