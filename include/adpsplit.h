@@ -514,7 +514,8 @@ as_status as_reset_opacity(as_ctx *ctx, as_gaussians_mut *g, double max_opacity,
  * Python package measures them on the caller's workload). */
 typedef struct {
     int32_t lds_batch;       /* Gaussian records staged per LDS batch by the blend kernels: 256, 512 or 1024 */
-    int32_t longest_first;   /* nonzero: tiles are dispatched in descending order of list length */
+    int32_t longest_first;   /* nonzero: tiles are dispatched in descending order of list length (the forward's
+                                as they come where all of them run at once anyway) */
     int32_t persistent;      /* nonzero: the blend kernels run as one resident grid pulling tiles from a queue */
     int32_t radix_bits;      /* digit width aimed at by the (tile, entry) pair sort, 4..8: the key's
                                 bits are spread evenly over bits / width passes, to the nearest

@@ -740,6 +740,7 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
             launch_emit_sorted(n, order, vt, f->box, f->nt_sorted, f->offsets, f->key_cap, f->keys[0], f->vals[0],
                                f->n_keys, report, f->ranges, tiles, s);
     }
+    const BlendLaunch bl{ctx->lds_batch, ctx->persistent, ctx->n_cu, ctx->block_cull};
     int sel;
     bool fwd_order;
     {
@@ -761,10 +762,9 @@ as_status as_render_batch(as_ctx *ctx, const as_gaussians *scenes, const as_came
         }
         f->sorted_sel = sel;
         f->use_order = ctx->longest_first;
-        fwd_order = f->use_order && (tiles > ORDER_TILES || n > ORDER_ENTRIES);
+        fwd_order = f->use_order && forward_order(bl, tiles, n);
         if (fwd_order) launch_tile_order(f, vt, s);
     }
-    const BlendLaunch bl{ctx->lds_batch, ctx->persistent, ctx->n_cu, ctx->block_cull};
     {
         StageTimer t(ctx, AS_STAGE_BLEND_FWD, s);
         f->ck_written = f->ckpt != nullptr;

@@ -1271,6 +1271,21 @@ void launch_debug_alpha(const as_frame *f, int64_t n, const int32_t *pix, const 
                        reinterpret_cast<const short4 *>(f->box), n, pix, ent, out);
 }
 
+// Where every block of the forward starts at once the order's launch (3 us and a
+// gap) buys nothing, up to some entries, from which on it still spreads the long lists over
+// the CUs.  640x480 (1200 tiles), five blocks of a batch of 256 on each of 256 CUs, us
+// ordered / as they come: 20,000 entries 83 / 79, 100,000 146.5 / 141.5, 400,000
+// 198 / 200.5, bins of 32 86 / 80, 165 / 161, 207 / 214; three blocks of a batch of
+// 512 a CU, in less than two rounds: 102.3 / 100.1, 138.0 / 131.7.  A batch of 1024 leaves room for
+// one: 20,000 entries 122.7 / 125.9, 100,000 169.6 / 183.5, and 480x320 (600 tiles)
+// 112.3 / 131.0, 141.5 / 172.2, but 320x240 (300) 98.3 / 95.4.  A persistent grid's queue
+// gains from the order from fewer tiles on: batch 512, 640x480 112.1 / 115.2, 480x320 119.5 / 119.1.
+bool forward_order(const BlendLaunch &bl, int64_t tiles, int64_t entries) {
+    constexpr int64_t ENTRIES = 1 << 17;
+    const int64_t per_cu = bl.batch >= 1024 ? 2 : bl.batch >= 512 && bl.persistent ? 3 : 5;
+    return tiles > per_cu * bl.n_cu || entries > ENTRIES;
+}
+
 size_t order_table_words(int64_t tiles) {
     return (size_t)((tiles + ORDER_BLOCK - 1) / ORDER_BLOCK) * ORDER_NC_WORK;
 }

@@ -317,14 +317,8 @@ struct BlendLaunch {
     int n_cu;
     int ellipse;       // 1: per-block culling by the alpha >= 1/255 ellipse, not only the box
 };
-// The forward blend's LDS depth for a launch (256, 512 or 1024 records).
-// Renders of up to ORDER_TILES tiles and ORDER_ENTRIES entries are dispatched as
-// they come: five blocks of the forward fit on each of 256 CUs, so all of them
-// start together and the order's launch (3 us and a gap) buys nothing.  With more
-// entries it still spreads the long lists over the CUs.  640x480, us ordered / as they
-// come: 20,000 entries 83 / 79, 100,000 146.5 / 141.5, 400,000 198 / 200.5, bins
-// of 32 86 / 80, 165 / 161, 207 / 214.
-constexpr int64_t ORDER_TILES = 1280, ORDER_ENTRIES = 1 << 17;
+// Whether a forward asked for longest lists first is dispatched in that order.
+bool forward_order(const BlendLaunch &bl, int64_t tiles, int64_t entries);
 size_t order_table_words(int64_t tiles);
 void launch_tile_order(const as_frame *f, const ViewTable &vt, hipStream_t s);
 // After the forward blend of a render with targets: the views' error ranges.
