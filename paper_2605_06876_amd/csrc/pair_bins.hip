@@ -40,6 +40,11 @@ constexpr int PB_WAVES = 4;                       // waves of a block of count a
 constexpr int PB_BATCH = 6;                       // rounds of 64 pairs of a wave (place and count, 82.8M pairs / 0.6M: 236 / 12.5 us; 4: 246 / 11.7, 8: 238 / 13.4)
 constexpr int PB_SLICE = 64 * PB_BATCH;
 constexpr int PB_ITEM = PB_WAVES * PB_SLICE;      // pairs of a work item
+// Items of a list are summed in groups as well, so that an item that looks up what
+// the list holds before it reads a few sums however long the list is: 8M entries in two
+// lists, counting and placing 168 us by items alone, 127 like this (spread over all lists 83);
+// 8M in four lists around one point 197, 145.
+constexpr uint32_t PB_GROUP = 64;
 // Most blocks of count and of place, which loop over the items.  The placing's items
 // are uneven and wait for their writes, so it takes many more blocks than
 // are resident: 2048 blocks 245 us at 82.8M pairs, 16384 209.
@@ -313,15 +318,17 @@ __device__ __forceinline__ CoarsePlace coarse_place(const ViewTable &vt, const C
 // each list's start, and each list takes its items' places from a counter (which
 // list gets which is left to chance, and shows in nothing).  An item is
 // (coarse bin, part of its list, list start, list length).  Also clears the
-// bins' counts for the launch that adds them, and the tiles' ranges.
+// bins' counts and the groups' for the launch that adds them, and the tiles' ranges.
 __global__ void __launch_bounds__(1024) k_bins_lists(const uint32_t *__restrict__ keys,
                                                      const uint32_t *__restrict__ n_keys, int64_t key_cap, int cbins,
                                                      uint4 *__restrict__ items, uint32_t *__restrict__ n_items,
                                                      uint32_t *__restrict__ counts, int64_t bins,
+                                                     uint32_t *__restrict__ groups, int64_t group_words,
                                                      uint32_t *__restrict__ ranges, int64_t range_words) {
     __shared__ uint32_t s_at[PB_LISTS + 1], s_item[PB_LISTS + 1];
     const int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x, tn = (int64_t)gridDim.x * 1024;
     for (int64_t i = t0; i < bins; i += tn) counts[i] = 0u;
+    for (int64_t i = t0; i < group_words; i += tn) groups[i] = 0u;
     for (int64_t i = t0; i < range_words; i += tn) ranges[i] = 0u;
     const int w = (int)(threadIdx.x >> 4), sub = (int)(threadIdx.x & 15);
     const int cid = (int)blockIdx.x * PB_LISTS + w;
@@ -339,13 +346,18 @@ __global__ void __launch_bounds__(1024) k_bins_lists(const uint32_t *__restrict_
     for (uint32_t k = sub; k < ni; k += 16) items[at + k] = make_uint4((uint32_t)cid, k, p, m);
 }
 
-// Pairs of each bin in every wave's slice of an item and in the item, and the bins' sums.
+// The first group of the list whose first item is `first`: groups of lists after one
+// another do not overlap (rounding up a first item and down a number of items).
+__device__ __forceinline__ uint32_t first_group(uint32_t first) { return (first + PB_GROUP - 1) / PB_GROUP; }
+
+// Pairs of each bin in every wave's slice of an item, in the item and in its group,
+// and the bins' sums.
 template <int F>
 __global__ void __launch_bounds__(PB_WAVES * 64) k_bins_count(const uint32_t *__restrict__ keys, const ViewTable vt,
                                                               const CoarseBins cb, const uint4 *__restrict__ items,
                                                               const uint32_t *__restrict__ n_items,
                                                               uint32_t *__restrict__ slices, uint32_t *__restrict__ sums,
-                                                              uint32_t *__restrict__ counts) {
+                                                              uint32_t *__restrict__ groups, uint32_t *__restrict__ counts) {
     constexpr int NC = F * F;
     __shared__ uint32_t s_c[2][PB_WAVES][4][4];   // per wave and row of 16 lanes: 16 counts of a byte
     static_assert(PB_BATCH * 16 < 256 && PB_BATCH < 16, "counts of a lane in four bits, of a row in eight");
@@ -384,6 +396,9 @@ __global__ void __launch_bounds__(PB_WAVES * 64) k_bins_count(const uint32_t *__
             for (int o = NC; o < PB_WAVES * NC; o *= 2) t += (uint32_t)__shfl_xor((int)t, o, 64);
             if (sw == 0) {
                 sums[(size_t)it * NC + k] = t;
+                // (the groups that are whole; the items of a list's last few are read one by one)
+                const uint32_t g = item.y / PB_GROUP;
+                if (t && g < m / (PB_GROUP * PB_ITEM)) atomicAdd(groups + (size_t)(first_group(it - item.y) + g) * NC + k, t);
                 const CoarsePlace p = coarse_place(vt, cb, (int)item.x);
                 if (t) atomicAdd(counts + p.bin0 + (k / F) * p.pitch + k % F, t);   // (bins past the border hold no pair)
             }
@@ -401,6 +416,7 @@ __global__ void __launch_bounds__(PB_WAVES * 64) k_bins_place(const uint32_t *__
                                                               const uint32_t *__restrict__ n_items,
                                                               const uint32_t *__restrict__ slices,
                                                               const uint32_t *__restrict__ sums,
+                                                              const uint32_t *__restrict__ groups,
                                                               const uint32_t *__restrict__ starts,
                                                               const uint32_t *__restrict__ counts,
                                                               uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
@@ -424,7 +440,9 @@ __global__ void __launch_bounds__(PB_WAVES * 64) k_bins_place(const uint32_t *__
         const CoarsePlace p = coarse_place(vt, cb, (int)item.x);
         // the pairs of each bin in the list's items before this one
         uint32_t pre = 0;
-        for (uint32_t k = (uint32_t)(tid / NC); k < part; k += G) pre += sums[(size_t)(it - part + k) * NC + tid % NC];
+        const uint32_t first = it - part, gs = part / PB_GROUP;
+        for (uint32_t k = (uint32_t)(tid / NC); k < gs; k += G) pre += groups[(size_t)(first_group(first) + k) * NC + tid % NC];
+        for (uint32_t k = gs * PB_GROUP + (uint32_t)(tid / NC); k < part; k += G) pre += sums[(size_t)(first + k) * NC + tid % NC];
         s_sum[tid / NC][tid % NC] = pre;
         uint32_t own[PB_WAVES], s0 = 0, all = 0;
         const int dx = tid % F, dy = tid / F, bin = p.bin0 + dy * p.pitch + dx;
@@ -484,19 +502,20 @@ __global__ void __launch_bounds__(PB_WAVES * 64) k_bins_place(const uint32_t *__
 }
 
 // The scratch: the items (at most one per coarse bin and one per PB_ITEM pairs),
-// the pairs of each bin by slice and by item, the bins' counts and starts, and
-// the number of items.
+// the pairs of each bin by slice, by item and by group, the bins' counts and starts,
+// and the number of items.
 struct PbWs {
     uint4 *items;
-    uint32_t *slices, *sums, *counts, *starts, *n_items;
+    uint32_t *slices, *sums, *groups, *counts, *starts, *n_items;
 };
+int64_t most_groups(int64_t items) { return items / PB_GROUP + 1; }
 int64_t most_items(int64_t cbins, int64_t key_cap) { return cbins + key_cap / PB_ITEM; }
 PbWs pb_ws(void *ws, const CoarseBins &cb, int64_t key_cap, int64_t bins) {
     const int64_t ni = most_items(cb.bins, key_cap), nc = (int64_t)1 << (2 * cb.shift);
     uint4 *items = reinterpret_cast<uint4 *>(ws);
     uint32_t *p = reinterpret_cast<uint32_t *>(items + ni);
-    uint32_t *sums = p + ni * PB_WAVES * nc, *counts = sums + ni * nc;
-    return PbWs{items, p, sums, counts, counts + bins, counts + 2 * bins};
+    uint32_t *sums = p + ni * PB_WAVES * nc, *groups = sums + ni * nc, *counts = groups + most_groups(ni) * nc;
+    return PbWs{items, p, sums, groups, counts, counts + bins, counts + 2 * bins};
 }
 
 int64_t fill_coarse(const ViewTable &vt, int shift, CoarseBins *cb) {
@@ -537,9 +556,10 @@ size_t pairs_tmp_bytes(int64_t n) {
 
 size_t coarse_bins_bytes(int64_t tiles, int64_t key_cap) {
     // Bins are at most the tiles, and coarse_bins() takes at most two bins'
-    // worth of slots per bin; per item and slot PB_WAVES + 1 words.
-    const int64_t per_item = 4 + (PB_WAVES + 1) * 16;
-    return (size_t)(tiles * (4 + 2 * (PB_WAVES + 1) + 2) + key_cap / PB_ITEM * per_item + 1) * 4 + 256;
+    // worth of slots per bin; per item and slot PB_WAVES + 1 words, and one per group.
+    static_assert(16 <= PB_GROUP, "at most a word of the groups per item");
+    const int64_t per_item = 4 + (PB_WAVES + 1) * 16 + 1;
+    return (size_t)(tiles * (4 + 2 * (PB_WAVES + 1) + 1 + 2) + key_cap / PB_ITEM * per_item + 16 + 1) * 4 + 256;
 }
 
 // Two launches more than the one-level path, against the pairs' traffic
@@ -582,18 +602,21 @@ void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_ca
     const dim3 grid((unsigned)(most < PB_GRID_COUNT ? most : PB_GRID_COUNT)), block(PB_WAVES * 64);
     const dim3 wide((unsigned)(most < PB_GRID_PLACE ? most : PB_GRID_PLACE));
     hipLaunchKernelGGL(k_bins_lists, dim3((unsigned)(cb.bins + PB_LISTS - 1) / PB_LISTS), dim3(1024), 0, s, ckeys, n_keys,
-                       key_cap, cb.bins, p.items, p.n_items, p.counts, bins, ranges, 2 * n_tiles);
+                       key_cap, cb.bins, p.items, p.n_items, p.counts, bins, p.groups,
+                       most_groups(most) << (2 * cb.shift), ranges, 2 * n_tiles);
     if (cb.shift == 2)
-        hipLaunchKernelGGL(k_bins_count<4>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.counts);
+        hipLaunchKernelGGL(k_bins_count<4>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.groups,
+                           p.counts);
     else
-        hipLaunchKernelGGL(k_bins_count<2>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.counts);
+        hipLaunchKernelGGL(k_bins_count<2>, grid, block, 0, s, ckeys, vt, cb, p.items, p.n_items, p.slices, p.sums, p.groups,
+                           p.counts);
     scan_u32(p.counts, p.starts, bins, nullptr, tmp, s);
     if (cb.shift == 2)
         hipLaunchKernelGGL(k_bins_place<4>, wide, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
-                           p.starts, p.counts, keys, vals, ranges);
+                           p.groups, p.starts, p.counts, keys, vals, ranges);
     else
         hipLaunchKernelGGL(k_bins_place<2>, wide, block, 0, s, ckeys, cvals, vt, cb, p.items, p.n_items, p.slices, p.sums,
-                           p.starts, p.counts, keys, vals, ranges);
+                           p.groups, p.starts, p.counts, keys, vals, ranges);
 }
 
 AS_WARM_KERNEL(pair_bins)
