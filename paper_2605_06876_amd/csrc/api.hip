@@ -106,19 +106,20 @@ hipError_t dmalloc(T **p, size_t count) {
 }
 
 // scratch slots of ctx->tr (the optimisation loop's calls)
-enum { TR_PART, TR_FLAG, TR_SCAN, TR_TMP, TR_DUP, TR_DSCAN, TR_TOT, TR_TMP2 };
+enum { TR_PART, TR_FLAG, TR_SCAN, TR_TMP, TR_DUP, TR_DSCAN, TR_TOT, TR_COUNT };
+
+static_assert(sizeof(as_ctx::tr) == TR_COUNT * sizeof(DevBuf), "a buffer for each slot");
 
 // Bytes of the loop's Gaussian-sized slots for up to n rows (TR_PART and
 // TR_TOT are fixed and allocated with the context).
-void tr_need(int64_t n, size_t need[8]) {
+void tr_need(int64_t n, size_t need[TR_COUNT]) {
     const size_t m = (size_t)(n > 0 ? n : 1);
-    for (int k = 0; k < 8; k++) need[k] = 0;
+    for (int k = 0; k < TR_COUNT; k++) need[k] = 0;
     need[TR_FLAG] = m;
     need[TR_DUP] = m;
     need[TR_SCAN] = m * 8;
     need[TR_DSCAN] = m * 8;
     need[TR_TMP] = scan_tmp_bytes((int64_t)m);
-    need[TR_TMP2] = scan_tmp_bytes((int64_t)m);
 }
 
 size_t round256(size_t b) { return ((b < 256 ? 256 : b) + 255) & ~(size_t)255; }
@@ -346,9 +347,9 @@ static bool reserve_ok(const as_reserve *r, const char *what) {
 
 static size_t loop_reserve_bytes(int64_t n) {
     if (n <= 0) return 0;
-    size_t need[8], total = 0;
+    size_t need[TR_COUNT], total = 0;
     tr_need(n, need);
-    for (int k = 0; k < 8; k++)
+    for (int k = 0; k < TR_COUNT; k++)
         if (need[k]) total += devbuf_size(need[k]);
     return total;
 }
@@ -362,9 +363,9 @@ as_status as_ctx_reserve(as_ctx *ctx, const as_reserve *r) {
     hipError_t e = errstats_reserve(ctx, nr.max_pixels);
     if (e == hipSuccess) e = split_reserve(ctx, nr);
     if (e == hipSuccess && nr.max_gaussians > 0) {
-        size_t need[8];
+        size_t need[TR_COUNT];
         tr_need(nr.max_gaussians, need);
-        for (int k = 0; k < 8 && e == hipSuccess; k++)
+        for (int k = 0; k < TR_COUNT && e == hipSuccess; k++)
             if (need[k]) e = devbuf_ensure(ctx->tr[k], need[k]);
     }
     if (e != hipSuccess) {

@@ -425,9 +425,7 @@ void launch_ranges(const uint32_t *keys, const uint32_t *n_dev, int64_t cap, int
     hipLaunchKernelGGL(k_ranges, dim3(2048), dim3(256), 0, s, keys, n_dev, cap, n_bins, vt, ranges);
 }
 
-void launch_fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s) { fill_impl<uint8_t>(p, v, n, s); }
 void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) { fill_impl<uint32_t>(p, v, n, s); }
-void launch_fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s) { fill_impl<uint64_t>(p, v, n, s); }
 void launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s) { fill_impl<int64_t>(p, v, n, s); }
 void launch_copy_u32(const uint32_t *src, uint32_t *dst, int64_t n, hipStream_t s) {
     if (n <= 0) return;

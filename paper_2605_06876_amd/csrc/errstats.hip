@@ -40,7 +40,7 @@ void es_need(int64_t P, size_t need[ES_COUNT]) {
     need[ES_LABEL] = p * 4;
     need[ES_MOM] = p * 48;
     need[ES_BASE] = 8;
-    need[ES_KIDX] = ((p + 255) / 256 + ES_MAX_BATCH) * 8;
+    need[ES_KIDX] = ((p + ES_CHUNK - 1) / ES_CHUNK + ES_MAX_BATCH) * 8;
 }
 
 // One view of a call.  Its pixels, 16x16 tiles and chunks of ES_CHUNK pixels
@@ -702,8 +702,8 @@ constexpr size_t ES_NA_PIX = (size_t)AS_NOALLOC_MAX_PIXELS;
 constexpr size_t ES_NA_OFF_LABEL = es_slot(ES_NA_PIX);
 constexpr size_t ES_NA_OFF_MOM = ES_NA_OFF_LABEL + es_slot(ES_NA_PIX * 4);
 constexpr size_t ES_NA_OFF_BASE = ES_NA_OFF_MOM + es_slot(ES_NA_PIX * 48);
-constexpr size_t ES_NA_OFF_KIDX = ES_NA_OFF_BASE + es_slot(ES_NA_PIX);
-constexpr size_t ES_NA_BYTES = ES_NA_OFF_KIDX + es_slot((ES_NA_PIX + 255) / 256 * 8);
+constexpr size_t ES_NA_OFF_KIDX = ES_NA_OFF_BASE + es_slot(8);
+constexpr size_t ES_NA_BYTES = ES_NA_OFF_KIDX + es_slot((ES_NA_PIX + ES_CHUNK - 1) / ES_CHUNK * 8);
 constexpr int ES_NA_MAX_DEVICES = 64;
 
 std::mutex g_na_mutex;

@@ -176,7 +176,7 @@ struct as_ctx {
     DevBuf es[16];    // error-statistics scratch (errstats.hip names the slots)
     DevBuf sp[24];    // adaptive-split scratch (split.hip names the slots)
     DevBuf dbg[6];    // test hooks
-    DevBuf tr[8];     // optimisation-loop scratch (train.hip kernels; slots named in api.hip)
+    DevBuf tr[7];     // optimisation-loop scratch (train.hip kernels; slots named in api.hip)
     as_reserve res{};             // what es, sp and tr hold (as_ctx_reserve)
     int lds_batch = 256;          // launch tuning (as_set_tuning)
     int longest_first = 1;
@@ -304,9 +304,7 @@ void launch_pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, co
 void launch_bins_place(const ViewTable &vt, const CoarseBins &cb, int64_t key_cap, const uint32_t *ckeys,
                        const uint32_t *cvals, uint32_t *keys, uint32_t *vals, const uint32_t *n_keys, uint32_t *ranges,
                        int64_t n_tiles, void *ws, void *tmp, hipStream_t s);
-void launch_fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s);
 void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
-void launch_fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s);
 void launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s);
 void launch_copy_u32(const uint32_t *src, uint32_t *dst, int64_t n, hipStream_t s);
 
