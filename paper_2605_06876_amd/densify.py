@@ -29,7 +29,7 @@ import torch
 
 from . import api
 
-STAT_PIXELS = 1 << 23   # pixels of one batched error-statistics call (424 MiB of scratch)
+STAT_PIXELS = 1 << 23   # pixels of one batched error-statistics call (424 MiB of scratch, 53 bytes a pixel)
 
 
 class DensifyStep:
@@ -46,10 +46,13 @@ class DensifyStep:
     cand_cap : candidates the split takes at most (default n)
     key_cap_per_entry : pair capacity of the renders per (view, Gaussian); a
                render over it drops the deepest pairs, so it is generous
+    stat_pixels : the error statistics of as many views run together as have no
+               more pixels (a view at least); the context holds 53 bytes of
+               scratch for each of those pixels.  The result does not depend on it.
     """
 
     def __init__(self, ctx, n, deg, method="adpsplit", params=None, views=(), gts=(), regions=None, cand_cap=None,
-                 key_cap_per_entry=32):
+                 key_cap_per_entry=32, stat_pixels=STAT_PIXELS):
         assert method in ("adpsplit", "vanilla")
         self.ctx, self.n, self.deg, self.method = ctx, n, deg, method
         if method == "adpsplit":
@@ -101,10 +104,9 @@ class DensifyStep:
             self.frame = api.BatchFrame.for_views(ctx, n, self.views[:k], key_cap=key_cap_per_entry * n * k,
                                                   auto_grow=False, forward_only=True)
             self.images = [torch.empty(3, H, W, dtype=torch.float32, **dev) for _ in range(k)]
-        # views whose error statistics run together: their scratch is 53 bytes a
-        # pixel, so no more than STAT_PIXELS pixels unless one view alone has more
+        # views whose error statistics run together
         px = max([(v.width * v.height + 3) // 4 * 4 for v in self.views] + [1])
-        self.stat_views = max(1, min(len(self.views), api.MAX_VIEWS, STAT_PIXELS // px))
+        self.stat_views = max(1, min(len(self.views), api.MAX_VIEWS, stat_pixels // px))
         # set-up: the context scratch of every call of the step (none allocates)
         ctx.reserve(max_gaussians=max(self.cap2, 1), max_candidates=self.cc, max_pixels=self.stat_views * px,
                     max_regions=self.regions.capacity, max_views=max(len(self.views), 1))
