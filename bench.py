@@ -188,8 +188,13 @@ def training_step_bench(args):
     K = frame.n_keys()
     if K > key_cap:
         raise RuntimeError("bench: %d pairs exceed the frame's capacity of %d" % (K, key_cap))
+    # pairs of the coarse bins, where the pairs are binned in two levels (frames of this
+    # capacity, unless the pair sort takes one launch a digit)
+    coarse = None
+    if not best["single_pass_sort"] & 2:
+        coarse = int(frame._dev(frame.view().n_keys, 12).view(np.uint32)[2])
     n_regions = int(regions.count.item())
-    return dict(ms=ms, ms_sequential=ms_seq, ms_overlapped=ms_ovl, stages=stages, K=K, n=n, W=W, H=H,
+    return dict(ms=ms, ms_sequential=ms_seq, ms_overlapped=ms_ovl, stages=stages, K=K, coarse=coarse, n=n, W=W, H=H,
                 n_regions=n_regions, steps=args.steps,
                 stage_steps=stage_steps, ctx=ctx,
                 tuning=best, tuning_ms={k: round(v, 4) for k, v in tune_ms.items()})
@@ -577,13 +582,19 @@ KERNEL_SOURCES = {
     "ranges": "binning.hip", "blend_fwd": "blend.hip", "blend_bwd": "blend.hip", "project_bwd": "project_bwd.hip",
     "error_stats": "errstats.hip",
 }
+# further sources of a stage's kernels: the depth order belongs to "sort", two-level
+# binning emits in "emit" and counts and places in "ranges", which also holds the dispatch order
+MORE_SOURCES = {"sort": ("depth_sort.hip",), "emit": ("pair_bins.hip", "pair_count.h"),
+                "ranges": ("pair_bins.hip", "blend.hip")}
 
 
 def source_hash(stage):
     import hashlib
-    path = os.path.join(ROOT, "paper_2605_06876_amd", "csrc", KERNEL_SOURCES[stage])
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in (KERNEL_SOURCES[stage],) + MORE_SOURCES.get(stage, ()):
+        with open(os.path.join(ROOT, "paper_2605_06876_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(stage):
@@ -624,13 +635,20 @@ def main():
     n, W, H, K = res["n"], res["W"], res["H"], res["K"]
     # stage time per step (a stage may record more than one segment per step)
     per_step = {k: v[0] / res["stage_steps"] for k, v in res["stages"].items() if v[1]}
-    # algorithmic work per launch of each stage
+    # algorithmic work per launch of each stage: "sort" is the depth order (a key and an entry
+    # each) and the pairs read and written once, "ranges" what follows the sort
+    tile_bytes = 8 * ((W + 15) // 16) * ((H + 15) // 16)
+    C = res["coarse"]
+    if C is None:
+        emit, pairs, ranges = n * 16 + K * 12, K, K * 8 + tile_bytes
+    else:   # boxes gathered into depth order, coarse pairs emitted and sorted, the bins' pairs placed
+        emit, pairs, ranges = n * 20 + C * 8, C, C * 8 + K * 8 + tile_bytes
     work = {
         "project": ("hbm", n * (sh3_bytes() + 64) / 1e9, "GB"),
         "scan": ("hbm", n * 8 / 1e9, "GB"),
-        "emit": ("hbm", (n * 16 + K * 12) / 1e9, "GB"),
-        "sort": ("hbm", K * 24 / 1e9, "GB"),
-        "ranges": ("hbm", (K * 8 + 8 * ((W + 15) // 16) * ((H + 15) // 16)) / 1e9, "GB"),
+        "emit": ("hbm", emit / 1e9, "GB"),
+        "sort": ("hbm", (n * 8 + pairs * 16) / 1e9, "GB"),
+        "ranges": ("hbm", ranges / 1e9, "GB"),
         "blend_fwd": ("alu", ops_fwd / 1e12, "TOP"),
         "blend_bwd": ("alu", ops_bwd / 1e12, "TOP"),
         "project_bwd": ("hbm", n * (2 * sh3_bytes() + 36 + 4 + 16) / 1e9, "GB"),
@@ -655,7 +673,7 @@ def main():
             all_roofs[k] = dict(ms=round(per_step[k], 4), achieved=round(ach, 2),
                                 unit="GB/s" if b == "hbm" else "TOP/s", frac=round(ach / pk, 4))
     # both blends against the VALU roofline together (the forward stage
-    # includes the single-block post-forward kernel)
+    # includes the error range's kernel, the reverse stage that of its work items)
     blend_roof = None
     if per_step.get("blend_fwd", 0) > 0 and per_step.get("blend_bwd", 0) > 0:
         t_fb = (per_step["blend_fwd"] + per_step["blend_bwd"]) / 1e3

@@ -4,8 +4,10 @@
 // per Gaussian, FP64, struct-of-arrays reads and writes.  A batch of views is
 // one launch: each thread walks the views in order and sums their
 // contributions (a fixed order, so the sum is deterministic), then writes
-// every gradient once; a single view uses a leaner kernel with the same
-// arithmetic.
+// every gradient once.  A single view uses a leaner kernel.  Both follow the
+// same chain in FP64, but the several-view kernel regroups it (contracted
+// multiply-adds, shared reciprocals, one direction gradient of the channels'
+// summed coefficients), so their results differ by FP64 rounding.
 //
 // Chain: colour = max(0, sum_k Y_k(d) sh_k + 1/2) with d = (mu - o_v)/|mu - o_v|;
 // mean2d = (fx tx/tz + cx, fy ty/tz + cy); conic = inverse(J W Sigma W^T J^T
