@@ -859,14 +859,20 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, int tiles, uint32_t 
     constexpr int I = DS_ITEMS, SB = 4 * T;
     __shared__ BucketShared<T, I, SB> sh;
     __shared__ struct {
-        uint32_t a[T / 64], b[T / 64], c[T / 64];
+        uint32_t a[T / 64], b[T / 64], c[T / 64], m, one;
     } pl;
     const int tid = threadIdx.x, b = (int)blockIdx.x;
-    const bool one = b > 0 && b < NB - 1 && one_depth(ws.split, b);
-    // this bucket's place: the totals and the tile-count sums before it
+    // this bucket's place: the totals and the tile-count sums before it; its own keys,
+    // and whether they are of one depth
     uint32_t first = 0, pre = 0, all = 0;
     if (tid < NB) {
         const uint32_t cn = ws.ntsum[tid], tot = ws.total[tid];
+        const bool inner = tid > 0 && tid < NB - 1;
+        const uint32_t lo = inner ? ws.split[tid - 1] : 0u, hi = inner ? ws.split[tid] : 0xFFFFFFFFu;
+        if (tid == b) {
+            pl.m = tot;
+            pl.one = hi - lo <= 1u ? 1u : 0u;   // (as one_depth)
+        }
         if (tid < b) {
             first += tot;
             pre += cn;
@@ -894,10 +900,10 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, int tiles, uint32_t 
     // (uniform: scalar bases for the bucket's addresses)
     const int64_t start = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)first);
     const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)pre);
-    const uint32_t m = ws.total[b];
+    const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)pl.m);
     const uint32_t *kin = k1 + start, *vin = v1 + start;
     uint32_t *o = v0 + start, *ns = nt ? nt_sorted + start : nullptr, *off = offsets + start;
-    if (one) {
+    if (__builtin_amdgcn_readfirstlane((int)pl.one)) {
         share_bucket<T>(ws, tiles, b, vin, o, base, nt, ns, off, sh.digits.d);
         return;
     }
