@@ -369,7 +369,7 @@ as_status as_accumulate_error_stats_batch(as_ctx *ctx, int32_t n_views, const as
 /* For callers that cannot allocate device memory (code under graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): as_accumulate_error_stats
  * with the same arguments, kernels and results, but its scratch in one static
- * device array of the library (54 MiB plus 32 KiB, sized for views of up to
+ * device array of the library (53 MiB and 2,304 bytes, sized for views of up to
  * AS_NOALLOC_MAX_PIXELS pixels) instead of the context's reservation, which it
  * does not need.  Each device the library runs on holds its own copy of that
  * array until the process ends; its address is taken when a context is
