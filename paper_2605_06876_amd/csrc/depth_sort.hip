@@ -32,7 +32,8 @@
 // Depth order, scan and pair sort of 1,048,576 entries (us; in brackets with one
 // block for every bucket, then with the radix sort): spread depths 110 (110, 141), all
 // equal 103 (1467, 132), nine in ten equal 122 (3063, 136), 160 depths 174 (468, 139),
-// two clouds' entries in turn 176 (3919, 141).
+// two clouds' entries in turn 155 (3894, 140), a third of the entries behind the camera
+// 103 (317, 128).
 // Values are the entry ids, so the first scatter reads only keys, straight
 // from the projection's depth keys.
 #include <type_traits>
@@ -68,6 +69,14 @@ DsWs ds_ws(void *ws, int64_t tiles) {
     uint32_t *p = reinterpret_cast<uint32_t *>(ws);
     return DsWs{p, p + NB, p + 2 * NB, p + 3 * NB, reinterpret_cast<uint2 *>(p + 3 * NB + tiles * NB)};
 }
+
+// A depth's key, from the least depth kept (AS_NEAR, rounded to float) on.  The projection
+// keeps nothing nearer or behind, so those entries' order shows in nothing (they touch no
+// tile): they take one key above all others.  With their own bits, which span both
+// signs and all exponents down to zero, they would stretch the range of the buckets
+// at both ends, whose cells then hold too many keys.  (Infinity and NaN stay below CULLED.)
+constexpr uint32_t KEY_LEAST = __builtin_bit_cast(uint32_t, (float)AS_NEAR), CULLED = 0x80000000u - KEY_LEAST;
+__device__ __forceinline__ uint32_t live_key(uint32_t depth_bits) { return min(depth_bits - KEY_LEAST, CULLED); }
 
 // f(0), f(1), .. f(N - 1) with compile-time indices: the per-thread arrays
 // below are then registers from the start (as loops to be unrolled, those of
@@ -124,12 +133,14 @@ __device__ __forceinline__ void block_range(uint32_t mn, uint32_t mx, uint32_t *
 // Placing keys by counting: SB cells divide the keys' range, a key's
 // place is the first of its cell plus its rank in the cell, by (key, index)
 // against the few others there.  The cells are even over the range, or, for
-// the first and the last bucket, which hold the tails of the distribution, of
+// the nearest and the deepest bucket, which hold the tails of the distribution, of
 // widths growing from the range's dense end (CELLS_FROM_HI, CELLS_FROM_LO: SB / 32
 // cells per octave of the distance to it).  No digit passes and no ballots: four barriers
 // apart from the scan of the cells.  Where a cell holds more than CELL_MAX keys
 // (many equal keys, or a range stretched by outliers) nothing is placed
 // and false returned, to the whole block: the caller takes the digit passes.
+// With CULL, keys may be CULLED: those are placed after the others, in any order (a
+// bucket's keys are not: they have one of their own).
 constexpr uint32_t CELL_MAX = 64;
 
 enum CellMap { CELLS_EVEN, CELLS_FROM_HI, CELLS_FROM_LO };
@@ -153,16 +164,17 @@ struct CellShared {
     uint32_t cell[SB + 1];
     uint32_t key[CAP];
     uint16_t idx[CAP];
-    uint32_t w[T / 64], mn[T / 64], mx[T / 64];
+    uint32_t w[T / 64], mn[T / 64], mx[T / 64], culled;
 };
 
 // Element j of thread t is index i0 + stride j (valid below m).
-template <int T, int ITEMS, int CAP, int SB>
+template <int T, int ITEMS, int CAP, int SB, bool CULL>
 __device__ __forceinline__ bool cell_places(const uint32_t (&key)[ITEMS], uint32_t i0, uint32_t stride, uint32_t m,
                                             CellMap map, CellShared<T, CAP, SB> &sh, uint32_t (&place)[ITEMS]) {
     constexpr int PER = SB / T;
     const int tid = threadIdx.x;
-    auto ok = [&](int j) { return i0 + (uint32_t)j * stride < m; };
+    auto valid = [&](int j) { return i0 + (uint32_t)j * stride < m; };
+    auto ok = [&](int j) { return valid(j) && (!CULL || key[j] != CULLED); };
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
     each<ITEMS>([&](auto J) {
         constexpr int j = J;
@@ -173,6 +185,7 @@ __device__ __forceinline__ bool cell_places(const uint32_t (&key)[ITEMS], uint32
     });
 #pragma unroll
     for (int k = 0; k < PER; k++) sh.cell[tid + k * T] = 0u;
+    if (CULL && tid == 0) sh.culled = 0u;
     block_range<T>(lo, hi, sh.mn, sh.mx, &lo, &hi);   // (its barrier: the cells are clear)
     const int bits = hi > lo ? 32 - __clz(hi - lo) : 0;
     const int shift = bits > __builtin_ctz(SB) ? bits - __builtin_ctz(SB) : 0;
@@ -199,6 +212,18 @@ __device__ __forceinline__ bool cell_places(const uint32_t (&key)[ITEMS], uint32
         run += c[k];
     }
     if (tid == T - 1) sh.cell[SB] = run;
+    if (CULL)
+        each<ITEMS>([&](auto J) {   // (all: the keys that are not culled)
+            constexpr int j = J;
+            const bool cull = valid(j) && key[j] == CULLED;
+            const uint64_t bal = __builtin_amdgcn_ballot_w64(cull);
+            if (bal) {
+                uint32_t first = 0;
+                if ((tid & 63) == 0) first = atomicAdd(&sh.culled, (uint32_t)__popcll(bal));
+                first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+                if (cull) place[j] = all + first + (uint32_t)__popcll(bal & lanemask_lt());
+            }
+        });
     __syncthreads();
     each<ITEMS>([&](auto J) {
         constexpr int j = J;
@@ -269,8 +294,9 @@ __device__ __forceinline__ uint32_t sample_at(uint32_t k, uint32_t n) {
     return lo + __umulhi(h, hi - lo);
 }
 
-// NB - 1 splitters from a sample of S keys, into s_split.  The sample is
-// placed by cells, a skewed one (see cell_places) sorted.
+// NB - 1 splitters from a sample of S keys, into s_split: NB - 3 quantiles of it, and
+// the last two around CULLED, which thus has the last bucket but one (the last
+// is empty).  The sample is placed by cells, a skewed one (see cell_places) sorted.
 //
 // Where splitters are equal, a depth holds more than about one in 128 of the
 // entries.  Of a run of equal splitters the last is raised by one: the bucket
@@ -285,8 +311,8 @@ __device__ __forceinline__ void splitters(const uint32_t *__restrict__ keys, int
     const int tid = threadIdx.x;
     uint32_t v[I], place[I];
 #pragma unroll
-    for (int j = 0; j < I; j++) v[j] = keys[sample_at<S>((uint32_t)(tid + j * DT), (uint32_t)n)];
-    if (!cell_places<DT, I, S, 2 * DT>(v, (uint32_t)tid, DT, (uint32_t)S, CELLS_EVEN, sh, place)) {
+    for (int j = 0; j < I; j++) v[j] = live_key(keys[sample_at<S>((uint32_t)(tid + j * DT), (uint32_t)n)]);
+    if (!cell_places<DT, I, S, 2 * DT, true>(v, (uint32_t)tid, DT, (uint32_t)S, CELLS_EVEN, sh, place)) {
         __syncthreads();
         bitonic_block<I>(v, sh.key);
         each<I>([&](auto J) {
@@ -294,14 +320,15 @@ __device__ __forceinline__ void splitters(const uint32_t *__restrict__ keys, int
             place[j] = (uint32_t)(j * DT + tid);
         });
     }
-    each<I>([&](auto J) {
+    each<I>([&](auto J) {   // places k S / (NB - 2), k = 1 .. NB - 3, rounded up
         constexpr int j = J;
-        if (place[j] % (S / NB) == 0 && place[j] > 0) s_split[place[j] / (S / NB) - 1] = v[j];
+        const uint32_t k = place[j] * (NB - 2) / S;
+        if (place[j] > 0 && k != (place[j] - 1) * (NB - 2) / S) s_split[k - 1] = v[j];
     });
+    if (tid < 2) s_split[NB - 3 + tid] = CULLED + (uint32_t)tid;
     __syncthreads();
     const uint32_t x = tid < NB - 1 ? s_split[tid] : 0u;
-    const bool raise = tid > 0 && tid < NB - 1 && s_split[tid - 1] == x && (tid == NB - 2 || s_split[tid + 1] != x) &&
-                       x != 0xFFFFFFFFu;
+    const bool raise = tid > 0 && tid < NB - 3 && s_split[tid - 1] == x && s_split[tid + 1] != x && x < CULLED;
     __syncthreads();
     if (raise) s_split[tid] = x + 1;
 }
@@ -362,7 +389,7 @@ __global__ void __launch_bounds__(DT) k_ds_up(const uint32_t *__restrict__ keys,
 #pragma unroll
     for (int j = 0; j < R; j++) {
         const int64_t i = base + j * DT + tid;
-        key[j] = i < n ? keys[i] : 0u;
+        key[j] = i < n ? live_key(keys[i]) : 0u;
     }
     splitters<S>(keys, n, s_cells, s_split);
     if (tile == 0 && tid < NB - 1) ws.split[tid] = s_split[tid];
@@ -441,7 +468,7 @@ __global__ void __launch_bounds__(DT) k_ds_down(const uint32_t *__restrict__ key
 #pragma unroll
     for (int j = 0; j < R; j++) {
         const int i = w * (64 * R) + j * 64 + lane;
-        key[j] = ok(j) ? keys[base + i] : 0u;
+        key[j] = ok(j) ? live_key(keys[base + i]) : 0u;
         cn[j] = nt && ok(j) ? nt[base + i] : 0u;
     }
     // the tile's offset in each bucket and the bucket totals
@@ -629,7 +656,7 @@ __device__ __forceinline__ uint32_t write_bucket(const uint32_t (&val)[ITEMS], u
 
 // A bucket of m <= T * ITEMS keys (kin, vin: its first; vin NULL: the ids are
 // the positions) placed by cells; false when they are too skewed for that.
-template <int T, int ITEMS, int CAP, int SB>
+template <int T, int ITEMS, int CAP, int SB, bool CULL>
 __device__ __forceinline__ bool cell_sort(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint32_t m,
                                           uint32_t base, const uint32_t *__restrict__ nt, uint32_t *__restrict__ order,
                                           uint32_t *__restrict__ nt_sorted, uint32_t *__restrict__ offsets, CellMap map,
@@ -641,11 +668,11 @@ __device__ __forceinline__ bool cell_sort(const uint32_t *__restrict__ kin, cons
         const uint32_t i = (uint32_t)(tid + j * T);
         key[j] = val[j] = 0u;
         if (i < m) {
-            key[j] = kin[i];
+            key[j] = CULL ? live_key(kin[i]) : kin[i];
             val[j] = vin ? vin[i] : i;
         }
     });
-    if (!cell_places<T, ITEMS, CAP, SB>(key, (uint32_t)tid, T, m, map, sh, place)) return false;
+    if (!cell_places<T, ITEMS, CAP, SB, CULL>(key, (uint32_t)tid, T, m, map, sh, place)) return false;
     // into sorted order through the cells' keys, which are read
     const uint32_t i0 = (uint32_t)(w * (64 * ITEMS) + lane);
     __syncthreads();
@@ -665,7 +692,7 @@ __device__ __forceinline__ bool cell_sort(const uint32_t *__restrict__ kin, cons
 }
 
 // The same by digit passes in registers and LDS, whatever the distribution.
-template <int T, int ITEMS>
+template <int T, int ITEMS, bool RAW = false>
 __device__ __forceinline__ void local_sort(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint32_t m,
                                            uint32_t base, const uint32_t *__restrict__ nt, uint32_t *__restrict__ order,
                                            uint32_t *__restrict__ nt_sorted, uint32_t *__restrict__ offsets,
@@ -678,7 +705,7 @@ __device__ __forceinline__ void local_sort(const uint32_t *__restrict__ kin, con
         const uint32_t i = i0 + j * 64;
         key[j] = val[j] = 0u;
         if (i < m) {
-            key[j] = kin[i];
+            key[j] = RAW ? live_key(kin[i]) : kin[i];
             val[j] = vin ? vin[i] : i;
             mn = min(mn, key[j]);
             mx = max(mx, key[j]);
@@ -801,7 +828,7 @@ __device__ __attribute__((noinline)) void share_bucket(DsWs ws, int tiles, int b
     const uint32_t depth = ws.split[b - 1], x = tid < NB - 1 ? ws.split[tid] : 0xFFFFFFFFu;
     const int first = __syncthreads_count(tid < NB - 1 && x < depth);
     const int own = __syncthreads_count(tid < NB - 1 && x <= depth);
-    if (own == NB - 1 || ws.split[own] != depth + 1) return;   // (two equal splitters: b is empty)
+    if (own == NB - 1 || ws.split[own] != depth + 1) return;   // (b is empty)
     const uint32_t m = ws.total[own], parts = (uint32_t)(own - first), k = (uint32_t)(b - 1 - first);
     if (m == 0) return;
     const uint32_t p0 = (uint32_t)((uint64_t)m * k / parts), p1 = (uint32_t)((uint64_t)m * (k + 1) / parts);
@@ -842,11 +869,11 @@ struct BucketShared {
 };
 
 // A bucket of m <= T * ITEMS keys in one block, by cells if they are even enough.
-template <int T, int ITEMS, int MAXI, int SB>
+template <int T, int ITEMS, int MAXI, int SB, bool CULL = false>
 __device__ __forceinline__ bool bucket_cells(const uint32_t *kin, const uint32_t *vin, uint32_t m, uint32_t base,
                                              const uint32_t *nt, uint32_t *order, uint32_t *nt_sorted,
                                              uint32_t *offsets, CellMap map, BucketShared<T, MAXI, SB> &sh) {
-    return cell_sort<T, ITEMS, T * MAXI, SB>(kin, vin, m, base, nt, order, nt_sorted, offsets, map, sh.cells);
+    return cell_sort<T, ITEMS, T * MAXI, SB, CULL>(kin, vin, m, base, nt, order, nt_sorted, offsets, map, sh.cells);
 }
 
 // One block per bucket: up to T * DS_ITEMS keys by cells, or where cells are too full by
@@ -859,11 +886,11 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, int tiles, uint32_t 
     constexpr int I = DS_ITEMS, SB = 4 * T;
     __shared__ BucketShared<T, I, SB> sh;
     __shared__ struct {
-        uint32_t a[T / 64], b[T / 64], c[T / 64], m, one;
+        uint32_t a[T / 64], b[T / 64], c[T / 64], m, kind;
     } pl;
     const int tid = threadIdx.x, b = (int)blockIdx.x;
-    // this bucket's place: the totals and the tile-count sums before it; its own keys,
-    // and whether they are of one depth
+    // this bucket's place: the totals and the tile-count sums before it; its own keys, and
+    // whether they are of one depth (1) or the deepest (2)
     uint32_t first = 0, pre = 0, all = 0;
     if (tid < NB) {
         const uint32_t cn = ws.ntsum[tid], tot = ws.total[tid];
@@ -871,7 +898,7 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, int tiles, uint32_t 
         const uint32_t lo = inner ? ws.split[tid - 1] : 0u, hi = inner ? ws.split[tid] : 0xFFFFFFFFu;
         if (tid == b) {
             pl.m = tot;
-            pl.one = hi - lo <= 1u ? 1u : 0u;   // (as one_depth)
+            pl.kind = hi - lo <= 1u ? 1u : hi == CULLED ? 2u : 0u;   // (as one_depth)
         }
         if (tid < b) {
             first += tot;
@@ -903,12 +930,13 @@ __global__ void __launch_bounds__(T, 4) k_ds_local(DsWs ws, int tiles, uint32_t 
     const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)pl.m);
     const uint32_t *kin = k1 + start, *vin = v1 + start;
     uint32_t *o = v0 + start, *ns = nt ? nt_sorted + start : nullptr, *off = offsets + start;
-    if (__builtin_amdgcn_readfirstlane((int)pl.one)) {
+    const uint32_t kind = (uint32_t)__builtin_amdgcn_readfirstlane((int)pl.kind);
+    if (kind == 1u) {
         share_bucket<T>(ws, tiles, b, vin, o, base, nt, ns, off, sh.digits.d);
         return;
     }
     if (m == 0) return;
-    const CellMap map = b == 0 ? CELLS_FROM_HI : b == NB - 1 ? CELLS_FROM_LO : CELLS_EVEN;
+    const CellMap map = b == 0 ? CELLS_FROM_HI : kind == 2u ? CELLS_FROM_LO : CELLS_EVEN;
     bool done = false;
     if (m <= T) done = bucket_cells<T, 1, I, SB>(kin, vin, m, base, nt, o, ns, off, map, sh);
     else if (m <= 4 * T) done = bucket_cells<T, 4, I, SB>(kin, vin, m, base, nt, o, ns, off, map, sh);
@@ -928,12 +956,12 @@ __global__ void __launch_bounds__(DT) k_ds_one(const uint32_t *__restrict__ keys
     constexpr int T = DT, SB = 4 * DT, I = (int)(DS_ONE / DT);
     __shared__ BucketShared<T, I, SB> sh;
     bool done;
-    if (n <= T) done = bucket_cells<T, 1, I, SB>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, CELLS_EVEN, sh);
-    else if (n <= 2 * T) done = bucket_cells<T, 2, I, SB>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, CELLS_EVEN, sh);
-    else done = bucket_cells<T, I, I, SB>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, CELLS_EVEN, sh);
+    if (n <= T) done = bucket_cells<T, 1, I, SB, true>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, CELLS_EVEN, sh);
+    else if (n <= 2 * T) done = bucket_cells<T, 2, I, SB, true>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, CELLS_EVEN, sh);
+    else done = bucket_cells<T, I, I, SB, true>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, CELLS_EVEN, sh);
     if (!done) {
         __syncthreads();
-        local_sort<T, I>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, sh.digits.d, sh.digits.buf);
+        local_sort<T, I, true>(keys, nullptr, n, 0u, nt, order, nt_sorted, offsets, sh.digits.d, sh.digits.buf);
     }
     __syncthreads();
     if (threadIdx.x == 0 && nt) *n_keys = offsets[n - 1] + nt_sorted[n - 1];   // the last entry's end

@@ -84,12 +84,19 @@ __device__ __forceinline__ uint64_t wave_sum_sat(uint64_t v) {
     const uint64_t bins = ((uint64_t)last_lane(wave_prefix(b >> 16)) << 16) + last_lane(wave_prefix(b & 0xFFFFu));
     return bins >> 32 ? ~0ull : (bins << 32) | last_lane(wave_prefix((uint32_t)v));
 }
+// Counts added: with SAT saturating, else of a render whose entries could touch all bins
+// of their views without the sum reaching 2^32 (1M entries, 1040 bins: 10.3 us, 11.0 saturating).
+template <bool SAT>
+__device__ __forceinline__ uint64_t add(uint64_t a, uint64_t b) {
+    return SAT ? sat_add(a, b) : a + b;
+}
 // The waves' sums added (every thread gets it); s of PB_THREADS / 64 words.
+template <bool SAT>
 __device__ __forceinline__ uint64_t block_sum(uint64_t wave, uint64_t *s) {
     if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = wave;
     __syncthreads();
     uint64_t t = 0;
-    for (int k = 0; k < PB_THREADS / 64; k++) t = sat_add(t, s[k]);
+    for (int k = 0; k < PB_THREADS / 64; k++) t = add<SAT>(t, s[k]);
     __syncthreads();
     return t;
 }
@@ -156,7 +163,7 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_sum(int64_t n, const uint3
             sum += rect_counts(bin_rect(b[j].x, b[j].y, bs), cs);
         }
     }
-    sum = block_sum(wave_sum(sum), s_w);
+    sum = block_sum<true>(wave_sum(sum), s_w);
     if (threadIdx.x == 0) partials[blockIdx.x] = sum;
 }
 
@@ -164,7 +171,7 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_sum(int64_t n, const uint3
 // Most entries touch one to four coarse bins, so each lane writes the first
 // PB_OWN pairs of its own rank (a wave's stores of one step lie within a few
 // lines), and the wave together what a larger entry has beyond them.
-template <int R>
+template <int R, bool SAT>
 __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint32_t *__restrict__ order,
                                                            const ViewTable vt, const CoarseBins cb,
                                                            const uint32_t *__restrict__ box_lo,
@@ -199,8 +206,8 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
     if (scanned) {
         pre = partials[blockIdx.x];
     } else {
-        for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += PB_THREADS) pre = sat_add(pre, partials[b]);
-        pre = block_sum(wave_sum_sat(pre), s_w);
+        for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += PB_THREADS) pre = add<SAT>(pre, partials[b]);
+        pre = block_sum<SAT>(SAT ? wave_sum_sat(pre) : wave_sum(pre), s_w);
     }
     sum = wave_sum(sum);
     if (lane == 0) s_w[w] = sum;
@@ -208,8 +215,8 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
     uint64_t all = pre;
     for (int k = 0; k < W; k++) {
         const uint64_t x = s_w[k];
-        if (k < w) pre = sat_add(pre, x);
-        all = sat_add(all, x);
+        if (k < w) pre = add<SAT>(pre, x);
+        all = add<SAT>(all, x);
     }
     // n_keys: the pairs of the bins needed and written, and the coarse pairs written
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
@@ -224,8 +231,8 @@ __global__ void __launch_bounds__(PB_THREADS) k_pairs_emit(int64_t n, const uint
 #pragma unroll
     for (int j = 0; j < R; j++) {
         const BinRect b = bin_rect(lo[j], hi[j], bs);
-        const uint64_t c = rect_counts(b, cs), inc = wave_prefix2(c), at = sat_add(pre, inc - c);
-        pre = sat_add(pre, last_lane2(inc));
+        const uint64_t c = rect_counts(b, cs), inc = wave_prefix2(c), at = add<SAT>(pre, inc - c);
+        pre = add<SAT>(pre, last_lane2(inc));
         const PairCut cut = pair_cut(at, c, (uint64_t)key_cap);
         if (cut.crosses) {
             n_keys[1] = (uint32_t)(at >> 32);
@@ -542,8 +549,14 @@ void pairs_emit(int64_t n, const uint32_t *order, const ViewTable &vt, const Coa
                        reinterpret_cast<const uint2 *>(box), box_lo, box_hi, partials, n_items);
     const int scanned = nb > PB_DIRECT;
     if (scanned) hipLaunchKernelGGL(k_pairs_scan, dim3(1), block, 0, s, partials, nb);
-    hipLaunchKernelGGL((k_pairs_emit<R>), grid, block, 0, s, n, order, vt, cb, box_lo, box_hi, partials, scanned, key_cap,
-                       keys, vals, n_keys, report);
+    int64_t most = 0;   // bins of a view
+    for (int v = 0; v < vt.n_views; v++) most = most > vt.bin_base[v + 1] - vt.bin_base[v] ? most : vt.bin_base[v + 1] - vt.bin_base[v];
+    if (n * most <= MAX_PAIR_CAP)
+        hipLaunchKernelGGL((k_pairs_emit<R, false>), grid, block, 0, s, n, order, vt, cb, box_lo, box_hi, partials, scanned,
+                           key_cap, keys, vals, n_keys, report);
+    else
+        hipLaunchKernelGGL((k_pairs_emit<R, true>), grid, block, 0, s, n, order, vt, cb, box_lo, box_hi, partials, scanned,
+                           key_cap, keys, vals, n_keys, report);
 }
 
 }  // namespace
