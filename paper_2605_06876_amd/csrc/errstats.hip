@@ -27,8 +27,10 @@ constexpr int ES_MAX_BATCH = AS_MAX_VIEWS;   // views of one call
 
 enum { ES_B, ES_LABEL, ES_MOM, ES_BASE, ES_KIDX, ES_COUNT };
 
-// Pixels per block of the region passes (four consecutive ones a thread).
+// Pixels per block of the pass that counts kept regions (four consecutive ones
+// a thread), and blocks that write a chunk's records.
 constexpr int ES_CHUNK = 4096;
+constexpr int ES_PARTS = 4;
 
 // Bytes of each scratch slot for views of P pixels in all (each view's pixels
 // rounded up to a multiple of four): bands, labels, the six integer moments
@@ -472,8 +474,10 @@ __device__ __forceinline__ uint32_t kept_bits(const EsView &ev, const int32_t *l
     return bits;
 }
 
-// Kept components per chunk; the first block also notes the records already
-// in the buffer, which the next pass counts on while it advances the count.
+// Kept components per chunk (the low 16 bits of its word; above them, those
+// before its second, third and fourth part); the first block also notes the
+// records already in the buffer, which the next pass counts on while it
+// advances the count.
 template <int CAP>
 __global__ void __launch_bounds__(ES_CHUNK / 4) k_region_keep(const EsBatch<CAP> eb, const int32_t *__restrict__ label_all,
                                                               const unsigned long long *__restrict__ mom_all, int m_min,
@@ -487,8 +491,13 @@ __global__ void __launch_bounds__(ES_CHUNK / 4) k_region_keep(const EsBatch<CAP>
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < ES_CHUNK / 256; k++) c += s_w[k];
-        part[blockIdx.x] = c;
+        constexpr int WAVES = ES_CHUNK / 256 / ES_PARTS;   // of a part
+        uint64_t word = 0;
+        for (int k = 1; k < ES_CHUNK / 256; k++) {
+            if (k % WAVES == 0) word |= (uint64_t)c << 16 * (k / WAVES);
+            c += s_w[k];
+        }
+        part[blockIdx.x] = (int64_t)(word | (uint64_t)c);
         if (blockIdx.x == 0) *base = *count;
     }
 }
@@ -503,49 +512,57 @@ __device__ __forceinline__ double central_moment(int64_t A, int64_t sab, int64_t
 }
 
 // One record per kept component, in ascending (view, label) order.  A block
-// sums the chunk counts before its own (at most a few loads a thread, less
-// than a launch of a scan between the passes) and the last one advances the
-// buffer's count.
+// sums the chunk counts before its own (a few loads a thread, less than a
+// launch of a scan between the passes) and the last one advances the buffer's
+// count.  A record is a long chain in FP64, so what bounds a view of few
+// pixels is the records that fall to one thread and to one CU: a block has a
+// quarter of a chunk, and its kept pixels are listed in LDS for the threads to
+// take one each.  With a block for a chunk and a thread's records left to it, a
+// noisy 244x183 view took 19 us, now 7.
 template <int CAP>
-__global__ void __launch_bounds__(ES_CHUNK / 4) k_region_emit(const EsBatch<CAP> eb, const int32_t *__restrict__ label_all,
-                                                              const unsigned long long *__restrict__ mom_all, int m_min,
-                                                              const uint8_t *__restrict__ B_all,
-                                                              const int64_t *__restrict__ base,
-                                                              const int64_t *__restrict__ part,
-                                                              as_region *__restrict__ out, int64_t out_cap,
-                                                              int64_t *__restrict__ count) {
-    constexpr int NW = ES_CHUNK / 256;
+__global__ void __launch_bounds__(ES_CHUNK / ES_PARTS / 4)
+k_region_emit(const EsBatch<CAP> eb, const int32_t *__restrict__ label_all,
+              const unsigned long long *__restrict__ mom_all, int m_min, const uint8_t *__restrict__ B_all,
+              const int64_t *__restrict__ base, const int64_t *__restrict__ part, as_region *__restrict__ out,
+              int64_t out_cap, int64_t *__restrict__ count) {
+    constexpr int PX = ES_CHUNK / ES_PARTS, THREADS = PX / 4, NW = THREADS / 64;
+    static_assert(ES_PARTS == 4 && ES_CHUNK < 65536, "a chunk's word");
     __shared__ int64_t s_pre[NW];
     __shared__ int s_w[NW];
+    __shared__ uint16_t s_kept[PX];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int blk = (int)blockIdx.x;
+    const int blk = (int)blockIdx.x / ES_PARTS, q = (int)blockIdx.x % ES_PARTS;
     const EsView &ev = view_of_es_chunk(eb, blk);
     const int32_t *label = label_all + ev.pix0;
     const unsigned long long *mom = mom_all + 6 * ev.pix0;
-    const int64_t u = (int64_t)(blk - ev.chunk0) * ES_CHUNK + 4 * (int64_t)threadIdx.x;
+    const int64_t u0 = (int64_t)(blk - ev.chunk0) * ES_CHUNK + q * PX;
     int64_t pre = 0;
-    for (int b = (int)threadIdx.x; b < blk; b += ES_CHUNK / 4) pre += part[b];
+    for (int b = (int)threadIdx.x; b < blk; b += THREADS) pre += part[b] & 0xffff;
     for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
-    const uint32_t bits = kept_bits(ev, label, mom, u, m_min);
-    int inc = __popc(bits);
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += t;
-    }
+    const uint32_t bits = kept_bits(ev, label, mom, u0 + 4 * (int64_t)threadIdx.x, m_min);
+    const int own = __popc(bits);
+    const int inc = (int)wave_prefix((uint32_t)own);
     if (lane == 63) s_w[w] = inc;
     if (lane == 0) s_pre[w] = pre;
     __syncthreads();
+    int kept = 0, at = inc - own;
     int64_t first = *base;
-    for (int k = 0; k < NW; k++) first += s_pre[k];
-    if (blk == (int)gridDim.x - 1 && threadIdx.x == 0) *count = first + part[blk];
-    for (int k = 0; k < w; k++) first += s_w[k];
-    first += inc - __popc(bits);
+    for (int k = 0; k < NW; k++) {
+        first += s_pre[k];
+        kept += s_w[k];
+        at += k < w ? s_w[k] : 0;
+    }
+    const uint64_t word = (uint64_t)part[blk];
+    if ((int)blockIdx.x == (int)gridDim.x - 1 && threadIdx.x == 0) *count = first + (int64_t)(word & 0xffff);
+    if (q > 0) first += (int64_t)(word >> 16 * q & 0xffff);
+    for (uint32_t left = bits; left; left &= left - 1) s_kept[at++] = (uint16_t)(4 * threadIdx.x + __ffs((int)left) - 1);
+    __syncthreads();
     const int W = ev.W;
     const int64_t P = (int64_t)W * ev.H;
     const uint8_t *B = B_all + ev.pix0;
-    for (uint32_t left = bits; left; left &= left - 1, first++) {
-        const int64_t s = u + __ffs((int)left) - 1;
-        const int64_t pos = first;
+    for (int k = (int)threadIdx.x; k < kept; k += THREADS) {
+        const int64_t s = u0 + s_kept[k];
+        const int64_t pos = first + k;
         if (pos >= out_cap) return;
         as_region r;
         const int32_t root = (int32_t)s;
@@ -777,8 +794,8 @@ void es_launch(const EsScratch &sc, const EsBatch<CAP> &eb, const uint8_t *is_ca
     hipLaunchKernelGGL(k_moments<CAP>, tiles, dim3(ET * ET), 0, s, eb, sc.label, sc.mom);
     // kept roots per chunk, then their records (advancing the buffer's count)
     hipLaunchKernelGGL(k_region_keep<CAP>, chunks, cb, 0, s, eb, sc.label, sc.mom, p.m_min, rb.count, sc.base, sc.part);
-    hipLaunchKernelGGL(k_region_emit<CAP>, chunks, cb, 0, s, eb, sc.label, sc.mom, p.m_min, sc.B, sc.base, sc.part,
-                       rb.records, rb.capacity, rb.count);
+    hipLaunchKernelGGL(k_region_emit<CAP>, dim3(chunks.x * ES_PARTS), dim3(ES_CHUNK / ES_PARTS / 4), 0, s, eb, sc.label,
+                       sc.mom, p.m_min, sc.B, sc.base, sc.part, rb.records, rb.capacity, rb.count);
 }
 }  // namespace
 
