@@ -16,7 +16,7 @@
 // Every kernel covers the views of one call together (one view, or a batch):
 // a view of a megapixel keeps the chip busy for a few microseconds per pass,
 // less than a launch costs, so view by view the passes were launch-bound
-// (16 views of 1256x828: 70 us a view, 1120 us; 393 us in two batches of eight).
+// (16 views of 1256x828: 70 us a view, 1120 us; 375 us in two batches of eight).
 #include <mutex>
 
 #include "internal.h"
